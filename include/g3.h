@@ -516,10 +516,9 @@ int g3_system_step(g3_ctx *ctx, g3_tree **tree, int64_t n, int32_t pos_t,
  *              snapshot from its member count m as floor(log8(m / 128)),
  *              the level whose cells hold about 128 members (no level
  *              break where that is below 1);
- *   streams    density on FP32 trees: 1 or 4 candidate streams per
- *              wavefront; with 4, each quarter of the 64 lanes scans only
- *              the candidates some lane of its quarter can reach (other
- *              kinds and FP64 trees ignore it).
+ *   streams    density on FP32 trees: 1 or 4, kept in queries and files. Both
+ *              launch the same kernel (a team of waves serves each group; the
+ *              candidate streams that 4 once selected were slower).
  * Choices are kept per ctx for each kind (G3_TUNE_*) and size class
  * floor(log2(number of targets)); a call uses its class's choice, else the
  * nearest tuned class's, else the defaults: density walk_leaf 128, split
@@ -529,9 +528,8 @@ int g3_system_step(g3_ctx *ctx, g3_tree **tree, int64_t n, int32_t pos_t,
 enum { G3_TUNE_DENSITY = 0, G3_TUNE_HYDRO = 1, G3_TUNE_GRAVITY = 2 };
 enum { G3_SPLIT_AUTO = -2 };
 /* Time every candidate (walk_leaf 16, 32, 64, 128 x split -1,
- * G3_SPLIT_AUTO, 2, 3, 4, 5 for the SPH kernels, times streams 1, 4 for the
- * density; split for gravity) on this tree and active set, and keep the
- * fastest per kind for this size class. The density runs its h solve on a
+ * G3_SPLIT_AUTO, 2, 3, 4, 5 for the SPH kernels; split for gravity) on this
+ * tree and active set, and keep the fastest per kind for this size class. The density runs its h solve on a
  * copy of h (tree dtype; h[i] > 0 is a first guess); hydro is tuned only
  * when vel, u, rho and omega are given. Writes no output, and leaves the
  * ctx statistics unchanged. SYNCS. */

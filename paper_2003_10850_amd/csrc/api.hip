@@ -440,7 +440,25 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
   return G3_OK;
 }
 
-unsigned persistent_grid(const void *kern, int block, int64_t max_groups) {
+// Waves of a team from the host's bound on the targets. Measured (us, cold
+// density solve and hydro force of clustered sets of 2^10..2^14 groups):
+//   groups          1024        2048        4096        8192       16384
+//   density 4/16    2421/1913   2836/2750   3659/5076   4345/8718  6040/13969
+//   FP64    4/16    4185/2477   4686/3564   6685/6383   8297/10882
+//   hydro 1/4/16    4203/1408/1126  2675/1261/1419  2294/1601/2283
+//                   2538/2413/4142 (8192)  3883/4145/7676 (16384)
+// Below 2^10 groups the widest team is up to 2 times faster than the next
+// one: with fewer groups than CUs the time is that of the slowest group.
+int density_team(int64_t max_targets, int f64) {
+  const int64_t groups = (max_targets + kWave - 1) / kWave;
+  return groups <= (f64 ? 4096 : 1536) ? 16 : 4;
+}
+int hydro_team(int64_t max_targets) {
+  const int64_t groups = (max_targets + kWave - 1) / kWave;
+  return groups <= 1536 ? 16 : (groups <= 12288 ? 4 : 1);
+}
+
+unsigned persistent_grid(const void *kern, int block, int64_t max_groups, int team) {
   static std::mutex mu;
   static std::map<std::pair<int, const void *>, int64_t> resident;
   int dev = 0;
@@ -461,8 +479,8 @@ unsigned persistent_grid(const void *kern, int block, int64_t max_groups) {
     }
     cap = it->second;
   }
-  const int64_t waves_per_block = block / kWave;
-  const int64_t need = (max_groups + waves_per_block - 1) / waves_per_block;
+  const int64_t per_block = block / kWave / team;  // groups at a time
+  const int64_t need = (max_groups + per_block - 1) / per_block;
   return (unsigned)std::max<int64_t>(1, std::min(need, cap));
 }
 
@@ -893,11 +911,16 @@ static SphParams sph_params(const g3_ctx *c, const g3_params *p, const g3_tree *
   sp.alpha = (float)p->alpha;
   sp.max_iter = c->max_iter;
   sp.walk_leaf = tu.walk_leaf;
-  // candidate streams exist for the FP32 density only
-  sp.streams = (!t->f64 && tu.streams == 4) ? 4 : 1;
   sp.f64 = t->f64;
   sp.absmax = t->absmax;
   return sp;
+}
+
+// The largest h of the nodes that a symmetric search reads: the terminals'
+// for a team, every node's for a walk (from o.vh, filled just before).
+static hipError_t sph_radii(const g3_tree *t, Octree &o, const SphParams &sp, const TermBufs &tb,
+                            hipStream_t s) {
+  return sp.team > 1 ? build_terms(o, t->n_snap, sp.walk_leaf, true, tb, s) : refit_hmax(o, s);
 }
 
 static int active_args_ok(g3_ctx *c, const g3_tree *t, int64_t n_act, const int32_t *active,
@@ -989,13 +1012,19 @@ int g3_density(g3_ctx *c, const g3_tree *t, int64_t n_act, const int32_t *active
   c->last_stream = s;
   const Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneDensity, active ? std::min<int64_t>(n_act, o.n) : o.n);
-  const SphParams sp = sph_params(c, p, t, tu);
+  SphParams sp = sph_params(c, p, t, tu);
+  sp.team = density_team(active ? std::min<int64_t>(n_act, o.n) : o.n, t->f64);
+  TermBufs tb;
+  if (o.n > 0 && !reserve_terms(c, o, t->n_snap, &tb))
+    return fail(c, G3_ENOMEM, "g3_density: allocation of the terminal list failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, n_act, active, &wk, s, tu.split);
   if (st) return st;
+  hipError_t e = build_terms(o, t->n_snap, sp.walk_leaf, false, tb, s);
+  if (e != hipSuccess) return hip_fail(c, e, "g3_density");
   KernelTimer timer(c, kTuneDensity, s);
-  hipError_t e = launch_density(o, wk.gs, wk.max_groups, sp, solve_h ? 1 : 0, h, rho, drho_dh,
-                                omega, nngb, c->counters, s);
+  e = launch_density(o, wk.gs, wk.max_groups, sp, tb.terms(), solve_h ? 1 : 0, h, rho, drho_dh,
+                     omega, nngb, c->counters, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_density");
   timer.stop();
   c->err.clear();
@@ -1020,17 +1049,21 @@ int g3_hydro_force(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active,
   c->last_stream = s;
   Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneHydro, active ? std::min<int64_t>(n_act, o.n) : o.n);
-  const SphParams sp = sph_params(c, p, t, tu);
+  SphParams sp = sph_params(c, p, t, tu);
+  sp.team = hydro_team(active ? std::min<int64_t>(n_act, o.n) : o.n);
   st = ensure_h64(c, t, o);
   if (st) return st;
+  TermBufs tb;
+  if (sp.team > 1 && o.n > 0 && !reserve_terms(c, o, t->n_snap, &tb))
+    return fail(c, G3_ENOMEM, "g3_hydro_force: allocation of the terminal list failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, n_act, active, &wk, s, tu.split);
   if (st) return st;
   hipError_t e = launch_hydro_prep(o, vel, u, h, rho, omega, sp.gamma, t->f64, s);
-  if (e == hipSuccess) e = refit_hmax(o, s);
+  if (e == hipSuccess) e = sph_radii(t, o, sp, tb, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_hydro_force prep");
   KernelTimer timer(c, kTuneHydro, s);
-  e = launch_hydro(o, wk.gs, wk.max_groups, sp, acc, dudt, vsig, npairs, s);
+  e = launch_hydro(o, wk.gs, wk.max_groups, sp, tb.terms(), acc, dudt, vsig, npairs, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_hydro_force");
   timer.stop();
   c->err.clear();
@@ -1199,20 +1232,24 @@ int g3_hydro_force_switches(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t 
   c->last_stream = s;
   Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneHydro, active ? std::min<int64_t>(n_act, o.n) : o.n);
-  const SphParams sp = sph_params(c, p, t, tu);
+  SphParams sp = sph_params(c, p, t, tu);
+  sp.team = hydro_team(active ? std::min<int64_t>(n_act, o.n) : o.n);
   st = ensure_h64(c, t, o);
   if (st) return st;
+  TermBufs tb;
+  if (sp.team > 1 && o.n > 0 && !reserve_terms(c, o, t->n_snap, &tb))
+    return fail(c, G3_ENOMEM, "g3_hydro_force_switches: allocation of the terminal list failed");
   float4 *ext = (float4 *)scratch(c, kHydroExt, (size_t)std::max<int64_t>(o.n, 1) * sizeof(float4));
   if (!ext) return fail(c, G3_ENOMEM, "g3_hydro_force_switches: allocation failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, n_act, active, &wk, s, tu.split);
   if (st) return st;
   hipError_t e = launch_hydro_prep(o, vel, u, h, rho, omega, sp.gamma, t->f64, s);
-  if (e == hipSuccess) e = refit_hmax(o, s);
+  if (e == hipSuccess) e = sph_radii(t, o, sp, tb, s);
   if (e == hipSuccess)
     e = launch_hydro_ext_prep(o, u, rho, alpha, balsara, sp.alpha, ext, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_hydro_force_switches prep");
-  e = launch_hydro(o, wk.gs, wk.max_groups, sp, acc, dudt, vsig, npairs, s, ext,
+  e = launch_hydro(o, wk.gs, wk.max_groups, sp, tb.terms(), acc, dudt, vsig, npairs, s, ext,
                    (float)sw->alpha_u);
   if (e != hipSuccess) return hip_fail(c, e, "g3_hydro_force_switches");
   c->err.clear();
@@ -1287,13 +1324,19 @@ static int tick_forces(g3_ctx *c, g3_tree *t, int64_t n, const g3_state *st,
   hipError_t e = hipSuccess;
   if (gas.n > 0) {
     const Tuning td = tuning_for(c, kTuneDensity, gas.n);
-    const SphParams spd = sph_params(c, p, t, td);
+    SphParams spd = sph_params(c, p, t, td);
+    spd.team = density_team(gas.n, t->f64);
+    TermBufs tb;
+    if (!reserve_terms(c, gas, t->n_snap, &tb))
+      return fail(c, G3_ENOMEM, "tick: allocation of the terminal list failed");
     Work wd;
     rc = prepare_work(c, t, gas, t->iperm_gas, gas.n, nullptr, &wd, s, td.split, nullptr, bins,
                       kmin);
     if (rc) return rc;
-    e = launch_density(gas, wd.gs, wd.max_groups, spd, 1, st->h, st->rho, nullptr, st->omega,
-                       nullptr, c->counters, s);
+    e = build_terms(gas, t->n_snap, spd.walk_leaf, false, tb, s);
+    if (e == hipSuccess)
+      e = launch_density(gas, wd.gs, wd.max_groups, spd, tb.terms(), 1, st->h, st->rho, nullptr,
+                         st->omega, nullptr, c->counters, s);
     if (e != hipSuccess) return hip_fail(c, e, "density at a tick");
     const float *vh = st->vel, *uh = st->u;
     if (T > 0) {
@@ -1304,15 +1347,16 @@ static int tick_forces(g3_ctx *c, g3_tree *t, int64_t n, const g3_state *st,
       uh = up;
     }
     const Tuning th = tuning_for(c, kTuneHydro, gas.n);
-    const SphParams sp = sph_params(c, p, t, th);
+    SphParams sp = sph_params(c, p, t, th);
+    sp.team = hydro_team(gas.n);
     e = launch_hydro_prep(gas, vh, uh, st->h, st->rho, st->omega, sp.gamma, t->f64, s);
-    if (e == hipSuccess) e = refit_hmax(gas, s);
+    if (e == hipSuccess) e = sph_radii(t, gas, sp, tb, s);
     if (e != hipSuccess) return hip_fail(c, e, "hydro prep at a tick");
     Work wh;
     rc = prepare_work(c, t, gas, t->iperm_gas, gas.n, nullptr, &wh, s, th.split, nullptr, bins,
                       kmin);
     if (rc) return rc;
-    e = launch_hydro(gas, wh.gs, wh.max_groups, sp, acc_h, st->dudt, st->vsig, nullptr, s);
+    e = launch_hydro(gas, wh.gs, wh.max_groups, sp, tb.terms(), acc_h, st->dudt, st->vsig, nullptr, s);
     if (e != hipSuccess) return hip_fail(c, e, "hydro at a tick");
   }
   const Octree &all = t->all;
@@ -1570,20 +1614,21 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
   };
   Octree &gas = t->gas;
   const int64_t ng = active ? std::min<int64_t>(n_act, gas.n) : gas.n;
+  const int team = hydro_team(ng);
+  TermBufs tb;
+  if (gas.n > 0 && !reserve_terms(c, gas, t->n_snap, &tb))
+    return finish(fail(c, G3_ENOMEM, "g3_autotune: allocation failed"));
   // density, with the h solve on a copy of h
   if (gas.n > 0 && h) {
     void *hs = scratch(c, kAdjPQ, (size_t)t->n * hsz);
     if (!hs) return finish(fail(c, G3_ENOMEM, "g3_autotune: allocation failed"));
     Tuning best;
     float best_ms = INFINITY;
-    for (int streams : {1, 4})
     for (int leaf : kLeaves)
       for (int split : kSplits) {
-        if (streams > 1 && t->f64) continue;
         Tuning tu;
         tu.walk_leaf = leaf;
         tu.split = split;
-        tu.streams = streams;
         Work wk;
         float ms = 0.f;
         st = time_candidate(c, s, e0, e1, [&]() -> hipError_t {
@@ -1591,8 +1636,12 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
           if (r != hipSuccess) return r;
           if (prepare_work(c, t, gas, t->iperm_gas, n_act, active, &wk, s, tu.split))
             return hipErrorUnknown;
-          return launch_density(gas, wk.gs, wk.max_groups, sph_params(c, p, t, tu), 1, hs,
-                                nullptr, nullptr, nullptr, nullptr, c->counters, s);
+          SphParams sp = sph_params(c, p, t, tu);
+          sp.team = density_team(ng, t->f64);
+          r = build_terms(gas, t->n_snap, sp.walk_leaf, false, tb, s);
+          if (r != hipSuccess) return r;
+          return launch_density(gas, wk.gs, wk.max_groups, sp, tb.terms(), 1, hs, nullptr,
+                                nullptr, nullptr, nullptr, c->counters, s);
         }, &ms);
         if (st) return finish(st);
         if (ms < best_ms) {
@@ -1608,7 +1657,7 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
     st = ensure_h64(c, t, gas);
     if (st) return finish(st);
     e = launch_hydro_prep(gas, vel, u, h, rho, omega, base.gamma, t->f64, s);
-    if (e == hipSuccess) e = refit_hmax(gas, s);
+    if (e == hipSuccess && team == 1) e = refit_hmax(gas, s);
     if (e != hipSuccess) return finish(hip_fail(c, e, "g3_autotune"));
     Tuning best;
     float best_ms = INFINITY;
@@ -1622,8 +1671,13 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
         st = time_candidate(c, s, e0, e1, [&]() -> hipError_t {
           if (prepare_work(c, t, gas, t->iperm_gas, n_act, active, &wk, s, tu.split))
             return hipErrorUnknown;
-          return launch_hydro(gas, wk.gs, wk.max_groups, sph_params(c, p, t, tu), nullptr, nullptr,
-                              nullptr, nullptr, s);
+          SphParams sp = sph_params(c, p, t, tu);
+          sp.team = team;
+          const hipError_t r =
+              team > 1 ? build_terms(gas, t->n_snap, sp.walk_leaf, true, tb, s) : hipSuccess;
+          if (r != hipSuccess) return r;
+          return launch_hydro(gas, wk.gs, wk.max_groups, sp, tb.terms(), nullptr, nullptr, nullptr,
+                              nullptr, s);
         }, &ms);
         if (st) return finish(st);
         if (ms < best_ms) {

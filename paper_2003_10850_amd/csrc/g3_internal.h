@@ -21,7 +21,8 @@ struct __align__(16) Node {
   float4 com_m;  // centre of mass (FP32 copy of the FP64 moment), mass
   float4 lo_h;   // tight bounding box lower corner, max h of gas members
   float4 hi_l;   // tight bounding box upper corner, cube side l
-  int4 meta;     // skip, first member, member count, level | leaf << 8
+  int4 meta;     // skip, first member, member count,
+                 // level | leaf << 8 | min(parent's member count, 65535) << 16
 };
 static_assert(sizeof(Node) == 64, "node must be 64 bytes");
 
@@ -80,7 +81,7 @@ constexpr int kSplitAuto = -2;
 struct Tuning {
   int walk_leaf = 64;
   int split = -1;  // -1 none, kSplitAuto, or a level
-  int streams = 1;  // density: candidate streams per wave (1 or 4)
+  int streams = 1;  // 1 or 4: kept in files and queries, launches the same kernel
 };
 enum TuneKind { kTuneDensity = 0, kTuneHydro = 1, kTuneGravity = 2, kTuneKinds = 3 };
 
@@ -155,7 +156,7 @@ enum Slot {
   kFlags, kTargets, kRows, kIds, kLevel, kWalkCounts, kMisc,
   kSnapKeys, kSnapKeysAlt, kGroups, kAdjSrc, kAdjNode, kAdjPQ, kAdjR,
   kGasFlags, kGasSlot, kGasScan, kIntAccH, kIntVp, kIntUp, kCondCh, kHydroExt,
-  kAdjSrcFx, kAdjNodeFx, kNumSlots
+  kAdjSrcFx, kAdjNodeFx, kTermBuf, kNumSlots
 };
 static_assert(kNumSlots <= g3_ctx::kBankSlots, "more scratch slots than a bank holds");
 
@@ -235,6 +236,35 @@ inline int64_t max_groups_of(int64_t max_targets, int64_t n_snap) {
 
 
 
+// The terminal nodes of one octree for a walk_leaf: the nodes of at most
+// walk_leaf members (and larger leaves) whose parent holds more, in tree
+// order. They partition the sorted members, so a terminal's member count is
+// the difference of two starts. 64 consecutive terminals form a window.
+struct Terms {
+  const float4 *lo, *hi;    // [count + 1] box, lo.w = largest h, hi.w = first
+                            // member as bits (entry `count`: the member count)
+  const float4 *wlo, *whi;  // windows: box, wlo.w = largest h
+  const int2 *range;        // [n_snap] terminals of each snapshot
+};
+
+// Buffers of a terminal list (ctx scratch), taken before a call's launches.
+struct TermBufs {
+  int32_t *node = nullptr, *bcount = nullptr, *count = nullptr;
+  float4 *lo = nullptr, *hi = nullptr, *wlo = nullptr, *whi = nullptr;
+  int2 *range = nullptr;
+  Terms terms() const { return Terms{lo, hi, wlo, whi, range}; }
+};
+// False when the scratch cannot be had.
+bool reserve_terms(g3_ctx *c, const Octree &o, int n_snap, TermBufs *b);
+// Fills the list; largest h of the members from o.vh when `with_h` (else 0).
+hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, const TermBufs &b,
+                       hipStream_t s);
+
+// Waves of the team that serves one group, from the (host-side bound on the)
+// number of targets: 4 or 16, for the hydro force also 1 (no team).
+int density_team(int64_t max_targets, int f64);
+int hydro_team(int64_t max_targets);
+
 // Active set -> group table of one octree (scratch owned by the ctx).
 // rows[t] is the index in `active` of target t (nullptr with every member
 // active: rows are then caller ids). max_groups bounds the group count.
@@ -275,19 +305,21 @@ void *noalloc_region(int device);
 
 // Grid of a persistent launch: the workgroups that can be resident at once
 // (occupancy of `kern` x compute units), or fewer if there are few groups.
-unsigned persistent_grid(const void *kern, int block, int64_t max_groups);
+// `team`: waves that serve one group.
+unsigned persistent_grid(const void *kern, int block, int64_t max_groups, int team = 1);
 
 struct SphParams {
   float n_ngb, h_tol, gamma, alpha;
   int max_iter;
   int walk_leaf;  // SPH walks take subtrees of at most this many members whole
-  int streams;    // density candidate streams per wave (1 or 4; FP32 trees)
   int f64;        // FP64 positions and h: mixed-precision kernels
+  int team = 1;   // waves that serve one group together
   const unsigned *absmax;  // FP64 trees: device bits of max |x| (walk pad 2^-20 of it)
 };
 
+// tm: the terminals of sp.walk_leaf (the hydro force: when sp.team > 1).
 hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_groups,
-                          const SphParams &sp, int solve_h, void *h, float *rho,
+                          const SphParams &sp, const Terms &tm, int solve_h, void *h, float *rho,
                           float *drho_dh, float *omega, int32_t *nngb,
                           unsigned long long *counters, hipStream_t s);
 hipError_t launch_hydro_prep(Octree &gas, const float *vel, const float *u, const void *h,
@@ -296,8 +328,8 @@ hipError_t launch_hydro_prep(Octree &gas, const float *vel, const float *u, cons
 // ext (nullable): the improved-SPH switches' sorted inputs (alpha, Balsara
 // factor, u, rho) from launch_hydro_ext_prep, with conduction strength alpha_u.
 hipError_t launch_hydro(const Octree &gas, const Groups &gs, int64_t max_groups,
-                        const SphParams &sp, float *acc, float *dudt, float *vsig,
-                        int32_t *npairs, hipStream_t s, const float4 *ext = nullptr,
+                        const SphParams &sp, const Terms &tm, float *acc, float *dudt,
+                        float *vsig, int32_t *npairs, hipStream_t s, const float4 *ext = nullptr,
                         float alpha_u = 0.0f);
 hipError_t launch_hydro_ext_prep(Octree &gas, const float *u, const float *rho,
                                  const float *alpha, const float *balsara, float alpha0,

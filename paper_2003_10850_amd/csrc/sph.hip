@@ -1,26 +1,28 @@
 // SPH density (with the smoothing-length solve) and hydro force.
 //
-// One wavefront serves a group of 64 Morton-consecutive target particles,
-// one per lane, as in the paper's walk over groups of active particles
-// (section 1). The wave walks the gas octree in preorder with one scalar
-// node load per step; a node is opened when any lane's search sphere
-// reaches its tight bounding box. Leaf members are appended to a 64-entry
-// candidate tile in LDS (the paper's neighbour chunks, section 2.4, here one
-// wave wide); every lane then scans the tile against its own target with the
-// exact neighbour test, so walk and interaction sums are decoupled without a
-// per-particle list in memory.
+// A group of up to 64 Morton-consecutive target particles, one per lane, as in
+// the paper's walk over groups of active particles (section 1), is served by
+// a team of waves (g3_team.h) or by one wave. The gas octree's nodes are
+// opened while some lane's search sphere reaches their tight bounding box.
+// Leaf members are appended to 64-entry candidate tiles in LDS (the paper's
+// neighbour chunks, section 2.4, here one wave wide); every lane then scans
+// a tile against its own target with the exact neighbour test, so search and
+// interaction sums are decoupled without a per-particle list in memory.
 #include <type_traits>
 
 #include "g3_device.h"
 #include "g3_internal.h"
+#include "g3_team.h"
 
 namespace g3 {
 
 namespace {
 
-constexpr int kBlock = 256;
-constexpr int kWpb = kBlock / kWave;  // waves per block
 constexpr int kTile = kWave;
+// Threads of a workgroup: four independent waves, or one team of kT waves.
+template <int kT>
+constexpr int kBlockOf = (kT > 1 ? kT : 4) * kWave;
+struct NoLds {};
 
 // Wendland C6 in 3D, support radius h: W = C/h^3 w(q),
 // w(q) = (1-q)^8 (1 + 8q + 25q^2 + 32q^3); h dW/dh = C/h^3 wh(q),
@@ -95,37 +97,36 @@ constexpr float kBandOff = 1.9073486e-6f;  // 2^-19
 constexpr float kFineExt = 1.0f;
 
 
-// Candidate streams per wave (kQ > 1, FP32 path): the lanes are split into
-// kQ quarters of 64/kQ targets, and a leaf or small subtree the walk accepts
-// is queued only for the quarters that have a lane reaching its box. A round
-// loads up to 64 queued candidates of every quarter into that quarter's
-// tile and each lane scans its own quarter's tile, so a lane tests the union
-// of its quarter's candidates instead of the whole wave's.
-constexpr int kRing = 256;  // queued candidate indices per quarter
-
-template <bool kF64, int kQ>
-__global__ __launch_bounds__(kBlock) void k_density(
+// A team of kT waves (g3_team.h) serves a group: every wave holds the group's
+// targets and takes the same solve steps, the search and the tiles are shared.
+// Bound by vector issue on a full chip (a neighbour pass of one wave is about
+// 5e4 instructions) and by the slowest groups otherwise. Cold solve of the
+// 2^20 gas particles of a clustered 2^21 box: 8.0 ms with a wave a group, 6.0
+// with teams of 4 (the solve's uneven passes and the uneven groups spread over
+// four waves; held to 6 waves a SIMD: 6.9 ms at the 4 that 120 registers
+// allow); 14 with teams of 16. 2^15 gas particles: 7.0, 2.4 and 1.6 ms.
+template <bool kF64, int kT>
+__global__ __launch_bounds__(kBlockOf<kT>, kT == 4 && !kF64 ? 6 : 1) void k_density(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const int32_t *__restrict__ perm, const Groups gs,
-    float n_ngb, float tol, int solve, int max_iter, int walk_leaf,
+    const Terms tm, float n_ngb, float tol, int solve, int max_iter, int walk_leaf,
     const unsigned *__restrict__ absmax,
     void *__restrict__ hptr, float *__restrict__ rho, float *__restrict__ drho_dh,
     float *__restrict__ omega, int32_t *__restrict__ nngb,
     unsigned long long *__restrict__ counters) {
   using HT = typename std::conditional<kF64, double, float>::type;
   HT *h = (HT *)hptr;
-  static_assert(kQ == 1 || !kF64, "candidate streams are for the FP32 path");
+  __shared__ TeamLds<kT> search;
+  __shared__ TeamSums<kT, 3> sums;
   // FP64 positions: the walk's pad for the rounding of the FP32 copies
   const float slack = kF64 ? ldexpf(__uint_as_float(*absmax), -20) : 0.0f;
-  __shared__ float4 tiles[kWpb][kQ > 1 ? 1 : kTile];
+  __shared__ float4 tiles[kT][kTile];
   // mixed precision: the low parts of the offsets, and the sorted index of
   // each entry as the fourth component
-  __shared__ float4 tlos[kWpb][kF64 ? kTile : 1];
-  __shared__ int32_t ring[kWpb][kQ > 1 ? kQ : 1][kQ > 1 ? kRing : 1];
-  __shared__ float4 qtile[kWpb][kQ > 1 ? kQ : 1][kQ > 1 ? kTile : 1];
+  __shared__ float4 tlos[kT][kF64 ? kTile : 1];
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
   int range = 0;
-  for (int g; (g = next_group(gs, range)) >= 0;) {
+  for (int g; (g = team_next_group(gs, range, search)) >= 0;) {
   const Group grp = group_at(gs, g);
   const int64_t t = grp.t0 + lane;
   const bool valid = lane < grp.count;
@@ -189,9 +190,8 @@ __global__ __launch_bounds__(kBlock) void k_density(
 
     const float hinv = 1.0f / hf;
     // sums of m w, m wh and m wss: plain per tile, compensated across tiles
-    float sw = 0.0f, swh = 0.0f, sss = 0.0f, csw = 0.0f, cswh = 0.0f, csss = 0.0f;
-    int cnt = 0;
-    int tc = 0, cand = 0;
+    float sw, swh, sss;
+    int cnt = 0, cand = 0;
     // the box of this pass's live targets and their largest squared radius:
     // a candidate whose box_dist2 to that box is not below it fails every
     // lane's neighbour test (box_dist2 never exceeds the r2 of a point in
@@ -202,18 +202,18 @@ __global__ __launch_bounds__(kBlock) void k_density(
                              live ? xi.z : -INFINITY, 0.f);
     // (with FP64 positions: the FP32 copies and the walk's padded radius)
     float hmax2 = kF64 ? hw2 : h2;
-    if constexpr (kQ == 1) {
 #pragma unroll
-      for (int m = 1; m < kWave; m <<= 1) {
-        tlo.x = fminf(tlo.x, __shfl_xor(tlo.x, m));
-        tlo.y = fminf(tlo.y, __shfl_xor(tlo.y, m));
-        tlo.z = fminf(tlo.z, __shfl_xor(tlo.z, m));
-        thi.x = fmaxf(thi.x, __shfl_xor(thi.x, m));
-        thi.y = fmaxf(thi.y, __shfl_xor(thi.y, m));
-        thi.z = fmaxf(thi.z, __shfl_xor(thi.z, m));
-        hmax2 = fmaxf(hmax2, __shfl_xor(hmax2, m));
-      }
-      // wave-uniform now: held in scalar registers through the walk
+    for (int m = 1; m < kWave; m <<= 1) {
+      tlo.x = fminf(tlo.x, __shfl_xor(tlo.x, m));
+      tlo.y = fminf(tlo.y, __shfl_xor(tlo.y, m));
+      tlo.z = fminf(tlo.z, __shfl_xor(tlo.z, m));
+      thi.x = fmaxf(thi.x, __shfl_xor(thi.x, m));
+      thi.y = fmaxf(thi.y, __shfl_xor(thi.y, m));
+      thi.z = fmaxf(thi.z, __shfl_xor(thi.z, m));
+      hmax2 = fmaxf(hmax2, __shfl_xor(hmax2, m));
+    }
+    {
+      // wave-uniform now: held in scalar registers through the search
       auto su = [](float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); };
       tlo = make_float4(su(tlo.x), su(tlo.y), su(tlo.z), 0.f);
       thi = make_float4(su(thi.x), su(thi.y), su(thi.z), 0.f);
@@ -233,7 +233,8 @@ __global__ __launch_bounds__(kBlock) void k_density(
       for (int m = 1; m < kWave; m <<= 1) hmin = fminf(hmin, __shfl_xor(hmin, m));
       fine = ext <= kFineExt * hmin;
     }
-    auto flush = [&](int nc) {
+    // one tile's plain FP32 sums over the lane's neighbours in it
+    auto tile_sums = [&](int nc, float &pw, float &pwh, float &pss) {
       // unused slots sit at infinity and fail every neighbour test
       if constexpr (kF64) {
         float4 o = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(kBlock) void k_density(
           tlo64[slot] = l;
         }
         nc = __popcll(km);
-      } else if constexpr (kQ == 1) {
+      } else {
         const float4 v = (lane < nc) ? xm[cand] : make_float4(INFINITY, INFINITY, INFINITY, 0.f);
         const bool keep = lane < nc && box_dist2(make_float3(v.x, v.y, v.z), tlo, thi) < hmax2;
         const uint64_t km = __ballot(keep);
@@ -268,15 +269,13 @@ __global__ __launch_bounds__(kBlock) void k_density(
         tile[lane] = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
         if (keep) tile[slot] = v;
         nc = __popcll(km);
-      } else {
-        tile[lane] = (lane < nc) ? xm[cand] : make_float4(INFINITY, INFINITY, INFINITY, 0.f);
       }
       wave_sync();
       // every lane tests every entry (read by broadcast); the kernel sum runs
       // under the lanes that pass, and is skipped when none does. (Marking
       // each lane's entries first and then visiting only its own measured
       // slower: it costs occupancy and per-lane LDS addressing.)
-      float pw = 0.0f, pwh = 0.0f, pss = 0.0f;
+      pw = pwh = pss = 0.0f;
       auto pair = [&](float r2, float mj) {
         const float u = __builtin_amdgcn_sqrtf(r2) * hinv;
         float wv, whv, wsv;
@@ -340,137 +339,35 @@ __global__ __launch_bounds__(kBlock) void k_density(
           }
         }
       }
-      neumaier_add(sw, csw, pw);
-      neumaier_add(swh, cswh, pwh);
-      neumaier_add(sss, csss, pss);
       wave_sync();
     };
-    // candidate streams: queue positions (wave-uniform, monotone) and one
-    // round of evaluation over up to 64 queued candidates of every quarter
-    constexpr int kQl = kWave / kQ;
-    constexpr uint64_t kQmask = kQ > 1 ? ((1ull << kQl) - 1ull) : ~0ull;
-    int qhead[kQ], qtail[kQ];
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) qhead[q] = qtail[q] = 0;
-    auto qround = [&]() {
-      if constexpr (kQ > 1) {
-        wave_sync();  // the queued indices are visible
-        int mx = 0;
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) {
-          const int nq = min(kTile, qtail[q] - qhead[q]);
-          mx = max(mx, nq);
-          float4 v = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
-          if (lane < nq) v = xm[ring[w][q][(qhead[q] + lane) & (kRing - 1)]];
-          qtile[w][q][lane] = v;
-          qhead[q] += nq;
-        }
-        wave_sync();
-        const float4 *tq = qtile[w][lane / kQl];
-        float pw = 0.0f, pwh = 0.0f, pss = 0.0f;
-        const int ngr = (mx + 3) >> 2;
-        float4 a0 = tq[0], a1 = tq[1], a2 = tq[2], a3 = tq[3];
-        for (int gq = 0; gq < ngr; ++gq) {
-          const float4 q0 = a0, q1 = a1, q2 = a2, q3 = a3;
-          const int nx = min(4 * gq + 4, kTile - 4);
-          a0 = tq[nx];
-          a1 = tq[nx + 1];
-          a2 = tq[nx + 2];
-          a3 = tq[nx + 3];
-          const float4 qs[4] = {q0, q1, q2, q3};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float4 qq = qs[e];
-            const float r2 = dist2_exact(sub_exact(qq.x, xi.x), sub_exact(qq.y, xi.y),
-                                         sub_exact(qq.z, xi.z));
-            if (r2 < h2) {
-              const float u = __builtin_amdgcn_sqrtf(r2) * hinv;
-              float wv, whv, wsv;
-              wc6_w_wh(u, wv, whv, wsv);
-              pw += qq.w * wv;
-              pwh += qq.w * whv;
-              pss += qq.w * wsv;
-              ++cnt;
+    {
+      float ts = 0.0f, tcmp = 0.0f;  // this wave's component of the totals
+      team_search(
+          tm, grp.snap, search, xi, hw2, tlo, thi, hmax2,
+          [](float want2, float) { return want2; },
+          [&](int ntiles, int count) {
+            for (int j; (j = team_next_tile(search)) < ntiles;) {
+              const int nc = min(kTile, count - j * kTile);
+              cand = lane < nc ? search.cand[j * kTile + lane] : 0;
+              float p[3];
+              tile_sums(nc, p[0], p[1], p[2]);
+              sums.put(j, lane, p);
             }
-          }
-        }
-        neumaier_add(sw, csw, pw);
-        neumaier_add(swh, cswh, pwh);
-        neumaier_add(sss, csss, pss);
-        wave_sync();
-      }
-    };
-    // The next node is either cur + 1 (descend) or the skip target: both
-    // are loaded while the current one is tested, so the walk waits for one
-    // load latency per step instead of a load after every decision.
-    const int last = grp.end - 1;
-    int cur = grp.root;
-    Node nd = nodes[cur];
-    while (cur < grp.end) {
-      const int next_a = cur + 1, next_b = nd.meta.x;
-      const Node nda = nodes[min(next_a, last)];
-      const Node ndb = nodes[min(next_b, last)];
-      const bool want = box_dist2(xi, nd.lo_h, nd.hi_l) < hw2;
-      bool descend = false;
-      const uint64_t wm = __ballot(want);
-      if (wm != 0ull) {
-        // a small subtree is taken whole: its members are one contiguous run
-        if (!(nd.meta.w & kLeafBit) && nd.meta.z > walk_leaf) {
-          descend = true;
-        } else if constexpr (kQ > 1) {
-          const int st = nd.meta.y, c = nd.meta.z;
+            sums.merge(ntiles, w, lane, ts, tcmp);
+          });
+      // totals and counts to every wave
+      if (w < 3) sums.part[0][w][lane] = ts + tcmp;
+      sums.count[w][lane] = cnt;
+      __syncthreads();
+      sw = sums.part[0][0][lane];
+      swh = sums.part[0][1][lane];
+      sss = sums.part[0][2][lane];
+      cnt = 0;
 #pragma unroll
-          for (int q = 0; q < kQ; ++q) {
-            if (((wm >> (q * kQl)) & kQmask) == 0ull) continue;
-            // appended a tile at a time: a leaf of coincident particles can
-            // hold more than the ring, and a round frees up to a tile
-            for (int off = 0; off < c; off += kTile) {
-              const int take = min(kTile, c - off);
-              while (qtail[q] - qhead[q] + take > kRing) qround();
-              if (lane < take) ring[w][q][(qtail[q] + lane) & (kRing - 1)] = st + off + lane;
-              qtail[q] += take;
-            }
-          }
-          // a round once every quarter has a full tile waiting
-          for (;;) {
-            bool full = true;
-#pragma unroll
-            for (int q = 0; q < kQ; ++q) full = full && qtail[q] - qhead[q] >= kTile;
-            if (!full) break;
-            qround();
-          }
-        } else {
-          int st = nd.meta.y, c = nd.meta.z;
-          while (c > 0) {
-            const int take = min(c, kTile - tc);
-            if (lane >= tc && lane < tc + take) cand = st + lane - tc;
-            tc += take;
-            st += take;
-            c -= take;
-            if (tc == kTile) {
-              flush(kTile);
-              tc = 0;
-            }
-          }
-        }
-      }
-      cur = descend ? next_a : next_b;
-      nd = descend ? nda : ndb;
+      for (int v = 0; v < kT; ++v) cnt += sums.count[v][lane];
+      __syncthreads();
     }
-    if constexpr (kQ > 1) {
-      for (;;) {  // drain
-        bool any = false;
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) any = any || qtail[q] > qhead[q];
-        if (!any) break;
-        qround();
-      }
-    } else if (tc > 0) {
-      flush(tc);
-    }
-    sw += csw;
-    swh += cswh;
-    sss += csss;
 
     if (live) {
       if (!solve) {
@@ -575,12 +472,12 @@ __global__ __launch_bounds__(kBlock) void k_density(
     }
   }
   // counters: [0] non-converged particles, [1] walk passes, [2] waves
-  if (lane == 0) {
+  if (threadIdx.x == 0) {
     atomicAdd(&counters[1], (unsigned long long)passes);
     atomicAdd(&counters[2], 1ull);
   }
 
-  if (valid) {
+  if (valid && w == 0) {
     const float hinv = 1.0f / (float)res_h;
     const float r = kC * res_sw * hinv * hinv * hinv;
     if (solve) h[cid] = res_h;
@@ -637,6 +534,7 @@ __device__ __forceinline__ float rho_u_difference(float ri, float ui, float rj, 
   return __builtin_fmaf(ri, ui, -pj) - ej;
 }
 
+template <int kWpb>
 struct HydroTile {
   float4 xm[kWpb][kTile];
   float4 vh[kWpb][kTile];
@@ -644,24 +542,35 @@ struct HydroTile {
 };
 
 // The extra tile of the switches' inputs (a one-entry stand-in without them).
-template <bool kExt>
+template <bool kExt, int kWpb>
 struct ExtTile {
   float4 e[kWpb][kExt ? kTile : 1];
 };
 
 // kExt: the improved-SPH switches (per-particle viscosity strengths and
 // Balsara factors, artificial conduction of strength alpha_u) from ext.
-template <bool kF64, bool kExt>
-__global__ __launch_bounds__(kBlock) void k_hydro(
+// kT > 1: a team serves a group, as in the density; else a wave walks the
+// octree itself. 2^20 gas particles of the clustered 2^21 box: 3.8 ms with a
+// wave a group, 4.1 with teams of 4 (their LDS holds 4 waves a SIMD, not 6),
+// 7.7 with 16; 2^15 gas particles: 2.9, 0.90 and 0.53 ms. Bound by vector
+// issue on a full chip, by the slowest groups otherwise.
+template <bool kF64, bool kExt, int kT>
+__global__ __launch_bounds__(kBlockOf<kT>) void k_hydro(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const double *__restrict__ h64,
     const float4 *__restrict__ vh, const float4 *__restrict__ aux,
     const float4 *__restrict__ ext, const int32_t *__restrict__ perm, const Groups gs,
-    float alpha, float alpha_u, float gm1, int walk_leaf, const unsigned *__restrict__ absmax,
+    const Terms tm, float alpha, float alpha_u, float gm1, int walk_leaf, const unsigned *__restrict__ absmax,
     float *__restrict__ acc,
     float *__restrict__ dudt, float *__restrict__ vsig, int32_t *__restrict__ npairs) {
-  __shared__ HydroTile T;
-  __shared__ ExtTile<kExt> E;
+  constexpr int kWpb = kBlockOf<kT> / kWave;
+  constexpr int kTeam = kT > 1 ? kT : 4;
+  using SearchLds = typename std::conditional<(kT > 1), TeamLds<kTeam>, NoLds>::type;
+  using SumLds = typename std::conditional<(kT > 1), TeamSums<kTeam, 4>, NoLds>::type;
+  __shared__ SearchLds search;
+  __shared__ SumLds sums;
+  __shared__ HydroTile<kWpb> T;
+  __shared__ ExtTile<kExt, kWpb> E;
   // mixed precision: the low parts of the offsets, and the sorted index of
   // each entry as the fourth component
   __shared__ float4 tlos[kWpb][kF64 ? kTile : 1];
@@ -669,7 +578,11 @@ __global__ __launch_bounds__(kBlock) void k_hydro(
   // FP64 positions: the walk's pad for the rounding of the FP32 copies
   const float slack = kF64 ? ldexpf(__uint_as_float(*absmax), -20) : 0.0f;
   int range = 0;
-  for (int g; (g = next_group(gs, range)) >= 0;) {
+  auto take_group = [&]() {
+    if constexpr (kT > 1) return team_next_group<kTeam>(gs, range, search);
+    else return next_group(gs, range);
+  };
+  for (int g; (g = take_group()) >= 0;) {
   const Group grp = group_at(gs, g);
   const int64_t t = grp.t0 + lane;
   const bool valid = lane < grp.count;
@@ -734,8 +647,14 @@ __global__ __launch_bounds__(kBlock) void k_hydro(
     thi = make_float4(su(thi.x), su(thi.y), su(thi.z), 0.f);
     hmax2 = su(hmax2);
   }
+  float gh = hi;  // teams: the group's largest h
+  if constexpr (kT > 1) {
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) gh = fmaxf(gh, __shfl_xor(gh, m));
+  }
 
-  auto flush = [&](int nc) {
+  // one tile's plain FP32 sums over the lane's pairs in it
+  auto tile_sums = [&](int nc, float &px, float &py, float &pz, float &pu) {
     {
       float4 vx = make_float4(INFINITY, INFINITY, INFINITY, 0.f), vv = make_float4(0.f, 0.f, 0.f, 0.f);
       float4 va = vv, ve = vv;
@@ -773,7 +692,7 @@ __global__ __launch_bounds__(kBlock) void k_hydro(
       nc = __popcll(km);
     }
     wave_sync();
-    float px = 0.f, py = 0.f, pz = 0.f, pu = 0.f;
+    px = py = pz = pu = 0.f;
     // one pair (i, entry k) that passed the symmetric neighbour test; the
     // self pair (r = 0) passes too: it is counted and subtracted at the end,
     // and any pair at r = 0 adds nothing to the sums
@@ -873,13 +792,52 @@ __global__ __launch_bounds__(kBlock) void k_hydro(
       scan(std::true_type{});
     else
       scan(std::false_type{});
+    wave_sync();
+  };
+  auto flush = [&](int nc) {
+    float px, py, pz, pu;
+    tile_sums(nc, px, py, pz, pu);
     neumaier_add(ax, cax, px);
     neumaier_add(ay, cay, py);
     neumaier_add(az, caz, pz);
     neumaier_add(du, cdu, pu);
-    wave_sync();
   };
 
+  if constexpr (kT > 1) {
+    float ts = 0.f, tcmp = 0.f;  // this wave's component of the totals
+    team_search<kTeam>(
+        tm, grp.snap, search, xi, hi, tlo, thi, gh,
+        [&](float h, float hmax) {
+          // a lane without a target (-1) reaches nothing
+          const float hm = fmaxf(h, hmax);
+          return h > 0.0f ? sq_exact(kF64 ? walk_radius64(hm, slack) : hm) : -1.0f;
+        },
+        [&](int ntiles, int count) {
+          for (int j; (j = team_next_tile(search)) < ntiles;) {
+            const int nc = min(kTile, count - j * kTile);
+            cand = lane < nc ? search.cand[j * kTile + lane] : 0;
+            float p[4];
+            tile_sums(nc, p[0], p[1], p[2], p[3]);
+            sums.put(j, lane, p);
+          }
+          sums.merge(ntiles, w, lane, ts, tcmp);
+        });
+    // totals, counts and signal speeds to wave 0
+    if (w < 4) sums.part[0][w][lane] = ts + tcmp;
+    sums.count[w][lane] = np;
+    T.xm[w][lane].x = vs;
+    __syncthreads();
+    ax = sums.part[0][0][lane];
+    ay = sums.part[0][1][lane];
+    az = sums.part[0][2][lane];
+    du = sums.part[0][3][lane];
+    np = 0;
+#pragma unroll
+    for (int v = 0; v < kT; ++v) {
+      np += sums.count[v][lane];
+      vs = fmaxf(vs, T.xm[v][lane].x);
+    }
+  } else {
   int cur = grp.root;
   while (cur < grp.end) {
     const Node nd = nodes[cur];
@@ -916,8 +874,9 @@ __global__ __launch_bounds__(kBlock) void k_hydro(
   ay += cay;
   az += caz;
   du += cdu;
+  }
 
-  if (valid) {
+  if (valid && (kT == 1 || w == 0)) {
     const int cid = perm[s];
     if (acc) {
       acc[3 * cid] = ax;
@@ -936,14 +895,16 @@ inline unsigned nblk(int64_t n, int per) { return (unsigned)((n + per - 1) / per
 }  // namespace
 
 hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_groups,
-                          const SphParams &sp, int solve_h, void *h, float *rho,
+                          const SphParams &sp, const Terms &tm, int solve_h, void *h, float *rho,
                           float *drho_dh, float *omega, int32_t *nngb,
                           unsigned long long *counters, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = sp.f64 ? k_density<true, 1>
-                     : (sp.streams == 4 ? k_density<false, 4> : k_density<false, 1>);
-  kern<<<persistent_grid((const void *)kern, kBlock, max_groups), kBlock, 0, s>>>(
-      gas.nodes, gas.xm, gas.x64, gas.perm, gs, sp.n_ngb, sp.h_tol, solve_h, sp.max_iter,
+  const bool wide = sp.team == 16;
+  auto kern = sp.f64 ? (wide ? k_density<true, 16> : k_density<true, 4>)
+                     : (wide ? k_density<false, 16> : k_density<false, 4>);
+  const int block = sp.team * kWave;
+  kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(
+      gas.nodes, gas.xm, gas.x64, gas.perm, gs, tm, sp.n_ngb, sp.h_tol, solve_h, sp.max_iter,
       sp.walk_leaf, sp.absmax, h, rho, drho_dh, omega, nngb, counters);
   return hipGetLastError();
 }
@@ -967,13 +928,21 @@ hipError_t launch_hydro_prep(Octree &gas, const float *vel, const float *u, cons
 }
 
 hipError_t launch_hydro(const Octree &gas, const Groups &gs, int64_t max_groups,
-                        const SphParams &sp, float *acc, float *dudt, float *vsig,
-                        int32_t *npairs, hipStream_t s, const float4 *ext, float alpha_u) {
+                        const SphParams &sp, const Terms &tm, float *acc, float *dudt,
+                        float *vsig, int32_t *npairs, hipStream_t s, const float4 *ext,
+                        float alpha_u) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = sp.f64 ? (ext ? k_hydro<true, true> : k_hydro<true, false>)
-                     : (ext ? k_hydro<false, true> : k_hydro<false, false>);
-  kern<<<persistent_grid((const void *)kern, kBlock, max_groups), kBlock, 0, s>>>(
-      gas.nodes, gas.xm, gas.x64, gas.h64, gas.vh, gas.aux, ext, gas.perm, gs, sp.alpha,
+  auto pick = [&](auto f64_c, auto ext_c) {
+    constexpr bool f = decltype(f64_c)::value, e = decltype(ext_c)::value;
+    return sp.team == 16 ? k_hydro<f, e, 16> : (sp.team == 4 ? k_hydro<f, e, 4> : k_hydro<f, e, 1>);
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  auto kern = sp.f64 ? (ext ? pick(yes, yes) : pick(yes, no))
+                     : (ext ? pick(no, yes) : pick(no, no));
+  const int block = (sp.team > 1 ? sp.team : 4) * kWave;
+  kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(
+      gas.nodes, gas.xm, gas.x64, gas.h64, gas.vh, gas.aux, ext, gas.perm, gs, tm, sp.alpha,
       alpha_u, sp.gamma - 1.0f, sp.walk_leaf, sp.absmax, acc, dudt, vsig, npairs);
   return hipGetLastError();
 }

@@ -245,7 +245,10 @@ __global__ void k_nodes(const uint64_t *__restrict__ keys, int64_t m,
     nd.com_m = make_float4(0.f, 0.f, 0.f, 0.f);
     nd.lo_h = make_float4(0.f, 0.f, 0.f, 0.f);
     nd.hi_l = make_float4(0.f, 0.f, 0.f, ldexpf(side, -l));
-    nd.meta = make_int4((int)skip, (int)p, (int)(end - p), l | (l == d ? kLeafBit : 0));
+    // the parent's member count is written by its parent's moments; a root
+    // has none and counts as inside an unbounded node
+    nd.meta = make_int4((int)skip, (int)p, (int)(end - p),
+                        l | (l == d ? kLeafBit : 0) | (l == 0 ? (int)0xffff0000u : 0));
     nodes[idx] = nd;
   }
 }
@@ -275,10 +278,12 @@ __global__ void k_moments_level(Node *__restrict__ nodes, double4 *__restrict__ 
       hi.x = fmaxf(hi.x, p.x); hi.y = fmaxf(hi.y, p.y); hi.z = fmaxf(hi.z, p.z);
     }
   } else {
+    const int pc = (int)((unsigned)min(meta.z, 65535) << 16);
     int64_t c = k + 1;
     while (c < meta.x) {
       const double4 cm = mom[c];
       const float4 clo = nodes[c].lo_h, chi = nodes[c].hi_l;
+      nodes[c].meta.w = (nodes[c].meta.w & 0xffff) | pc;
       M += cm.x;
       Sx += cm.y;
       Sy += cm.z;
@@ -354,6 +359,148 @@ __global__ __launch_bounds__(kBlock) void k_absmax(const double4 *__restrict__ x
 
 __global__ void k_zero_one(unsigned *p) {
   if (threadIdx.x == 0) *p = 0u;
+}
+
+// ---- terminal lists (see Terms)
+
+constexpr int kTermPer = 8;  // nodes per thread
+constexpr int kTermTile = kBlock * kTermPer;
+
+__device__ __forceinline__ bool is_terminal(int4 meta, int walk_leaf) {
+  return ((meta.w & kLeafBit) || meta.z <= walk_leaf) && (int)((unsigned)meta.w >> 16) > walk_leaf;
+}
+
+__device__ __forceinline__ int block_sum(int v, int *lds /* [kBlock / kWave] */) {
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) v += __shfl_xor(v, d);
+  if ((threadIdx.x & 63u) == 0u) lds[threadIdx.x >> 6] = v;
+  __syncthreads();
+  int t = 0;
+#pragma unroll
+  for (int k = 0; k < kBlock / kWave; ++k) t += lds[k];
+  __syncthreads();
+  return t;
+}
+
+__global__ __launch_bounds__(kBlock) void k_term_count(const Node *__restrict__ nodes, int nn,
+                                                       int walk_leaf,
+                                                       int32_t *__restrict__ bcount) {
+  __shared__ int lds[kBlock / kWave];
+  int c = 0;
+  for (int q = 0; q < kTermPer; ++q) {
+    const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
+    if (k < nn && is_terminal(nodes[k].meta, walk_leaf)) ++c;
+  }
+  c = block_sum(c, lds);
+  if (threadIdx.x == 0) bcount[blockIdx.x] = c;
+}
+
+// The terminals' node indices in tree order, and each snapshot's range of
+// them: a snapshot's root sets its first one and the end of the snapshot
+// before it.
+__global__ __launch_bounds__(kBlock) void k_term_write(
+    const Node *__restrict__ nodes, int nn, int walk_leaf, const int32_t *__restrict__ bcount,
+    const int32_t *__restrict__ nroot, int n_snap, int32_t *__restrict__ tnode,
+    int32_t *__restrict__ tcount, int2 *__restrict__ range) {
+  __shared__ int lds[kBlock / kWave];
+  int pre = 0;
+  for (int b = (int)threadIdx.x; b < (int)blockIdx.x; b += kBlock) pre += bcount[b];
+  int base = block_sum(pre, lds);
+  const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
+  for (int q = 0; q < kTermPer; ++q) {
+    const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
+    int4 meta = make_int4(0, 0, 0, 0);
+    if (k < nn) meta = nodes[k].meta;
+    const bool f = k < nn && is_terminal(meta, walk_leaf);
+    const uint64_t m = __ballot(f);
+    if (lane == 0) lds[w] = __popcll(m);
+    __syncthreads();
+    int at = base, tot = 0;
+#pragma unroll
+    for (int v = 0; v < kBlock / kWave; ++v) {
+      if (v < w) at += lds[v];
+      tot += lds[v];
+    }
+    at += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    if (f) tnode[at] = k;
+    if (k < nn && (meta.w & 255) == 0) {  // a root
+      if (n_snap == 1) {
+        range[0].x = at;
+      } else {
+        range[segment_of(nroot, n_snap, k)].x = at;
+        if (k > 0) range[segment_of(nroot, n_snap, k - 1)].y = at;
+      }
+    }
+    if (k == nn - 1) {
+      const int end = at + (f ? 1 : 0);
+      *tcount = end;
+      range[n_snap == 1 ? 0 : segment_of(nroot, n_snap, k)].y = end;
+    }
+    base += tot;
+    __syncthreads();
+  }
+}
+
+// Boxes, first members and (vh given) largest h of the terminals and their
+// windows: 16 lanes a terminal, a block a window. Bound by the latency of
+// the members' loads; one launch, where a refit of every node's largest h
+// takes one launch a level (11 of them, 5-6 us each, on 10^6 gas particles).
+constexpr int kFillBlock = 1024;
+__global__ __launch_bounds__(kFillBlock) void k_term_fill(
+    const Node *__restrict__ nodes, const int32_t *__restrict__ tnode,
+    const int32_t *__restrict__ tcount, const float4 *__restrict__ vh, int m,
+    float4 *__restrict__ lo, float4 *__restrict__ hi, float4 *__restrict__ wlo,
+    float4 *__restrict__ whi) {
+  __shared__ float4 sl[kWave], sh[kWave];
+  const int n = *tcount;
+  const int sub = (int)(threadIdx.x & 15u), q = (int)(threadIdx.x >> 4);
+  for (int b = (int)blockIdx.x; b * kWave < n; b += (int)gridDim.x) {
+    const int t = b * kWave + q;
+    float4 l = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+    float4 h = make_float4(-INFINITY, -INFINITY, -INFINITY, 0.f);
+    if (t < n) {
+      const Node &nd = nodes[tnode[t]];
+      const int4 meta = nd.meta;
+      l = nd.lo_h;
+      h = nd.hi_l;
+      float hm = 0.f;
+      if (vh)
+        for (int s = meta.y + sub; s < meta.y + meta.z; s += 16) hm = fmaxf(hm, vh[s].w);
+#pragma unroll
+      for (int d = 1; d < 16; d <<= 1) hm = fmaxf(hm, __shfl_xor(hm, d));
+      l.w = hm;
+      h.w = __int_as_float(meta.y);
+      if (sub == 0) {
+        lo[t] = l;
+        hi[t] = h;
+        if (t == n - 1) hi[n] = make_float4(0.f, 0.f, 0.f, __int_as_float(m));
+      }
+    }
+    if (sub == 0) {
+      sl[q] = l;
+      sh[q] = h;
+    }
+    __syncthreads();
+    if (threadIdx.x < (unsigned)kWave) {
+      float4 a = sl[threadIdx.x], c = sh[threadIdx.x];
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        a.x = fminf(a.x, __shfl_xor(a.x, d));
+        a.y = fminf(a.y, __shfl_xor(a.y, d));
+        a.z = fminf(a.z, __shfl_xor(a.z, d));
+        a.w = fmaxf(a.w, __shfl_xor(a.w, d));
+        c.x = fmaxf(c.x, __shfl_xor(c.x, d));
+        c.y = fmaxf(c.y, __shfl_xor(c.y, d));
+        c.z = fmaxf(c.z, __shfl_xor(c.z, d));
+      }
+      if (threadIdx.x == 0) {
+        wlo[b] = a;
+        whi[b] = c;
+      }
+    }
+    __syncthreads();
+  }
 }
 
 // The gravity walk's 32-byte node copies (after the moments).
@@ -564,6 +711,37 @@ hipError_t update_absmax(g3_tree *t, hipStream_t s) {
 hipError_t refit_hmax(Octree &o, hipStream_t s) {
   for (int l = o.max_level; l >= 0 && o.nnodes > 0; --l)
     k_hmax_level<<<nblk(o.nnodes), kBlock, 0, s>>>(o.nodes, o.nnodes, o.vh, l);
+  return hipGetLastError();
+}
+
+bool reserve_terms(g3_ctx *c, const Octree &o, int n_snap, TermBufs *b) {
+  const size_t nn = (size_t)o.nnodes, nw = nn / kWave + 2, nb = nn / kTermTile + 2;
+  const size_t f4 = 2 * (nn + 1) + 2 * nw;
+  char *p = (char *)scratch(c, kTermBuf, f4 * sizeof(float4) + (size_t)n_snap * sizeof(int2) +
+                                             (nn + nb + 4) * sizeof(int32_t));
+  if (!p) return false;
+  b->lo = (float4 *)p;
+  b->hi = b->lo + nn + 1;
+  b->wlo = b->hi + nn + 1;
+  b->whi = b->wlo + nw;
+  b->range = (int2 *)(b->whi + nw);
+  b->node = (int32_t *)(b->range + n_snap);
+  b->bcount = b->node + nn;
+  b->count = b->bcount + nb;
+  return true;
+}
+
+hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, const TermBufs &b,
+                       hipStream_t s) {
+  if (o.nnodes == 0) return hipSuccess;
+  const int nn = (int)o.nnodes;
+  const unsigned nb = (unsigned)((nn + kTermTile - 1) / kTermTile);
+  k_term_count<<<nb, kBlock, 0, s>>>(o.nodes, nn, walk_leaf, b.bcount);
+  k_term_write<<<nb, kBlock, 0, s>>>(o.nodes, nn, walk_leaf, b.bcount, o.nroot, n_snap, b.node,
+                                     b.count, b.range);
+  const unsigned nf = (unsigned)std::min<int64_t>((nn + kWave - 1) / kWave, 512);
+  k_term_fill<<<nf, kFillBlock, 0, s>>>(o.nodes, b.node, b.count, with_h ? o.vh : nullptr,
+                                        (int)o.n, b.lo, b.hi, b.wlo, b.whi);
   return hipGetLastError();
 }
 

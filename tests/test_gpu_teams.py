@@ -1,0 +1,126 @@
+"""Teams of waves that serve one group (density, hydro force): the terminal
+list, its windows and the tiles at the sizes where they can go wrong, against
+the oracle, and the same bits from every team size.
+
+Tolerances: counts exact; the density within 2e-6 of the FP64 sums (FP32 terms
+of one sign, each good to a few 1e-7, added with compensation), the hydro
+acceleration within 1e-5 of the L1 sum of its terms, as the parity tests have.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2003_10850_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def dev_t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2003_10850_amd import ops
+    return ops.Context(torch.device("cuda", 0))
+
+
+def gas_set(kind, n, seed=3):
+    rng = np.random.default_rng(seed)
+    pos = rng.random((n, 3))
+    if kind == "coincident":  # one leaf larger than a tile and a round
+        pos[: n - n // 4] = 0.371
+    elif kind == "line":  # wide groups, many terminals each
+        pos[:, 1:] = 0.5 + 1e-3 * pos[:, 1:]
+    return pos.astype(np.float32)
+
+
+def check(ctx, pos, h, p, box, snap_off=None, act=None):
+    """Density at given h and hydro of one set (or forest) with the oracle,
+    snapshot by snapshot."""
+    from paper_2003_10850_amd import ops
+    n = len(pos)
+    rng = np.random.default_rng(11)
+    mass = np.full(n, 1.0 / n, np.float32)
+    vel = rng.normal(0, 0.1, (n, 3)).astype(np.float32)
+    u, rho, om = [rng.uniform(0.5, 1.5, n).astype(np.float32) for _ in range(3)]
+    off = [0, n] if snap_off is None else list(snap_off)
+    boxes = [box] if snap_off is None else box
+    tree = ops.Tree(ctx, dev_t(pos), dev_t(mass), None, box, p, snap_off=snap_off)
+    a_dev = None if act is None else dev_t(act)
+    d = ops.density(tree, h=dev_t(h), active=a_dev, solve_h=False)
+    f = ops.hydro_force(tree, dev_t(vel), dev_t(u), dev_t(h), dev_t(rho), dev_t(om), active=a_dev)
+    act = np.arange(n) if act is None else act
+    for k, b in enumerate(boxes):
+        r = slice(off[k], off[k + 1])
+        a = act[(act >= off[k]) & (act < off[k + 1])] - off[k]
+        if a.size == 0:
+            continue
+        t = oracle.Tree(pos[r].astype(np.float64), mass[r].astype(np.float64), b,
+                        type=np.zeros(off[k + 1] - off[k], np.uint8), gas_only=True)
+        ref = oracle.density(t, p, active=a, h=h[r].astype(np.float64), solve_h=False)
+        got = {q: v.cpu().numpy()[r] for q, v in {**d, **f}.items()}
+        np.testing.assert_array_equal(got["nngb"][a], ref["nngb"][a])
+        assert (np.abs(got["rho"][a] - ref["rho"][a]) / ref["rho"][a]).max() < 2e-6
+        ry = oracle.hydro(t, p, vel[r], u[r], h[r].astype(np.float64), rho[r].astype(np.float64),
+                          om[r].astype(np.float64), active=a)
+        np.testing.assert_array_equal(got["npairs"][a], ry["npairs"][a])
+        S = ry["S"][a]
+        err = np.linalg.norm(got["acc"][a] - ry["acc"][a], axis=1)
+        assert (err[S > 0] / S[S > 0]).max(initial=0) < 1e-5
+
+
+@pytest.mark.parametrize("kind,n", [("uniform", 1), ("uniform", 2), ("uniform", 63),
+                                    ("uniform", 65), ("uniform", 129), ("uniform", 4100),
+                                    ("coincident", 5000), ("line", 3000)])
+def test_sets_against_oracle(ctx, kind, n):
+    print(f"teams {kind} n={n}", flush=True)
+    p = inputs.Params(n_ngb=64.0)
+    rng = np.random.default_rng(n)
+    h = (min(1.0, 0.9 * n ** (-1.0 / 3.0) * 2.5) * rng.uniform(0.4, 1.6, n)).astype(np.float32)
+    check(ctx, gas_set(kind, n), h, p, (0.0, 0.0, 0.0, 1.0))
+
+
+def test_forest_of_uneven_snapshots_against_oracle(ctx):
+    # snapshots' terminals share windows; one snapshot is empty, one has one particle
+    sizes = [1, 200, 0, 3000, 70, 64, 900]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    rng = np.random.default_rng(5)
+    boxes, pos = [], []
+    for k, m in enumerate(sizes):
+        boxes.append((float(k), 0.0, 0.0, 1.0))
+        pos.append(rng.random((m, 3)) + [k, 0, 0])
+    pos = np.concatenate(pos).astype(np.float32)
+    h = np.concatenate([np.full(m, 2.3 * max(m, 1) ** (-1.0 / 3.0)) for m in sizes])
+    act = np.sort(rng.choice(len(pos), 1700, replace=False)).astype(np.int32)
+    check(ctx, pos, h.astype(np.float32), inputs.Params(n_ngb=64.0), boxes, off, act)
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+def test_every_team_size_gives_the_same_bits(ctx, fp64):
+    # 2^19 targets in unsplit groups take teams of 4; the first 2^15 in tree
+    # order form the same groups and take teams of 16 (the hydro force of 2^20
+    # targets takes no team)
+    from paper_2003_10850_amd import g3, ops
+    n = 1 << (19 if fp64 else 20)
+    w = inputs.uniform(n=n, seed=21)
+    pos = w.pos if fp64 else w.pos.astype(np.float32)
+    ht = torch.float64 if fp64 else torch.float32
+    p = inputs.Params(n_ngb=48.0)
+    c = ops.Context(torch.device("cuda", 0))
+    c.set_tuning(g3.G3_TUNE_DENSITY, 128, -1)
+    tree = ops.Tree(c, dev_t(pos), dev_t(w.mass.astype(np.float32)), None, tuple(w.box), p)
+    order = tree.export(1)["order"]
+    few = torch.sort(order[: 1 << 15]).values
+    g = torch.Generator(device="cuda").manual_seed(2)
+    R = lambda *s: torch.rand(*s, generator=g, device="cuda")
+    h = (2.25 * n ** (-1.0 / 3.0) * (0.8 + 0.4 * R(n))).to(ht)
+    vel, u, rho, om = R(n, 3) - 0.5, 0.5 + R(n), 0.5 + R(n), 0.5 + R(n)
+    all_d, few_d = ops.density(tree, h=h), ops.density(tree, h=h, active=few)
+    all_f = ops.hydro_force(tree, vel, u, h, rho, om)
+    few_f = ops.hydro_force(tree, vel, u, h, rho, om, active=few)
+    at = few.long()
+    for a, b in ((all_d, few_d), (all_f, few_f)):
+        for k in a:
+            assert torch.equal(a[k][at], b[k][at]), k
