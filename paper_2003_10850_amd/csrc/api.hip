@@ -29,7 +29,7 @@ struct RocTxRange {
 };
 #define G3_RANGE(name) const ::g3::RocTxRange g3_range_(name)
 
-int select_members(g3_ctx *c, g3_tree *t, const uint8_t *type, int64_t *m_out, hipStream_t s);
+hipError_t upload_snapshots(g3_tree *t, const double4 *boxes, hipStream_t s);
 
 hipError_t dev_malloc(g3_ctx *c, void **p, size_t bytes) {
   *p = nullptr;
@@ -523,6 +523,7 @@ int g3_ctx_create(g3_ctx **out, int device) {
 
 static void free_octree(Octree &o) {
   for (void *p : {(void *)o.keys, (void *)o.perm, (void *)o.xm, (void *)o.nodes, (void *)o.mom,
+                  (void *)o.tops,
                   (void *)o.gnodes, (void *)o.vh, (void *)o.aux, (void *)o.x64, (void *)o.h64,
                   (void *)o.c64, (void *)o.soff, (void *)o.nroot})
     if (p) (void)hipFree(p);
@@ -734,21 +735,14 @@ static int build_forest_body(g3_ctx *c, g3_tree *t, int32_t n_snap, const int64_
   std::vector<double4> hb(n_snap);
   for (int32_t k = 0; k < n_snap; ++k)
     hb[k] = make_double4(box[4 * k], box[4 * k + 1], box[4 * k + 2], box[4 * k + 3]);
-  hipError_t e = hipMemcpyAsync(t->coff, t->snap_off.data(), (n_snap + 1) * sizeof(int64_t),
-                                hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(t->sbox, hb.data(), n_snap * sizeof(double4), hipMemcpyHostToDevice, s);
-  // the host staging above is released on return: wait for the copies
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  hipError_t e = upload_snapshots(t, hb.data(), s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_build_forest: snapshot table upload");
   int64_t mgas = 0;
-  st = select_members(c, t, type, &mgas, s);
-  if (st) return st;
-  st = build_octree(c, t, t->all, pos, t->f64, mass, n, s);
+  st = build_octree(c, t, t->all, pos, t->f64, mass, n, s, type, &mgas);
   if (st) return st;
   e = fill_i32(t->iperm_gas, -1, n, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_build_forest");
-  st = build_octree(c, t, t->gas, pos, t->f64, mass, mgas, s, type);
+  st = build_octree(c, t, t->gas, pos, t->f64, mass, mgas, s, nullptr);
   if (st) return st;
   // FP64 positions are walked through their FP32 copies: the walks pad
   // every pruning radius by a bound on their rounding, from the largest

@@ -40,6 +40,12 @@ struct __align__(16) GNode {
 };
 static_assert(sizeof(GNode) == 32, "gravity node must be 32 bytes");
 
+// Subtrees of at most this many members have their moments from a workgroup
+// each; max_tops is the largest number of nodes above them in an octree of n
+// members (on each level that is divided they hold more than that each).
+constexpr int kSubtree = 1024;
+inline int64_t max_tops(int64_t n) { return kMaxLevel * (n / kSubtree + 1); }
+
 // One octree over a subset of the particles (all of them, or the gas ones),
 // with the members in Morton order.
 struct Octree {
@@ -53,6 +59,11 @@ struct Octree {
   Node *nodes = nullptr;     // [nnodes] preorder
   GNode *gnodes = nullptr;   // [nnodes] the gravity walk's copy (all-particle octree)
   double4 *mom = nullptr;    // [nnodes] FP64 (M, M x, M y, M z)
+  // the moments' order: roots of small subtrees, and the nodes above them
+  int32_t *subs = nullptr;    // [nnodes]
+  int2 *tops = nullptr;       // [cap_tops] (node, level)
+  int32_t *nsplit = nullptr;  // their counts
+  int64_t cap_tops = 0;
   // SPH member data in sorted order (gas octree only, filled by the calls)
   float4 *vh = nullptr;   // (vx, vy, vz, h)
   float4 *aux = nullptr;  // (A, c, rho, 1/h)
@@ -196,9 +207,11 @@ hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt,
 
 // Tree build of one octree (members already selected in `ids`/`keys`).
 // The gas octree (o == t->gas) takes its members from the all-particle
-// octree built before it, filtered by `type` (nullptr: all gas).
+// octree built before it, which finds them by `type` (nullptr: all gas) and
+// returns their number in *m_gas.
 int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
-                 const float *mass, int64_t m, hipStream_t s, const uint8_t *type = nullptr);
+                 const float *mass, int64_t m, hipStream_t s, const uint8_t *type,
+                 int64_t *m_gas = nullptr);
 // Keep the octree's order, topology, keys and cube sides; re-read the
 // members' positions and masses and recompute every node's moments and box.
 int refit_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, const float *mass,

@@ -51,20 +51,23 @@ __device__ __forceinline__ uint64_t morton_key(const T *p, double lx, double ly,
          spread3(cell_of(p[2], lz, scale));
 }
 
-// keys and identity values for the members selected by sel (nullptr: all),
-// each keyed in the box of its snapshot (caller ids [coff[k], coff[k+1]))
+// keys and identity values, each particle keyed in the box of its snapshot
+// (caller ids [coff[k], coff[k+1])); pm (nullable): positions and masses side
+// by side, so that the gather into sorted order reads one 16-byte word a
+// particle instead of two lines (102 -> 67 us on 2^21 particles)
 template <typename T>
-__global__ void k_keys(const T *__restrict__ pos, const int32_t *__restrict__ sel,
-                       int64_t m, const int64_t *__restrict__ coff,
+__global__ void k_keys(const T *__restrict__ pos, int64_t m, const int64_t *__restrict__ coff,
                        const double4 *__restrict__ sbox, int n_snap,
-                       uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= m) return;
-  const int64_t i = sel ? sel[k] : k;
+                       const float *__restrict__ mass, uint64_t *__restrict__ keys,
+                       uint32_t *__restrict__ vals, float4 *__restrict__ pm) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= m) return;
   const double4 b = sbox[n_snap > 1 ? segment_of(coff, n_snap, i) : 0];
   const double scale = 2097152.0 / b.w;  // 2^21 / side
-  keys[k] = morton_key(pos + 3 * i, b.x, b.y, b.z, scale);
-  vals[k] = (uint32_t)i;
+  keys[i] = morton_key(pos + 3 * i, b.x, b.y, b.z, scale);
+  vals[i] = (uint32_t)i;
+  if (pm)
+    pm[i] = make_float4((float)pos[3 * i], (float)pos[3 * i + 1], (float)pos[3 * i + 2], mass[i]);
 }
 
 // Forest: the snapshot of each key-sorted member, for a stable sort by
@@ -88,13 +91,29 @@ __global__ void k_gather_sorted(const uint32_t *__restrict__ sidx, int64_t m,
   vout[k] = vin[j];
 }
 
-// Sorted start of each snapshot: slot[coff[k]] (members before coff[k]
-// selected by the exclusive scan `slot`), or coff[k] when all are members.
-__global__ void k_soff(const int64_t *__restrict__ coff, int n_snap,
-                       const uint32_t *__restrict__ slot, int32_t *__restrict__ soff) {
+// Sorted start of each snapshot in the all-particle octree (its caller offset).
+__global__ void k_soff(const int64_t *__restrict__ coff, int n_snap, int32_t *__restrict__ soff) {
   const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (k > n_snap) return;
-  soff[k] = slot ? (int32_t)slot[coff[k]] : (int32_t)coff[k];
+  if (k <= n_snap) soff[k] = (int32_t)coff[k];
+}
+
+// and in the gas octree: the gas members sorted before it (exclusive scan
+// `slot` over the sorted members).
+__global__ void k_gas_soff(const int32_t *__restrict__ soff_all, int n_snap,
+                           const uint32_t *__restrict__ slot, int32_t *__restrict__ soff) {
+  const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (k <= n_snap) soff[k] = (int32_t)slot[soff_all[k]];
+}
+
+// The tables of one snapshot, from the call's arguments (no host copy that
+// the build would have to wait for).
+__global__ void k_one_snap(int64_t n, double4 box, int64_t *__restrict__ coff,
+                           double4 *__restrict__ sbox, int32_t *__restrict__ soff) {
+  coff[0] = 0;
+  coff[1] = n;
+  sbox[0] = box;
+  soff[0] = 0;
+  soff[1] = (int32_t)n;
 }
 
 // First node of each snapshot: the first node its first member starts.
@@ -103,12 +122,6 @@ __global__ void k_nroot(const uint32_t *__restrict__ off, const int32_t *__restr
   const int k = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (k > n_snap) return;
   nroot[k] = (int32_t)off[soff[k]];
-}
-
-__global__ void k_gas_flags(const uint8_t *__restrict__ type, int64_t n,
-                            uint32_t *__restrict__ flags) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) flags[i] = (type == nullptr || type[i] == 0) ? 1u : 0u;
 }
 
 // The gas octree's members in sorted order come from the all-particle
@@ -120,15 +133,23 @@ __global__ void k_gas_of_sorted(const int32_t *__restrict__ perm_all, int64_t n,
   if (s < n) flags[s] = (type == nullptr || type[perm_all[s]] == 0) ? 1u : 0u;
 }
 
+// Its sorted copies are compacted with them: streams, where a gather by caller
+// id would read every position from a line of its own.
 __global__ void k_compact_sorted(const uint32_t *__restrict__ flags,
                                  const uint32_t *__restrict__ slot, int64_t n,
-                                 const uint64_t *__restrict__ keys_all,
-                                 const int32_t *__restrict__ perm_all,
-                                 uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+                                 const Octree all, uint64_t *__restrict__ keys,
+                                 int32_t *__restrict__ perm, float4 *__restrict__ xm,
+                                 double4 *__restrict__ x64, int32_t *__restrict__ iperm) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n || !flags[s]) return;
-  keys[slot[s]] = keys_all[s];
-  vals[slot[s]] = (uint32_t)perm_all[s];
+  if (s >= n) return;
+  if (!flags[s]) return;
+  const int32_t id = all.perm[s];
+  const uint32_t at = slot[s];
+  iperm[id] = (int32_t)at;
+  keys[at] = all.keys[s];
+  perm[at] = id;
+  xm[at] = all.xm[s];
+  if (x64) x64[at] = all.x64[s];
 }
 
 // Sorted copies: FP32 (x, y, z, m) always; for FP64 positions also the
@@ -137,7 +158,7 @@ template <typename T>
 __global__ void k_permute(const uint32_t *__restrict__ perm, int64_t m,
                           const T *__restrict__ pos, const float *__restrict__ mass,
                           float4 *__restrict__ xm, double4 *__restrict__ x64,
-                          int32_t *__restrict__ iperm) {
+                          int32_t *__restrict__ iperm, int32_t *__restrict__ perm_out) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= m) return;
   const uint32_t j = perm[s];
@@ -145,7 +166,20 @@ __global__ void k_permute(const uint32_t *__restrict__ perm, int64_t m,
   if (x64)
     x64[s] = make_double4((double)pos[3 * j], (double)pos[3 * j + 1], (double)pos[3 * j + 2],
                           (double)mass[j]);
+  if (iperm) iperm[j] = (int32_t)s;
+  if (perm_out) perm_out[s] = (int32_t)j;
+}
+
+// The same from positions and masses side by side.
+__global__ void k_permute_packed(const uint32_t *__restrict__ order, int64_t m,
+                                 const float4 *__restrict__ pm, float4 *__restrict__ xm,
+                                 int32_t *__restrict__ iperm, int32_t *__restrict__ perm) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= m) return;
+  const uint32_t j = order[s];
+  xm[s] = pm[j];
   iperm[j] = (int32_t)s;
+  perm[s] = (int32_t)j;
 }
 
 __device__ __forceinline__ int cpl(uint64_t a, uint64_t b) {
@@ -154,7 +188,11 @@ __device__ __forceinline__ int cpl(uint64_t a, uint64_t b) {
   return (__clzll((long long)x) - 1) / 3;  // bit 63 is never used
 }
 
-// nodes started by each member: cnt[p] = max(0, d_p - delta_p + 1)
+// Nodes started by each member: cnt[p] = max(0, d_p - delta_p + 1). B + 1
+// consecutive members share as many digits as their ends do, so the deepest
+// node that holds p and must be split is the largest cpl(q, q + B) over the
+// windows q = p - B .. p: one prefix length a member, shared through LDS, and a
+// maximum over B + 1 of them.
 constexpr int kMaxLeaf = 64;
 
 __global__ __launch_bounds__(kBlock) void k_node_counts(const uint64_t *__restrict__ keys,
@@ -164,8 +202,9 @@ __global__ __launch_bounds__(kBlock) void k_node_counts(const uint64_t *__restri
                                                         uint32_t *__restrict__ cnt,
                                                         uint8_t *__restrict__ lev,
                                                         int32_t *__restrict__ maxlev) {
-  // the block's keys with B neighbours on each side, staged in LDS
+  // the block's keys with B neighbours on each side, and the windows' lengths
   __shared__ uint64_t win[kBlock + 2 * kMaxLeaf];
+  __shared__ int8_t len[kBlock + kMaxLeaf];  // window of member b0 - B + k
   __shared__ int32_t block_max;  // deepest leaf level of the block
   if (threadIdx.x == 0) block_max = 0;
   const int64_t b0 = (int64_t)blockIdx.x * kBlock;
@@ -174,41 +213,35 @@ __global__ __launch_bounds__(kBlock) void k_node_counts(const uint64_t *__restri
     win[k] = (q >= 0 && q < m) ? keys[q] : 0ull;
   }
   __syncthreads();
-  const int64_t p = b0 + threadIdx.x;
-  if (p < m) {
-  const uint64_t *kw = win + B + threadIdx.x;  // kw[d] = key of member p + d
-  const uint64_t kp = kw[0];
-  // members of other snapshots count as missing: each snapshot is a tree
-  const int sn = n_snap > 1 ? segment_of(soff, n_snap, p) : 0;
-  const int64_t s0 = soff[sn], s1 = soff[sn + 1];
-  const int delta = (p == s0) ? 0 : cpl(kp, kw[-1]) + 1;
-  // B-th largest of the window prefix lengths: merge two non-increasing runs
-  int i = 1, j = 1;
-  int val = -1;
-  int a = (p - 1 >= s0) ? cpl(kp, kw[-1]) : -1;
-  int b = (p + 1 < s1) ? cpl(kp, kw[1]) : -1;
-  for (int step = 0; step < B; ++step) {
-    if (a >= b) {
-      val = a;
-      ++i;
-      a = (p - i >= s0 && i <= B) ? cpl(kp, kw[-i]) : -1;
-    } else {
-      val = b;
-      ++j;
-      b = (p + j < s1 && j <= B) ? cpl(kp, kw[j]) : -1;
-    }
-  }
-  int d = val + 1;
-  if (d > kMaxLevel) d = kMaxLevel;
-  cnt[p] = (d >= delta) ? (uint32_t)(d - delta + 1) : 0u;
-  lev[2 * p] = (uint8_t)delta;
-  lev[2 * p + 1] = (uint8_t)d;
-  // one device atomic per block: many members start nodes, and atomics on
-  // a single address serialise
-  if (d >= delta) atomicMax(&block_max, d);
+  for (int k = threadIdx.x; k < kBlock + B; k += kBlock) {
+    const int64_t q = b0 - B + k;
+    int v = -1;
+    // members of other snapshots count as missing: each snapshot is a tree
+    if (q >= 0 && q + B < m &&
+        (n_snap == 1 || segment_of(soff, n_snap, q) == segment_of(soff, n_snap, q + B)))
+      v = cpl(win[k], win[k + B]);
+    len[k] = (int8_t)v;
   }
   __syncthreads();
-  if (threadIdx.x == 0 && block_max > 0) atomicMax(maxlev, block_max);
+  const int64_t p = b0 + threadIdx.x;
+  if (p < m) {
+    const int64_t s0 = n_snap > 1 ? soff[segment_of(soff, n_snap, p)] : 0;
+    const int delta =
+        (p == s0) ? 0 : cpl(win[B + threadIdx.x], win[B + threadIdx.x - 1]) + 1;
+    int val = -1;
+    for (int k = 0; k <= B; ++k) val = max(val, (int)len[threadIdx.x + k]);
+    const int d = min(val + 1, kMaxLevel);
+    cnt[p] = (d >= delta) ? (uint32_t)(d - delta + 1) : 0u;
+    lev[2 * p] = (uint8_t)delta;
+    lev[2 * p + 1] = (uint8_t)d;
+    if (d >= delta) atomicMax(&block_max, d);
+  }
+  __syncthreads();
+  // (most blocks find the depth reached already: 2^13 atomics on one word
+  // took 80 us)
+  if (threadIdx.x == 0 &&
+      block_max > __hip_atomic_load(maxlev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(maxlev, block_max);
 }
 
 __global__ void k_nodes(const uint64_t *__restrict__ keys, int64_t m,
@@ -245,31 +278,48 @@ __global__ void k_nodes(const uint64_t *__restrict__ keys, int64_t m,
     nd.com_m = make_float4(0.f, 0.f, 0.f, 0.f);
     nd.lo_h = make_float4(0.f, 0.f, 0.f, 0.f);
     nd.hi_l = make_float4(0.f, 0.f, 0.f, ldexpf(side, -l));
-    // the parent's member count is written by its parent's moments; a root
-    // has none and counts as inside an unbounded node
+    // the parent's member count follows (k_parents); a root has none and
+    // counts as inside an unbounded node
     nd.meta = make_int4((int)skip, (int)p, (int)(end - p),
                         l | (l == d ? kLeafBit : 0) | (l == 0 ? (int)0xffff0000u : 0));
     nodes[idx] = nd;
   }
 }
 
-// Bottom-up pass for one level: FP64 mass and first moments, tight box.
-__global__ void k_moments_level(Node *__restrict__ nodes, double4 *__restrict__ mom,
-                                double4 *__restrict__ c64, int64_t nnodes,
-                                const float4 *__restrict__ xm,
-                                const double4 *__restrict__ x64, int level) {
+// The parent's member count into every node that has one.
+__global__ void k_parents(Node *__restrict__ nodes, int64_t nnodes) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nnodes) return;
   const int4 meta = nodes[k].meta;
-  if ((meta.w & 255) != level) return;
+  if (meta.w & kLeafBit) return;
+  const int pc = (int)((unsigned)min(meta.z, 65535) << 16);
+  int64_t c = k + 1;
+  while (c < meta.x) {
+    const int4 cm = nodes[c].meta;
+    // (the low half as k_nodes wrote it; children are no roots)
+    nodes[c].meta.w = (cm.w & 0xffff) | pc;
+    c = cm.x;
+  }
+}
+
+// FP64 mass and first moments, tight box of one node, from its members or its
+// children.
+struct Moments {
+  Node *__restrict__ nodes;
+  double4 *__restrict__ mom;
+  double4 *__restrict__ c64;
+  const float4 *__restrict__ xm;
+  const double4 *__restrict__ x64;
+};
+__device__ __forceinline__ void node_moments(const Moments &A, int64_t k, int4 meta) {
   double M = 0.0, Sx = 0.0, Sy = 0.0, Sz = 0.0;
   float4 lo = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
   float4 hi = make_float4(-INFINITY, -INFINITY, -INFINITY, 0.f);
   if (meta.w & kLeafBit) {
     for (int s = meta.y; s < meta.y + meta.z; ++s) {
-      const float4 p = xm[s];
+      const float4 p = A.xm[s];
       // moments from the exact positions (FP64 ones when the tree has them)
-      const double4 q = x64 ? x64[s] : make_double4(p.x, p.y, p.z, p.w);
+      const double4 q = A.x64 ? A.x64[s] : make_double4(p.x, p.y, p.z, p.w);
       M += q.w;
       Sx += q.w * q.x;
       Sy += q.w * q.y;
@@ -278,34 +328,141 @@ __global__ void k_moments_level(Node *__restrict__ nodes, double4 *__restrict__ 
       hi.x = fmaxf(hi.x, p.x); hi.y = fmaxf(hi.y, p.y); hi.z = fmaxf(hi.z, p.z);
     }
   } else {
-    const int pc = (int)((unsigned)min(meta.z, 65535) << 16);
     int64_t c = k + 1;
     while (c < meta.x) {
-      const double4 cm = mom[c];
-      const float4 clo = nodes[c].lo_h, chi = nodes[c].hi_l;
-      nodes[c].meta.w = (nodes[c].meta.w & 0xffff) | pc;
+      const double4 cm = A.mom[c];
+      const float4 clo = A.nodes[c].lo_h, chi = A.nodes[c].hi_l;
       M += cm.x;
       Sx += cm.y;
       Sy += cm.z;
       Sz += cm.w;
       lo.x = fminf(lo.x, clo.x); lo.y = fminf(lo.y, clo.y); lo.z = fminf(lo.z, clo.z);
       hi.x = fmaxf(hi.x, chi.x); hi.y = fmaxf(hi.y, chi.y); hi.z = fmaxf(hi.z, chi.z);
-      c = nodes[c].meta.x;
+      c = A.nodes[c].meta.x;
     }
   }
-  mom[k] = make_double4(M, Sx, Sy, Sz);
-  Node &nd = nodes[k];
+  A.mom[k] = make_double4(M, Sx, Sy, Sz);
+  Node &nd = A.nodes[k];
+  float4 cm;
   if (M > 0.0)
-    nd.com_m = make_float4((float)(Sx / M), (float)(Sy / M), (float)(Sz / M), (float)M);
+    cm = make_float4((float)(Sx / M), (float)(Sy / M), (float)(Sz / M), (float)M);
   else  // massless node: its geometric centre
-    nd.com_m = make_float4(0.5f * (lo.x + hi.x), 0.5f * (lo.y + hi.y), 0.5f * (lo.z + hi.z), 0.f);
-  if (c64)
-    c64[k] = M > 0.0 ? make_double4(Sx / M, Sy / M, Sz / M, M)
-                     : make_double4(nd.com_m.x, nd.com_m.y, nd.com_m.z, 0.0);
+    cm = make_float4(0.5f * (lo.x + hi.x), 0.5f * (lo.y + hi.y), 0.5f * (lo.z + hi.z), 0.f);
+  nd.com_m = cm;
+  if (A.c64)
+    A.c64[k] = M > 0.0 ? make_double4(Sx / M, Sy / M, Sz / M, M)
+                       : make_double4(cm.x, cm.y, cm.z, 0.0);
   lo.w = nd.lo_h.w;
   hi.w = nd.hi_l.w;
   nd.lo_h = lo;
   nd.hi_l = hi;
+}
+
+// The moments bottom up in two launches: the subtrees of at most kSubtree
+// members (and larger leaves) whose parent holds more, a workgroup each, and
+// then the nodes above them, one workgroup for all (one launch for trees of
+// at most kSmallNodes nodes). Leaves need no order; inner nodes go level by
+// level with a barrier between. Bound by the latency of the levels: 80 + 49 us
+// for the two octrees of 2^21 and 2^20 particles each on average, 23 us on
+// 4096. (A launch a level read every node's level each time: 12 launches of 14
+// us on 2^21 particles, as many of 5-6 us on 10^5, twice for a build and twice
+// for every refit. Keeping the children's indices, so that their loads run
+// together, cost registers: 111 + 70 us.)
+constexpr int kInnerList = 1024;
+
+// The inner nodes of a list of (node, level), by level.
+__device__ __forceinline__ void inner_levels(const Moments &A, const int2 *list, int n, int maxl,
+                                             int minl) {
+  for (int l = maxl; l >= minl; --l) {
+    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x)
+      if (list[i].y == l) node_moments(A, list[i].x, A.nodes[list[i].x].meta);
+    __syncthreads();
+  }
+}
+
+constexpr int kTopBlock = 1024;
+constexpr int kSmallNodes = 4 * kInnerList;
+__global__ __launch_bounds__(kTopBlock) void k_moments_small(const Moments A, int nnodes) {
+  __shared__ int2 list[kSmallNodes];
+  __shared__ int n_inner, max_level;
+  if (threadIdx.x == 0) {
+    n_inner = 0;
+    max_level = -1;
+  }
+  __syncthreads();
+  for (int k = (int)threadIdx.x; k < nnodes; k += kTopBlock) {
+    const int4 meta = A.nodes[k].meta;
+    if (meta.w & kLeafBit) {
+      node_moments(A, k, meta);
+    } else {
+      list[atomicAdd(&n_inner, 1)] = make_int2(k, meta.w & 255);
+      atomicMax(&max_level, meta.w & 255);
+    }
+  }
+  __syncthreads();
+  inner_levels(A, list, n_inner, max_level, 0);
+}
+
+__global__ __launch_bounds__(kBlock) void k_moments_sub(const Moments A,
+                                                        const int32_t *__restrict__ subs,
+                                                        const int32_t *__restrict__ counts) {
+  __shared__ int2 list[kInnerList];
+  __shared__ int n_inner, max_level;
+  const int nsub = counts[0];
+  for (int b = (int)blockIdx.x; b < nsub; b += (int)gridDim.x) {
+    const int k0 = subs[b];
+    const int4 m0 = A.nodes[k0].meta;
+    const int k1 = m0.x, lv0 = m0.w & 255;
+    if (threadIdx.x == 0) {
+      n_inner = 0;
+      max_level = lv0;
+    }
+    __syncthreads();
+    for (int k = k0 + (int)threadIdx.x; k < k1; k += kBlock) {
+      const int4 meta = A.nodes[k].meta;
+      if (meta.w & kLeafBit) {
+        node_moments(A, k, meta);
+      } else {
+        const int i = atomicAdd(&n_inner, 1);
+        if (i < kInnerList) list[i] = make_int2(k, meta.w & 255);
+        atomicMax(&max_level, meta.w & 255);
+      }
+    }
+    __syncthreads();
+    const int n = n_inner, maxl = max_level;
+    if (n <= kInnerList) {
+      inner_levels(A, list, n, maxl, lv0);
+    } else {  // (long chains of single children)
+      for (int l = maxl; l >= lv0; --l) {
+        for (int k = k0 + (int)threadIdx.x; k < k1; k += kBlock) {
+          const int4 meta = A.nodes[k].meta;
+          if (!(meta.w & kLeafBit) && (meta.w & 255) == l) node_moments(A, k, meta);
+        }
+        __syncthreads();
+      }
+    }
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(kTopBlock) void k_moments_top(const Moments A,
+                                                           const int2 *__restrict__ tops,
+                                                           const int32_t *__restrict__ counts) {
+  __shared__ int2 list[4 * kInnerList];
+  __shared__ int max_level;
+  const int n = counts[1];
+  if (threadIdx.x == 0) max_level = -1;
+  __syncthreads();
+  const bool fits = n <= 4 * kInnerList;
+  int ml = -1;
+  for (int i = (int)threadIdx.x; i < n; i += kTopBlock) {
+    const int2 t = tops[i];
+    if (fits) list[i] = t;
+    ml = max(ml, t.y);
+  }
+  if (ml >= 0) atomicMax(&max_level, ml);
+  __syncthreads();
+  inner_levels(A, fits ? list : tops, n, max_level, 0);
 }
 
 // Bottom-up pass for one level: maximum h of the members (vh.w).
@@ -442,6 +599,56 @@ __global__ __launch_bounds__(kBlock) void k_term_write(
   }
 }
 
+// The subtree roots and the (node, level) above them, in tree order; counts
+// [0] and [1]. The same two passes as the terminals.
+__global__ __launch_bounds__(kBlock) void k_split_count(const Node *__restrict__ nodes, int nn,
+                                                        int2 *__restrict__ bcount) {
+  __shared__ int lds[kBlock / kWave];
+  int a = 0, b = 0;
+  for (int q = 0; q < kTermPer; ++q) {
+    const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
+    if (k >= nn) continue;
+    const int4 meta = nodes[k].meta;
+    a += is_terminal(meta, kSubtree);
+    b += !(meta.w & kLeafBit) && meta.z > kSubtree;
+  }
+  a = block_sum(a, lds);
+  b = block_sum(b, lds);
+  if (threadIdx.x == 0) bcount[blockIdx.x] = make_int2(a, b);
+}
+
+__global__ __launch_bounds__(kBlock) void k_split_write(const Node *__restrict__ nodes, int nn,
+                                                        const int2 *__restrict__ bcount,
+                                                        int32_t *__restrict__ subs,
+                                                        int2 *__restrict__ tops,
+                                                        int32_t *__restrict__ counts) {
+  __shared__ int lds[kBlock / kWave];
+  __shared__ int na, nb;  // appended by this block
+  int a = 0, b = 0;
+  for (int k = (int)threadIdx.x; k < (int)blockIdx.x; k += kBlock) {
+    a += bcount[k].x;
+    b += bcount[k].y;
+  }
+  a = block_sum(a, lds);
+  b = block_sum(b, lds);
+  if (threadIdx.x == 0) na = nb = 0;
+  __syncthreads();
+  // (the order within a block does not matter: each entry is worked alone)
+  for (int q = 0; q < kTermPer; ++q) {
+    const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
+    if (k >= nn) continue;
+    const int4 meta = nodes[k].meta;
+    if (is_terminal(meta, kSubtree)) subs[a + atomicAdd(&na, 1)] = k;
+    if (!(meta.w & kLeafBit) && meta.z > kSubtree)
+      tops[b + atomicAdd(&nb, 1)] = make_int2(k, meta.w & 255);
+  }
+  __syncthreads();
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    counts[0] = a + na;
+    counts[1] = b + nb;
+  }
+}
+
 // Boxes, first members and (vh given) largest h of the terminals and their
 // windows: 16 lanes a terminal, a block a window. Bound by the latency of
 // the members' loads; one launch, where a refit of every node's largest h
@@ -518,13 +725,26 @@ __global__ void k_gnodes(const Node *__restrict__ nodes, int64_t nnodes,
 
 }  // namespace
 
+static void launch_moments(const g3_tree *t, const Octree &o, hipStream_t s) {
+  const Moments A{o.nodes, o.mom, t->f64 ? o.c64 : nullptr, o.xm, t->f64 ? o.x64 : nullptr};
+  if (o.nnodes <= kSmallNodes) {
+    k_moments_small<<<1, kTopBlock, 0, s>>>(A, (int)o.nnodes);
+    return;
+  }
+  const unsigned nb = (unsigned)std::min<int64_t>(o.nnodes, 4096);
+  k_moments_sub<<<nb, kBlock, 0, s>>>(A, o.subs, o.nsplit);
+  k_moments_top<<<1, kTopBlock, 0, s>>>(A, o.tops, o.nsplit);
+}
+
 // Selects the members (gas only for the gas octree), sorts them and builds
 // the topology and moments. SYNCS once to read the node count.
 int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
-                 const float *mass, int64_t m, hipStream_t s, const uint8_t *type) {
+                 const float *mass, int64_t m, hipStream_t s, const uint8_t *type,
+                 int64_t *m_gas) {
   o.n = m;
   o.nnodes = 0;
   o.max_level = 0;
+  if (m_gas) *m_gas = 0;
   if (m == 0) {  // no members: every snapshot's node range is empty
     const hipError_t e = fill_i32(o.nroot, 0, t->n_snap + 1, s);
     if (e != hipSuccess) { c->err = "fill launch failed"; return G3_EHIP; }
@@ -570,26 +790,24 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
     return G3_ENOMEM;
   }
   const bool gas = (&o == &t->gas);
+  const int64_t n = t->n;
+  uint32_t *flags = (uint32_t *)scratch(c, kGasFlags, (n + 1) * sizeof(uint32_t));
+  uint32_t *slot = (uint32_t *)scratch(c, kGasSlot, (n + 1) * sizeof(uint32_t));
+  uint32_t *stmp2 = (uint32_t *)scratch(c, kGasScan, scan_tmp_elems(n) * sizeof(uint32_t));
+  if (!flags || !slot || !stmp2) { c->err = "device allocation of build scratch failed"; return G3_ENOMEM; }
   hipError_t e;
   if (gas) {
-    // filter the all-particle octree's sorted members (built just before)
-    const int64_t n = t->n;
-    uint32_t *flags = (uint32_t *)scratch(c, kGasFlags, (n + 1) * sizeof(uint32_t));
-    uint32_t *slot = (uint32_t *)scratch(c, kGasSlot, (n + 1) * sizeof(uint32_t));
-    uint32_t *stmp2 = (uint32_t *)scratch(c, kGasScan, scan_tmp_elems(n) * sizeof(uint32_t));
-    if (!flags || !slot || !stmp2) { c->err = "device allocation of build scratch failed"; return G3_ENOMEM; }
-    k_gas_of_sorted<<<nblk(n), kBlock, 0, s>>>(t->all.perm, n, type, flags);
-    e = scan_u32(flags, slot, n, stmp2, s);
-    if (e != hipSuccess) { c->err = "scan launch failed"; return G3_EHIP; }
-    k_compact_sorted<<<nblk(n), kBlock, 0, s>>>(flags, slot, n, t->all.keys, t->all.perm, o.keys,
-                                                 vals);
+    // the all-particle octree's sorted members (built just before, with the
+    // flags and slots of the gas ones)
+    k_compact_sorted<<<nblk(n), kBlock, 0, s>>>(flags, slot, n, t->all, o.keys, o.perm, o.xm, x64,
+                                                 t->iperm_gas);
   } else {
     if (f64)
-      k_keys<double><<<nblk(m), kBlock, 0, s>>>((const double *)pos, nullptr, m, t->coff, t->sbox,
-                                                t->n_snap, o.keys, vals);
-    else
-      k_keys<float><<<nblk(m), kBlock, 0, s>>>((const float *)pos, nullptr, m, t->coff, t->sbox,
-                                               t->n_snap, o.keys, vals);
+      k_keys<double><<<nblk(m), kBlock, 0, s>>>((const double *)pos, m, t->coff, t->sbox,
+                                                t->n_snap, mass, o.keys, vals, nullptr);
+    else  // (this octree's vh is free: the SPH calls fill the gas octree's)
+      k_keys<float><<<nblk(m), kBlock, 0, s>>>((const float *)pos, m, t->coff, t->sbox, t->n_snap,
+                                               mass, o.keys, vals, o.vh);
     e = radix_sort_pairs(o.keys, vals, kalt, valt, m, 64, rtmp, s);
     if (e != hipSuccess) { c->err = "radix sort launch failed"; return G3_EHIP; }
     if (t->n_snap > 1) {
@@ -610,15 +828,19 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
       if (e != hipSuccess) { c->err = "snapshot sort copy failed"; return G3_EHIP; }
     }
   }
-  int32_t *iperm = gas ? t->iperm_gas : t->iperm_all;
-  if (f64)
-    k_permute<double><<<nblk(m), kBlock, 0, s>>>(vals, m, (const double *)pos, mass, o.xm, x64,
-                                                 iperm);
-  else
-    k_permute<float><<<nblk(m), kBlock, 0, s>>>(vals, m, (const float *)pos, mass, o.xm, nullptr,
-                                                iperm);
-  e = hipMemcpyAsync(o.perm, vals, m * sizeof(int32_t), hipMemcpyDeviceToDevice, s);
-  if (e != hipSuccess) { c->err = "perm copy failed"; return G3_EHIP; }
+  if (!gas) {
+    if (f64)
+      k_permute<double><<<nblk(m), kBlock, 0, s>>>(vals, m, (const double *)pos, mass, o.xm, x64,
+                                                   t->iperm_all, o.perm);
+    else
+      k_permute_packed<<<nblk(m), kBlock, 0, s>>>(vals, m, o.vh, o.xm, t->iperm_all, o.perm);
+    // the gas members among the sorted ones: their number comes back with the
+    // node count
+    k_gas_of_sorted<<<nblk(n), kBlock, 0, s>>>(o.perm, n, type, flags);
+    e = scan_u32(flags, slot, n, stmp2, s);
+    if (e != hipSuccess) { c->err = "scan launch failed"; return G3_EHIP; }
+    k_gas_soff<<<nblk(t->n_snap + 1), kBlock, 0, s>>>(o.soff, t->n_snap, slot, t->gas.soff);
+  }
   e = fill_i32(maxlev, 0, 1, s);
   if (e != hipSuccess) { c->err = "fill launch failed"; return G3_EHIP; }
   k_node_counts<<<nblk(m), kBlock, 0, s>>>(o.keys, m, o.soff, t->n_snap, t->leaf, cnt, lev,
@@ -628,25 +850,31 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
   int64_t *pin = c->pinned;
   e = hipMemcpyAsync(&pin[0], off + m, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipMemcpyAsync(&pin[1], maxlev, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess && !gas)
+    e = hipMemcpyAsync(&pin[2], slot + n, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) { c->err = std::string("node count readback: ") + hipGetErrorString(e); return G3_EHIP; }
   const int64_t nnodes = (int64_t)(uint32_t)(pin[0] & 0xffffffffll);
   const int32_t maxl = (int32_t)(pin[1] & 0xffffffffll);
+  if (m_gas) *m_gas = (int64_t)(uint32_t)(pin[2] & 0xffffffffll);
   if (nnodes <= 0 || nnodes >= (int64_t)INT32_MAX) { c->err = "node count out of range"; return G3_EHIP; }
   const bool grav = (&o == &t->all);
-  if (nnodes > o.cap_nodes || (grav && !o.gnodes)) {
-    if (o.nodes) (void)hipFree(o.nodes);
-    if (o.mom) (void)hipFree(o.mom);
-    if (o.gnodes) (void)hipFree(o.gnodes);
-    o.nodes = nullptr; o.mom = nullptr; o.gnodes = nullptr; o.cap_nodes = 0;
+  if (nnodes > o.cap_nodes || (grav && !o.gnodes) || o.cap_tops < max_tops(o.cap_n)) {
+    for (void *p : {(void *)o.nodes, (void *)o.mom, (void *)o.gnodes, (void *)o.tops})
+      if (p) (void)hipFree(p);
+    o.nodes = nullptr; o.mom = nullptr; o.gnodes = nullptr; o.tops = nullptr; o.cap_nodes = 0;
     const int64_t cap = nnodes + nnodes / 8 + 64;
+    // (the lists of the moments in one buffer)
     if (dev_malloc(c, (void **)&o.nodes, cap * sizeof(Node)) != hipSuccess ||
         dev_malloc(c, (void **)&o.mom, cap * sizeof(double4)) != hipSuccess ||
+        dev_malloc(c, (void **)&o.tops, max_tops(o.cap_n) * sizeof(int2) +
+                                            (cap + 2) * sizeof(int32_t)) != hipSuccess ||
         (grav && dev_malloc(c, (void **)&o.gnodes, cap * sizeof(GNode)) != hipSuccess)) {
       c->err = "device allocation of the octree nodes failed";
       return G3_ENOMEM;
     }
     o.cap_nodes = cap;
+    o.cap_tops = max_tops(o.cap_n);
   }
   if (f64 && (!o.c64 || o.cap_c64 < nnodes)) {
     if (o.c64) (void)hipFree(o.c64);
@@ -659,14 +887,24 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
     }
     o.cap_c64 = cap;
   }
+  o.subs = (int32_t *)(o.tops + o.cap_tops);
+  o.nsplit = o.subs + o.cap_nodes;
+  // per-block counts of the list pass
+  int2 *bcount = (int2 *)scratch(c, kMisc, 64 + (nnodes / kTermTile + 2) * sizeof(int2));
+  if (!bcount) { c->err = "device allocation of build scratch failed"; return G3_ENOMEM; }
+  bcount += 8;
   o.nnodes = nnodes;
   o.max_level = maxl;
   k_nodes<<<nblk(m), kBlock, 0, s>>>(o.keys, m, o.soff, t->n_snap, t->sbox, off, lev, nnodes,
                                      o.nodes);
   k_nroot<<<nblk(t->n_snap + 1), kBlock, 0, s>>>(off, o.soff, t->n_snap, o.nroot);
-  for (int l = maxl; l >= 0; --l)
-    k_moments_level<<<nblk(nnodes), kBlock, 0, s>>>(o.nodes, o.mom, f64 ? o.c64 : nullptr,
-                                                     nnodes, o.xm, x64, l);
+  k_parents<<<nblk(nnodes), kBlock, 0, s>>>(o.nodes, nnodes);
+  if (nnodes > kSmallNodes) {
+    const unsigned nb = (unsigned)((nnodes + kTermTile - 1) / kTermTile);
+    k_split_count<<<nb, kBlock, 0, s>>>(o.nodes, (int)nnodes, bcount);
+    k_split_write<<<nb, kBlock, 0, s>>>(o.nodes, (int)nnodes, bcount, o.subs, o.tops, o.nsplit);
+  }
+  launch_moments(t, o, s);
   if (o.gnodes) k_gnodes<<<nblk(nnodes), kBlock, 0, s>>>(o.nodes, nnodes, o.gnodes);
   e = hipGetLastError();
   if (e != hipSuccess) { c->err = std::string("tree build launch: ") + hipGetErrorString(e); return G3_EHIP; }
@@ -676,19 +914,15 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
 int refit_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, const float *mass,
                  hipStream_t s) {
   if (o.n == 0 || o.nnodes == 0) return G3_OK;
-  const bool gas = (&o == &t->gas);
-  int32_t *iperm = gas ? t->iperm_gas : t->iperm_all;
+  // (the order and its inverse stay)
   const uint32_t *order = (const uint32_t *)o.perm;
   if (t->f64)
     k_permute<double><<<nblk(o.n), kBlock, 0, s>>>(order, o.n, (const double *)pos, mass, o.xm,
-                                                   o.x64, iperm);
+                                                   o.x64, nullptr, nullptr);
   else
     k_permute<float><<<nblk(o.n), kBlock, 0, s>>>(order, o.n, (const float *)pos, mass, o.xm,
-                                                  nullptr, iperm);
-  for (int l = o.max_level; l >= 0; --l)
-    k_moments_level<<<nblk(o.nnodes), kBlock, 0, s>>>(o.nodes, o.mom, t->f64 ? o.c64 : nullptr,
-                                                       o.nnodes, o.xm, t->f64 ? o.x64 : nullptr,
-                                                       l);
+                                                  nullptr, nullptr, nullptr);
+  launch_moments(t, o, s);
   if (o.gnodes) k_gnodes<<<nblk(o.nnodes), kBlock, 0, s>>>(o.nodes, o.nnodes, o.gnodes);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
@@ -745,31 +979,22 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
   return hipGetLastError();
 }
 
-// Gas member count and the sorted start of each snapshot in the gas
-// octree; returns the count (SYNCS to read it).
-// The all-particle octree's snapshot starts are the caller offsets.
-int select_members(g3_ctx *c, g3_tree *t, const uint8_t *type, int64_t *m_out, hipStream_t s) {
-  const int64_t n = t->n;
-  const unsigned sb = nblk(t->n_snap + 1);
-  k_soff<<<sb, kBlock, 0, s>>>(t->coff, t->n_snap, nullptr, t->all.soff);
-  if (!type) {
-    k_soff<<<sb, kBlock, 0, s>>>(t->coff, t->n_snap, nullptr, t->gas.soff);
-    *m_out = n;
-    return G3_OK;
+// The snapshot tables on the device. One snapshot's come from the launch's
+// arguments; more are copied, and the copies waited for (the host staging is
+// the caller's).
+hipError_t upload_snapshots(g3_tree *t, const double4 *boxes, hipStream_t s) {
+  if (t->n_snap == 1) {
+    k_one_snap<<<1, 1, 0, s>>>(t->n, boxes[0], t->coff, t->sbox, t->all.soff);
+    return hipGetLastError();
   }
-  uint32_t *flags = (uint32_t *)scratch(c, kCounts, (n + 1) * sizeof(uint32_t));
-  uint32_t *slot = (uint32_t *)scratch(c, kOffsets, (n + 1) * sizeof(uint32_t));
-  uint32_t *stmp = (uint32_t *)scratch(c, kScanTmp, scan_tmp_elems(n) * sizeof(uint32_t));
-  if (!flags || !slot || !stmp) { c->err = "device allocation failed"; return G3_ENOMEM; }
-  k_gas_flags<<<nblk(n), kBlock, 0, s>>>(type, n, flags);
-  hipError_t e = scan_u32(flags, slot, n, stmp, s);
-  if (e != hipSuccess) { c->err = "scan launch failed"; return G3_EHIP; }
-  k_soff<<<sb, kBlock, 0, s>>>(t->coff, t->n_snap, slot, t->gas.soff);
-  e = hipMemcpyAsync(&c->pinned[2], slot + n, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
+  hipError_t e = hipMemcpyAsync(t->coff, t->snap_off.data(), (t->n_snap + 1) * sizeof(int64_t),
+                                hipMemcpyHostToDevice, s);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(t->sbox, boxes, t->n_snap * sizeof(double4), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) { c->err = std::string("gas count readback: ") + hipGetErrorString(e); return G3_EHIP; }
-  *m_out = (int64_t)(uint32_t)(c->pinned[2] & 0xffffffffll);
-  return G3_OK;
+  if (e != hipSuccess) return e;
+  k_soff<<<nblk(t->n_snap + 1), kBlock, 0, s>>>(t->coff, t->n_snap, t->all.soff);
+  return hipGetLastError();
 }
 
 }  // namespace g3
