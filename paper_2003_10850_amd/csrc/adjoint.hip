@@ -436,6 +436,9 @@ struct __align__(16) GEntry {
 // 32-bit words 5 and 6 of an entry
 constexpr int kGMaskWord = 5;
 
+// items that wait: at most 7 siblings on each of the 22 levels
+constexpr int kGStack = 7 * (kMaxLevel + 1) + 1;
+
 __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
 #pragma clang fp contract(off)
   const float lhs = l * l;
@@ -455,15 +458,17 @@ __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
 // gnode).
 template <bool kFixed, bool kInside>
 __global__ __launch_bounds__(kBlock) void k_gravity_bwd(
-    const GNode *__restrict__ nodes, const float4 *__restrict__ xm,
-    const uint64_t *__restrict__ keys, const int32_t *__restrict__ perm, const Groups gs,
+    const CNode *__restrict__ cnodes, const uint64_t *__restrict__ ckeys,
+    const float4 *__restrict__ xm, const uint64_t *__restrict__ keys, const int32_t *__restrict__ perm, const Groups gs,
     float theta2, float eps2, float G, const float *__restrict__ g_acc,
     const float *__restrict__ g_pot, float4 *__restrict__ gsrc, float4 *__restrict__ gnode,
     unsigned long long *__restrict__ gsrc_fx, unsigned long long *__restrict__ gnode_fx,
     const unsigned *__restrict__ mx, int64_t n_all, int64_t n_act) {
   __shared__ GEntry tiles[kWpb][kTile];
+  __shared__ int4 stacks[kWpb][kGStack];
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
   GEntry *tile = tiles[w];
+  int4 *stack = stacks[w];
   const double scale = kFixed ? fx_scale(mx, eps2, G, n_all, n_act) : 1.0;
   int range = 0;
   for (int g; (g = next_group(gs, range)) >= 0;) {
@@ -544,87 +549,106 @@ __global__ __launch_bounds__(kBlock) void k_gravity_bwd(
       neumaier_add(oz, coz, pz);
       wave_sync();
     };
-    // the walk of the forward kernel over the 32-byte node copies: the same
-    // decisions, one compare each without the containment test (an idle
-    // lane compares with NaN, for which both are false)
+    // the walk of the forward kernel: the same items, decisions and masks
     const int root_exp = ilogbf((float)gs.sbox[grp.snap].w);
-    const int groot = __builtin_amdgcn_readfirstlane(grp.root);
-    const int gend = __builtin_amdgcn_readfirstlane(grp.end);
-    int resume = valid ? groot : INT32_MAX;
-    int cur = groot;
-    while (cur < gend) {
-      const GNode nd = nodes[cur];
-      const float l = __int_as_float(nd.meta.w);
-      const bool act = cur >= resume;
-      const float r2 = dist2_exact(sub_exact(nd.com_m.x, me.x), sub_exact(nd.com_m.y, me.y),
-                                   sub_exact(nd.com_m.z, me.z));
-      bool accept, open;
-      if constexpr (!kInside) {
-        float t;
-        {
+    int first = __builtin_amdgcn_readfirstlane(grp.snap), count = 1, sp = 0;
+    uint64_t mask = grp.count < kWave ? (1ull << grp.count) - 1ull : ~0ull;
+    for (;;) {
+      int nf = 0, nc = 0;  // the next item (nc = 0: none yet)
+      uint64_t nm = 0ull;
+      const bool act = __builtin_amdgcn_inverse_ballot_w64(mask);
+      if (count > 0) {
+        auto visit = [&](const CNode &nd, uint64_t nk) {
+          const float l = __int_as_float(nd.meta.w);
+          const float r2 = dist2_exact(sub_exact(nd.com_m.x, me.x), sub_exact(nd.com_m.y, me.y),
+                                       sub_exact(nd.com_m.z, me.z));
+          bool accept, open;
+          if constexpr (!kInside) {
+            float rhs;
+            {
 #pragma clang fp contract(off)
-          t = act ? theta2 * r2 : __builtin_nanf("");
-        }
-        const float lhs = sq_exact(l);
-        accept = lhs < t;
-        open = lhs >= t;
+              rhs = theta2 * r2;
+            }
+            const float lhs = sq_exact(l);
+            accept = act && lhs < rhs;
+            open = act && lhs >= rhs;
+          } else {
+            const int level = root_exp - ilogbf(l);
+            accept = act && open_accept(l, theta2, r2) &&
+                     ((ki ^ nk) >> (3 * (kMaxLevel - level))) != 0ull;
+            open = act && !accept;
+          }
+          const uint64_t amask = __ballot(accept), om = __ballot(open);
+          if (amask) {
+            if (tc == kTile) {
+              flush(kTile);
+              tc = 0;
+            }
+            if (lane == 0) {
+              GEntry e;
+              e.p = nd.com_m;
+              e.meta = make_int4(-(nd.meta.z + 1), (int)(uint32_t)amask,
+                                 (int)(uint32_t)(amask >> 32), 0);
+              tile[tc] = e;
+            }
+            ++tc;
+          }
+          if (om) {
+            if (nc) {
+              if (lane == 0)
+                stack[sp] = make_int4(nf, nc, (int)(uint32_t)nm, (int)(uint32_t)(nm >> 32));
+              ++sp;
+            }
+            nf = nd.meta.x;
+            nc = nd.meta.y;
+            nm = om;
+          }
+        };
+        for (int c = 0; c < count; ++c)
+          visit(cnodes[first + c], kInside ? ckeys[first + c] : 0ull);
       } else {
-        accept = act && open_accept(l, theta2, r2);
-        const int level = root_exp - ilogbf(l);
-        const uint64_t nk = keys[nd.meta.y];
-        accept = accept && (((ki ^ nk) >> (3 * (kMaxLevel - level))) != 0ull);
-        open = act && !accept;
-      }
-      const uint64_t amask = __ballot(accept);
-      const uint64_t omask = __ballot(open);
-      if (accept) resume = nd.meta.x;
-      if (amask) {
-        if (tc == kTile) {
-          flush(kTile);
-          tc = 0;
+        int st = first, c = -count;
+        while (c > 0) {
+          if (tc == kTile) {
+            flush(kTile);
+            tc = 0;
+          }
+          const int take = min(c, kTile - tc);
+          if (lane < take) {
+            GEntry e;
+            e.p = xm[st + lane];
+            e.meta = make_int4(st + lane, (int)(uint32_t)mask, (int)(uint32_t)(mask >> 32), 0);
+            tile[tc + lane] = e;
+          }
+          wave_sync();
+          // an opening lane whose own target is among these members clears
+          // its bit in that member's entry (one lane per entry)
+          const int rel = s - st;
+          if (act && rel >= 0 && rel < take) {
+            uint32_t *wd = (uint32_t *)&tile[tc + rel] + kGMaskWord + (hiword ? 1 : 0);
+            *wd &= ~(1u << bitpos);
+          }
+          tc += take;
+          st += take;
+          c -= take;
         }
-        if (lane == 0) {
-          GEntry e;
-          e.p = nd.com_m;
-          e.meta = make_int4(-(cur + 1), (int)(uint32_t)amask, (int)(uint32_t)(amask >> 32), 0);
-          tile[tc] = e;
-        }
-        ++tc;
       }
-      if (omask == 0ull) {
-        cur = nd.meta.x;
-        continue;
-      }
-      if (nd.meta.z < 0) {  // internal
-        ++cur;
-        continue;
-      }
-      int st = nd.meta.y, c = nd.meta.z;
-      while (c > 0) {
-        if (tc == kTile) {
-          flush(kTile);
-          tc = 0;
-        }
-        const int take = min(c, kTile - tc);
-        if (lane < take) {
-          GEntry e;
-          e.p = xm[st + lane];
-          e.meta = make_int4(st + lane, (int)(uint32_t)omask, (int)(uint32_t)(omask >> 32), 0);
-          tile[tc + lane] = e;
-        }
+      if (nc) {
+        first = nf;
+        count = nc;
+        mask = nm;
+      } else if (sp > 0) {
+        --sp;
         wave_sync();
-        // an opening lane whose own target is among these members clears
-        // its bit in that member's entry (one lane per entry)
-        const int rel = s - st;
-        if (open && rel >= 0 && rel < take) {
-          uint32_t *wd = (uint32_t *)&tile[tc + rel] + kGMaskWord + (hiword ? 1 : 0);
-          *wd &= ~(1u << bitpos);
-        }
-        tc += take;
-        st += take;
-        c -= take;
+        const int4 e = stack[sp];
+        first = __builtin_amdgcn_readfirstlane(e.x);
+        count = __builtin_amdgcn_readfirstlane(e.y);
+        mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.w) << 32) |
+               (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.z);
+        wave_sync();
+      } else {
+        break;
       }
-      cur = nd.meta.x;
     }
     if (tc > 0) flush(tc);
     if (valid) {
@@ -1023,7 +1047,7 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
                               double *rr, float *g_pos, float *g_mass, hipStream_t s) {
   const int64_t m = all.n, nn = all.nnodes;
   if (m == 0 || nn == 0) return hipSuccess;
-  if (!all.gnodes) return hipErrorInvalidValue;
+  if (!all.cnodes) return hipErrorInvalidValue;
   const int64_t na = active ? n_act : m;
   if (gp.eps2 > 0.0f) {
     // fixed-point counters (two words per component, four components)
@@ -1036,7 +1060,7 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
     if (max_groups > 0) {
       auto kern = gp.inside_test ? k_gravity_bwd<true, true> : k_gravity_bwd<true, false>;
       kern<<<persistent_grid((const void *)kern, kBlock, max_groups), kBlock, 0, s>>>(
-          all.gnodes, all.xm, all.keys, all.perm, gs, gp.theta2, gp.eps2, gp.G, g_acc, g_pot,
+          all.cnodes, all.ckeys, all.xm, all.keys, all.perm, gs, gp.theta2, gp.eps2, gp.G, g_acc, g_pot,
           gsrc, gnode, gsrc_fx, gnode_fx, mx, m, na);
     }
     k_fx_to_f4<<<nblk(m), kBlock, 0, s>>>(gsrc_fx, m, mx, gp.eps2, gp.G, m, na, gsrc);
@@ -1047,7 +1071,7 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
     if (max_groups > 0) {
       auto kern = gp.inside_test ? k_gravity_bwd<false, true> : k_gravity_bwd<false, false>;
       kern<<<persistent_grid((const void *)kern, kBlock, max_groups), kBlock, 0, s>>>(
-          all.gnodes, all.xm, all.keys, all.perm, gs, gp.theta2, gp.eps2, gp.G, g_acc, g_pot,
+          all.cnodes, all.ckeys, all.xm, all.keys, all.perm, gs, gp.theta2, gp.eps2, gp.G, g_acc, g_pot,
           gsrc, gnode, nullptr, nullptr, nullptr, m, na);
     }
   }

@@ -436,6 +436,7 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
   w->gs.n_snap = n_snap;
   w->rows = rw;
   w->ntarg = ntarg;
+  w->max_targets = max_t;
   w->max_groups = split_on ? max_t : max_groups_of(max_t, n_snap);
   return G3_OK;
 }
@@ -456,6 +457,11 @@ int density_team(int64_t max_targets, int f64) {
 int hydro_team(int64_t max_targets) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
   return groups <= 1536 ? 16 : (groups <= 12288 ? 4 : 1);
+}
+// Gravity (us, clustered sets of 2^11, 2^12 and 2^13 groups, teams of 4/16):
+// FP32 553/437, 817/902, 1321/1811; FP64 664/637, 1046/1315, 1843/2666.
+int gravity_team(int64_t max_targets) {
+  return (max_targets + kWave - 1) / kWave <= 2560 ? 16 : 4;
 }
 
 unsigned persistent_grid(const void *kern, int block, int64_t max_groups, int team) {
@@ -523,8 +529,8 @@ int g3_ctx_create(g3_ctx **out, int device) {
 
 static void free_octree(Octree &o) {
   for (void *p : {(void *)o.keys, (void *)o.perm, (void *)o.xm, (void *)o.nodes, (void *)o.mom,
-                  (void *)o.tops,
-                  (void *)o.gnodes, (void *)o.vh, (void *)o.aux, (void *)o.x64, (void *)o.h64,
+                  (void *)o.tops, (void *)o.cnodes, (void *)o.ckeys, (void *)o.cc64,
+                  (void *)o.cbase, (void *)o.vh, (void *)o.aux, (void *)o.x64, (void *)o.h64,
                   (void *)o.c64, (void *)o.soff, (void *)o.nroot})
     if (p) (void)hipFree(p);
   o = Octree();
@@ -832,8 +838,10 @@ int g3_tree_export(g3_ctx *c, const g3_tree *t, int32_t which, int32_t *order, u
   return G3_OK;
 }
 
-static GravParams grav_params(const g3_params *p, const g3_tree *t) {
+// max_targets: the host's bound on the call's targets.
+static GravParams grav_params(const g3_params *p, const g3_tree *t, int64_t max_targets = 0) {
   GravParams gp;
+  gp.team = gravity_team(max_targets);
   gp.theta2 = (float)(p->theta * p->theta);
   gp.eps2 = (float)(p->eps * p->eps);
   gp.G = (float)p->G;
@@ -1083,7 +1091,8 @@ int g3_gravity(g3_ctx *c, const g3_tree *t, int64_t n_act, const int32_t *active
   st = prepare_work(c, t, o, t->iperm_all, n_act, active, &wk, s, tu.split);
   if (st) return st;
   KernelTimer timer(c, kTuneGravity, s);
-  hipError_t e = launch_gravity(o, wk.gs, wk.max_groups, grav_params(p, t), acc, pot, nterms, s);
+  hipError_t e = launch_gravity(o, wk.gs, wk.max_groups, grav_params(p, t, wk.max_targets), acc,
+                                pot, nterms, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_gravity");
   timer.stop();
   c->err.clear();
@@ -1271,7 +1280,8 @@ int g3_gravity_noalloc(g3_ctx *c, const g3_tree *t, int64_t n_act, const int32_t
   Work wk;
   st = prepare_work(c, t, o, t->iperm_all, n_act, active, &wk, s, tu.split, &arena);
   if (st) return st;
-  hipError_t e = launch_gravity(o, wk.gs, wk.max_groups, grav_params(p, t), acc, pot, nterms, s);
+  hipError_t e = launch_gravity(o, wk.gs, wk.max_groups, grav_params(p, t, wk.max_targets), acc,
+                                pot, nterms, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_gravity_noalloc");
   c->err.clear();
   return G3_OK;
@@ -1359,7 +1369,8 @@ static int tick_forces(g3_ctx *c, g3_tree *t, int64_t n, const g3_state *st,
   rc = prepare_work(c, t, all, t->iperm_all, all.n, nullptr, &wg, s, tg.split, nullptr, bins,
                     kmin);
   if (rc) return rc;
-  e = launch_gravity(all, wg.gs, wg.max_groups, grav_params(p, t), st->acc, st->pot, nullptr, s);
+  e = launch_gravity(all, wg.gs, wg.max_groups, grav_params(p, t, wg.max_targets), st->acc,
+                     st->pot, nullptr, s);
   if (e == hipSuccess && count_out) e = launch_store_count(wg.ntarg, count_out, s);
   if (e == hipSuccess)
     e = launch_update(n, t->f64, iu, st->type, st->vel, st->u, st->acc, acc_h, st->dudt,
@@ -1695,8 +1706,8 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
       st = time_candidate(c, s, e0, e1, [&]() -> hipError_t {
         if (prepare_work(c, t, all, t->iperm_all, n_act, active, &wk, s, tu.split))
           return hipErrorUnknown;
-        return launch_gravity(all, wk.gs, wk.max_groups, grav_params(p, t), nullptr, nullptr,
-                              nullptr, s);
+        return launch_gravity(all, wk.gs, wk.max_groups, grav_params(p, t, wk.max_targets), nullptr,
+                              nullptr, nullptr, s);
       }, &ms);
       if (st) return finish(st);
       if (ms < best_ms) {

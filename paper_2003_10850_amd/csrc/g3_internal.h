@@ -28,17 +28,21 @@ static_assert(sizeof(Node) == 64, "node must be 64 bytes");
 
 constexpr int kLeafBit = 256;
 
-// The gravity walk's copy of a node, 32 bytes: two nodes per 64-byte line,
-// so a descent to cur + 1 often finds its node in the line just loaded.
+// The gravity walk's copy of a node, 32 bytes, with the children of a node
+// side by side: a walk opens a node with a few scalar loads of all its
+// children, where the preorder array costs a dependent load a child.
 //   com_m   centre of mass, mass
-//   meta    skip, first member, member count of a leaf (-1: internal), the
-//           cube side l as bits; l = side of the root cube * 2^-level
-//           exactly, so the level is the difference of the two exponents
-struct __align__(16) GNode {
+//   meta    first child (internal) or first member (leaf); number of children
+//           or minus the number of members; preorder index; the cube side l
+//           as bits (l = side of the root cube * 2^-level exactly, so the
+//           level is the difference of the two exponents)
+struct __align__(32) CNode {
   float4 com_m;
   int4 meta;
 };
-static_assert(sizeof(GNode) == 32, "gravity node must be 32 bytes");
+static_assert(sizeof(CNode) == 32, "gravity node must be 32 bytes");
+// Entries past the end that a block of children may be read into.
+constexpr int kChildPad = 8;
 
 // Subtrees of at most this many members have their moments from a workgroup
 // each; max_tops is the largest number of nodes above them in an octree of n
@@ -57,7 +61,13 @@ struct Octree {
   int32_t *perm = nullptr;   // [n] sorted position -> caller id
   float4 *xm = nullptr;      // [n] sorted (x, y, z, m)
   Node *nodes = nullptr;     // [nnodes] preorder
-  GNode *gnodes = nullptr;   // [nnodes] the gravity walk's copy (all-particle octree)
+  // the gravity walk's copy (all-particle octree): the roots of the snapshots
+  // at [0, n_snap), then each internal node's children at cbase[node] + n_snap
+  CNode *cnodes = nullptr;   // [n_snap + nnodes + kChildPad]
+  uint64_t *ckeys = nullptr; // key of the first member, same order
+  double4 *cc64 = nullptr;   // FP64 centre of mass and mass (FP64 trees)
+  uint32_t *cbase = nullptr; // [nnodes + 1]
+  int64_t cap_cnodes = 0, cap_cc64 = 0;
   double4 *mom = nullptr;    // [nnodes] FP64 (M, M x, M y, M z)
   // the moments' order: roots of small subtrees, and the nodes above them
   int32_t *subs = nullptr;    // [nnodes]
@@ -167,7 +177,7 @@ enum Slot {
   kFlags, kTargets, kRows, kIds, kLevel, kWalkCounts, kMisc,
   kSnapKeys, kSnapKeysAlt, kGroups, kAdjSrc, kAdjNode, kAdjPQ, kAdjR,
   kGasFlags, kGasSlot, kGasScan, kIntAccH, kIntVp, kIntUp, kCondCh, kHydroExt,
-  kAdjSrcFx, kAdjNodeFx, kTermBuf, kNumSlots
+  kAdjSrcFx, kAdjNodeFx, kTermBuf, kChildren, kNumSlots
 };
 static_assert(kNumSlots <= g3_ctx::kBankSlots, "more scratch slots than a bank holds");
 
@@ -277,6 +287,7 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
 // number of targets: 4 or 16, for the hydro force also 1 (no team).
 int density_team(int64_t max_targets, int f64);
 int hydro_team(int64_t max_targets);
+int gravity_team(int64_t max_targets);
 
 // Active set -> group table of one octree (scratch owned by the ctx).
 // rows[t] is the index in `active` of target t (nullptr with every member
@@ -284,7 +295,7 @@ int hydro_team(int64_t max_targets);
 struct Work {
   Groups gs;
   const int32_t *rows;
-  int64_t max_groups;
+  int64_t max_groups, max_targets;
   const uint32_t *ntarg;  // device count of the targets (nullptr: every member)
 };
 // A caller-given device region that stands in for the ctx's scratch slots:
@@ -367,6 +378,7 @@ struct GravParams {
   int inside_test;  // evaluate the cube-containment test (theta^2 >= 1/3)
   int f64;          // FP64 positions: mixed-precision kernels, FP64 decisions
   double theta;     // opening angle (FP64 decisions)
+  int team = 4;     // forward: waves that serve one group together (4 or 16)
 };
 hipError_t launch_gravity(const Octree &all, const Groups &gs, int64_t max_groups,
                           const GravParams &gp, float *acc, float *pot, int32_t *nterms,

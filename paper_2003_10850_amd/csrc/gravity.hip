@@ -1,18 +1,23 @@
 // Barnes-Hut gravity with per-particle opening decisions, walked by a whole
 // wavefront at a time.
 //
-// A wave serves 64 Morton-consecutive targets. It visits the all-particle
-// octree in preorder with one scalar node load per step, and every lane
-// takes the per-particle Barnes-Hut decision for that node (Barnes & Hut
-// 1986): accept the monopole, open it, or skip it because an ancestor was
-// already accepted (the lane then resumes at the ancestor's skip index).
-// The wave descends while any lane opens. Accepted monopoles and the members
-// of opened leaves become entries of a 64-entry interaction tile in LDS,
-// each with the 64-bit mask of lanes that use it; the tile is then
-// evaluated by all lanes with the mask applied to the inverse distance. This
-// keeps the interaction step out of the walk's branches (the limitation the
-// paper names for gravity, section 2.4) and reproduces the per-particle
-// interaction list exactly.
+// A wave serves 64 Morton-consecutive targets, one per lane, and every lane
+// takes the per-particle Barnes-Hut decision for each node the wave visits
+// (Barnes & Hut 1986): accept the monopole or open it; a lane whose ancestor
+// was accepted is out of the node's mask. A work item is the children of an
+// opened node (they lie side by side, see CNode) or the members of an opened
+// leaf, with the 64-bit mask of the lanes that opened it. The wave reads an
+// item with a few scalar loads, decides and sums each child or member from
+// scalar registers, all lanes at once with the mask on the inverse distance,
+// and stacks the children that some lane opens.
+//
+// Bound by vector issue on a full chip: a child costs about 25 instructions
+// with its term (the distance of the decision serves the term). The walk
+// before this one read one node a step in preorder, a dependent scalar load
+// each (0.5 us, 2600 steps a group), and wrote what it accepted to LDS tiles
+// that it summed later, about 40 instructions a node.
+#include <type_traits>
+
 #include "g3_device.h"
 #include "g3_internal.h"
 
@@ -20,18 +25,23 @@ namespace g3 {
 
 namespace {
 
-constexpr int kBlock = 256;
-constexpr int kWpb = kBlock / kWave;
-constexpr int kTile = kWave;
-
-struct __align__(16) Entry {
-  float4 p;       // source position, mass
-  int4 meta;      // source sorted index (-1: node), mask low, mask high, unused
+// Items that wait in a depth-first walk: at most 7 siblings on each of the 22
+// levels.
+constexpr int kDepth = 7 * (kMaxLevel + 1) + 1;
+// A team of kT waves takes up to kItems items a round from the end of the
+// list; while more than one is taken the list stays below kStack - kDepth, so
+// a depth-first descent always fits.
+template <int kT>
+struct Team {
+  static constexpr int kItems = 4 * kT;
+  static constexpr int kStack = kDepth + 16 * kItems;
+  int4 stack[kStack];
+  int4 out[8 * kItems];  // the items that an item opens
+  int32_t nout[kItems];
+  int32_t group;
 };
-// A lane's mask word is meta.y (lanes 0..31) or meta.z (lanes 32..63); the
-// bit of a lane whose own target is the source is cleared when the entry is
-// made, so the tile loop needs no self test.
-constexpr int kMaskWord = 5;  // meta.y as the 32-bit word index within Entry
+// Terms of plain FP32 partial sums between two compensated additions.
+constexpr int kFlush = 64;
 
 // The opening test, exact in FP32: fl(l * l) < fl(theta2 * r2).
 __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
@@ -41,29 +51,43 @@ __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
   return lhs < rhs;
 }
 
-
 // Mixed precision (kF64): positions are stored in FP64 and the node centres
-// of mass come from FP64 moments. Each term works on the FP32 difference of
-// the source's and the target's FP32 offsets from the group's FP64 centre;
-// the opening test on the FP32 rounding of the node's FP64 offset from the
-// target, and near the threshold, where that test could disagree with the
-// FP64 one, the FP64 test decides.
-template <bool kF64, bool kInside>
-__global__ __launch_bounds__(kBlock) void k_gravity(
-    const GNode *__restrict__ nodes, const double4 *__restrict__ c64n,
-    const float4 *__restrict__ xm, const double4 *__restrict__ x64,
-    const uint64_t *__restrict__ keys, const int32_t *__restrict__ perm, const Groups gs,
-    float theta2, float eps2, float G, int inside_test, double theta64,
-    float *__restrict__ acc, float *__restrict__ pot, int32_t *__restrict__ nterms) {
-  __shared__ Entry tiles[kWpb][kTile];
-  // running totals (acc, pot) and their Neumaier compensations, and the term
-  // count, one slot per lane: touched only at a flush, so the walk loop
-  // carries no per-lane sums from one node to the next
-  __shared__ float4 tot[kWpb][kTile], comp[kWpb][kTile];
-  __shared__ int32_t nts[kWpb][kTile];
+// of mass come from FP64 moments. Decision and term work on the FP32 rounding
+// of the FP64 offset of the source from the target; near the threshold, where
+// the FP32 test could disagree with the FP64 one, the FP64 test decides.
+// The waves of a workgroup share a group: they take its items in rounds, item
+// j of a round by wave j % kT, and the items that these open follow in the
+// order of their parents, so the sums do not depend on timing. All particles
+// of a clustered 2^21 box: 6.5 ms with the preorder walk of one wave a group,
+// 4.9 with the items of one wave, 4.3 with teams of 4, 7.5 with teams of 16;
+// of 2^12 particles: 0.50, 0.38, 0.15 and 0.07 ms.
+template <bool kF64, bool kInside, int kT>
+__global__ __launch_bounds__(kT * kWave, kT > 4 ? 4 : 8) void k_gravity(
+    const CNode *__restrict__ cnodes, const uint64_t *__restrict__ ckeys,
+    const double4 *__restrict__ cc64, const float4 *__restrict__ xm,
+    const double4 *__restrict__ x64, const uint64_t *__restrict__ keys,
+    const int32_t *__restrict__ perm, const Groups gs, float theta2, float eps2, float G,
+    int inside_test, double theta64, float *__restrict__ acc, float *__restrict__ pot,
+    int32_t *__restrict__ nterms) {
+  __shared__ Team<kT> S;
+  // running totals (acc, pot) and their Neumaier compensations, one slot per
+  // lane: touched only every kFlush terms, so the walk carries no totals in
+  // registers
+  __shared__ float4 tots[kT][kWave], comps[kT][kWave];
+  __shared__ int32_t nts[kT][kWave];
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
+  float4 *tot = tots[w], *comp = comps[w];
   int range = 0;
-  for (int g; (g = next_group(gs, range)) >= 0;) {
+  auto take_group = [&]() {
+    __syncthreads();  // the previous group's LDS use is over
+    if (w == 0) {
+      const int g = next_group(gs, range);
+      if (lane == 0) S.group = g;
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(S.group);
+  };
+  for (int g; (g = take_group()) >= 0;) {
   const Group grp = group_at(gs, g);
   const int64_t t = grp.t0 + lane;
   const bool valid = lane < grp.count;
@@ -72,188 +96,212 @@ __global__ __launch_bounds__(kBlock) void k_gravity(
   // a node's level from its cube side: l = (float)side * 2^-level exactly
   const int root_exp = ilogbf((float)side);
   const float4 me = xm[s];
-  const float3 xi = make_float3(me.x, me.y, me.z);
-  // mixed precision: tile entries hold FP32 offsets from the group's FP64
-  // centre and each term takes the FP32 difference of the source's and this
-  // target's offsets; the opening test takes the FP32 rounding of the FP64
-  // difference from this target (FP64 near the threshold)
   const double4 p64 = kF64 ? x64[s] : make_double4(0, 0, 0, 0);
-  const double4 c64 = kF64 ? group_centre(x64[gs.targets ? gs.targets[grp.t0] : grp.t0], p64, valid)
-                           : make_double4(0, 0, 0, 0);
-  const float3 xo = kF64 ? make_float3((float)(p64.x - c64.x), (float)(p64.y - c64.y),
-                                       (float)(p64.z - c64.z))
-                         : xi;
   const uint64_t ki = keys[s];
-  Entry *tile = tiles[w];
 
-  tot[w][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-  comp[w][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-  nts[w][lane] = 0;
-  int tc = 0;
-
-  // this lane's bit in an entry's mask: word (low or high half) and offset
-  const bool hiword = lane >= 32;
-  const uint32_t bitpos = (uint32_t)lane & 31u;
-  // this lane's mask word of entry k sits at word kMaskWord + hiword of it
-  const uint32_t *maskw = (const uint32_t *)tile + kMaskWord + (hiword ? 1 : 0);
-  auto flush = [&](int nc) {
-    wave_sync();
-    float px = 0.f, py = 0.f, pz = 0.f, pp = 0.f;
-    int pn = 0;  // terms: entries whose mask holds this lane's bit
-    for (int k = 0; k < nc; ++k) {
-      const float4 ep = tile[k].p;
-      // branch-free use: the signed extract of the lane's bit is 0 or all
-      // ones, and masks the inverse distance
-      const int32_t use = __builtin_amdgcn_sbfe((int32_t)maskw[k * (int)(sizeof(Entry) / 4)],
-                                                bitpos, 1u);
-      const float dx = ep.x - xo.x, dy = ep.y - xo.y, dz = ep.z - xo.z;
-      const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
-      // masked here (not the mass), so that an unused entry adds exact
-      // zeros even at r2 = 0 (the own entry with zero softening)
-      const float rinv = __int_as_float(__float_as_int(__builtin_amdgcn_rsqf(r2)) & use);
-      const float mr = ep.w * rinv;
-      const float mr3 = mr * rinv * rinv;
-      px += mr3 * dx;
-      py += mr3 * dy;
-      pz += mr3 * dz;
-      pp -= mr;
-      pn -= use;
-    }
-    float4 t = tot[w][lane], c = comp[w][lane];
-    neumaier_add(t.x, c.x, px);
-    neumaier_add(t.y, c.y, py);
-    neumaier_add(t.z, c.z, pz);
-    neumaier_add(t.w, c.w, pp);
-    tot[w][lane] = t;
-    comp[w][lane] = c;
-    nts[w][lane] += pn;
-    wave_sync();
+  tot[lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+  comp[lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+  float px = 0.f, py = 0.f, pz = 0.f, pp = 0.f;
+  int pn = 0, since = 0;
+  auto flush = [&]() {
+    float4 a = tot[lane], c = comp[lane];
+    neumaier_add(a.x, c.x, px);
+    neumaier_add(a.y, c.y, py);
+    neumaier_add(a.z, c.z, pz);
+    neumaier_add(a.w, c.w, pp);
+    tot[lane] = a;
+    comp[lane] = c;
+    px = py = pz = pp = 0.f;
+    since = 0;
+  };
+  // one source at offset (dx, dy, dz), squared softened distance r2s, for the
+  // lanes that use it: masked here (not the mass), so that an unused source
+  // adds exact zeros also at r2s = 0 (the own particle with zero softening)
+  auto term = [&](bool use, float dx, float dy, float dz, float r2s, float m) {
+    const float rinv = use ? __builtin_amdgcn_rsqf(r2s) : 0.0f;
+    const float mr = m * rinv;
+    const float mr3 = mr * rinv * rinv;
+    px += mr3 * dx;
+    py += mr3 * dy;
+    pz += mr3 * dz;
+    pp -= mr;
+    pn += use ? 1 : 0;
   };
 
-  // the group's node range, wave-uniform (in scalar registers for the
-  // FP32 walk; the mixed-precision walk measured faster without)
-  const int groot = kF64 ? grp.root : __builtin_amdgcn_readfirstlane(grp.root);
-  const int gend = kF64 ? grp.end : __builtin_amdgcn_readfirstlane(grp.end);
-  int resume = valid ? groot : INT32_MAX;  // lanes idle while cur < resume
-  int cur = groot;
-  while (cur < gend) {
-    const GNode nd = nodes[cur];
-    const float l = __int_as_float(nd.meta.w);
-    const bool act = cur >= resume;
-    double4 cn = make_double4(0, 0, 0, 0);
-    float r2;
-    if constexpr (kF64) {
-      cn = c64n[cur];
-      r2 = dist2_exact((float)(cn.x - p64.x), (float)(cn.y - p64.y), (float)(cn.z - p64.z));
-    } else {
-      r2 = dist2_exact(sub_exact(nd.com_m.x, xi.x), sub_exact(nd.com_m.y, xi.y),
-                       sub_exact(nd.com_m.z, xi.z));
-    }
-    bool accept, open;
-    if constexpr (!kF64 && !kInside) {
-      // one compare per decision: an idle lane compares with NaN, for which
-      // both are false; otherwise the exact test fl(l l) < fl(theta2 r2)
-      float t;
-      {
-#pragma clang fp contract(off)
-        t = act ? theta2 * r2 : __builtin_nanf("");
-      }
-      const float lhs = sq_exact(l);
-      accept = lhs < t;
-      open = lhs >= t;
-    } else {
-      accept = act && open_accept(l, theta2, r2);
-      if constexpr (kF64) {
-        // the FP32 r2 of exact-to-2^-24 offsets is within about 2^-22 of the
-        // FP64 value (relative); inside 2^-19 of the threshold FP64 decides
-        const float lhs = l * l, rhs = theta2 * r2;
-        if (act && fabsf(lhs - rhs) <= rhs * 1.9073486e-6f)
-          accept = open_accept64(ldexp(side, -(root_exp - ilogbf(l))), theta64, cn, p64);
-      }
-      if (kInside || (kF64 && inside_test)) {
-        const int level = root_exp - ilogbf(l);
-        const uint64_t nk = keys[nd.meta.y];
-        const bool inside = ((ki ^ nk) >> (3 * (kMaxLevel - level))) == 0ull;
-        accept = accept && !inside;
-      }
-      open = act && !accept;
-    }
-    const uint64_t amask = __ballot(accept);
-    const uint64_t omask = __ballot(open);
-    if (accept) resume = nd.meta.x;
-    if (amask) {
-      if (tc == kTile) {
-        flush(kTile);
-        tc = 0;
-      }
-      if (lane == 0) {
-        Entry e;
-        e.p = nd.com_m;
-        if constexpr (kF64)
-          e.p = make_float4((float)(cn.x - c64.x), (float)(cn.y - c64.y), (float)(cn.z - c64.z),
-                            nd.com_m.w);
-        e.meta = make_int4(-1, (int)(uint32_t)amask, (int)(uint32_t)(amask >> 32), 0);
-        tile[tc] = e;
-      }
-      ++tc;
-    }
-    if (omask == 0ull) {
-      cur = nd.meta.x;
-      continue;
-    }
-    if (nd.meta.z < 0) {  // internal
-      ++cur;
-      continue;
-    }
-    int st = nd.meta.y, c = nd.meta.z;
-    while (c > 0) {
-      if (tc == kTile) {
-        flush(kTile);
-        tc = 0;
-      }
-      const int take = min(c, kTile - tc);
-      if (lane < take) {
-        Entry e;
+  // One item: `count` children at cnodes[first], or -count members from
+  // `first`, for the lanes of `mask` (all wave-uniform); open(first, count,
+  // mask) receives the items that it opens.
+  auto item = [&](int first, int count, uint64_t mask, const auto &opened) {
+    const bool act = __builtin_amdgcn_inverse_ballot_w64(mask);
+    if (count > 0) {
+      auto visit = [&](const CNode &nd, const double4 &cn, uint64_t nk) {
+        const float l = __int_as_float(nd.meta.w);
+        float dx, dy, dz;
         if constexpr (kF64) {
-          // the FP32 offset from the group centre; the fourth slot holds the
-          // (FP32) mass exactly
-          const double4 q = x64[st + lane];
-          e.p = make_float4((float)(q.x - c64.x), (float)(q.y - c64.y), (float)(q.z - c64.z),
-                            (float)q.w);
+          dx = (float)(cn.x - p64.x);
+          dy = (float)(cn.y - p64.y);
+          dz = (float)(cn.z - p64.z);
         } else {
-          e.p = xm[st + lane];
+          dx = sub_exact(nd.com_m.x, me.x);
+          dy = sub_exact(nd.com_m.y, me.y);
+          dz = sub_exact(nd.com_m.z, me.z);
         }
-        e.meta = make_int4(st + lane, (int)(uint32_t)omask, (int)(uint32_t)(omask >> 32), 0);
-        tile[tc + lane] = e;
+        const float r2 = dist2_exact(dx, dy, dz);
+        bool accept, open;
+        if constexpr (!kF64 && !kInside) {
+          // the exact test fl(l l) < fl(theta2 r2); neither holds for a
+          // distance that is not a number
+          float rhs;
+          {
+#pragma clang fp contract(off)
+            rhs = theta2 * r2;
+          }
+          const float lhs = sq_exact(l);
+          accept = act && lhs < rhs;
+          open = act && lhs >= rhs;
+        } else {
+          accept = act && open_accept(l, theta2, r2);
+          if constexpr (kF64) {
+            // the FP32 r2 of exact-to-2^-24 offsets is within about 2^-22 of
+            // the FP64 value (relative); inside 2^-19 of the threshold FP64
+            // decides
+            const float lhs = l * l, rhs = theta2 * r2;
+            if (act && fabsf(lhs - rhs) <= rhs * 1.9073486e-6f)
+              accept = open_accept64(ldexp(side, -(root_exp - ilogbf(l))), theta64, cn, p64);
+          }
+          if (kInside || (kF64 && inside_test)) {
+            const int level = root_exp - ilogbf(l);
+            const bool inside = ((ki ^ nk) >> (3 * (kMaxLevel - level))) == 0ull;
+            accept = accept && !inside;
+          }
+          open = act && !accept;
+        }
+        term(accept, dx, dy, dz, r2 + eps2, nd.com_m.w);
+        const uint64_t om = __ballot(open);
+        if (om) opened(nd.meta.x, nd.meta.y, om);
+      };
+      constexpr int kBatch = kF64 ? 2 : 4;  // children in scalar registers at a time
+      for (int c0 = 0; c0 < count; c0 += kBatch) {
+        CNode nd[kBatch];
+        double4 cn[kBatch];
+        uint64_t nk[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) {  // (the arrays are padded)
+          nd[q] = cnodes[first + c0 + q];
+          cn[q] = kF64 ? cc64[first + c0 + q] : make_double4(0, 0, 0, 0);
+          nk[q] = kInside || kF64 ? ckeys[first + c0 + q] : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q)
+          if (c0 + q < count) visit(nd[q], cn[q], nk[q]);
       }
-      wave_sync();
-      // an opening lane whose own target is among these members clears its
-      // bit in that member's entry (one lane per entry)
-      const int rel = s - st;
-      if (open && rel >= 0 && rel < take) {
-        uint32_t *wd = (uint32_t *)&tile[tc + rel] + kMaskWord + (hiword ? 1 : 0);
-        *wd &= ~(1u << bitpos);
+      since += count;
+    } else {
+      const int end = first - count;
+      int m = first;
+      auto member = [&](int j) {
+        const bool use = act && s != j;
+        if constexpr (kF64) {
+          const double4 q = x64[j];
+          const float dx = (float)(q.x - p64.x), dy = (float)(q.y - p64.y),
+                      dz = (float)(q.z - p64.z);
+          term(use, dx, dy, dz, dist2_exact(dx, dy, dz) + eps2, (float)q.w);
+        } else {
+          const float4 q = xm[j];
+          const float dx = q.x - me.x, dy = q.y - me.y, dz = q.z - me.z;
+          term(use, dx, dy, dz, dist2_exact(dx, dy, dz) + eps2, q.w);
+        }
+      };
+      for (; m + 4 <= end; m += 4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) member(m + q);
+        since += 4;
+        if (since >= kFlush) flush();
       }
-      tc += take;
-      st += take;
-      c -= take;
+      for (; m < end; ++m, ++since) member(m);
     }
-    cur = nd.meta.x;
+    if (since >= kFlush) flush();
+  };
+
+  const int root = __builtin_amdgcn_readfirstlane(grp.snap);
+  const uint64_t all = grp.count < kWave ? (1ull << grp.count) - 1ull : ~0ull;
+  auto pack = [](int first, int count, uint64_t m) {
+    return make_int4(first, count, (int)(uint32_t)m, (int)(uint32_t)(m >> 32));
+  };
+  auto unpack = [&](const int4 &e, int &first, int &count, uint64_t &m) {
+    first = __builtin_amdgcn_readfirstlane(e.x);
+    count = __builtin_amdgcn_readfirstlane(e.y);
+    m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.w) << 32) |
+        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.z);
+  };
+  {
+    constexpr int kItems = Team<kT>::kItems;
+    if (threadIdx.x == 0) S.stack[0] = pack(root, 1, all);
+    int sp = 1;
+    while (sp > 0) {
+      __syncthreads();
+      // (7 more entries an item at most)
+      const int room = (Team<kT>::kStack - kDepth - sp) / 7;
+      const int n = min(min(kItems, sp), max(room, 1));
+      for (int j = w; j < n; j += kT) {
+        int first, count, r = 0;
+        uint64_t mask;
+        unpack(S.stack[sp - n + j], first, count, mask);
+        item(first, count, mask, [&](int f, int c, uint64_t m) {
+          if (lane == 0) S.out[8 * j + r] = pack(f, c, m);
+          ++r;
+        });
+        if (lane == 0) S.nout[j] = r;
+      }
+      __syncthreads();
+      sp -= n;
+      int tot_new = 0;
+      for (int j0 = 0; j0 < n; j0 += kWave) {  // every wave counts, all copy
+        const int mine = j0 + lane < n ? S.nout[j0 + lane] : 0;
+        int inc = mine;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+          const int o = __shfl_up(inc, (unsigned)d, kWave);
+          if (lane >= d) inc += o;
+        }
+        for (int q = w; q * 8 < min(n - j0, kWave); q += kT) {
+          const int j = q * 8 + (lane >> 3), r = lane & 7;  // 8 items' slots
+          const int cnt = __shfl(mine, j, kWave), at = __shfl(inc, j, kWave) - cnt;
+          if (r < cnt) S.stack[sp + tot_new + at + r] = S.out[8 * (j0 + j) + r];
+        }
+        tot_new += __shfl(inc, kWave - 1, kWave);
+      }
+      sp += __builtin_amdgcn_readfirstlane(tot_new);
+    }
   }
-  if (tc > 0) flush(tc);
-  const float4 tt = tot[w][lane], tc4 = comp[w][lane];
-  const float ax = tt.x + tc4.x, ay = tt.y + tc4.y, az = tt.z + tc4.z, ph = tt.w + tc4.w;
-  const int nt = nts[w][lane];
+  flush();
+  float4 tt = tot[lane], tc4 = comp[lane];
+  nts[w][lane] = pn;
+  __syncthreads();
+  if (w > 0) continue;
+#pragma unroll 1
+  for (int v = 1; v < kT; ++v) {  // the waves' totals in their order
+    const float4 a = tots[v][lane], c = comps[v][lane];
+    neumaier_add(tt.x, tc4.x, a.x);
+    neumaier_add(tt.y, tc4.y, a.y);
+    neumaier_add(tt.z, tc4.z, a.z);
+    neumaier_add(tt.w, tc4.w, a.w);
+    tc4.x += c.x;
+    tc4.y += c.y;
+    tc4.z += c.z;
+    tc4.w += c.w;
+    pn += nts[v][lane];
+  }
 
   if (valid) {
     const int cid = perm[s];
     if (acc) {
-      acc[3 * cid] = G * ax;
-      acc[3 * cid + 1] = G * ay;
-      acc[3 * cid + 2] = G * az;
+      acc[3 * cid] = G * (tt.x + tc4.x);
+      acc[3 * cid + 1] = G * (tt.y + tc4.y);
+      acc[3 * cid + 2] = G * (tt.z + tc4.z);
     }
-    if (pot) pot[cid] = G * ph;
-    if (nterms) nterms[cid] = nt;
+    if (pot) pot[cid] = G * (tt.w + tc4.w);
+    if (nterms) nterms[cid] = pn;
   }
   }  // groups
 }
@@ -264,13 +312,19 @@ hipError_t launch_gravity(const Octree &all, const Groups &gs, int64_t max_group
                           const GravParams &gp, float *acc, float *pot, int32_t *nterms,
                           hipStream_t s) {
   if (max_groups <= 0 || all.nnodes == 0) return hipSuccess;
+  if (!all.cnodes) return hipErrorInvalidValue;
   // FP32: the containment test is compiled in or out; FP64: a runtime flag
-  auto kern = gp.f64 ? k_gravity<true, false>
-                     : (gp.inside_test ? k_gravity<false, true> : k_gravity<false, false>);
-  if (!all.gnodes) return hipErrorInvalidValue;
-  kern<<<persistent_grid((const void *)kern, kBlock, max_groups), kBlock, 0, s>>>(
-      all.gnodes, all.c64, all.xm, all.x64, all.keys, all.perm, gs, gp.theta2, gp.eps2, gp.G,
-      gp.inside_test, gp.theta, acc, pot, nterms);
+  auto pick = [&](auto team_c) {
+    constexpr int kT = decltype(team_c)::value;
+    return gp.f64 ? k_gravity<true, false, kT>
+                  : (gp.inside_test ? k_gravity<false, true, kT> : k_gravity<false, false, kT>);
+  };
+  auto kern = gp.team == 16 ? pick(std::integral_constant<int, 16>{})
+                            : pick(std::integral_constant<int, 4>{});
+  const int block = gp.team * kWave;
+  kern<<<persistent_grid((const void *)kern, block, max_groups, gp.team), block, 0, s>>>(
+      all.cnodes, all.ckeys, all.cc64, all.xm, all.x64, all.keys, all.perm, gs, gp.theta2,
+      gp.eps2, gp.G, gp.inside_test, gp.theta, acc, pot, nterms);
   return hipGetLastError();
 }
 

@@ -286,20 +286,26 @@ __global__ void k_nodes(const uint64_t *__restrict__ keys, int64_t m,
   }
 }
 
-// The parent's member count into every node that has one.
-__global__ void k_parents(Node *__restrict__ nodes, int64_t nnodes) {
+// The parent's member count into every node that has one; nch (nullable): the
+// number of children of every node.
+__global__ void k_parents(Node *__restrict__ nodes, int64_t nnodes, uint32_t *__restrict__ nch) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nnodes) return;
   const int4 meta = nodes[k].meta;
-  if (meta.w & kLeafBit) return;
+  if (meta.w & kLeafBit) {
+    if (nch) nch[k] = 0;
+    return;
+  }
   const int pc = (int)((unsigned)min(meta.z, 65535) << 16);
+  uint32_t nc = 0;
   int64_t c = k + 1;
-  while (c < meta.x) {
+  for (; c < meta.x; ++nc) {
     const int4 cm = nodes[c].meta;
     // (the low half as k_nodes wrote it; children are no roots)
     nodes[c].meta.w = (cm.w & 0xffff) | pc;
     c = cm.x;
   }
+  if (nch) nch[k] = nc;
 }
 
 // FP64 mass and first moments, tight box of one node, from its members or its
@@ -710,17 +716,35 @@ __global__ __launch_bounds__(kFillBlock) void k_term_fill(
   }
 }
 
-// The gravity walk's 32-byte node copies (after the moments).
-__global__ void k_gnodes(const Node *__restrict__ nodes, int64_t nnodes,
-                         GNode *__restrict__ gnodes) {
+// The gravity walk's node copies (after the moments): every internal node
+// writes its children's, a root also its own.
+__global__ void k_cnodes(const Node *__restrict__ nodes, const double4 *__restrict__ c64,
+                         const uint64_t *__restrict__ keys, int64_t nnodes,
+                         const uint32_t *__restrict__ cbase, const int32_t *__restrict__ nroot,
+                         int n_snap, CNode *__restrict__ cnodes, uint64_t *__restrict__ ckeys,
+                         double4 *__restrict__ cc64) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nnodes) return;
-  const Node nd = nodes[k];
-  GNode g;
-  g.com_m = nd.com_m;
-  g.meta = make_int4(nd.meta.x, nd.meta.y, (nd.meta.w & kLeafBit) ? nd.meta.z : -1,
-                     __float_as_int(nd.hi_l.w));
-  gnodes[k] = g;
+  const Node me = nodes[k];
+  auto put = [&](int64_t at, int64_t c, const Node &nd) {
+    CNode g;
+    g.com_m = nd.com_m;
+    const bool leaf = nd.meta.w & kLeafBit;
+    g.meta = make_int4(leaf ? nd.meta.y : (int)(cbase[c] + (uint32_t)n_snap),
+                       leaf ? -nd.meta.z : (int)(cbase[c + 1] - cbase[c]), (int)c,
+                       __float_as_int(nd.hi_l.w));
+    cnodes[at] = g;
+    ckeys[at] = keys[nd.meta.y];
+    if (cc64) cc64[at] = c64[c];
+  };
+  if ((me.meta.w & 255) == 0) put(n_snap == 1 ? 0 : segment_of(nroot, n_snap, k), k, me);
+  if (me.meta.w & kLeafBit) return;
+  int64_t at = (int64_t)cbase[k] + n_snap;
+  for (int64_t c = k + 1; c < me.meta.x; ++at) {
+    const Node nd = nodes[c];
+    put(at, c, nd);
+    c = nd.meta.x;
+  }
 }
 
 }  // namespace
@@ -734,6 +758,12 @@ static void launch_moments(const g3_tree *t, const Octree &o, hipStream_t s) {
   const unsigned nb = (unsigned)std::min<int64_t>(o.nnodes, 4096);
   k_moments_sub<<<nb, kBlock, 0, s>>>(A, o.subs, o.nsplit);
   k_moments_top<<<1, kTopBlock, 0, s>>>(A, o.tops, o.nsplit);
+}
+
+static void fill_cnodes(const g3_tree *t, const Octree &o, hipStream_t s) {
+  k_cnodes<<<nblk(o.nnodes), kBlock, 0, s>>>(o.nodes, t->f64 ? o.c64 : nullptr, o.keys, o.nnodes,
+                                             o.cbase, o.nroot, t->n_snap, o.cnodes, o.ckeys,
+                                             t->f64 ? o.cc64 : nullptr);
 }
 
 // Selects the members (gas only for the gas octree), sorts them and builds
@@ -859,22 +889,53 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
   if (m_gas) *m_gas = (int64_t)(uint32_t)(pin[2] & 0xffffffffll);
   if (nnodes <= 0 || nnodes >= (int64_t)INT32_MAX) { c->err = "node count out of range"; return G3_EHIP; }
   const bool grav = (&o == &t->all);
-  if (nnodes > o.cap_nodes || (grav && !o.gnodes) || o.cap_tops < max_tops(o.cap_n)) {
-    for (void *p : {(void *)o.nodes, (void *)o.mom, (void *)o.gnodes, (void *)o.tops})
+  if (nnodes > o.cap_nodes || o.cap_tops < max_tops(o.cap_n)) {
+    for (void *p : {(void *)o.nodes, (void *)o.mom, (void *)o.tops})
       if (p) (void)hipFree(p);
-    o.nodes = nullptr; o.mom = nullptr; o.gnodes = nullptr; o.tops = nullptr; o.cap_nodes = 0;
+    o.nodes = nullptr; o.mom = nullptr; o.tops = nullptr; o.cap_nodes = 0;
     const int64_t cap = nnodes + nnodes / 8 + 64;
     // (the lists of the moments in one buffer)
     if (dev_malloc(c, (void **)&o.nodes, cap * sizeof(Node)) != hipSuccess ||
         dev_malloc(c, (void **)&o.mom, cap * sizeof(double4)) != hipSuccess ||
         dev_malloc(c, (void **)&o.tops, max_tops(o.cap_n) * sizeof(int2) +
-                                            (cap + 2) * sizeof(int32_t)) != hipSuccess ||
-        (grav && dev_malloc(c, (void **)&o.gnodes, cap * sizeof(GNode)) != hipSuccess)) {
+                                            (cap + 2) * sizeof(int32_t)) != hipSuccess) {
       c->err = "device allocation of the octree nodes failed";
       return G3_ENOMEM;
     }
     o.cap_nodes = cap;
     o.cap_tops = max_tops(o.cap_n);
+  }
+  uint32_t *nch = nullptr, *ctmp = nullptr;
+  if (grav) {
+    const int64_t need = t->n_snap + nnodes + kChildPad;
+    if (need > o.cap_cnodes) {
+      for (void *p : {(void *)o.cnodes, (void *)o.ckeys, (void *)o.cbase})
+        if (p) (void)hipFree(p);
+      o.cnodes = nullptr; o.ckeys = nullptr; o.cbase = nullptr; o.cap_cnodes = 0;
+      const int64_t cap = need + nnodes / 8 + 64;
+      if (dev_malloc(c, (void **)&o.cnodes, cap * sizeof(CNode)) != hipSuccess ||
+          dev_malloc(c, (void **)&o.ckeys, cap * sizeof(uint64_t)) != hipSuccess ||
+          dev_malloc(c, (void **)&o.cbase, (cap + 1) * sizeof(uint32_t)) != hipSuccess) {
+        c->err = "device allocation of the gravity nodes failed";
+        return G3_ENOMEM;
+      }
+      o.cap_cnodes = cap;
+    }
+    if (f64 && need > o.cap_cc64) {
+      if (o.cc64) (void)hipFree(o.cc64);
+      o.cc64 = nullptr;
+      o.cap_cc64 = 0;
+      const int64_t cap = need + nnodes / 8 + 64;
+      if (dev_malloc(c, (void **)&o.cc64, cap * sizeof(double4)) != hipSuccess) {
+        c->err = "device allocation of the gravity nodes failed";
+        return G3_ENOMEM;
+      }
+      o.cap_cc64 = cap;
+    }
+    nch = (uint32_t *)scratch(c, kChildren,
+                              (nnodes + 1 + scan_tmp_elems(nnodes)) * sizeof(uint32_t));
+    if (!nch) { c->err = "device allocation of build scratch failed"; return G3_ENOMEM; }
+    ctmp = nch + nnodes + 1;
   }
   if (f64 && (!o.c64 || o.cap_c64 < nnodes)) {
     if (o.c64) (void)hipFree(o.c64);
@@ -898,14 +959,18 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
   k_nodes<<<nblk(m), kBlock, 0, s>>>(o.keys, m, o.soff, t->n_snap, t->sbox, off, lev, nnodes,
                                      o.nodes);
   k_nroot<<<nblk(t->n_snap + 1), kBlock, 0, s>>>(off, o.soff, t->n_snap, o.nroot);
-  k_parents<<<nblk(nnodes), kBlock, 0, s>>>(o.nodes, nnodes);
+  k_parents<<<nblk(nnodes), kBlock, 0, s>>>(o.nodes, nnodes, nch);
   if (nnodes > kSmallNodes) {
     const unsigned nb = (unsigned)((nnodes + kTermTile - 1) / kTermTile);
     k_split_count<<<nb, kBlock, 0, s>>>(o.nodes, (int)nnodes, bcount);
     k_split_write<<<nb, kBlock, 0, s>>>(o.nodes, (int)nnodes, bcount, o.subs, o.tops, o.nsplit);
   }
   launch_moments(t, o, s);
-  if (o.gnodes) k_gnodes<<<nblk(nnodes), kBlock, 0, s>>>(o.nodes, nnodes, o.gnodes);
+  if (grav) {
+    e = scan_u32(nch, o.cbase, nnodes, ctmp, s);
+    if (e != hipSuccess) { c->err = "scan launch failed"; return G3_EHIP; }
+    fill_cnodes(t, o, s);
+  }
   e = hipGetLastError();
   if (e != hipSuccess) { c->err = std::string("tree build launch: ") + hipGetErrorString(e); return G3_EHIP; }
   return G3_OK;
@@ -923,7 +988,7 @@ int refit_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, const float 
     k_permute<float><<<nblk(o.n), kBlock, 0, s>>>(order, o.n, (const float *)pos, mass, o.xm,
                                                   nullptr, nullptr, nullptr);
   launch_moments(t, o, s);
-  if (o.gnodes) k_gnodes<<<nblk(o.nnodes), kBlock, 0, s>>>(o.nodes, o.nnodes, o.gnodes);
+  if (&o == &t->all) fill_cnodes(t, o, s);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     c->err = std::string("tree refit launch: ") + hipGetErrorString(e);

@@ -1,0 +1,82 @@
+"""Gravity's work items (children side by side, members of leaves) at the
+sizes where their lists can go wrong, against the oracle: the smallest sets,
+leaves larger than a batch and a flush, chains of single children to the
+deepest level, forests, and active sets on both sides of the team rule.
+
+Counts of terms exact; acceleration within 1e-5 of the L1 sum of its terms (the
+parity tests' bound: FP32 terms good to a few 1e-7, compensated sums); the
+potential, of one sign, within 2e-6.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2003_10850_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def dev_t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2003_10850_amd import ops
+    return ops.Context(torch.device("cuda", 0))
+
+
+def points(kind, n):
+    rng = np.random.default_rng(n + 7)
+    pos = rng.random((n, 3))
+    if kind == "pairs":  # close pairs: chains of single-child nodes
+        pos[1::2] = pos[: n - n // 2][: len(pos[1::2])] + 3e-6
+    elif kind == "coincident":  # one deepest leaf of many members
+        pos[: n // 2] = 0.625
+    elif kind == "halo":
+        pos = 0.5 + 0.02 * rng.normal(0, 1, (n, 3))
+    return np.clip(pos, 0.0, 1.0 - 1e-6)
+
+
+def check(tree, t, p, act, rows):
+    from paper_2003_10850_amd import ops
+    g = {k: v.cpu().numpy() for k, v in ops.gravity(tree, params=p, active=act).items()}
+    ref = oracle.gravity(t, p, active=rows)
+    np.testing.assert_array_equal(g["nterms"][rows], ref["nterms"][rows])
+    err = np.linalg.norm(g["acc"][rows] - ref["acc"][rows], axis=1)
+    S = ref["S"][rows]
+    assert (err[S > 0] / S[S > 0]).max(initial=0) < 1e-5
+    some = ref["nterms"][rows] > 0
+    rel = np.abs(g["pot"][rows] - ref["pot"][rows])[some] / np.abs(ref["pot"][rows])[some]
+    assert rel.max(initial=0) < 2e-6
+
+
+@pytest.mark.parametrize("theta,leaf", [(0.5, 8), (0.8, 1), (0.0, 64)])
+@pytest.mark.parametrize("kind,n", [("uniform", 1), ("uniform", 2), ("uniform", 9),
+                                    ("uniform", 65), ("pairs", 300), ("coincident", 700),
+                                    ("halo", 2049)])
+def test_sets_against_oracle(ctx, kind, n, theta, leaf):
+    from paper_2003_10850_amd import ops
+    print(f"gravity items {kind} n={n} theta={theta} leaf={leaf}", flush=True)
+    p = inputs.Params(theta=theta, eps=1e-3, leaf_size=leaf)
+    pos, m = points(kind, n).astype(np.float32), np.full(n, 1.0 / n, np.float32)
+    tree = ops.Tree(ctx, dev_t(pos), dev_t(m), None, (0.0, 0.0, 0.0, 1.0), p)
+    t = oracle.Tree(pos.astype(np.float64), m.astype(np.float64), (0.0, 0.0, 0.0, 1.0),
+                    type=np.zeros(n, np.uint8), leaf_size=leaf)
+    check(tree, t, p, None, np.arange(n))
+
+
+@pytest.mark.parametrize("n_act", [1, 64, 65, 160000, 170000])
+def test_active_sets_on_both_sides_of_the_team_rule(ctx, n_act):
+    from paper_2003_10850_amd import ops
+    n = 200000
+    p = inputs.Params(theta=0.5, eps=1e-3)
+    pos, m = points("halo", n).astype(np.float32), np.full(n, 1.0 / n, np.float32)
+    rng = np.random.default_rng(n_act)
+    act = np.sort(rng.choice(n, n_act, replace=False)).astype(np.int32)
+    tree = ops.Tree(ctx, dev_t(pos), dev_t(m), None, (0.0, 0.0, 0.0, 1.0), p)
+    t = oracle.Tree(pos.astype(np.float64), m.astype(np.float64), (0.0, 0.0, 0.0, 1.0),
+                    type=np.zeros(n, np.uint8))
+    rows = act if n_act <= 300 else np.sort(rng.choice(act, 300, replace=False))
+    check(tree, t, p, dev_t(act), rows)
