@@ -17,6 +17,7 @@
 // adjoints are then pushed down to the members.
 #include "g3_device.h"
 #include "g3_internal.h"
+#include "g3_team.h"
 
 namespace g3 {
 
@@ -36,23 +37,29 @@ inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); 
 //   F    = (1/r) dW/dr  = -22 C/h^5 (1-q)^7 (1 + 7q + 16q^2)
 //   G    = (1/r) dW_h/dr = dF/dh = 22 C/h^6 (1-q)^6 (5 + 30q + 21q^2 - 224q^3)
 //   W_hh = d^2W/dh^2    = 6 C/h^5 (1-q)^6 (2 + 12q - 13q^2 - 218q^3 - 287q^4 + 1120q^5)
-struct Wc6 {
-  float W, Wh, F, G, Whh;
+// An SPH sum's gradients weigh F and G together, W_h and W_hh, and W and W_h,
+// each with the same two upstream factors (y, z); with the particle's powers
+// of 1/h folded into four coefficients a pair needs only the polynomials:
+//   y F  + z G    = t6 (f1 t p1 + f2 p2)
+//   y W_h + z W_hh = t6 (e1 t p3 + e2 p4)
+//   y W  + z W_h  = t7 (w1 t p5 + w2 p3)
+struct WcCoef {
+  float f1, f2, e1, e2, w1, w2;
 };
-
-__device__ __forceinline__ Wc6 wc6_all(float r, float hinv) {
-  const float q = r * hinv;
-  const float t = fmaxf(1.0f - q, 0.0f);
-  const float t2 = t * t, t3 = t2 * t, t6 = t3 * t3, t7 = t6 * t;
+__device__ __forceinline__ WcCoef wc6_coef(float y, float z, float hinv) {
   const float h2 = hinv * hinv, h3 = h2 * hinv, h4 = h2 * h2, h5 = h4 * hinv, h6 = h3 * h3;
-  Wc6 k;
-  k.W = kC * h3 * t7 * t * (1.0f + q * (8.0f + q * (25.0f + q * 32.0f)));
-  k.Wh = kC * h4 * t7 * (-3.0f + q * (-21.0f + q * (-29.0f + q * (133.0f + q * 448.0f))));
-  k.F = -22.0f * kC * h5 * t7 * (1.0f + q * (7.0f + q * 16.0f));
-  k.G = 22.0f * kC * h6 * t6 * (5.0f + q * (30.0f + q * (21.0f - q * 224.0f)));
-  k.Whh = 6.0f * kC * h5 * t6 *
-          (2.0f + q * (12.0f + q * (-13.0f + q * (-218.0f + q * (-287.0f + q * 1120.0f)))));
-  return k;
+  return {-22.0f * kC * h5 * y, 22.0f * kC * h6 * z, kC * h4 * y,
+          6.0f * kC * h5 * z,   kC * h3 * y,         kC * h4 * z};
+}
+__device__ __forceinline__ float wc6_yf_zg(float q, float t, float t6, float f1, float f2) {
+  return t6 * (f1 * t * (1.0f + q * (7.0f + q * 16.0f)) +
+               f2 * (5.0f + q * (30.0f + q * (21.0f - q * 224.0f))));
+}
+__device__ __forceinline__ float wc6_wh_poly(float q) {
+  return -3.0f + q * (-21.0f + q * (-29.0f + q * (133.0f + q * 448.0f)));
+}
+__device__ __forceinline__ float wc6_whh_poly(float q) {
+  return 2.0f + q * (12.0f + q * (-13.0f + q * (-218.0f + q * (-287.0f + q * 1120.0f))));
 }
 
 // ---------------------------------------------------------------- density
@@ -62,7 +69,7 @@ __device__ __forceinline__ Wc6 wc6_all(float r, float hinv) {
 //   gbar_rho  = g_rho  - g_omega h rho' / (3 rho^2)
 //   gbar_rho' = g_rho' + g_omega h / (3 rho)
 //   dL/dh    += g_omega rho' / (3 rho)        (the explicit h of Omega)
-// written into bw[s] = (h, gbar_rho, gbar_rho', 0) at the active gas rows.
+// written into bw[s] = (h, gbar_rho, gbar_rho', 1/h) at the active gas rows.
 __global__ void k_density_bwd_prep(const int32_t *__restrict__ active, int64_t n_act,
                                    const int32_t *__restrict__ iperm, int64_t n_caller,
                                    const float *__restrict__ h, const float *__restrict__ rho,
@@ -80,14 +87,16 @@ __global__ void k_density_bwd_prep(const int32_t *__restrict__ active, int64_t n
   const float go = g_omega ? g_omega[id] : 0.0f;
   const float gr = (g_rho ? g_rho[id] : 0.0f) - go * hi * rp / (3.0f * r * r);
   const float gd = (g_drho ? g_drho[id] : 0.0f) + go * hi / (3.0f * r);
-  bw[s] = make_float4(hi, gr, gd, 0.0f);
+  bw[s] = make_float4(hi, gr, gd, 1.0f / hi);
   if (g_h && go != 0.0f) g_h[id] += go * rp / (3.0f * r);
 }
 
 __global__ void k_density_bwd_init(const int32_t *__restrict__ perm, int64_t m,
                                    const float *__restrict__ h, float4 *__restrict__ bw) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < m) bw[s] = make_float4(h[perm[s]], 0.0f, 0.0f, 0.0f);
+  if (s >= m) return;
+  const float hs = h[perm[s]];
+  bw[s] = make_float4(hs, 0.0f, 0.0f, 1.0f / hs);
 }
 
 // Adjoint of the smoothing-length solve. Each active gas h_i is the root of
@@ -115,7 +124,7 @@ __global__ void k_hsolve_bwd_prep(const int32_t *__restrict__ active, int64_t n_
   const float N = 4.18879020f * hi * hi * hi * r / mi;  // (4 pi/3) h^3 rho / m
   const float den = 3.0f * r + hi * rp;                 // 3 rho Omega
   if (!(fabsf(N / n_ngb - 1.0f) <= 1e-3f) || !(den > 0.0f) || gh == 0.0f) return;
-  bw[s] = make_float4(hi, -gh * hi / den, 0.0f, 0.0f);
+  bw[s] = make_float4(hi, -gh * hi / den, 0.0f, 1.0f / hi);
   if (g_mass) g_mass[id] += gh * hi * r / (mi * den);
 }
 
@@ -127,25 +136,38 @@ __global__ void k_hsolve_bwd_prep(const int32_t *__restrict__ active, int64_t n_
 //       dL/dx_p += b (x_p - x_q)
 //       dL/dm_p += gbar_rho_q W(r,h_q) + gbar_rho'_q W_h(r,h_q)
 // The pair q = p (r = 0) adds the self terms of h and m.
-__global__ __launch_bounds__(kBlock) void k_density_bwd(
-    const Node *__restrict__ nodes, const float4 *__restrict__ xm,
-    const float4 *__restrict__ bw, const int32_t *__restrict__ perm, const Groups gs,
+// A team of waves serves a group (g3_team.h); the tiles go to the waves in
+// turn and the waves' totals are added in their order, so the gradients are
+// the same on every run. 1.25e5 members of ~295 neighbours: 2886 us with one
+// wave a group, 1179 with teams of 4, 1108 at 80 registers (6 waves a SIMD),
+// 930 with the coefficients formed once a particle.
+struct DTile {
+  float4 x[kTile];  // position, mass
+  float4 b[kTile];  // fl(h^2) or -1, 1/h, f1, f2
+  float2 w[kTile];  // w1, w2
+};
+template <int kT>
+__global__ __launch_bounds__(kT * kWave, kT == 4 ? 6 : 1) void k_density_bwd(
+    const float4 *__restrict__ xm, const float4 *__restrict__ bw,
+    const int32_t *__restrict__ perm, const Groups gs, const Terms tm,
     float *__restrict__ g_pos, float *__restrict__ g_mass, float *__restrict__ g_h) {
-  __shared__ float4 tx[kWpb][kTile];
-  __shared__ float4 tb[kWpb][kTile];
+  __shared__ TeamLds<kT> search;
+  __shared__ DTile tiles[kT];
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
+  float4 *tx = tiles[w].x, *tb = tiles[w].b;
+  float2 *tw = tiles[w].w;
   int range = 0;
-  for (int g; (g = next_group(gs, range)) >= 0;) {
+  for (int g; (g = team_next_group(gs, range, search)) >= 0;) {
     const Group grp = group_at(gs, g);
     const bool valid = lane < grp.count;
     const int s = valid ? grp.t0 + lane : grp.t0;
     const float4 me = xm[s], mb = bw[s];
     const float hp = valid ? mb.x : -1.0f;
-    const float hp2 = sq_exact(hp), hinv = 1.0f / mb.x;
+    const float hp2 = sq_exact(hp), hinv = mb.w;
+    const WcCoef kp = wc6_coef(mb.y, mb.z, hinv);
     const bool own_on = valid && (mb.y != 0.0f || mb.z != 0.0f);
-    float gx = 0.f, gy = 0.f, gz = 0.f, gm = 0.f, gh = 0.f;
-    float cx = 0.f, cy = 0.f, cz = 0.f, cm = 0.f, ch = 0.f;
-    int tc = 0, cand = 0;
+    float sum[5] = {}, cmp[5] = {};  // position, mass, h
+    int cand = 0;
     // the box of the group's particles and the largest radius of their own
     // sums: a candidate q whose box_dist2 to the box reaches that radius and
     // (when q's sums carry gradients) fl(h_q^2) meets no lane's test, since
@@ -154,9 +176,12 @@ __global__ __launch_bounds__(kBlock) void k_density_bwd(
                              valid ? me.z : INFINITY, 0.f);
     float4 thi = make_float4(valid ? me.x : -INFINITY, valid ? me.y : -INFINITY,
                              valid ? me.z : -INFINITY, 0.f);
-    float hmax2 = own_on ? hp2 : -1.0f;
+    // a member without h (or with a NaN) is still its neighbours' neighbour
+    const float want = valid ? fmaxf(hp, 0.0f) : -1.0f;
+    float hmax2 = own_on ? hp2 : -1.0f, hg = want;  // hg: the group's largest
 #pragma unroll
     for (int m = 1; m < kWave; m <<= 1) {
+      hg = fmaxf(hg, __shfl_xor(hg, m));
       tlo.x = fminf(tlo.x, __shfl_xor(tlo.x, m));
       tlo.y = fminf(tlo.y, __shfl_xor(tlo.y, m));
       tlo.z = fminf(tlo.z, __shfl_xor(tlo.z, m));
@@ -170,6 +195,7 @@ __global__ __launch_bounds__(kBlock) void k_density_bwd(
       tlo = make_float4(su(tlo.x), su(tlo.y), su(tlo.z), 0.f);
       thi = make_float4(su(thi.x), su(thi.y), su(thi.z), 0.f);
       hmax2 = su(hmax2);
+      hg = su(hg);
     }
     auto flush = [&](int nc) {
       {
@@ -179,39 +205,43 @@ __global__ __launch_bounds__(kBlock) void k_density_bwd(
           vb = bw[cand];
         }
         const float d2 = box_dist2(make_float3(vx.x, vx.y, vx.z), tlo, thi);
-        const bool keep = lane < nc && (d2 < hmax2 || ((vb.y != 0.0f || vb.z != 0.0f) &&
-                                                       d2 < sq_exact(vb.x)));
+        const bool on = vb.y != 0.0f || vb.z != 0.0f;
+        const bool keep = lane < nc && (d2 < hmax2 || (on && d2 < sq_exact(vb.x)));
         const uint64_t km = __ballot(keep);
         const int slot = (int)__builtin_amdgcn_mbcnt_hi(
             (uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
         // kept candidates in their order at the front; the scan stops at nc
         if (keep) {
-          tx[w][slot] = vx;
-          tb[w][slot] = vb;
+          const WcCoef kq = wc6_coef(vb.y, vb.z, vb.w);
+          tx[slot] = vx;
+          tb[slot] = make_float4(on ? sq_exact(vb.x) : -1.0f, vb.w, kq.f1, kq.f2);
+          tw[slot] = make_float2(kq.w1, kq.w2);
         }
         nc = __popcll(km);
       }
       wave_sync();
       float px = 0.f, py = 0.f, pz = 0.f, pm = 0.f, ph = 0.f;
       for (int k = 0; k < nc; ++k) {
-        const float4 q = tx[w][k], qb = tb[w][k];
+        const float4 q = tx[k], qb = tb[k];
         const float dx = sub_exact(q.x, me.x), dy = sub_exact(q.y, me.y),
                     dz = sub_exact(q.z, me.z);
         const float r2 = dist2_exact(dx, dy, dz);
         const bool own = own_on && r2 < hp2;
-        const bool nbr = valid && (qb.y != 0.0f || qb.z != 0.0f) && r2 < sq_exact(qb.x);
+        const bool nbr = valid && r2 < qb.x;
         if (own || nbr) {
           const float r = __builtin_amdgcn_sqrtf(r2);
           float a = 0.0f;
           if (own) {
-            const Wc6 kp = wc6_all(r, hinv);
-            a = q.w * (mb.y * kp.F + mb.z * kp.G);
-            ph += q.w * (mb.y * kp.Wh + mb.z * kp.Whh);
+            const float u = r * hinv, v = fmaxf(1.0f - u, 0.0f), v3 = v * v * v, v6 = v3 * v3;
+            a = q.w * wc6_yf_zg(u, v, v6, kp.f1, kp.f2);
+            ph += q.w * v6 * (kp.e1 * v * wc6_wh_poly(u) + kp.e2 * wc6_whh_poly(u));
           }
           if (nbr) {
-            const Wc6 kq = wc6_all(r, 1.0f / qb.x);
-            a += me.w * (qb.y * kq.F + qb.z * kq.G);
-            pm += qb.y * kq.W + qb.z * kq.Wh;
+            const float2 qw = tw[k];
+            const float u = r * qb.y, v = fmaxf(1.0f - u, 0.0f), v3 = v * v * v, v6 = v3 * v3;
+            a += me.w * wc6_yf_zg(u, v, v6, qb.z, qb.w);
+            pm += v6 * v * (qw.x * v * (1.0f + u * (8.0f + u * (25.0f + u * 32.0f))) +
+                            qw.y * wc6_wh_poly(u));
           }
           // x_p - x_q = -(dx, dy, dz)
           px -= a * dx;
@@ -219,51 +249,33 @@ __global__ __launch_bounds__(kBlock) void k_density_bwd(
           pz -= a * dz;
         }
       }
-      neumaier_add(gx, cx, px);
-      neumaier_add(gy, cy, py);
-      neumaier_add(gz, cz, pz);
-      neumaier_add(gm, cm, pm);
-      neumaier_add(gh, ch, ph);
+      neumaier_add(sum[0], cmp[0], px);
+      neumaier_add(sum[1], cmp[1], py);
+      neumaier_add(sum[2], cmp[2], pz);
+      neumaier_add(sum[3], cmp[3], pm);
+      neumaier_add(sum[4], cmp[4], ph);
       wave_sync();
     };
-    int cur = grp.root;
-    while (cur < grp.end) {
-      const Node nd = nodes[cur];
-      const float hm = fmaxf(hp, nd.lo_h.w);
-      const bool want = valid && box_dist2(make_float3(me.x, me.y, me.z), nd.lo_h, nd.hi_l) <
-                                     sq_exact(hm);
-      if (__ballot(want) == 0ull) {
-        cur = nd.meta.x;
-        continue;
-      }
-      if (!(nd.meta.w & kLeafBit) && nd.meta.z > kTile) {
-        ++cur;
-        continue;
-      }
-      int st = nd.meta.y, c = nd.meta.z;
-      while (c > 0) {
-        const int take = min(c, kTile - tc);
-        if (lane >= tc && lane < tc + take) cand = st + lane - tc;
-        tc += take;
-        st += take;
-        c -= take;
-        if (tc == kTile) {
-          flush(kTile);
-          tc = 0;
-        }
-      }
-      cur = nd.meta.x;
-    }
-    if (tc > 0) flush(tc);
-    if (valid) {
+    team_search(
+        tm, grp.snap, search, make_float3(me.x, me.y, me.z), want, tlo, thi, hg,
+        [](float h, float hmax) { return h < 0.0f ? -1.0f : sq_exact(fmaxf(h, hmax)); },
+        [&](int ntiles, int count) {
+          for (int j = w; j < ntiles; j += kT) {
+            const int nc = min(kTile, count - j * kTile);
+            cand = lane < nc ? search.cand[j * kTile + lane] : 0;
+            flush(nc);
+          }
+        });
+    team_totals<kT, 5, sizeof(DTile) / 4>((float *)tiles, w, lane, sum, cmp);
+    if (valid && w == 0) {
       const int cid = perm[s];
       if (g_pos) {
-        g_pos[3 * cid] += gx + cx;
-        g_pos[3 * cid + 1] += gy + cy;
-        g_pos[3 * cid + 2] += gz + cz;
+        g_pos[3 * cid] += sum[0] + cmp[0];
+        g_pos[3 * cid + 1] += sum[1] + cmp[1];
+        g_pos[3 * cid + 2] += sum[2] + cmp[2];
       }
-      if (g_mass) g_mass[cid] += gm + cm;
-      if (g_h) g_h[cid] += gh + ch;
+      if (g_mass) g_mass[cid] += sum[3] + cmp[3];
+      if (g_h) g_h[cid] += sum[4] + cmp[4];
     }
   }
 }
@@ -775,67 +787,67 @@ struct HSide {
   float4 xm, vh, aux, up;
 };
 
-// Partials of one pair term (target i, neighbour j) of
+// What one particle p of a pair is owed: by the pair term whose target is p,
+// and by the one whose target is its neighbour q. A term with target i and
+// neighbour j is
 //   l = g_acc_i . a_ij + g_dudt_i du_ij,
 //   a_ij  = -m_j (A_i g_i + A_j g_j + Pi gbar) x,   x = x_i - x_j, v = v_i - v_j
 //   du_ij = m_j (A_i g_i + Pi gbar / 2) v.x,        g_k = F(r, h_k), gbar = (g_i + g_j)/2
-//   Pi = -alpha (c_i + c_j - 3w) w / (rho_i + rho_j) if w = v.x / r < 0, else 0,
-// with respect to the target's inputs (side 0) or the neighbour's (side 1):
+//   Pi = -alpha (c_i + c_j - 3w) w / (rho_i + rho_j) if w = v.x / r < 0, else 0.
 // d[0..2] position, d[3..5] velocity, d[6] h, d[7] A, d[8] c, d[9] rho
-// through Pi, d[10] m (neighbour only). The chain rules used:
+// through Pi, d[10] m. The chain rules used:
 //   dl/dx = coef g_acc + L_vx v + (L_r / r) x,  dl/dv = L_vx x,
 //   L_vx = dl/dvx + dl/dPi dPi/dw / r,  L_r = sum_k dl/dg_k F_r(r,h_k) - dl/dPi dPi/dw w / r.
-__device__ __forceinline__ void hydro_pair_partials(const HSide &I, const HSide &J, float alpha,
-                                                    float dx, float dy, float dz, float r,
-                                                    int side, float *d) {
-  // x = x_i - x_j (dx, dy, dz given as that difference)
-  const float mj = J.xm.w;
-  const float vxx = I.vh.x - J.vh.x, vyy = I.vh.y - J.vh.y, vzz = I.vh.z - J.vh.z;
+// v.x, w, Pi and the kernel factors are the same in both terms (x and v change
+// sign together) and are formed once; with x = x_p - x_q throughout, the
+// second term's position and velocity partials take the sign of its neighbour
+// side.
+__device__ __forceinline__ void hydro_pair_adjoint(const HSide &P, const HSide &Q, float alpha,
+                                                   bool q_on, float dx, float dy, float dz,
+                                                   float r2, float *d) {
+  const float rinv = __builtin_amdgcn_rsqf(r2), r = r2 * rinv;
+  const float vxx = P.vh.x - Q.vh.x, vyy = P.vh.y - Q.vh.y, vzz = P.vh.z - Q.vh.z;
   const float vx = vxx * dx + vyy * dy + vzz * dz;
-  const float rinv = 1.0f / r;
   const float w = vx * rinv;
-  float gi, gir, gih, gj, gjr, gjh;
-  wc6_f_derivs(r, I.aux.w, gi, gir, gih);
-  wc6_f_derivs(r, J.aux.w, gj, gjr, gjh);
-  const float Ai = I.aux.x, Aj = J.aux.x, ci = I.aux.y, cj = J.aux.y;
-  const float rsum = I.aux.z + J.aux.z;
+  float gp, gpr, gph, gq, gqr, gqh;
+  wc6_f_derivs(r, P.aux.w, gp, gpr, gph);
+  wc6_f_derivs(r, Q.aux.w, gq, gqr, gqh);
+  const float csum = P.aux.y + Q.aux.y;
+  const float rs = 1.0f / (P.aux.z + Q.aux.z), ar = alpha * rs;
   const bool neg = w < 0.0f;
-  const float Pi = neg ? -alpha * (ci + cj - 3.0f * w) * w / rsum : 0.0f;
-  const float Pw = neg ? -alpha * (ci + cj - 6.0f * w) / rsum : 0.0f;
-  const float Pc = neg ? -alpha * w / rsum : 0.0f;
-  const float Prho = neg ? -Pi / rsum : 0.0f;
-  const float gbar = 0.5f * (gi + gj);
-  const float gax = I.up.x, gay = I.up.y, gaz = I.up.z, gd = I.up.w;
-  const float sdot = gax * dx + gay * dy + gaz * dz;
-  const float T1 = Ai * gi, T2 = Aj * gj;
-  const float dPi = mj * gbar * (0.5f * gd * vx - sdot);
-  const float dgb = mj * Pi * (0.5f * gd * vx - sdot);
-  const float dgi = mj * Ai * (gd * vx - sdot) + 0.5f * dgb;
-  const float dgj = -mj * Aj * sdot + 0.5f * dgb;
-  const float coef = -mj * (T1 + T2 + Pi * gbar);
-  const float Lvx = gd * mj * (T1 + 0.5f * Pi * gbar) + dPi * Pw * rinv;
-  const float Lr = dgi * gir + dgj * gjr - dPi * Pw * w * rinv;
-  const float lr = Lr * rinv;
-  const float px = coef * gax + Lvx * vxx + lr * dx;
-  const float py = coef * gay + Lvx * vyy + lr * dy;
-  const float pz = coef * gaz + Lvx * vzz + lr * dz;
-  if (side == 0) {
-    d[0] = px; d[1] = py; d[2] = pz;
-    d[3] = Lvx * dx; d[4] = Lvx * dy; d[5] = Lvx * dz;
-    d[6] = dgi * gih;
-    d[7] = mj * gi * (gd * vx - sdot);
-    d[8] = dPi * Pc;
-    d[9] = dPi * Prho;
-    d[10] = 0.0f;
-  } else {
-    d[0] = -px; d[1] = -py; d[2] = -pz;
-    d[3] = -Lvx * dx; d[4] = -Lvx * dy; d[5] = -Lvx * dz;
-    d[6] = dgj * gjh;
-    d[7] = -mj * gj * sdot;
-    d[8] = dPi * Pc;
-    d[9] = dPi * Prho;
-    d[10] = -(T1 + T2 + Pi * gbar) * sdot + gd * (T1 + 0.5f * Pi * gbar) * vx;  // l / m_j
-  }
+  const float Pi = neg ? -ar * (csum - 3.0f * w) * w : 0.0f;
+  const float Pw = neg ? -ar * (csum - 6.0f * w) : 0.0f;
+  const float Pc = neg ? -ar * w : 0.0f;
+  const float gbar = 0.5f * (gp + gq);
+  const float Tp = P.aux.x * gp, Tq = Q.aux.x * gq, V = Pi * gbar;
+  const float K = Tp + Tq + V;
+  const float mp = P.xm.w, mq = Q.xm.w;
+  // target p: sdot = g_acc_p . x; target q: its x is -x
+  const float sp = P.up.x * dx + P.up.y * dy + P.up.z * dz;
+  const float sq = -(Q.up.x * dx + Q.up.y * dy + Q.up.z * dz);
+  const float vp = P.up.w * vx, vq = Q.up.w * vx;  // g_dudt v.x
+  const float bp = mq * (0.5f * vp - sp), bq = mp * (0.5f * vq - sq);
+  const float ep = mq * (vp - sp), eq = mp * (vq - sq);
+  const float b = bp + bq, dPi = b * gbar, hb = 0.5f * b * Pi;
+  // dl/dg_p and dl/dg_q over both terms
+  const float dgp = P.aux.x * (ep - mp * sq) + hb;
+  const float dgq = Q.aux.x * (eq - mq * sp) + hb;
+  const float dPw = dPi * Pw;
+  const float Lvx = mq * P.up.w * (Tp + 0.5f * V) + mp * Q.up.w * (Tq + 0.5f * V) + dPw * rinv;
+  const float lr = (dgp * gpr + dgq * gqr - dPw * w * rinv) * rinv;
+  const float cp = -mq * K, cq = mp * K;
+  d[0] += cp * P.up.x + cq * Q.up.x + Lvx * vxx + lr * dx;
+  d[1] += cp * P.up.y + cq * Q.up.y + Lvx * vyy + lr * dy;
+  d[2] += cp * P.up.z + cq * Q.up.z + Lvx * vzz + lr * dz;
+  d[3] += Lvx * dx;
+  d[4] += Lvx * dy;
+  d[5] += Lvx * dz;
+  d[6] += dgp * gph;
+  d[7] += gp * (ep - mp * sq);
+  d[8] += dPi * Pc;
+  d[9] -= dPi * Pi * rs;
+  // (only a target's neighbour is owed a mass partial: not 0 times its factors)
+  if (q_on) d[10] += vq * (Tq + 0.5f * V) - K * sq;
 }
 
 __global__ void k_hydro_bwd_up(const int32_t *__restrict__ active, int64_t n_act,
@@ -856,18 +868,23 @@ __global__ void k_hydro_bwd_up(const int32_t *__restrict__ active, int64_t n_act
 // the pair (target p, neighbour q) if p is active, and (target q,
 // neighbour p) if q is active. Then A and c are mapped back to u, rho and
 // Omega: A = (gamma-1) u / (Omega rho), c = sqrt(gamma (gamma-1) u).
-__global__ __launch_bounds__(kBlock) void k_hydro_bwd(
-    const Node *__restrict__ nodes, const float4 *__restrict__ xm,
-    const float4 *__restrict__ vh, const float4 *__restrict__ aux,
-    const float4 *__restrict__ up, const int32_t *__restrict__ perm, const Groups gs,
-    float alpha, float gamma, const float *__restrict__ u, const float *__restrict__ omega,
+// Bound by VALU issue (a pair is ~150 operations); 125 registers, four waves
+// a SIMD. Teams and tiles as in the density's adjoint. 1.25e5 particles of
+// ~295 neighbours: 10671 us with one wave a group and the two terms of a pair
+// by themselves, 2210 so.
+template <int kT>
+__global__ __launch_bounds__(kT * kWave, kT == 4 ? 4 : 1) void k_hydro_bwd(
+    const float4 *__restrict__ xm, const float4 *__restrict__ vh,
+    const float4 *__restrict__ aux, const float4 *__restrict__ up,
+    const int32_t *__restrict__ perm, const Groups gs, const Terms tm, float alpha, float gamma, const float *__restrict__ u, const float *__restrict__ omega,
     float *__restrict__ g_pos, float *__restrict__ g_vel, float *__restrict__ g_mass,
     float *__restrict__ g_h, float *__restrict__ g_u, float *__restrict__ g_rho,
     float *__restrict__ g_omega) {
-  __shared__ HSide T[kWpb][kTile];
+  __shared__ TeamLds<kT> search;
+  __shared__ HSide T[kT][kTile];
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
   int range = 0;
-  for (int g; (g = next_group(gs, range)) >= 0;) {
+  for (int g; (g = team_next_group(gs, range, search)) >= 0;) {
     const Group grp = group_at(gs, g);
     const bool valid = lane < grp.count;
     const int s = valid ? (gs.targets ? gs.targets[grp.t0 + lane] : grp.t0 + lane) : grp.t0;
@@ -882,7 +899,7 @@ __global__ __launch_bounds__(kBlock) void k_hydro_bwd(
     float acc[kN], cmp[kN];
 #pragma unroll
     for (int k = 0; k < kN; ++k) acc[k] = cmp[k] = 0.0f;
-    int tc = 0, cand = 0;
+    int cand = 0;
     // the box of the group's particles and their largest fl(h^2): a
     // candidate q whose box_dist2 to the box reaches both that and
     // fl(h_q^2) is in no lane's symmetric neighbourhood, since box_dist2
@@ -891,9 +908,12 @@ __global__ __launch_bounds__(kBlock) void k_hydro_bwd(
                              valid ? P.xm.z : INFINITY, 0.f);
     float4 thi = make_float4(valid ? P.xm.x : -INFINITY, valid ? P.xm.y : -INFINITY,
                              valid ? P.xm.z : -INFINITY, 0.f);
-    float hmax2 = valid ? sq_exact(hp) : -1.0f;
+    // a member without h (or with a NaN) is still its neighbours' neighbour
+    const float want = valid ? fmaxf(hp, 0.0f) : -1.0f;
+    float hmax2 = valid ? sq_exact(hp) : -1.0f, hg = want;  // hg: the group's largest
 #pragma unroll
     for (int m = 1; m < kWave; m <<= 1) {
+      hg = fmaxf(hg, __shfl_xor(hg, m));
       tlo.x = fminf(tlo.x, __shfl_xor(tlo.x, m));
       tlo.y = fminf(tlo.y, __shfl_xor(tlo.y, m));
       tlo.z = fminf(tlo.z, __shfl_xor(tlo.z, m));
@@ -907,6 +927,7 @@ __global__ __launch_bounds__(kBlock) void k_hydro_bwd(
       tlo = make_float4(su(tlo.x), su(tlo.y), su(tlo.z), 0.f);
       thi = make_float4(su(thi.x), su(thi.y), su(thi.z), 0.f);
       hmax2 = su(hmax2);
+      hg = su(hg);
     }
     auto flush = [&](int nc) {
       {
@@ -941,55 +962,24 @@ __global__ __launch_bounds__(kBlock) void k_hydro_bwd(
         const float r2 = dist2_exact(dx, dy, dz);
         const bool in = valid && r2 < sq_exact(fmaxf(hp, Q.vh.w)) && r2 > 0.0f;
         const bool q_on = Q.up.x != 0.f || Q.up.y != 0.f || Q.up.z != 0.f || Q.up.w != 0.f;
-        if (in && (p_on || q_on)) {
-          const float r = __builtin_amdgcn_sqrtf(r2);
-          float d[kN];
-          if (p_on) {  // target p, neighbour q: x = x_p - x_q
-            hydro_pair_partials(P, Q, alpha, -dx, -dy, -dz, r, 0, d);
-#pragma unroll
-            for (int k = 0; k < kN; ++k) part[k] += d[k];
-          }
-          if (q_on) {  // target q, neighbour p: x = x_q - x_p
-            hydro_pair_partials(Q, P, alpha, dx, dy, dz, r, 1, d);
-#pragma unroll
-            for (int k = 0; k < kN; ++k) part[k] += d[k];
-          }
-        }
+        if (in && (p_on || q_on)) hydro_pair_adjoint(P, Q, alpha, q_on, -dx, -dy, -dz, r2, part);
       }
 #pragma unroll
       for (int k = 0; k < kN; ++k) neumaier_add(acc[k], cmp[k], part[k]);
       wave_sync();
     };
-    int cur = grp.root;
-    while (cur < grp.end) {
-      const Node nd = nodes[cur];
-      const float hm = fmaxf(hp, nd.lo_h.w);
-      const bool want = valid && box_dist2(make_float3(P.xm.x, P.xm.y, P.xm.z), nd.lo_h,
-                                           nd.hi_l) < sq_exact(hm);
-      if (__ballot(want) == 0ull) {
-        cur = nd.meta.x;
-        continue;
-      }
-      if (!(nd.meta.w & kLeafBit) && nd.meta.z > kTile) {
-        ++cur;
-        continue;
-      }
-      int st = nd.meta.y, c = nd.meta.z;
-      while (c > 0) {
-        const int take = min(c, kTile - tc);
-        if (lane >= tc && lane < tc + take) cand = st + lane - tc;
-        tc += take;
-        st += take;
-        c -= take;
-        if (tc == kTile) {
-          flush(kTile);
-          tc = 0;
-        }
-      }
-      cur = nd.meta.x;
-    }
-    if (tc > 0) flush(tc);
-    if (valid) {
+    team_search(
+        tm, grp.snap, search, make_float3(P.xm.x, P.xm.y, P.xm.z), want, tlo, thi, hg,
+        [](float h, float hmax) { return h < 0.0f ? -1.0f : sq_exact(fmaxf(h, hmax)); },
+        [&](int ntiles, int count) {
+          for (int j = w; j < ntiles; j += kT) {
+            const int nc = min(kTile, count - j * kTile);
+            cand = lane < nc ? search.cand[j * kTile + lane] : 0;
+            flush(nc);
+          }
+        });
+    team_totals<kT, kN, sizeof(HSide) * kTile / 4>((float *)T, w, lane, acc, cmp);
+    if (valid && w == 0) {
       float tot[kN];
 #pragma unroll
       for (int k = 0; k < kN; ++k) tot[k] = acc[k] + cmp[k];
@@ -1020,8 +1010,9 @@ __global__ __launch_bounds__(kBlock) void k_hydro_bwd(
 }  // namespace
 
 hipError_t launch_hydro_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
-                            const Groups &all_gas, int64_t max_groups, int64_t n_act,
-                            const int32_t *active, float alpha, float gamma, const float *u,
+                            const Groups &all_gas, int64_t max_groups, const Terms &tm,
+                            int64_t n_act, const int32_t *active, float alpha, float gamma,
+                            const float *u,
                             const float *omega, const float *g_acc, const float *g_dudt,
                             float4 *up, float *g_pos, float *g_vel, float *g_mass, float *g_h,
                             float *g_u, float *g_rho, float *g_omega, hipStream_t s) {
@@ -1033,9 +1024,12 @@ hipError_t launch_hydro_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
     k_hydro_bwd_up<<<nblk(na), kBlock, 0, s>>>(active, na, iperm, n_caller, g_acc, g_dudt, up);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_hydro_bwd<<<persistent_grid((const void *)k_hydro_bwd, kBlock, max_groups), kBlock, 0, s>>>(
-      gas.nodes, gas.xm, gas.vh, gas.aux, up, gas.perm, all_gas, alpha, gamma, u, omega, g_pos,
-      g_vel, g_mass, g_h, g_u, g_rho, g_omega);
+  const int team = adjoint_team(m);
+  auto kern = team == 16 ? k_hydro_bwd<16> : k_hydro_bwd<4>;
+  const int block = team * kWave;
+  kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
+      gas.xm, gas.vh, gas.aux, up, gas.perm, all_gas, tm, alpha, gamma, u, omega, g_pos, g_vel,
+      g_mass, g_h, g_u, g_rho, g_omega);
   return hipGetLastError();
 }
 
@@ -1083,15 +1077,27 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
   return hipGetLastError();
 }
 
+static hipError_t density_bwd(const Octree &gas, const Groups &gs, int64_t max_groups,
+                              const Terms &tm, const float4 *bw, float *g_pos, float *g_mass,
+                              float *g_h, hipStream_t s) {
+  const int team = adjoint_team(gas.n);
+  auto kern = team == 16 ? k_density_bwd<16> : k_density_bwd<4>;
+  const int block = team * kWave;
+  kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
+      gas.xm, bw, gas.perm, gs, tm, g_pos, g_mass, g_h);
+  return hipGetLastError();
+}
+
 hipError_t launch_density_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
-                              const Groups &all_gas, int64_t max_groups, int64_t n_act,
-                              const int32_t *active, const float *h, const float *rho,
+                              const Groups &all_gas, int64_t max_groups, const Terms &tm,
+                              int64_t n_act, const int32_t *active, const float *h,
+                              const float *rho,
                               const float *drho, const float *g_rho, const float *g_drho,
                               const float *g_omega, float *g_pos, float *g_mass, float *g_h,
                               hipStream_t s) {
   const int64_t m = gas.n;
   if (m == 0) return hipSuccess;
-  float4 *bw = gas.aux;  // (h, gbar_rho, gbar_rho', 0) per sorted gas member
+  float4 *bw = gas.aux;  // (h, gbar_rho, gbar_rho', 1/h) per sorted gas member
   k_density_bwd_init<<<nblk(m), kBlock, 0, s>>>(gas.perm, m, h, bw);
   const int64_t na = active ? n_act : n_caller;
   if (na > 0)
@@ -1099,19 +1105,18 @@ hipError_t launch_density_bwd(Octree &gas, const int32_t *iperm, int64_t n_calle
                                                     g_rho, g_drho, g_omega, bw, g_h);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_density_bwd<<<persistent_grid((const void *)k_density_bwd, kBlock, max_groups), kBlock, 0,
-                  s>>>(gas.nodes, gas.xm, bw, gas.perm, all_gas, g_pos, g_mass, g_h);
-  return hipGetLastError();
+  return density_bwd(gas, all_gas, max_groups, tm, bw, g_pos, g_mass, g_h, s);
 }
 
 hipError_t launch_density_solve_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
-                                    const Groups &all_gas, int64_t max_groups, int64_t n_act,
-                                    const int32_t *active, float n_ngb, const float *h,
+                                    const Groups &all_gas, int64_t max_groups, const Terms &tm,
+                                    int64_t n_act, const int32_t *active, float n_ngb,
+                                    const float *h,
                                     const float *rho, const float *drho, const float *g_h,
                                     float *g_pos, float *g_mass, hipStream_t s) {
   const int64_t m = gas.n;
   if (m == 0) return hipSuccess;
-  float4 *bw = gas.aux;  // (h, gbar_rho, 0, 0) per sorted gas member
+  float4 *bw = gas.aux;  // (h, gbar_rho, 0, 1/h) per sorted gas member
   k_density_bwd_init<<<nblk(m), kBlock, 0, s>>>(gas.perm, m, h, bw);
   const int64_t na = active ? n_act : n_caller;
   if (na > 0)
@@ -1119,9 +1124,7 @@ hipError_t launch_density_solve_bwd(Octree &gas, const int32_t *iperm, int64_t n
                                                    gas.xm, n_ngb, bw, g_mass);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_density_bwd<<<persistent_grid((const void *)k_density_bwd, kBlock, max_groups), kBlock, 0,
-                  s>>>(gas.nodes, gas.xm, bw, gas.perm, all_gas, g_pos, g_mass, nullptr);
-  return hipGetLastError();
+  return density_bwd(gas, all_gas, max_groups, tm, bw, g_pos, g_mass, nullptr, s);
 }
 
 }  // namespace g3

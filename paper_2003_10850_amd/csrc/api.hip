@@ -463,6 +463,21 @@ int hydro_team(int64_t max_targets) {
 int gravity_team(int64_t max_targets) {
   return (max_targets + kWave - 1) / kWave <= 2560 ? 16 : 4;
 }
+// The SPH adjoints, conduction and velocity gradients, as the density: us of
+// one density solve and hydro force with their gradients, and of one pass of
+// the modules (viscosity, conduction, gradients), teams of 4/16:
+//   groups       256        512        1024       1536       2048       4096
+//   gradients    3032/2136  5011/3681  7902/6858  7408/7512  7555/8196
+//   modules                 1582/1001  3375/2960             3181/3553  3941/5200
+// Conduction's pair is so light that one wave a group wins again where
+// groups are plenty (us, 1/4: 3242/2748 of 8192 groups, 8181/9138 of 65536).
+int adjoint_team(int64_t members) {
+  return (members + kWave - 1) / kWave <= 1536 ? 16 : 4;
+}
+int velgrad_team(int64_t max_targets) { return adjoint_team(max_targets); }
+int conduction_team(int64_t max_targets) {
+  return (max_targets + kWave - 1) / kWave <= 24576 ? adjoint_team(max_targets) : 1;
+}
 
 unsigned persistent_grid(const void *kern, int block, int64_t max_groups, int team) {
   static std::mutex mu;
@@ -1124,17 +1139,23 @@ int g3_conduction(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active,
   }
   const Tuning tu = tuning_for(c, kTuneHydro, active ? std::min<int64_t>(n_act, o.n) : o.n);
   float4 *ch = (float4 *)scratch(c, kCondCh, (size_t)o.n * sizeof(float4));
-  if (!ch) return fail(c, G3_ENOMEM, "g3_conduction: allocation failed");
+  TermBufs tb;
+  const int team = conduction_team(active ? std::min<int64_t>(n_act, o.n) : o.n);
+  if (!ch || (team > 1 && !reserve_terms(c, o, t->n_snap, &tb)))
+    return fail(c, G3_ENOMEM, "g3_conduction: allocation failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, n_act, active, &wk, s, tu.split);
   if (st) return st;
-  // node hmax from h (the walk's symmetric radius), then the pair inputs
+  // the terminals' or nodes' largest h (the symmetric radius), then the pair
+  // inputs
   hipError_t e = launch_hydro_prep(o, nullptr, nullptr, h, nullptr, nullptr, 1.0f, 0, s);
-  if (e == hipSuccess) e = refit_hmax(o, s);
+  if (e == hipSuccess)
+    e = team > 1 ? build_terms(o, t->n_snap, tu.walk_leaf, true, tb, s) : refit_hmax(o, s);
   if (e == hipSuccess)
     e = launch_conduction_prep(o, u, h, 0, rho, (float)kappa0, (float)kappa_exp, ch, s);
   if (e == hipSuccess)
-    e = launch_conduction(o, wk.gs, wk.max_groups, tu.walk_leaf, ch, dudt, npairs, s);
+    e = launch_conduction(o, wk.gs, wk.max_groups, tu.walk_leaf, tb.terms(), team, ch, dudt,
+                          npairs, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_conduction");
   c->err.clear();
   return G3_OK;
@@ -1171,13 +1192,18 @@ int g3_velocity_gradients(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *a
     return G3_OK;
   }
   const Tuning tu = tuning_for(c, kTuneDensity, active ? std::min<int64_t>(n_act, o.n) : o.n);
+  TermBufs tb;
+  if (!reserve_terms(c, o, t->n_snap, &tb))
+    return fail(c, G3_ENOMEM, "g3_velocity_gradients: allocation failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, n_act, active, &wk, s, tu.split);
   if (st) return st;
-  // (v, h) in sorted order, then the gather walk
+  // (v, h) in sorted order, then the gather search
   hipError_t e = launch_hydro_prep(o, vel, nullptr, h, nullptr, nullptr, 1.0f, 0, s);
+  if (e == hipSuccess) e = build_terms(o, t->n_snap, tu.walk_leaf, false, tb, s);
   if (e == hipSuccess)
-    e = launch_velgrad(o, wk.gs, wk.max_groups, tu.walk_leaf, rho, omega, div_v, curl_v, s);
+    e = launch_velgrad(o, wk.gs, wk.max_groups, tb.terms(), velgrad_team(wk.max_targets), rho,
+                       omega, div_v, curl_v, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_velocity_gradients");
   c->err.clear();
   return G3_OK;
@@ -1741,14 +1767,17 @@ int g3_density_backward(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *act
   c->last_stream = s;
   Octree &o = t->gas;
   if (o.n == 0) return G3_OK;
+  TermBufs tb;
+  if (!reserve_terms(c, o, t->n_snap, &tb))
+    return fail(c, G3_ENOMEM, "g3_density_backward: scratch allocation failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, o.n, nullptr, &wk, s);
   if (st) return st;
   hipError_t e = launch_hydro_prep(o, nullptr, nullptr, h, nullptr, nullptr, 1.0f, 0, s);
-  if (e == hipSuccess) e = refit_hmax(o, s);
+  if (e == hipSuccess) e = build_terms(o, t->n_snap, kAdjointLeaf, true, tb, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_density_backward prep");
-  e = launch_density_bwd(o, t->iperm_gas, t->n, wk.gs, wk.max_groups, n_act, active, h, rho,
-                         drho_dh, g_rho, g_drho_dh, g_omega, g_pos, g_mass, g_h, s);
+  e = launch_density_bwd(o, t->iperm_gas, t->n, wk.gs, wk.max_groups, tb.terms(), n_act, active,
+                         h, rho, drho_dh, g_rho, g_drho_dh, g_omega, g_pos, g_mass, g_h, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_density_backward");
   c->err.clear();
   return G3_OK;
@@ -1773,14 +1802,17 @@ int g3_density_solve_backward(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_
   c->last_stream = s;
   Octree &o = t->gas;
   if (o.n == 0) return G3_OK;
+  TermBufs tb;
+  if (!reserve_terms(c, o, t->n_snap, &tb))
+    return fail(c, G3_ENOMEM, "g3_density_solve_backward: scratch allocation failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, o.n, nullptr, &wk, s);
   if (st) return st;
   hipError_t e = launch_hydro_prep(o, nullptr, nullptr, h, nullptr, nullptr, 1.0f, 0, s);
-  if (e == hipSuccess) e = refit_hmax(o, s);
+  if (e == hipSuccess) e = build_terms(o, t->n_snap, kAdjointLeaf, true, tb, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_density_solve_backward prep");
-  e = launch_density_solve_bwd(o, t->iperm_gas, t->n, wk.gs, wk.max_groups, n_act, active,
-                               (float)p->n_ngb, h, rho, drho_dh, g_h, g_pos, g_mass, s);
+  e = launch_density_solve_bwd(o, t->iperm_gas, t->n, wk.gs, wk.max_groups, tb.terms(), n_act,
+                               active, (float)p->n_ngb, h, rho, drho_dh, g_h, g_pos, g_mass, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_density_solve_backward");
   c->err.clear();
   return G3_OK;
@@ -1809,14 +1841,17 @@ int g3_hydro_force_backward(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t 
   if (o.n == 0) return G3_OK;
   const SphParams sp = sph_params(c, p, t, Tuning());
   float4 *up = (float4 *)scratch(c, kAdjSrc, o.n * sizeof(float4));
-  if (!up) return fail(c, G3_ENOMEM, "g3_hydro_force_backward: scratch allocation failed");
+  TermBufs tb;
+  if (!up || !reserve_terms(c, o, t->n_snap, &tb))
+    return fail(c, G3_ENOMEM, "g3_hydro_force_backward: scratch allocation failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, o.n, nullptr, &wk, s);
   if (st) return st;
   hipError_t e = launch_hydro_prep(o, vel, u, h, rho, omega, sp.gamma, 0, s);
-  if (e == hipSuccess) e = refit_hmax(o, s);
+  if (e == hipSuccess) e = build_terms(o, t->n_snap, kAdjointLeaf, true, tb, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_hydro_force_backward prep");
-  e = launch_hydro_bwd(o, t->iperm_gas, t->n, wk.gs, wk.max_groups, n_act, active, sp.alpha,
+  e = launch_hydro_bwd(o, t->iperm_gas, t->n, wk.gs, wk.max_groups, tb.terms(), n_act, active,
+                       sp.alpha,
                        sp.gamma, u, omega, g_acc, g_dudt, up, g_pos, g_vel, g_mass, g_h, g_u,
                        g_rho, g_omega, s);
   if (e != hipSuccess) return hip_fail(c, e, "g3_hydro_force_backward");

@@ -284,10 +284,15 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
                        hipStream_t s);
 
 // Waves of the team that serves one group, from the (host-side bound on the)
-// number of targets: 4 or 16, for the hydro force also 1 (no team).
+// number of targets: 4 or 16, for the hydro force and conduction also 1 (no
+// team).
 int density_team(int64_t max_targets, int f64);
 int hydro_team(int64_t max_targets);
 int gravity_team(int64_t max_targets);
+int adjoint_team(int64_t members);  // SPH adjoints: every gas member is a target
+int conduction_team(int64_t max_targets);
+int velgrad_team(int64_t max_targets);
+constexpr int kAdjointLeaf = 64;  // the SPH adjoints' walk_leaf
 
 // Active set -> group table of one octree (scratch owned by the ctx).
 // rows[t] is the index in `active` of target t (nullptr with every member
@@ -361,8 +366,8 @@ hipError_t launch_hydro_ext_prep(Octree &gas, const float *u, const float *rho,
 // Velocity divergence and curl (switches.hip), after the hydro prep of vh
 // (v, h); rho, omega in caller order.
 hipError_t launch_velgrad(const Octree &gas, const Groups &gs, int64_t max_groups,
-                          int walk_leaf, const float *rho, const float *omega, float *div_v,
-                          float *curl_v, hipStream_t s);
+                          const Terms &tm, int team, const float *rho, const float *omega,
+                          float *div_v, float *curl_v, hipStream_t s);
 // The viscosity strength step and the Balsara factor of the rows `active`
 // (nullptr: rows 0..n-1), see switches.hip.
 struct SwitchStep {
@@ -386,26 +391,29 @@ hipError_t launch_gravity(const Octree &all, const Groups &gs, int64_t max_group
 
 // Adjoints. Gradients are ADDED to the caller-order arrays (nullable).
 // Density: every gas member walks its symmetric neighbourhood (all_gas:
-// the groups of every gas member); the node hmax must be refit from h.
+// the groups of every gas member); tm: the terminals of kAdjointLeaf, with h.
 hipError_t launch_density_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
-                              const Groups &all_gas, int64_t max_groups, int64_t n_act,
-                              const int32_t *active, const float *h, const float *rho,
+                              const Groups &all_gas, int64_t max_groups, const Terms &tm,
+                              int64_t n_act, const int32_t *active, const float *h,
+                              const float *rho,
                               const float *drho, const float *g_rho, const float *g_drho,
                               const float *g_omega, float *g_pos, float *g_mass, float *g_h,
                               hipStream_t s);
 // Through the smoothing-length solve: the density adjoint seeded from g_h
 // by the implicit function theorem on N_eff(h) = N_ngb (rows that did not
-// converge pass nothing); hmax refit from h as above.
+// converge pass nothing); tm as above.
 hipError_t launch_density_solve_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
-                                    const Groups &all_gas, int64_t max_groups, int64_t n_act,
-                                    const int32_t *active, float n_ngb, const float *h,
+                                    const Groups &all_gas, int64_t max_groups, const Terms &tm,
+                                    int64_t n_act, const int32_t *active, float n_ngb,
+                                    const float *h,
                                     const float *rho, const float *drho, const float *g_h,
                                     float *g_pos, float *g_mass, hipStream_t s);
 // Hydro: like the density (every gas member, symmetric walk) after the
 // hydro prep of vh and aux; scratch up [n_gas].
 hipError_t launch_hydro_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
-                            const Groups &all_gas, int64_t max_groups, int64_t n_act,
-                            const int32_t *active, float alpha, float gamma, const float *u,
+                            const Groups &all_gas, int64_t max_groups, const Terms &tm,
+                            int64_t n_act, const int32_t *active, float alpha, float gamma,
+                            const float *u,
                             const float *omega, const float *g_acc, const float *g_dudt,
                             float4 *up, float *g_pos, float *g_vel, float *g_mass, float *g_h,
                             float *g_u, float *g_rho, float *g_omega, hipStream_t s);
@@ -421,13 +429,13 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
                               double *rr, float *g_pos, float *g_mass, hipStream_t s);
 
 // Thermal conduction (conduction.hip): ch [n_gas] scratch of the sorted
-// pair inputs; the gas octree's node hmax must be refit from h first.
+// pair inputs; tm: the terminals, with h.
 hipError_t launch_conduction_prep(Octree &gas, const float *u, const void *h, int f64,
                                   const float *rho, float kappa0, float kappa_exp,
                                   float4 *ch, hipStream_t s);
 hipError_t launch_conduction(const Octree &gas, const Groups &gs, int64_t max_groups,
-                             int walk_leaf, const float4 *ch, float *dudt, int32_t *npairs,
-                             hipStream_t s);
+                             int walk_leaf, const Terms &tm, int team, const float4 *ch,
+                             float *dudt, int32_t *npairs, hipStream_t s);
 
 // Time integration (integrate.hip). One tick's particle update, see
 // k_update: a particle takes part iff every_particle or bin >= kmin.

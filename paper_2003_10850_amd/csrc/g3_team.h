@@ -210,4 +210,43 @@ struct TeamSums {
   }
 };
 
+// The waves' own totals (sum, compensation) added into wave 0's, in the order
+// of the waves; buf: [T] areas of kWords floats, at least C x 64, whose earlier
+// use by their wave is over.
+template <int T, int C, int kWords>
+__device__ __forceinline__ void team_totals(float *buf, int w, int lane, float (&sum)[C],
+                                            float (&cmp)[C]) {
+  static_assert(kWords >= C * kWave, "the areas hold one float a lane and component");
+  float *mine = buf + (size_t)w * kWords + lane;
+#pragma unroll
+  for (int k = 0; k < C; ++k) mine[k * kWave] = sum[k];
+  __syncthreads();
+  if (w == 0)
+#pragma unroll 1
+    for (int v = 1; v < T; ++v)
+#pragma unroll
+      for (int k = 0; k < C; ++k)
+        neumaier_add(sum[k], cmp[k], buf[(size_t)v * kWords + k * kWave + lane]);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < C; ++k) mine[k * kWave] = cmp[k];
+  __syncthreads();
+  if (w == 0)
+#pragma unroll 1
+    for (int v = 1; v < T; ++v)
+#pragma unroll
+      for (int k = 0; k < C; ++k) cmp[k] += buf[(size_t)v * kWords + k * kWave + lane];
+}
+
+// The waves' counts added up (a wave's area holds one word a lane or more).
+template <int T, int kWords>
+__device__ __forceinline__ void team_count(int *buf, int w, int lane, int &n) {
+  __syncthreads();
+  buf[(size_t)w * kWords + lane] = n;
+  __syncthreads();
+  n = 0;
+#pragma unroll
+  for (int v = 0; v < T; ++v) n += buf[(size_t)v * kWords + lane];
+}
+
 }  // namespace g3

@@ -124,3 +124,72 @@ def test_every_team_size_gives_the_same_bits(ctx, fp64):
     for a, b in ((all_d, few_d), (all_f, few_f)):
         for k in a:
             assert torch.equal(a[k][at], b[k][at]), k
+
+
+def close(a, b, what):
+    # the same 64-candidate partial sums, compensated over the tiles in another
+    # order: a last rounding of the total and one or two of each factor on it
+    a, b = a.double(), b.double()
+    lim = 2e-6 * b.abs() + 1e-7 * b.abs().max()
+    assert bool(((a - b).abs() <= lim).all()), what
+
+
+@pytest.mark.parametrize("m", [64, 641, 5000])
+def test_adjoints_of_a_forest_equal_the_single_trees(ctx, m):
+    # the forest's 10^5 members and more take teams of 4, the single snapshots
+    # (which other tests hold against the oracle) teams of 16
+    from paper_2003_10850_amd import ops
+    count = -(-125000 // m)
+    some = 25
+    print(f"teams adjoint forest {count} x {m}", flush=True)
+    p = inputs.Params(n_ngb=48.0)
+    g = torch.Generator(device="cuda").manual_seed(m)
+    R = lambda *s: torch.rand(*s, generator=g, device="cuda")
+    n = count * m
+    pos, mass = R(n, 3), (0.5 + R(n)) / m
+    h = 2.25 * m ** (-1.0 / 3.0) * (0.8 + 0.4 * R(n))
+    vel, u, rho, om = R(n, 3) - 0.5, 0.5 + R(n), 0.5 + R(n), 0.5 + R(n)
+    box = (0.0, 0.0, 0.0, 1.0)
+    ups = [R(n) - 0.5 for _ in range(3)] + [R(n, 3) - 0.5, R(n) - 0.5]
+
+    def grads(tree, r):
+        x = [t[r].clone().requires_grad_(True) for t in (pos, mass, h, vel, u, rho, om)]
+        d = ops.density_ad(tree, x[0], x[1], x[2])
+        f = ops.hydro_force_ad(tree, x[0], x[3], x[1], x[4], x[2], x[5], x[6])
+        gd = torch.autograd.grad(d, x[:3], [t[r] for t in ups[:3]])
+        return gd + torch.autograd.grad(f, x, [t[r] for t in ups[3:]])
+
+    off = np.arange(count + 1, dtype=np.int64) * m
+    all_g = grads(ops.Tree(ctx, pos, mass, None, [box] * count, p, snap_off=off), slice(0, n))
+    for k in np.linspace(0, count - 1, some).astype(int):
+        r = slice(k * m, (k + 1) * m)
+        one = grads(ops.Tree(ctx, pos[r].clone(), mass[r].clone(), None, box, p), r)
+        for i, (a, b) in enumerate(zip(all_g, one)):
+            close(a[r], b, (int(k), i))
+
+
+@pytest.mark.parametrize("log_few", [10, 15, 19])
+def test_conduction_and_gradients_of_every_team_size(ctx, log_few):
+    # 1.6e6 targets: conduction without teams, gradients in teams of 4; the
+    # first 2^19 in teams of 4, fewer in teams of 16
+    from paper_2003_10850_amd import g3, ops
+    n = 1600000
+    w = inputs.uniform(n=n, seed=21)
+    p = inputs.Params(n_ngb=48.0)
+    c = ops.Context(torch.device("cuda", 0))
+    for kind in (g3.G3_TUNE_DENSITY, g3.G3_TUNE_HYDRO):
+        c.set_tuning(kind, 128, -1)
+    tree = ops.Tree(c, dev_t(w.pos.astype(np.float32)), dev_t(w.mass.astype(np.float32)), None,
+                    tuple(w.box), p)
+    few = torch.sort(tree.export(1)["order"][: 1 << log_few]).values
+    g = torch.Generator(device="cuda").manual_seed(2)
+    R = lambda *s: torch.rand(*s, generator=g, device="cuda")
+    h = 2.25 * n ** (-1.0 / 3.0) * (0.8 + 0.4 * R(n))
+    vel, u, rho, om = R(n, 3) - 0.5, 0.5 + R(n), 0.5 + R(n), 0.5 + R(n)
+    at = few.long()
+    a, b = [ops.conduction(tree, u, h, rho, 1.0, 2.5, active=x) for x in (None, few)]
+    assert torch.equal(a["npairs"][at], b["npairs"][at])
+    close(a["dudt"][at], b["dudt"][at], "dudt")
+    a, b = [ops.velocity_gradients(tree, vel, h, rho, om, active=x) for x in (None, few)]
+    for k in a:
+        close(a[k][at], b[k][at], k)
