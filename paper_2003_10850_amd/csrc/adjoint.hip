@@ -17,6 +17,7 @@
 // adjoints are then pushed down to the members.
 #include "g3_device.h"
 #include "g3_internal.h"
+#include "g3_items.h"
 #include "g3_team.h"
 
 namespace g3 {
@@ -24,7 +25,6 @@ namespace g3 {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kWpb = kBlock / kWave;
 constexpr int kTile = kWave;
 constexpr float kC = 6.7889530412636603f;  // 1365 / (64 pi)
 
@@ -295,28 +295,23 @@ __device__ __forceinline__ float dpp_from(float v) {
 // the lanes pair off across one lane bit (5, 4, 3, 2), and each keeps the
 // half of its values that its bit selects plus its partner's copy of that
 // half; two pairwise exchanges (bits 1, 0) then complete the quads' sums.
-// Lane pairs: xor 32 and xor 16 by LDS permute, then the DPP row mirror
-// (xor 15), half-row mirror (xor 7) and the quad permutations xor 3, xor 1;
-// each pairs lanes that differ in the step's bit and agree in the bits
-// above it. Every lane must be active.
+// Bits 5 and 4 by the half-wave and row swaps (one swap serves both
+// partners), then the DPP row mirror (xor 15), half-row mirror (xor 7) and
+// the quad permutations xor 3, xor 1; each pairs lanes that differ in the
+// step's bit and agree in the bits above it. Every lane must be active.
 __device__ __forceinline__ float wave_reduce_scatter16(float (&v)[16], int lane) {
-  {
-    const bool up = (lane & 32) != 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float send = up ? v[i] : v[i + 8];
-      const float keep = up ? v[i + 8] : v[i];
-      v[i] = keep + __shfl_xor(send, 32);
-    }
+  for (int i = 0; i < 8; ++i) {
+    // (a.lo, b.lo) and (a.hi, b.hi) of a = v[i], b = v[i + 8]
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]),
+                                                    __float_as_uint(v[i + 8]), false, false);
+    v[i] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
   }
-  {
-    const bool up = (lane & 16) != 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float send = up ? v[i] : v[i + 4];
-      const float keep = up ? v[i + 4] : v[i];
-      v[i] = keep + __shfl_xor(send, 16);
-    }
+  for (int i = 0; i < 4; ++i) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]),
+                                                    __float_as_uint(v[i + 4]), false, false);
+    v[i] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
   }
   {
     const bool up = (lane & 8) != 0;
@@ -448,9 +443,6 @@ struct __align__(16) GEntry {
 // 32-bit words 5 and 6 of an entry
 constexpr int kGMaskWord = 5;
 
-// items that wait: at most 7 siblings on each of the 22 levels
-constexpr int kGStack = 7 * (kMaxLevel + 1) + 1;
-
 __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
 #pragma clang fp contract(off)
   const float lhs = l * l;
@@ -458,7 +450,8 @@ __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
   return lhs < rhs;
 }
 
-// The Barnes-Hut walk of the forward kernel; each term of target i with
+// The Barnes-Hut walk of the forward kernel by teams (g3_items.h); what a wave
+// accepts waits in its own tile of 64 entries. Each term of target i with
 // source s (x = x_i - x_s, S = r^2 + eps^2) and upstream gradients
 // (ga, gp) of a_i and phi_i contributes
 //   dL/dx  = G m ( -ga / S^(3/2) + 3 (ga . x) x / S^(5/2) + gp x / S^(3/2) )
@@ -468,22 +461,27 @@ __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
 // kFixed: the sums go to fixed-point counter pairs (gsrc_fx [n][4][2],
 // gnode_fx [nnodes][4][2], scale from mx), else to FP32 atomics (gsrc,
 // gnode).
-template <bool kFixed, bool kInside>
-__global__ __launch_bounds__(kBlock) void k_gravity_bwd(
+// Bound by vector issue: about 65 instructions an entry, 10 of them the
+// reduction (16 and three LDS permutes before the half-wave swaps; sums by
+// the matrix cores, one-hot rows times the values, came to 4.8 ms, the FP32
+// products do not overlap), 3 the fixed-point conversion of 16 entries at
+// once; the atomics cost 0.3 ms. 5e5 targets of a clustered box: 3.95 ms with
+// one wave a group, 3.6 with teams of 4; 2^14 targets: 1.5 and 0.25.
+template <bool kFixed, bool kInside, int kT>
+__global__ __launch_bounds__(kT * kWave, kT == 4 ? 6 : 1) void k_gravity_bwd(
     const CNode *__restrict__ cnodes, const uint64_t *__restrict__ ckeys,
     const float4 *__restrict__ xm, const uint64_t *__restrict__ keys, const int32_t *__restrict__ perm, const Groups gs,
     float theta2, float eps2, float G, const float *__restrict__ g_acc,
     const float *__restrict__ g_pot, float4 *__restrict__ gsrc, float4 *__restrict__ gnode,
     unsigned long long *__restrict__ gsrc_fx, unsigned long long *__restrict__ gnode_fx,
     const unsigned *__restrict__ mx, int64_t n_all, int64_t n_act) {
-  __shared__ GEntry tiles[kWpb][kTile];
-  __shared__ int4 stacks[kWpb][kGStack];
+  __shared__ Team<kT> S;
+  __shared__ GEntry tiles[kT][kTile];
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
   GEntry *tile = tiles[w];
-  int4 *stack = stacks[w];
   const double scale = kFixed ? fx_scale(mx, eps2, G, n_all, n_act) : 1.0;
   int range = 0;
-  for (int g; (g = next_group(gs, range)) >= 0;) {
+  for (int g; (g = team_take_group(gs, range, S)) >= 0;) {
     const Group grp = group_at(gs, g);
     const int64_t t = grp.t0 + lane;
     const bool valid = lane < grp.count;
@@ -509,50 +507,55 @@ __global__ __launch_bounds__(kBlock) void k_gravity_bwd(
       }
       wave_sync();
       float px = 0.f, py = 0.f, pz = 0.f;
-      for (int k0 = 0; k0 < n4; k0 += 4) {
-        // the source sides of four entries: (-dL/dx_i, dL/dm_s) per entry
-        float v[16];
+      // sixteen entries a round: after their four sums every lane holds one
+      // total, of entry k0 + 4 (lane & 3) + (lane >> 4)
+      for (int k0 = 0; k0 < n4; k0 += 16) {
+        float tot = 0.0f;
+#pragma unroll 1
+        for (int q = 0; q < 4 && k0 + 4 * q < n4; ++q) {
+          // the source sides of four entries without the factor G:
+          // (-dL/dx_i, dL/dm_s) per entry
+          float v[16];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int k = k0 + e;
-          const float4 ep = tile[k].p;
-          // 0 or all ones: the lane's bit (its own target's bit is clear)
-          const int32_t use = __builtin_amdgcn_sbfe(
-              (int32_t)maskw[k * (int)(sizeof(GEntry) / 4)], bitpos, 1u);
-          const float dx = ep.x - me.x, dy = ep.y - me.y, dz = ep.z - me.z;  // x_s - x_i
-          const float S =
-              __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
-          // masked here, so that an unused entry adds exact zeros even at S = 0
-          const float inv = __int_as_float(__float_as_int(__builtin_amdgcn_rsqf(S)) & use);
-          const float inv3 = inv * inv * inv;
-          const float Gm = G * ep.w;
-          const float gx_ = -(gax * dx + gay * dy + gaz * dz);  // ga . x, x = x_i - x_s
-          const float c3 = 3.0f * gx_ * inv3 * inv * inv;
-          // dL/dx with x = -(dx, dy, dz)
-          const float Dx = Gm * (-gax * inv3 - c3 * dx - gpp * dx * inv3);
-          const float Dy = Gm * (-gay * inv3 - c3 * dy - gpp * dy * inv3);
-          const float Dz = Gm * (-gaz * inv3 - c3 * dz - gpp * dz * inv3);
-          const float Dm = -G * (gx_ * inv3 + gpp * inv);
-          px += Dx;
-          py += Dy;
-          pz += Dz;
-          v[4 * e] = -Dx;
-          v[4 * e + 1] = -Dy;
-          v[4 * e + 2] = -Dz;
-          v[4 * e + 3] = Dm;
+          for (int e = 0; e < 4; ++e) {
+            const int k = k0 + 4 * q + e;
+            const float4 ep = tile[k].p;
+            // 0 or all ones: the lane's bit (its own target's bit is clear)
+            const int32_t use = __builtin_amdgcn_sbfe(
+                (int32_t)maskw[k * (int)(sizeof(GEntry) / 4)], bitpos, 1u);
+            const float dx = ep.x - me.x, dy = ep.y - me.y, dz = ep.z - me.z;  // x_s - x_i
+            const float S =
+                __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
+            // masked here, so that an unused entry adds exact zeros even at S = 0
+            const float inv = __int_as_float(__float_as_int(__builtin_amdgcn_rsqf(S)) & use);
+            const float inv2 = inv * inv, inv3 = inv2 * inv;
+            const float gd = gax * dx + gay * dy + gaz * dz;  // -ga . x, x = x_i - x_s
+            const float m3 = ep.w * inv3;
+            // dL/dx = -m3 ga - c (dx, dy, dz), x = -(dx, dy, dz)
+            const float c = m3 * (gpp - 3.0f * gd * inv2);
+            const float Dx = m3 * gax + c * dx, Dy = m3 * gay + c * dy, Dz = m3 * gaz + c * dz;
+            px -= Dx;
+            py -= Dy;
+            pz -= Dz;
+            v[4 * e] = Dx;
+            v[4 * e + 1] = Dy;
+            v[4 * e + 2] = Dz;
+            v[4 * e + 3] = gd * inv3 - gpp * inv;
+          }
+          // lane l holds the wave's total of entry l >> 4, component (l >> 2) & 3
+          const float sum = wave_reduce_scatter16(v, lane);
+          tot = (lane & 3) == q ? sum : tot;
         }
-        // lane l holds the wave's total of entry l >> 4, component (l >> 2) & 3
-        const float tot = wave_reduce_scatter16(v, lane);
-        const int e = lane >> 4, comp = (lane >> 2) & 3;
-        if ((lane & 3) == 0 && k0 + e < nc) {
-          const int src = tile[k0 + e].meta.x;
+        const int k = k0 + 4 * (lane & 3) + (lane >> 4), comp = (lane >> 2) & 3;
+        if (k < nc) {
+          const int src = tile[k].meta.x;
           if constexpr (kFixed) {
             unsigned long long *dst = src >= 0 ? gsrc_fx + 8 * (int64_t)src
                                                : gnode_fx + 8 * (int64_t)(-src - 1);
-            fx_add(dst + 2 * comp, tot, scale);
+            fx_add(dst + 2 * comp, G * tot, scale);
           } else {
             float *dst = src >= 0 ? (float *)&gsrc[src] : (float *)&gnode[-src - 1];
-            atomicAdd(dst + comp, tot);
+            atomicAdd(dst + comp, G * tot);
           }
         }
       }
@@ -563,11 +566,9 @@ __global__ __launch_bounds__(kBlock) void k_gravity_bwd(
     };
     // the walk of the forward kernel: the same items, decisions and masks
     const int root_exp = ilogbf((float)gs.sbox[grp.snap].w);
-    int first = __builtin_amdgcn_readfirstlane(grp.snap), count = 1, sp = 0;
-    uint64_t mask = grp.count < kWave ? (1ull << grp.count) - 1ull : ~0ull;
-    for (;;) {
-      int nf = 0, nc = 0;  // the next item (nc = 0: none yet)
-      uint64_t nm = 0ull;
+    const int root = __builtin_amdgcn_readfirstlane(grp.snap);
+    const uint64_t all = grp.count < kWave ? (1ull << grp.count) - 1ull : ~0ull;
+    team_items(S, root, all, w, lane, [&](int first, int count, uint64_t mask, const auto &opened) {
       const bool act = __builtin_amdgcn_inverse_ballot_w64(mask);
       if (count > 0) {
         auto visit = [&](const CNode &nd, uint64_t nk) {
@@ -592,6 +593,7 @@ __global__ __launch_bounds__(kBlock) void k_gravity_bwd(
           }
           const uint64_t amask = __ballot(accept), om = __ballot(open);
           if (amask) {
+            tc = __builtin_amdgcn_readfirstlane(tc);
             if (tc == kTile) {
               flush(kTile);
               tc = 0;
@@ -605,22 +607,14 @@ __global__ __launch_bounds__(kBlock) void k_gravity_bwd(
             }
             ++tc;
           }
-          if (om) {
-            if (nc) {
-              if (lane == 0)
-                stack[sp] = make_int4(nf, nc, (int)(uint32_t)nm, (int)(uint32_t)(nm >> 32));
-              ++sp;
-            }
-            nf = nd.meta.x;
-            nc = nd.meta.y;
-            nm = om;
-          }
+          if (om) opened(nd.meta.x, nd.meta.y, om);
         };
         for (int c = 0; c < count; ++c)
           visit(cnodes[first + c], kInside ? ckeys[first + c] : 0ull);
       } else {
         int st = first, c = -count;
         while (c > 0) {
+          tc = __builtin_amdgcn_readfirstlane(tc);
           if (tc == kTile) {
             flush(kTile);
             tc = 0;
@@ -645,33 +639,17 @@ __global__ __launch_bounds__(kBlock) void k_gravity_bwd(
           c -= take;
         }
       }
-      if (nc) {
-        first = nf;
-        count = nc;
-        mask = nm;
-      } else if (sp > 0) {
-        --sp;
-        wave_sync();
-        const int4 e = stack[sp];
-        first = __builtin_amdgcn_readfirstlane(e.x);
-        count = __builtin_amdgcn_readfirstlane(e.y);
-        mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.w) << 32) |
-               (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.z);
-        wave_sync();
-      } else {
-        break;
-      }
-    }
+    });
     if (tc > 0) flush(tc);
     if (valid) {
       if constexpr (kFixed) {
-        fx_add(gsrc_fx + 8 * (int64_t)s, ox + cox, scale);
-        fx_add(gsrc_fx + 8 * (int64_t)s + 2, oy + coy, scale);
-        fx_add(gsrc_fx + 8 * (int64_t)s + 4, oz + coz, scale);
+        fx_add(gsrc_fx + 8 * (int64_t)s, G * (ox + cox), scale);
+        fx_add(gsrc_fx + 8 * (int64_t)s + 2, G * (oy + coy), scale);
+        fx_add(gsrc_fx + 8 * (int64_t)s + 4, G * (oz + coz), scale);
       } else {
-        atomicAdd(&gsrc[s].x, ox + cox);
-        atomicAdd(&gsrc[s].y, oy + coy);
-        atomicAdd(&gsrc[s].z, oz + coz);
+        atomicAdd(&gsrc[s].x, G * (ox + cox));
+        atomicAdd(&gsrc[s].y, G * (oy + coy));
+        atomicAdd(&gsrc[s].z, G * (oz + coz));
       }
     }
   }
@@ -1043,6 +1021,12 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
   if (m == 0 || nn == 0) return hipSuccess;
   if (!all.cnodes) return hipErrorInvalidValue;
   const int64_t na = active ? n_act : m;
+  auto pick = [&](auto fixed_c) {
+    constexpr bool f = decltype(fixed_c)::value;
+    if (gp.team == 16) return gp.inside_test ? k_gravity_bwd<f, true, 16> : k_gravity_bwd<f, false, 16>;
+    return gp.inside_test ? k_gravity_bwd<f, true, 4> : k_gravity_bwd<f, false, 4>;
+  };
+  const int block = gp.team * kWave;
   if (gp.eps2 > 0.0f) {
     // fixed-point counters (two words per component, four components)
     k_zero_f4<<<nblk(4 * m), kBlock, 0, s>>>((float4 *)gsrc_fx, 4 * m);
@@ -1052,8 +1036,8 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
     const unsigned gb = nblk(nb) < (unsigned)kFxBoundBlocks ? nblk(nb) : (unsigned)kFxBoundBlocks;
     k_fx_bound<<<gb, kBlock, 0, s>>>(active, na, g_acc, g_pot, all.xm, m, mx);
     if (max_groups > 0) {
-      auto kern = gp.inside_test ? k_gravity_bwd<true, true> : k_gravity_bwd<true, false>;
-      kern<<<persistent_grid((const void *)kern, kBlock, max_groups), kBlock, 0, s>>>(
+      auto kern = pick(std::true_type{});
+      kern<<<persistent_grid((const void *)kern, block, max_groups, gp.team), block, 0, s>>>(
           all.cnodes, all.ckeys, all.xm, all.keys, all.perm, gs, gp.theta2, gp.eps2, gp.G, g_acc, g_pot,
           gsrc, gnode, gsrc_fx, gnode_fx, mx, m, na);
     }
@@ -1063,8 +1047,8 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
     k_zero_f4<<<nblk(m), kBlock, 0, s>>>(gsrc, m);
     k_zero_f4<<<nblk(nn), kBlock, 0, s>>>(gnode, nn);
     if (max_groups > 0) {
-      auto kern = gp.inside_test ? k_gravity_bwd<false, true> : k_gravity_bwd<false, false>;
-      kern<<<persistent_grid((const void *)kern, kBlock, max_groups), kBlock, 0, s>>>(
+      auto kern = pick(std::false_type{});
+      kern<<<persistent_grid((const void *)kern, block, max_groups, gp.team), block, 0, s>>>(
           all.cnodes, all.ckeys, all.xm, all.keys, all.perm, gs, gp.theta2, gp.eps2, gp.G, g_acc, g_pot,
           gsrc, gnode, nullptr, nullptr, nullptr, m, na);
     }

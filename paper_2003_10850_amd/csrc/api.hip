@@ -463,6 +463,11 @@ int hydro_team(int64_t max_targets) {
 int gravity_team(int64_t max_targets) {
   return (max_targets + kWave - 1) / kWave <= 2560 ? 16 : 4;
 }
+// Its adjoint (us with the forward pass, teams of 4/16): 586/358 of 256 groups,
+// 942/983 of 1024, 1551/1774 of 2048, 4709/6357 of 7812.
+int gravity_bwd_team(int64_t max_targets) {
+  return (max_targets + kWave - 1) / kWave <= 768 ? 16 : 4;
+}
 // The SPH adjoints, conduction and velocity gradients, as the density: us of
 // one density solve and hydro force with their gradients, and of one pass of
 // the modules (viscosity, conduction, gradients), teams of 4/16:
@@ -1894,7 +1899,9 @@ int g3_gravity_backward(g3_ctx *c, const g3_tree *t, int64_t n_act, const int32_
   Work wk;
   st = prepare_work(c, t, o, t->iperm_all, n_act, active, &wk, s);
   if (st) return st;
-  hipError_t e = launch_gravity_bwd(o, wk.gs, wk.max_groups, grav_params(p, t), n_act, active,
+  GravParams gp = grav_params(p, t);
+  gp.team = gravity_bwd_team(wk.max_targets);
+  hipError_t e = launch_gravity_bwd(o, wk.gs, wk.max_groups, gp, n_act, active,
                                     g_acc, g_pot, gsrc, gnode, gsrc_fx, gnode_fx,
                                     fixed ? (unsigned *)(gsrc_fx + 8 * o.n) : nullptr, pq, rr,
                                     g_pos, g_mass, s);

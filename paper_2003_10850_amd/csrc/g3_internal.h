@@ -289,6 +289,7 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
 int density_team(int64_t max_targets, int f64);
 int hydro_team(int64_t max_targets);
 int gravity_team(int64_t max_targets);
+int gravity_bwd_team(int64_t max_targets);
 int adjoint_team(int64_t members);  // SPH adjoints: every gas member is a target
 int conduction_team(int64_t max_targets);
 int velgrad_team(int64_t max_targets);

@@ -20,26 +20,12 @@
 
 #include "g3_device.h"
 #include "g3_internal.h"
+#include "g3_items.h"
 
 namespace g3 {
 
 namespace {
 
-// Items that wait in a depth-first walk: at most 7 siblings on each of the 22
-// levels.
-constexpr int kDepth = 7 * (kMaxLevel + 1) + 1;
-// A team of kT waves takes up to kItems items a round from the end of the
-// list; while more than one is taken the list stays below kStack - kDepth, so
-// a depth-first descent always fits.
-template <int kT>
-struct Team {
-  static constexpr int kItems = 4 * kT;
-  static constexpr int kStack = kDepth + 16 * kItems;
-  int4 stack[kStack];
-  int4 out[8 * kItems];  // the items that an item opens
-  int32_t nout[kItems];
-  int32_t group;
-};
 // Terms of plain FP32 partial sums between two compensated additions.
 constexpr int kFlush = 64;
 
@@ -78,16 +64,7 @@ __global__ __launch_bounds__(kT * kWave, kT > 4 ? 4 : 8) void k_gravity(
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
   float4 *tot = tots[w], *comp = comps[w];
   int range = 0;
-  auto take_group = [&]() {
-    __syncthreads();  // the previous group's LDS use is over
-    if (w == 0) {
-      const int g = next_group(gs, range);
-      if (lane == 0) S.group = g;
-    }
-    __syncthreads();
-    return __builtin_amdgcn_readfirstlane(S.group);
-  };
-  for (int g; (g = take_group()) >= 0;) {
+  for (int g; (g = team_take_group(gs, range, S)) >= 0;) {
   const Group grp = group_at(gs, g);
   const int64_t t = grp.t0 + lane;
   const bool valid = lane < grp.count;
@@ -225,55 +202,7 @@ __global__ __launch_bounds__(kT * kWave, kT > 4 ? 4 : 8) void k_gravity(
 
   const int root = __builtin_amdgcn_readfirstlane(grp.snap);
   const uint64_t all = grp.count < kWave ? (1ull << grp.count) - 1ull : ~0ull;
-  auto pack = [](int first, int count, uint64_t m) {
-    return make_int4(first, count, (int)(uint32_t)m, (int)(uint32_t)(m >> 32));
-  };
-  auto unpack = [&](const int4 &e, int &first, int &count, uint64_t &m) {
-    first = __builtin_amdgcn_readfirstlane(e.x);
-    count = __builtin_amdgcn_readfirstlane(e.y);
-    m = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.w) << 32) |
-        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(e.z);
-  };
-  {
-    constexpr int kItems = Team<kT>::kItems;
-    if (threadIdx.x == 0) S.stack[0] = pack(root, 1, all);
-    int sp = 1;
-    while (sp > 0) {
-      __syncthreads();
-      // (7 more entries an item at most)
-      const int room = (Team<kT>::kStack - kDepth - sp) / 7;
-      const int n = min(min(kItems, sp), max(room, 1));
-      for (int j = w; j < n; j += kT) {
-        int first, count, r = 0;
-        uint64_t mask;
-        unpack(S.stack[sp - n + j], first, count, mask);
-        item(first, count, mask, [&](int f, int c, uint64_t m) {
-          if (lane == 0) S.out[8 * j + r] = pack(f, c, m);
-          ++r;
-        });
-        if (lane == 0) S.nout[j] = r;
-      }
-      __syncthreads();
-      sp -= n;
-      int tot_new = 0;
-      for (int j0 = 0; j0 < n; j0 += kWave) {  // every wave counts, all copy
-        const int mine = j0 + lane < n ? S.nout[j0 + lane] : 0;
-        int inc = mine;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-          const int o = __shfl_up(inc, (unsigned)d, kWave);
-          if (lane >= d) inc += o;
-        }
-        for (int q = w; q * 8 < min(n - j0, kWave); q += kT) {
-          const int j = q * 8 + (lane >> 3), r = lane & 7;  // 8 items' slots
-          const int cnt = __shfl(mine, j, kWave), at = __shfl(inc, j, kWave) - cnt;
-          if (r < cnt) S.stack[sp + tot_new + at + r] = S.out[8 * (j0 + j) + r];
-        }
-        tot_new += __shfl(inc, kWave - 1, kWave);
-      }
-      sp += __builtin_amdgcn_readfirstlane(tot_new);
-    }
-  }
+  team_items(S, root, all, w, lane, item);
   flush();
   float4 tt = tot[lane], tc4 = comp[lane];
   nts[w][lane] = pn;

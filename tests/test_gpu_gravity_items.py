@@ -80,3 +80,34 @@ def test_active_sets_on_both_sides_of_the_team_rule(ctx, n_act):
                     type=np.zeros(n, np.uint8))
     rows = act if n_act <= 300 else np.sort(rng.choice(act, 300, replace=False))
     check(tree, t, p, dev_t(act), rows)
+
+
+@pytest.mark.parametrize("theta,eps", [(0.5, 1e-2), (0.7, 1e-2), (0.5, 0.0)])
+def test_adjoint_of_all_is_the_sum_of_the_halves(theta, eps):
+    # linear in the upstream gradients; 6e4 targets take teams of 4, the halves
+    # (as the small sets that other tests hold against the oracle) teams of 16.
+    # Per source the FP32 sums over 64 targets are the same or regrouped: one
+    # rounding of 64 terms' sum each, 6e-8 x 64 of the largest at the worst
+    from paper_2003_10850_amd import ops
+    n = 60000
+    w = inputs.uniform(n=n, seed=4)
+    p = inputs.Params(theta=theta, eps=eps)
+    c = ops.Context(torch.device("cuda", 0))
+    D = lambda a: torch.from_numpy(np.ascontiguousarray(a.astype(np.float32))).to("cuda:0")
+    pos, mass = D(w.pos).requires_grad_(True), D(w.mass).requires_grad_(True)
+    tree = ops.Tree(c, pos.detach(), mass.detach(), None, tuple(w.box), p)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    ga = torch.randn(n, 3, generator=g, device="cuda")
+    gp = torch.randn(n, generator=g, device="cuda")
+
+    def grads(act):
+        acc, pot = ops.gravity_ad(tree, pos, mass, active=act)
+        z = [torch.zeros_like(ga), torch.zeros_like(gp)]
+        rows = slice(None) if act is None else act.long()
+        z[0][rows], z[1][rows] = ga[rows], gp[rows]
+        return torch.autograd.grad([acc, pot], [pos, mass], z)
+
+    ids = torch.arange(n, dtype=torch.int32, device="cuda")
+    for a, b, d in zip(grads(None), grads(ids[: n // 2]), grads(ids[n // 2:])):
+        b = b.double() + d.double()
+        assert float((a.double() - b).abs().max()) <= 4e-6 * float(b.abs().max())
