@@ -442,21 +442,26 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
 }
 
 // Waves of a team from the host's bound on the targets. Measured (us, cold
-// density solve and hydro force of clustered sets of 2^10..2^14 groups):
-//   groups          1024        2048        4096        8192       16384
-//   density 4/16    2421/1913   2836/2750   3659/5076   4345/8718  6040/13969
-//   FP64    4/16    4185/2477   4686/3564   6685/6383   8297/10882
-//   hydro 1/4/16    4203/1408/1126  2675/1261/1419  2294/1601/2283
-//                   2538/2413/4142 (8192)  3883/4145/7676 (16384)
-// Below 2^10 groups the widest team is up to 2 times faster than the next
-// one: with fewer groups than CUs the time is that of the slowest group.
+// density solve and hydro force of clustered sets; one column a team of
+// 4, 8 or 16 waves, for the hydro force first none):
+//   groups           512         1024        2048        4096        8192
+//   density      2474 1748 1659  2474 1829 1916  2958 2231 2746  3629 3393 5057
+//                4499 4848 8701 (8192)
+//   FP64         4110 2701 2089  4153 3225 2500  4716 4609 3555  6704 8037 6382
+//                8321 13116 10905 (8192)
+//   hydro        4203 921 654 553 (512)  1414 1078 1144 (1024)
+//                2675 1306 1222 1439 (2048)  2294 1619 1716 2288 (4096)
+//                2538 2452 2850 4125 (8192)  3883 4187 5118 7673 (16384)
+// With fewer groups than CUs the time is that of the slowest group, and the
+// widest team is up to 2 times faster than the next one.
 int density_team(int64_t max_targets, int f64) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
-  return groups <= (f64 ? 4096 : 1536) ? 16 : 4;
+  if (f64) return groups <= 4096 ? 16 : 4;
+  return groups <= 768 ? 16 : (groups <= 6144 ? 8 : 4);
 }
 int hydro_team(int64_t max_targets) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
-  return groups <= 1536 ? 16 : (groups <= 12288 ? 4 : 1);
+  return groups <= 768 ? 16 : (groups <= 2560 ? 8 : (groups <= 12288 ? 4 : 1));
 }
 // Gravity (us, clustered sets of 2^11, 2^12 and 2^13 groups, teams of 4/16):
 // FP32 553/437, 817/902, 1321/1811; FP64 664/637, 1046/1315, 1843/2666.

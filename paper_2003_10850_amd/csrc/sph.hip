@@ -104,9 +104,10 @@ constexpr float kFineExt = 1.0f;
 // 2^20 gas particles of a clustered 2^21 box: 8.0 ms with a wave a group, 6.0
 // with teams of 4 (the solve's uneven passes and the uneven groups spread over
 // four waves; held to 6 waves a SIMD: 6.9 ms at the 4 that 120 registers
-// allow); 14 with teams of 16. 2^15 gas particles: 7.0, 2.4 and 1.6 ms.
+// allow); 7.1 and 14 with teams of 8 and 16. 2^17: 2.9, 2.2 and 2.7 ms with
+// teams; 2^15 gas particles: 7.0, 2.5, 1.7 and 1.7 ms.
 template <bool kF64, int kT>
-__global__ __launch_bounds__(kBlockOf<kT>, kT == 4 && !kF64 ? 6 : 1) void k_density(
+__global__ __launch_bounds__(kBlockOf<kT>, kT < 16 && !kF64 ? 6 : 1) void k_density(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const int32_t *__restrict__ perm, const Groups gs,
     const Terms tm, float n_ngb, float tol, int solve, int max_iter, int walk_leaf,
@@ -552,7 +553,7 @@ struct ExtTile {
 // kT > 1: a team serves a group, as in the density; else a wave walks the
 // octree itself. 2^20 gas particles of the clustered 2^21 box: 3.8 ms with a
 // wave a group, 4.1 with teams of 4 (their LDS holds 4 waves a SIMD, not 6),
-// 7.7 with 16; 2^15 gas particles: 2.9, 0.90 and 0.53 ms. Bound by vector
+// 5.1 and 7.7 with 8 and 16; 2^15 gas particles: 2.9, 0.92, 0.65 and 0.55 ms. Bound by vector
 // issue on a full chip, by the slowest groups otherwise.
 template <bool kF64, bool kExt, int kT>
 __global__ __launch_bounds__(kBlockOf<kT>) void k_hydro(
@@ -899,9 +900,10 @@ hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_group
                           float *drho_dh, float *omega, int32_t *nngb,
                           unsigned long long *counters, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  const bool wide = sp.team == 16;
-  auto kern = sp.f64 ? (wide ? k_density<true, 16> : k_density<true, 4>)
-                     : (wide ? k_density<false, 16> : k_density<false, 4>);
+  auto kern = sp.f64 ? (sp.team == 16 ? k_density<true, 16> : k_density<true, 4>)
+                     : (sp.team == 16  ? k_density<false, 16>
+                        : sp.team == 8 ? k_density<false, 8>
+                                       : k_density<false, 4>);
   const int block = sp.team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(
       gas.nodes, gas.xm, gas.x64, gas.perm, gs, tm, sp.n_ngb, sp.h_tol, solve_h, sp.max_iter,
@@ -934,7 +936,10 @@ hipError_t launch_hydro(const Octree &gas, const Groups &gs, int64_t max_groups,
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
   auto pick = [&](auto f64_c, auto ext_c) {
     constexpr bool f = decltype(f64_c)::value, e = decltype(ext_c)::value;
-    return sp.team == 16 ? k_hydro<f, e, 16> : (sp.team == 4 ? k_hydro<f, e, 4> : k_hydro<f, e, 1>);
+    return sp.team == 16  ? k_hydro<f, e, 16>
+           : sp.team == 8 ? k_hydro<f, e, 8>
+           : sp.team == 4 ? k_hydro<f, e, 4>
+                          : k_hydro<f, e, 1>;
   };
   const std::true_type yes;
   const std::false_type no;

@@ -126,6 +126,33 @@ def test_every_team_size_gives_the_same_bits(ctx, fp64):
             assert torch.equal(a[k][at], b[k][at]), k
 
 
+
+@pytest.mark.parametrize("log_few", [16, 17, 18])
+def test_middle_team_sizes_give_the_same_bits(ctx, log_few):
+    # 2^20 targets: density in teams of 4, hydro force without; the first 2^16
+    # and 2^17 in tree order take teams of 8 for both, 2^18 for the density
+    from paper_2003_10850_amd import g3, ops
+    n = 1 << 20
+    w = inputs.uniform(n=n, seed=22)
+    p = inputs.Params(n_ngb=48.0)
+    c = ops.Context(torch.device("cuda", 0))
+    for kind in (g3.G3_TUNE_DENSITY, g3.G3_TUNE_HYDRO):
+        c.set_tuning(kind, 128, -1)
+    tree = ops.Tree(c, dev_t(w.pos.astype(np.float32)), dev_t(w.mass.astype(np.float32)), None,
+                    tuple(w.box), p)
+    few = torch.sort(tree.export(1)["order"][: 1 << log_few]).values
+    g = torch.Generator(device="cuda").manual_seed(2)
+    R = lambda *s: torch.rand(*s, generator=g, device="cuda")
+    h = 2.25 * n ** (-1.0 / 3.0) * (0.8 + 0.4 * R(n))
+    vel, u, rho, om = R(n, 3) - 0.5, 0.5 + R(n), 0.5 + R(n), 0.5 + R(n)
+    at = few.long()
+    for a, b in ((ops.density(tree, h=h), ops.density(tree, h=h, active=few)),
+                 (ops.hydro_force(tree, vel, u, h, rho, om),
+                  ops.hydro_force(tree, vel, u, h, rho, om, active=few))):
+        for k in a:
+            assert torch.equal(a[k][at], b[k][at]), k
+
+
 def close(a, b, what):
     # the same 64-candidate partial sums, compensated over the tiles in another
     # order: a last rounding of the total and one or two of each factor on it
