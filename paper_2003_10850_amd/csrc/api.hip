@@ -142,27 +142,6 @@ __global__ void k_mark(const int32_t *__restrict__ active, int64_t n_act,
   rowp1[s] = (int32_t)(a + 1);
 }
 
-// Targets by the time-bin rule: member s is a target iff the bin of its
-// particle is at least kmin (rows are then caller ids).
-__global__ void k_mark_bins(const int32_t *__restrict__ perm, int64_t m,
-                            const int32_t *__restrict__ bins, int32_t kmin,
-                            uint32_t *__restrict__ mark, int32_t *__restrict__ rowp1) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= m) return;
-  const int32_t cid = perm[s];
-  mark[s] = bins[cid] >= kmin ? 1u : 0u;
-  rowp1[s] = cid + 1;
-}
-
-__global__ void k_compact(const uint32_t *__restrict__ mark, const uint32_t *__restrict__ slot,
-                          const int32_t *__restrict__ rowp1, int64_t m,
-                          int32_t *__restrict__ targets, int32_t *__restrict__ rows) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= m || !mark[s]) return;
-  targets[slot[s]] = (int32_t)s;
-  rows[slot[s]] = rowp1[s] - 1;
-}
-
 __global__ void k_zero_u32(uint32_t *p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -393,16 +372,14 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
   int32_t *rowp1 = b.rowp1, *tg = b.tg, *rw = b.rw, *tab = b.tab;
   uint32_t *flags = b.flags, *segid = b.segid, *gcnt = b.gcnt;
   if (listed) {
-    if (bins) {
-      k_mark_bins<<<nblk(m), 256, 0, s>>>(o.perm, m, bins, kmin, mark, rowp1);
-    } else {
+    if (!bins) {
       k_zero_u32<<<nblk(m), 256, 0, s>>>(mark, m);
       if (n_act > 0)
         k_mark<<<nblk(n_act), 256, 0, s>>>(active, n_act, iperm, t->n, mark, rowp1);
     }
-    hipError_t e = scan_u32(mark, slot, m, stmp, s);
-    if (e != hipSuccess) return hip_fail(c, e, "active-set scan");
-    k_compact<<<nblk(m), 256, 0, s>>>(mark, slot, rowp1, m, tg, rw);
+    const hipError_t e =
+        list_targets(o.perm, m, bins, kmin, mark, rowp1, slot, tg, rw, stmp, s);
+    if (e != hipSuccess) return hip_fail(c, e, "active-set list");
   }
   const uint32_t *ntarg = listed ? slot + m : nullptr;
   int32_t *tstart = tab, *gstart = tab + max_seg + 2, *seg_snap = gstart + max_seg + 2;

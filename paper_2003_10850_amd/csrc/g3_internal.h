@@ -50,6 +50,11 @@ constexpr int kChildPad = 8;
 constexpr int kSubtree = 1024;
 inline int64_t max_tops(int64_t n) { return kMaxLevel * (n / kSubtree + 1); }
 
+// A node above the subtrees and its children in order (-1: no more).
+struct TopNode {
+  int32_t node, level, child[8];
+};
+
 // One octree over a subset of the particles (all of them, or the gas ones),
 // with the members in Morton order.
 struct Octree {
@@ -71,7 +76,7 @@ struct Octree {
   double4 *mom = nullptr;    // [nnodes] FP64 (M, M x, M y, M z)
   // the moments' order: roots of small subtrees, and the nodes above them
   int32_t *subs = nullptr;    // [nnodes]
-  int2 *tops = nullptr;       // [cap_tops] (node, level)
+  TopNode *tops = nullptr;    // [cap_tops]
   int32_t *nsplit = nullptr;  // their counts
   int64_t cap_tops = 0;
   // SPH member data in sorted order (gas octree only, filled by the calls)
@@ -207,6 +212,12 @@ hipError_t scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp,
                     hipStream_t s);
 hipError_t scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, int64_t *tmp,
                            hipStream_t s);
+// The targets among m members in their order, by marks or (bins) by time bin:
+// targets[k] and rows[k] of target k, and slot[0..m], the targets before each
+// member. tmp must hold scan_tmp_elems(m + 1) elements.
+hipError_t list_targets(const int32_t *perm, int64_t m, const int32_t *bins, int32_t kmin,
+                        const uint32_t *mark, const int32_t *rowp1, uint32_t *slot,
+                        int32_t *targets, int32_t *rows, uint32_t *tmp, hipStream_t s);
 
 // Stable LSD radix sort of (key, value) pairs by key bits [0, bits), bits a
 // multiple of 8. tmp must hold radix_tmp_bytes(n) bytes. Result ends in

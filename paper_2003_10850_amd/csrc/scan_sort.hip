@@ -23,10 +23,10 @@ __device__ T wave_incl_scan(T v) {
 }
 
 // Exclusive block scan of one value per thread; *total receives the sum.
-template <typename T>
-__device__ T block_excl_scan(T v, T *total, T *lds /* [kScanBlock/64 + 1] */) {
+template <typename T, int kBlock = kScanBlock>
+__device__ T block_excl_scan(T v, T *total, T *lds /* [kBlock/64 + 1] */) {
   const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
-  constexpr int kW = kScanBlock / kWave;
+  constexpr int kW = kBlock / kWave;
   T inc = wave_incl_scan(v);
   if (lane == kWave - 1) lds[w] = inc;
   __syncthreads();
@@ -57,12 +57,47 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_reduce(const TI *__restrict
   if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
+// The exclusive scan of one value per thread over all blocks. part: the blocks'
+// sums (null for a single block), scanned already or (raw) added up here by
+// every block for itself, in the barriers of its own scan. That takes a launch
+// off a scan (4 us in a chain of small kernels); up to kRawParts blocks, 8e6
+// items, it reads at most 16 values a thread.
+constexpr int64_t kRawParts = 4096;
+template <typename T>
+__device__ T grid_excl_scan(T v, const T *__restrict__ part, int raw,
+                            T *lds /* [2 kScanBlock/64 + 1] */) {
+  const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
+  constexpr int kW = kScanBlock / kWave;
+  T before = 0;
+  if (part) {
+    if (raw)
+      for (unsigned k = threadIdx.x; k < blockIdx.x; k += kScanBlock) before += part[k];
+    else if (threadIdx.x == 0)
+      before = part[blockIdx.x];
+  }
+  const T inc = wave_incl_scan(v), binc = wave_incl_scan(before);
+  if (lane == kWave - 1) {
+    lds[w] = inc;
+    lds[kW + w] = binc;
+  }
+  __syncthreads();
+  if (w == 0) {
+    const T t = lane < 2 * kW ? lds[lane] : T(0);
+    const T ti = wave_incl_scan(t);
+    // all of the earlier blocks, the earlier waves of this one
+    const T all = __shfl(ti, 2 * kW - 1, kWave) - __shfl(ti, kW - 1, kWave);
+    if (lane < kW) lds[lane] = all + ti - t;
+  }
+  __syncthreads();
+  return lds[w] + inc - v;
+}
+
 // Scans in[0..n) into out[0..n]; out may alias in (each thread reads its
-// items before writing them). part: exclusive per-block offsets or null.
+// items before writing them). part: the blocks' sums (raw or scanned) or null.
 template <typename TI, typename TO>
 __global__ __launch_bounds__(kScanBlock) void k_scan_down(const TI *in, int64_t n, TO *out,
-                                                          const TO *__restrict__ part) {
-  __shared__ TO lds[kScanBlock / kWave + 1];
+                                                          const TO *__restrict__ part, int raw) {
+  __shared__ TO lds[2 * kScanBlock / kWave];
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanIpt;
   TO v[kScanIpt];
   TO s = 0;
@@ -71,9 +106,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_down(const TI *in, int64_t 
     v[k] = (base + k < n) ? (TO)in[base + k] : TO(0);
     s += v[k];
   }
-  TO tot;
-  TO run = block_excl_scan<TO>(s, &tot, lds);
-  if (part) run += part[blockIdx.x];
+  TO run = grid_excl_scan<TO>(s, part, raw, lds);
 #pragma unroll
   for (int k = 0; k < kScanIpt; ++k) {
     if (base + k <= n) out[base + k] = run;
@@ -81,23 +114,123 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_down(const TI *in, int64_t 
   }
 }
 
+// The whole scan by one workgroup of 1024, tile after tile: one launch.
+constexpr int kOneBlock = 1024;
+constexpr int64_t kOneItems = 2 * kOneBlock * kScanIpt;
+template <typename TI, typename TO>
+__global__ __launch_bounds__(kOneBlock) void k_scan_one(const TI *in, int n, TO *out) {
+  __shared__ TO lds[kOneBlock / kWave + 1];
+  TO carry = 0;
+  for (int k0 = 0; k0 <= n; k0 += kOneBlock * kScanIpt) {
+    const int base = k0 + (int)threadIdx.x * kScanIpt;
+    TO v[kScanIpt];
+    TO s = 0;
+#pragma unroll
+    for (int k = 0; k < kScanIpt; ++k) {
+      v[k] = (base + k < n) ? (TO)in[base + k] : TO(0);
+      s += v[k];
+    }
+    TO tot;
+    TO run = carry + block_excl_scan<TO, kOneBlock>(s, &tot, lds);
+#pragma unroll
+    for (int k = 0; k < kScanIpt; ++k) {
+      if (base + k <= n) out[base + k] = run;
+      run += v[k];
+    }
+    carry += tot;
+  }
+}
+
+// One launch up to 2^14 items (two tiles of one workgroup: 5 us, as two
+// launches of many cost 2 x 4), two up to kRawParts blocks.
 template <typename TI, typename TO>
 hipError_t scan_impl(const TI *in, TO *out, int64_t n, TO *tmp, hipStream_t s) {
   const int64_t nb = (n + 1 + kScanTile - 1) / kScanTile;
   if (nb == 1) {
-    k_scan_down<TI, TO><<<1, kScanBlock, 0, s>>>(in, n, out, nullptr);
+    k_scan_down<TI, TO><<<1, kScanBlock, 0, s>>>(in, n, out, nullptr, 0);
     return hipGetLastError();
   }
+  if (n < kOneItems) {
+    k_scan_one<TI, TO><<<1, kOneBlock, 0, s>>>(in, (int)n, out);
+    return hipGetLastError();
+  }
+  const int raw = nb <= kRawParts ? 1 : 0;
   k_scan_reduce<TI, TO><<<(unsigned)nb, kScanBlock, 0, s>>>(in, n, tmp);
-  hipError_t e = scan_impl<TO, TO>(tmp, tmp, nb, tmp + nb + 1, s);
-  if (e != hipSuccess) return e;
-  k_scan_down<TI, TO><<<(unsigned)nb, kScanBlock, 0, s>>>(in, n, out, tmp);
+  if (!raw) {
+    hipError_t e = scan_impl<TO, TO>(tmp, tmp, nb, tmp + nb + 1, s);
+    if (e != hipSuccess) return e;
+  }
+  k_scan_down<TI, TO><<<(unsigned)nb, kScanBlock, 0, s>>>(in, n, out, tmp, raw);
   return hipGetLastError();
+}
+
+// ------------------------------------------------------------ target lists
+
+// Member s of an octree is a target when it is marked (mark[s], its row
+// rowp1[s] - 1) or, with a time-bin rule, when the bin of its particle is at
+// least kmin (its row is the caller id).
+struct MarkRule {
+  const int32_t *perm, *bins;
+  int32_t kmin;
+  const uint32_t *mark;
+  const int32_t *rowp1;
+  __device__ bool on(int64_t s) const { return bins ? bins[perm[s]] >= kmin : mark[s] != 0u; }
+  __device__ int32_t row(int64_t s) const { return bins ? perm[s] : rowp1[s] - 1; }
+};
+
+// A wave takes kScanIpt runs of 64 members (coalesced), ranked by ballots.
+// Counting and placing instead of marking, scanning and compacting: two
+// launches for five (one below a tile).
+__global__ __launch_bounds__(kScanBlock) void k_mark_count(const MarkRule r, int64_t m,
+                                                           uint32_t *__restrict__ part) {
+  __shared__ uint32_t lds[kScanBlock / kWave + 1];
+  const int w = (int)(threadIdx.x >> 6), lane = lane_id();
+  const int64_t t0 = (int64_t)blockIdx.x * kScanTile + (int64_t)w * (kWave * kScanIpt) + lane;
+  uint32_t cnt = 0;
+#pragma unroll
+  for (int c = 0; c < kScanIpt; ++c) {
+    const int64_t s = t0 + (int64_t)c * kWave;
+    cnt += s < m && r.on(s) ? 1u : 0u;
+  }
+  uint32_t tot;
+  (void)block_excl_scan<uint32_t>(cnt, &tot, lds);
+  if (threadIdx.x == 0) part[blockIdx.x] = tot;
+}
+
+__global__ __launch_bounds__(kScanBlock) void k_mark_place(
+    const MarkRule r, int64_t m, const uint32_t *__restrict__ part, int raw,
+    uint32_t *__restrict__ slot, int32_t *__restrict__ targets, int32_t *__restrict__ rows) {
+  __shared__ uint32_t lds[2 * kScanBlock / kWave];
+  const int w = (int)(threadIdx.x >> 6), lane = lane_id();
+  const int64_t t0 = (int64_t)blockIdx.x * kScanTile + (int64_t)w * (kWave * kScanIpt) + lane;
+  uint64_t on[kScanIpt];
+  uint32_t cnt = 0;  // the wave's
+#pragma unroll
+  for (int c = 0; c < kScanIpt; ++c) {
+    const int64_t s = t0 + (int64_t)c * kWave;
+    on[c] = __ballot(s < m && r.on(s));
+    cnt += (uint32_t)__popcll(on[c]);
+  }
+  // (a wave's count once, by its first lane: the other lanes' prefix includes it)
+  uint32_t at = __shfl(grid_excl_scan<uint32_t>(lane == 0 ? cnt : 0u, part, raw, lds), 0, kWave);
+#pragma unroll
+  for (int c = 0; c < kScanIpt; ++c) {
+    const int64_t s = t0 + (int64_t)c * kWave;
+    const uint32_t mine =
+        at + __builtin_amdgcn_mbcnt_hi((uint32_t)(on[c] >> 32),
+                                       __builtin_amdgcn_mbcnt_lo((uint32_t)on[c], 0u));
+    if (s <= m) slot[s] = mine;
+    if ((on[c] >> lane) & 1ull) {
+      targets[mine] = (int32_t)s;
+      rows[mine] = r.row(s);
+    }
+    at += (uint32_t)__popcll(on[c]);
+  }
 }
 
 // ------------------------------------------------------------ radix sort
 
-constexpr int kRsBlock = 256;
+constexpr int kRsBlock = 512;
 constexpr int kRsWaves = kRsBlock / kWave;
 constexpr int kRsChunks = 8;  // 64-item chunks per wave
 constexpr int kRsTile = kRsBlock * kRsChunks;
@@ -108,7 +241,7 @@ __global__ __launch_bounds__(kRsBlock) void k_rs_hist(const uint64_t *__restrict
                                                       int64_t n, int shift,
                                                       uint32_t *__restrict__ hist, int nb) {
   __shared__ uint32_t cnt[kRsBins];
-  cnt[threadIdx.x] = 0;
+  if (threadIdx.x < kRsBins) cnt[threadIdx.x] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * kRsTile;
   for (int k = threadIdx.x; k < kRsTile; k += kRsBlock) {
@@ -116,7 +249,7 @@ __global__ __launch_bounds__(kRsBlock) void k_rs_hist(const uint64_t *__restrict
     if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (kRsBins - 1)], 1u);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * nb + blockIdx.x] = cnt[threadIdx.x];
+  if (threadIdx.x < kRsBins) hist[(int64_t)threadIdx.x * nb + blockIdx.x] = cnt[threadIdx.x];
 }
 
 // Exclusive scan of each digit's counts over the blocks (a block a digit, in
@@ -149,23 +282,29 @@ __global__ __launch_bounds__(kScanBlock) void k_rs_rows(uint32_t *__restrict__ h
 }
 
 // Stable scatter: wave w ranks its 512 items chunk by chunk (lanes with equal
-// digits found by eight ballots), waves are ordered by a per-digit prefix.
+// digits found by eight ballots), waves are ordered by a per-digit prefix; the
+// tile is put in order in LDS and written out from there, a digit's items side
+// by side (16 on average: 128 bytes of keys). Bound by those writes: straight
+// from the registers, in tiles of 2048, a pass over 2^21 pairs took 29 us
+// (17 now).
 __global__ __launch_bounds__(kRsBlock) void k_rs_scatter(
     const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t n, int shift,
     const uint32_t *__restrict__ offs, const uint32_t *__restrict__ total, int nb) {
+  __shared__ uint64_t sk[kRsTile];
+  __shared__ uint32_t sv[kRsTile];
   __shared__ uint32_t cnt[kRsWaves][kRsBins];
-  __shared__ uint32_t base[kRsBins];
-  __shared__ uint32_t lds[kScanBlock / kWave + 1];
-  static_assert(kRsBlock == kRsBins && kRsBlock == kScanBlock, "a thread a digit");
-  const int w = (int)(threadIdx.x >> 6), lane = lane_id();
-  for (int i = threadIdx.x; i < kRsWaves * kRsBins; i += kRsBlock) (&cnt[0][0])[i] = 0;
+  __shared__ uint32_t base[kRsBins];  // where the tile's place 0 would go, by digit
+  __shared__ uint32_t lds[kRsBlock / kWave + 1];
+  static_assert(kRsBlock >= kRsBins, "a thread a digit");
+  const int w = (int)(threadIdx.x >> 6), lane = lane_id(), tid = (int)threadIdx.x;
+  for (int i = tid; i < kRsWaves * kRsBins; i += kRsBlock) (&cnt[0][0])[i] = 0;
+  uint32_t all, gbase = 0;
   {
-    uint32_t all;
-    const uint32_t smaller = block_excl_scan<uint32_t>(total[threadIdx.x], &all, lds);
-    base[threadIdx.x] = smaller + offs[(int64_t)threadIdx.x * nb + blockIdx.x];
+    const uint32_t smaller = block_excl_scan<uint32_t, kRsBlock>(
+        tid < kRsBins ? total[tid] : 0u, &all, lds);
+    if (tid < kRsBins) gbase = smaller + offs[(int64_t)tid * nb + blockIdx.x];
   }
-  __syncthreads();
   const int64_t t0 = (int64_t)blockIdx.x * kRsTile + (int64_t)w * (kWave * kRsChunks);
   uint64_t key[kRsChunks];
   uint32_t val[kRsChunks], rank[kRsChunks];
@@ -176,6 +315,10 @@ __global__ __launch_bounds__(kRsBlock) void k_rs_scatter(
     const bool valid = i < n;
     key[c] = valid ? kin[i] : 0ull;
     val[c] = valid ? vin[i] : 0u;
+  }
+#pragma unroll
+  for (int c = 0; c < kRsChunks; ++c) {
+    const bool valid = t0 + (int64_t)c * kWave + lane < n;
     const uint32_t d = (uint32_t)(key[c] >> shift) & (kRsBins - 1);
     uint64_t peers = __ballot(valid);
 #pragma unroll
@@ -192,26 +335,37 @@ __global__ __launch_bounds__(kRsBlock) void k_rs_scatter(
     wave_sync();
   }
   __syncthreads();
-  {
-    const int d = threadIdx.x;
-    uint32_t run = 0;
+  uint32_t run = 0;
+  if (tid < kRsBins) {
+#pragma unroll
+    for (int ww = 0; ww < kRsWaves; ++ww) run += cnt[ww][tid];
+  }
+  uint32_t at = block_excl_scan<uint32_t, kRsBlock>(run, &all, lds);  // the digit's place
+  if (tid < kRsBins) {
+    base[tid] = gbase - at;
 #pragma unroll
     for (int ww = 0; ww < kRsWaves; ++ww) {
-      const uint32_t t = cnt[ww][d];
-      cnt[ww][d] = run;
-      run += t;
+      const uint32_t t = cnt[ww][tid];
+      cnt[ww][tid] = at;
+      at += t;
     }
   }
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < kRsChunks; ++c) {
-    const int64_t i = t0 + (int64_t)c * kWave + lane;
-    if (i < n) {
+    if (t0 + (int64_t)c * kWave + lane < n) {
       const uint32_t d = (uint32_t)(key[c] >> shift) & (kRsBins - 1);
-      const uint32_t pos = base[d] + cnt[w][d] + rank[c];
-      kout[pos] = key[c];
-      vout[pos] = val[c];
+      const uint32_t pos = cnt[w][d] + rank[c];
+      sk[pos] = key[c];
+      sv[pos] = val[c];
     }
+  }
+  __syncthreads();
+  for (uint32_t p = (uint32_t)tid; p < all; p += kRsBlock) {
+    const uint64_t k = sk[p];
+    const uint32_t to = base[(uint32_t)(k >> shift) & (kRsBins - 1)] + p;
+    kout[to] = k;
+    vout[to] = sv[p];
   }
 }
 
@@ -341,6 +495,24 @@ hipError_t scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp,
 hipError_t scan_i32_to_i64(const int32_t *in, int64_t *out, int64_t n, int64_t *tmp,
                            hipStream_t s) {
   return scan_impl<int32_t, int64_t>(in, out, n, tmp, s);
+}
+
+hipError_t list_targets(const int32_t *perm, int64_t m, const int32_t *bins, int32_t kmin,
+                        const uint32_t *mark, const int32_t *rowp1, uint32_t *slot,
+                        int32_t *targets, int32_t *rows, uint32_t *tmp, hipStream_t s) {
+  const MarkRule r{perm, bins, kmin, mark, rowp1};
+  const int64_t nb = (m + 1 + kScanTile - 1) / kScanTile;
+  const int raw = nb <= kRawParts ? 1 : 0;
+  if (nb > 1) {
+    k_mark_count<<<(unsigned)nb, kScanBlock, 0, s>>>(r, m, tmp);
+    if (!raw) {
+      const hipError_t e = scan_u32(tmp, tmp, nb, tmp + nb + 1, s);
+      if (e != hipSuccess) return e;
+    }
+  }
+  k_mark_place<<<(unsigned)nb, kScanBlock, 0, s>>>(r, m, nb > 1 ? tmp : nullptr, raw, slot,
+                                                   targets, rows);
+  return hipGetLastError();
 }
 
 size_t radix_tmp_bytes(int64_t n) {

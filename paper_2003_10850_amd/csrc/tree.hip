@@ -244,45 +244,89 @@ __global__ __launch_bounds__(kBlock) void k_node_counts(const uint64_t *__restri
     atomicMax(maxlev, block_max);
 }
 
-__global__ void k_nodes(const uint64_t *__restrict__ keys, int64_t m,
-                        const int32_t *__restrict__ soff, int n_snap,
-                        const double4 *__restrict__ sbox,
-                        const uint32_t *__restrict__ off, const uint8_t *__restrict__ lev,
-                        int64_t nnodes, Node *__restrict__ nodes) {
+// The nodes that start at member p: levels lev[2p]..lev[2p+1], each up to the
+// first member that leaves its cell. A lane looks for a near end (kNearEnd
+// members) itself; a far one is found by the whole wave, 64 probes a step.
+// Bound by the longest chain of dependent loads: the first members of the
+// largest cells start a node on every level, and with a lane's own doubling
+// and halving search the chain was 170 loads on 2^21 particles: 60 us in the
+// average octree of 2^21 and 2^20, 32 on 6e4, 12 on 4096 (52, 11 and 9 now).
+constexpr int kNearEnd = 32;
+__global__ __launch_bounds__(kBlock) void k_nodes(
+    const uint64_t *__restrict__ keys, int64_t m, const int32_t *__restrict__ soff, int n_snap,
+    const double4 *__restrict__ sbox, const uint32_t *__restrict__ off,
+    const uint8_t *__restrict__ lev, int64_t nnodes, Node *__restrict__ nodes) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= m) return;
-  const int delta = lev[2 * p], d = lev[2 * p + 1];
-  if (d < delta) return;
-  const uint64_t kp = keys[p];
-  const int sn = n_snap > 1 ? segment_of(soff, n_snap, p) : 0;
-  const float side = (float)sbox[sn].w;
-  int64_t end = soff[sn + 1];  // members of the level-l node: [p, end)
-  for (int l = delta; l <= d; ++l) {
-    // first q in (p, end] with cpl(p, q) < l (end shrinks as l grows)
-    int64_t lo = p + 1, hi = end;  // answer in [lo, hi]
-    int64_t step = 1;
-    while (lo + step - 1 < hi && cpl(kp, keys[lo + step - 1]) >= l) {
-      lo += step;
-      step <<= 1;
+  const int lane = lane_id();
+  int delta = 1, d = 0;  // (none)
+  if (p < m) {
+    delta = lev[2 * p];
+    d = lev[2 * p + 1];
+  }
+  uint64_t kp = 0;
+  float side = 0.f;
+  int end = 0;  // members of the level-l node: [p, end)
+  uint32_t at = 0;
+  if (d >= delta) {
+    kp = keys[p];
+    const int sn = n_snap > 1 ? segment_of(soff, n_snap, p) : 0;
+    side = (float)sbox[sn].w;
+    end = soff[sn + 1];
+    at = off[p];
+  }
+  for (int l = delta; __ballot(l <= d) != 0ull; ++l) {
+    const bool work = l <= d;
+    // the first q in (p, end] with cpl(p, q) < l (end shrinks as l grows);
+    // answer in [lo, hi]
+    int lo = (int)p + 1, hi = end;
+    bool far = false;
+    if (work) {
+      const int q = lo + kNearEnd - 1;
+      if (q < hi) {
+        if (cpl(kp, keys[q]) >= l) {
+          lo = q + 1;
+          far = true;
+        } else {
+          hi = q;
+        }
+      }
+      while (!far && lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (cpl(kp, keys[mid]) >= l) lo = mid + 1;
+        else hi = mid;
+      }
     }
-    if (lo + step - 1 < hi) hi = lo + step - 1;
-    while (lo < hi) {
-      const int64_t mid = lo + (hi - lo) / 2;
-      if (cpl(kp, keys[mid]) >= l) lo = mid + 1;
-      else hi = mid;
+    uint64_t fm = __ballot(far);
+    while (fm) {
+      const int b = (int)__builtin_ctzll(fm);
+      fm &= fm - 1ull;
+      const uint64_t kb = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(kp >> 32), b) << 32) |
+                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)kp, b);
+      const int lb = __builtin_amdgcn_readlane(l, b);
+      int x = __builtin_amdgcn_readlane(lo, b), y = __builtin_amdgcn_readlane(hi, b);
+      while (x < y) {
+        const int step = (y - x + kWave - 1) / kWave;
+        const int64_t q = (int64_t)x + (int64_t)step * (lane + 1) - 1;
+        const int in = __popcll(__ballot(q < y && cpl(kb, keys[q < y ? q : x]) >= lb));
+        y = (int)min((int64_t)y, (int64_t)x + (int64_t)step * (in + 1) - 1);
+        x += step * in;
+      }
+      if (lane == b) lo = x;
     }
-    end = lo;
-    const int64_t idx = (int64_t)off[p] + (l - delta);
-    const int64_t skip = (end >= m) ? nnodes : (int64_t)off[end];
-    Node nd;
-    nd.com_m = make_float4(0.f, 0.f, 0.f, 0.f);
-    nd.lo_h = make_float4(0.f, 0.f, 0.f, 0.f);
-    nd.hi_l = make_float4(0.f, 0.f, 0.f, ldexpf(side, -l));
-    // the parent's member count follows (k_parents); a root has none and
-    // counts as inside an unbounded node
-    nd.meta = make_int4((int)skip, (int)p, (int)(end - p),
-                        l | (l == d ? kLeafBit : 0) | (l == 0 ? (int)0xffff0000u : 0));
-    nodes[idx] = nd;
+    if (work) {
+      end = lo;
+      Node nd;
+      nd.lo_h = make_float4(0.f, 0.f, 0.f, 0.f);
+      nd.hi_l = make_float4(0.f, 0.f, 0.f, ldexpf(side, -l));
+      // the parent's member count follows (k_parents); a root has none and
+      // counts as inside an unbounded node; the moments fill com_m and the boxes
+      nd.meta = make_int4(end >= m ? (int)nnodes : (int)off[end], (int)p, end - (int)p,
+                          l | (l == d ? kLeafBit : 0) | (l == 0 ? (int)0xffff0000u : 0));
+      Node &to = nodes[(int64_t)at + (l - delta)];
+      to.lo_h = nd.lo_h;
+      to.hi_l = nd.hi_l;
+      to.meta = nd.meta;
+    }
   }
 }
 
@@ -317,158 +361,236 @@ struct Moments {
   const float4 *__restrict__ xm;
   const double4 *__restrict__ x64;
 };
-__device__ __forceinline__ void node_moments(const Moments &A, int64_t k, int4 meta) {
+struct NodeSums {
   double M = 0.0, Sx = 0.0, Sy = 0.0, Sz = 0.0;
-  float4 lo = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
-  float4 hi = make_float4(-INFINITY, -INFINITY, -INFINITY, 0.f);
-  if (meta.w & kLeafBit) {
-    for (int s = meta.y; s < meta.y + meta.z; ++s) {
-      const float4 p = A.xm[s];
+  float3 lo = make_float3(INFINITY, INFINITY, INFINITY);
+  float3 hi = make_float3(-INFINITY, -INFINITY, -INFINITY);
+  __device__ __forceinline__ void add(double m, double x, double y, double z, float lx, float ly,
+                                      float lz, float hx, float hy, float hz) {
+    M += m;
+    Sx += x;
+    Sy += y;
+    Sz += z;
+    lo.x = fminf(lo.x, lx); lo.y = fminf(lo.y, ly); lo.z = fminf(lo.z, lz);
+    hi.x = fmaxf(hi.x, hx); hi.y = fmaxf(hi.y, hy); hi.z = fmaxf(hi.z, hz);
+  }
+};
+
+// A leaf's sums, four members' loads at a time.
+__device__ __forceinline__ NodeSums leaf_sums(const Moments &A, int4 meta) {
+  NodeSums r;
+  const int end = meta.y + meta.z;
+  for (int s = meta.y; s < end; s += 4) {
+    float4 p[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) p[q] = A.xm[min(s + q, end - 1)];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (s + q >= end) break;
       // moments from the exact positions (FP64 ones when the tree has them)
-      const double4 q = A.x64 ? A.x64[s] : make_double4(p.x, p.y, p.z, p.w);
-      M += q.w;
-      Sx += q.w * q.x;
-      Sy += q.w * q.y;
-      Sz += q.w * q.z;
-      lo.x = fminf(lo.x, p.x); lo.y = fminf(lo.y, p.y); lo.z = fminf(lo.z, p.z);
-      hi.x = fmaxf(hi.x, p.x); hi.y = fmaxf(hi.y, p.y); hi.z = fmaxf(hi.z, p.z);
-    }
-  } else {
-    int64_t c = k + 1;
-    while (c < meta.x) {
-      const double4 cm = A.mom[c];
-      const float4 clo = A.nodes[c].lo_h, chi = A.nodes[c].hi_l;
-      M += cm.x;
-      Sx += cm.y;
-      Sy += cm.z;
-      Sz += cm.w;
-      lo.x = fminf(lo.x, clo.x); lo.y = fminf(lo.y, clo.y); lo.z = fminf(lo.z, clo.z);
-      hi.x = fmaxf(hi.x, chi.x); hi.y = fmaxf(hi.y, chi.y); hi.z = fmaxf(hi.z, chi.z);
-      c = A.nodes[c].meta.x;
+      const double4 v = A.x64 ? A.x64[s + q] : make_double4(p[q].x, p[q].y, p[q].z, p[q].w);
+      r.add(v.w, v.w * v.x, v.w * v.y, v.w * v.z, p[q].x, p[q].y, p[q].z, p[q].x, p[q].y, p[q].z);
     }
   }
-  A.mom[k] = make_double4(M, Sx, Sy, Sz);
+  return r;
+}
+
+// Node k's moments, centre and box (the fourth components of its box stay).
+__device__ __forceinline__ void store_node(const Moments &A, int64_t k, const NodeSums &r) {
+  A.mom[k] = make_double4(r.M, r.Sx, r.Sy, r.Sz);
   Node &nd = A.nodes[k];
   float4 cm;
-  if (M > 0.0)
-    cm = make_float4((float)(Sx / M), (float)(Sy / M), (float)(Sz / M), (float)M);
+  if (r.M > 0.0)
+    cm = make_float4((float)(r.Sx / r.M), (float)(r.Sy / r.M), (float)(r.Sz / r.M), (float)r.M);
   else  // massless node: its geometric centre
-    cm = make_float4(0.5f * (lo.x + hi.x), 0.5f * (lo.y + hi.y), 0.5f * (lo.z + hi.z), 0.f);
+    cm = make_float4(0.5f * (r.lo.x + r.hi.x), 0.5f * (r.lo.y + r.hi.y),
+                     0.5f * (r.lo.z + r.hi.z), 0.f);
   nd.com_m = cm;
   if (A.c64)
-    A.c64[k] = M > 0.0 ? make_double4(Sx / M, Sy / M, Sz / M, M)
-                       : make_double4(cm.x, cm.y, cm.z, 0.0);
-  lo.w = nd.lo_h.w;
-  hi.w = nd.hi_l.w;
-  nd.lo_h = lo;
-  nd.hi_l = hi;
+    A.c64[k] = r.M > 0.0 ? make_double4(r.Sx / r.M, r.Sy / r.M, r.Sz / r.M, r.M)
+                         : make_double4(cm.x, cm.y, cm.z, 0.0);
+  nd.lo_h.x = r.lo.x; nd.lo_h.y = r.lo.y; nd.lo_h.z = r.lo.z;
+  nd.hi_l.x = r.hi.x; nd.hi_l.y = r.hi.y; nd.hi_l.z = r.hi.z;
+}
+
+__device__ __forceinline__ void node_moments(const Moments &A, int64_t k, int4 meta) {
+  if (meta.w & kLeafBit) {
+    store_node(A, k, leaf_sums(A, meta));
+    return;
+  }
+  NodeSums r;
+  for (int64_t c = k + 1; c < meta.x; c = A.nodes[c].meta.x) {
+    const double4 cm = A.mom[c];
+    const float4 lo = A.nodes[c].lo_h, hi = A.nodes[c].hi_l;
+    r.add(cm.x, cm.y, cm.z, cm.w, lo.x, lo.y, lo.z, hi.x, hi.y, hi.z);
+  }
+  store_node(A, k, r);
 }
 
 // The moments bottom up in two launches: the subtrees of at most kSubtree
 // members (and larger leaves) whose parent holds more, a workgroup each, and
 // then the nodes above them, one workgroup for all (one launch for trees of
 // at most kSmallNodes nodes). Leaves need no order; inner nodes go level by
-// level with a barrier between. Bound by the latency of the levels: 80 + 49 us
-// for the two octrees of 2^21 and 2^20 particles each on average, 23 us on
-// 4096. (A launch a level read every node's level each time: 12 launches of 14
-// us on 2^21 particles, as many of 5-6 us on 10^5, twice for a build and twice
-// for every refit. Keeping the children's indices, so that their loads run
-// together, cost registers: 111 + 70 us.)
-constexpr int kInnerList = 1024;
+// level with a barrier between. Bound by latency: a level costs one step of
+// its children's data. What a workgroup has summed stays in LDS for the
+// parents, and the nodes above hold their children's indices (found once, by
+// the build), so no step follows a chain of loads from one child to the next;
+// that chain took 80 us for the subtrees and 50 for the nodes above in the
+// average octree of 2^21 and 2^20 particles (57 and 46 now, the latter the
+// request rate of the one CU), 14 and 23 on 6e4 (10.5 and 13), 23 on 4096 (19).
+template <int kCap>
+struct MomLds {
+  double m[4][kCap];
+  float lo[3][kCap], hi[3][kCap];
+  int32_t skip[kCap];
+  int32_t inner[kCap];  // (local index << 8) | level
+  int32_t n_inner, max_level;
+};
 
-// The inner nodes of a list of (node, level), by level.
-__device__ __forceinline__ void inner_levels(const Moments &A, const int2 *list, int n, int maxl,
-                                             int minl) {
-  for (int l = maxl; l >= minl; --l) {
-    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x)
-      if (list[i].y == l) node_moments(A, list[i].x, A.nodes[list[i].x].meta);
-    __syncthreads();
-  }
-}
-
-constexpr int kTopBlock = 1024;
-constexpr int kSmallNodes = 4 * kInnerList;
-__global__ __launch_bounds__(kTopBlock) void k_moments_small(const Moments A, int nnodes) {
-  __shared__ int2 list[kSmallNodes];
-  __shared__ int n_inner, max_level;
-  if (threadIdx.x == 0) {
-    n_inner = 0;
-    max_level = -1;
+// The n nodes from k0 on (n <= kCap), whole subtrees.
+template <int kCap>
+__device__ __forceinline__ void lds_moments(const Moments &A, int k0, int n, MomLds<kCap> &S) {
+  const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
+  if (tid == 0) {
+    S.n_inner = 0;
+    S.max_level = -1;
   }
   __syncthreads();
-  for (int k = (int)threadIdx.x; k < nnodes; k += kTopBlock) {
-    const int4 meta = A.nodes[k].meta;
+  auto keep = [&](int q, const NodeSums &r) {
+    S.m[0][q] = r.M; S.m[1][q] = r.Sx; S.m[2][q] = r.Sy; S.m[3][q] = r.Sz;
+    S.lo[0][q] = r.lo.x; S.lo[1][q] = r.lo.y; S.lo[2][q] = r.lo.z;
+    S.hi[0][q] = r.hi.x; S.hi[1][q] = r.hi.y; S.hi[2][q] = r.hi.z;
+    store_node(A, k0 + q, r);
+  };
+  for (int q = tid; q < n; q += nthr) {
+    const int4 meta = A.nodes[k0 + q].meta;
+    S.skip[q] = meta.x - k0;
     if (meta.w & kLeafBit) {
-      node_moments(A, k, meta);
+      keep(q, leaf_sums(A, meta));
     } else {
-      list[atomicAdd(&n_inner, 1)] = make_int2(k, meta.w & 255);
-      atomicMax(&max_level, meta.w & 255);
+      S.inner[atomicAdd(&S.n_inner, 1)] = q << 8 | (meta.w & 255);
+      atomicMax(&S.max_level, meta.w & 255);
     }
   }
   __syncthreads();
-  inner_levels(A, list, n_inner, max_level, 0);
+  const int ni = S.n_inner;
+  for (int l = S.max_level, left = ni; left > 0; --l) {
+    int done = 0;
+    for (int i0 = 0; i0 < ni; i0 += nthr) {
+      const int e = i0 + tid < ni ? S.inner[i0 + tid] : -1;
+      const bool mine = e >= 0 && (e & 255) == l;
+      if (mine) {
+        const int q = e >> 8, end = S.skip[q];
+        NodeSums r;
+        for (int c = q + 1; c < end; c = S.skip[c])
+          r.add(S.m[0][c], S.m[1][c], S.m[2][c], S.m[3][c], S.lo[0][c], S.lo[1][c], S.lo[2][c],
+                S.hi[0][c], S.hi[1][c], S.hi[2][c]);
+        keep(q, r);
+      }
+      done += __syncthreads_count(mine);
+    }
+    left -= done;
+  }
+  __syncthreads();
+}
+
+constexpr int kTopBlock = 1024;
+constexpr int kSmallNodes = 2048, kSubNodes = 512;
+__global__ __launch_bounds__(kTopBlock) void k_moments_small(const Moments A, int nnodes) {
+  __shared__ MomLds<kSmallNodes> S;
+  lds_moments(A, 0, nnodes, S);
 }
 
 __global__ __launch_bounds__(kBlock) void k_moments_sub(const Moments A,
                                                         const int32_t *__restrict__ subs,
                                                         const int32_t *__restrict__ counts) {
-  __shared__ int2 list[kInnerList];
-  __shared__ int n_inner, max_level;
+  __shared__ MomLds<kSubNodes> S;
   const int nsub = counts[0];
   for (int b = (int)blockIdx.x; b < nsub; b += (int)gridDim.x) {
     const int k0 = subs[b];
     const int4 m0 = A.nodes[k0].meta;
     const int k1 = m0.x, lv0 = m0.w & 255;
-    if (threadIdx.x == 0) {
-      n_inner = 0;
-      max_level = lv0;
+    if (k1 - k0 <= kSubNodes) {
+      lds_moments(A, k0, k1 - k0, S);
+      continue;
     }
+    // small leaves or long chains of single children: from memory
+    if (threadIdx.x == 0) S.max_level = lv0;
     __syncthreads();
     for (int k = k0 + (int)threadIdx.x; k < k1; k += kBlock) {
       const int4 meta = A.nodes[k].meta;
-      if (meta.w & kLeafBit) {
-        node_moments(A, k, meta);
-      } else {
-        const int i = atomicAdd(&n_inner, 1);
-        if (i < kInnerList) list[i] = make_int2(k, meta.w & 255);
-        atomicMax(&max_level, meta.w & 255);
-      }
+      if (meta.w & kLeafBit) node_moments(A, k, meta);
+      else atomicMax(&S.max_level, meta.w & 255);
     }
     __syncthreads();
-    const int n = n_inner, maxl = max_level;
-    if (n <= kInnerList) {
-      inner_levels(A, list, n, maxl, lv0);
-    } else {  // (long chains of single children)
-      for (int l = maxl; l >= lv0; --l) {
-        for (int k = k0 + (int)threadIdx.x; k < k1; k += kBlock) {
-          const int4 meta = A.nodes[k].meta;
-          if (!(meta.w & kLeafBit) && (meta.w & 255) == l) node_moments(A, k, meta);
-        }
-        __syncthreads();
+    for (int l = S.max_level; l >= lv0; --l) {
+      for (int k = k0 + (int)threadIdx.x; k < k1; k += kBlock) {
+        const int4 meta = A.nodes[k].meta;
+        if (!(meta.w & kLeafBit) && (meta.w & 255) == l) node_moments(A, k, meta);
       }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
+// The nodes above the subtrees, level by level: eight threads a node read its
+// children, one adds them up in their order.
+constexpr int kTopList = 4096, kTopNodes = kTopBlock / 8;
 __global__ __launch_bounds__(kTopBlock) void k_moments_top(const Moments A,
-                                                           const int2 *__restrict__ tops,
+                                                           const TopNode *__restrict__ tops,
                                                            const int32_t *__restrict__ counts) {
-  __shared__ int2 list[4 * kInnerList];
-  __shared__ int max_level;
-  const int n = counts[1];
-  if (threadIdx.x == 0) max_level = -1;
-  __syncthreads();
-  const bool fits = n <= 4 * kInnerList;
-  int ml = -1;
-  for (int i = (int)threadIdx.x; i < n; i += kTopBlock) {
-    const int2 t = tops[i];
-    if (fits) list[i] = t;
-    ml = max(ml, t.y);
+  __shared__ int32_t order[kTopList];
+  __shared__ int32_t start[kMaxLevel + 2], fill[kMaxLevel + 2];
+  __shared__ double m[4][kTopBlock];
+  __shared__ float lo[3][kTopBlock], hi[3][kTopBlock];
+  __shared__ int32_t nchild[kTopNodes];
+  const int n = counts[1], tid = (int)threadIdx.x;
+  if (n > kTopList) {  // (trees of some 10^7 particles)
+    for (int l = kMaxLevel; l >= 0; --l) {
+      for (int i = tid; i < n; i += kTopBlock)
+        if (tops[i].level == l) node_moments(A, tops[i].node, A.nodes[tops[i].node].meta);
+      __syncthreads();
+    }
+    return;
   }
-  if (ml >= 0) atomicMax(&max_level, ml);
+  if (tid < kMaxLevel + 2) fill[tid] = 0;
   __syncthreads();
-  inner_levels(A, fits ? list : tops, n, max_level, 0);
+  for (int i = tid; i < n; i += kTopBlock) atomicAdd(&fill[tops[i].level], 1);
+  __syncthreads();
+  if (tid == 0)
+    for (int l = 0, at = 0; l < kMaxLevel + 2; ++l) {
+      const int c = fill[l];
+      start[l] = fill[l] = at;
+      at += c;
+    }
+  __syncthreads();
+  for (int i = tid; i < n; i += kTopBlock) order[atomicAdd(&fill[tops[i].level], 1)] = i;
+  __syncthreads();
+  for (int l = kMaxLevel; l >= 0; --l) {
+    const int b = start[l], e = start[l + 1];
+    for (int i0 = b; i0 < e; i0 += kTopNodes) {
+      const int i = i0 + (tid >> 3);
+      const int c = i < e ? tops[order[i]].child[tid & 7] : -1;
+      if (c >= 0) {
+        const double4 cm = A.mom[c];
+        const float4 cl = A.nodes[c].lo_h, ch = A.nodes[c].hi_l;
+        m[0][tid] = cm.x; m[1][tid] = cm.y; m[2][tid] = cm.z; m[3][tid] = cm.w;
+        lo[0][tid] = cl.x; lo[1][tid] = cl.y; lo[2][tid] = cl.z;
+        hi[0][tid] = ch.x; hi[1][tid] = ch.y; hi[2][tid] = ch.z;
+      }
+      const int have = __popcll(__ballot(c >= 0) & (0xffull << (tid & 56)));
+      if ((tid & 7) == 0) nchild[tid >> 3] = have;
+      __syncthreads();
+      if (tid < kTopNodes && i0 + tid < e) {
+        NodeSums r;
+        for (int q = 8 * tid; q < 8 * tid + nchild[tid]; ++q)
+          r.add(m[0][q], m[1][q], m[2][q], m[3][q], lo[0][q], lo[1][q], lo[2][q], hi[0][q],
+                hi[1][q], hi[2][q]);
+        store_node(A, tops[order[i0 + tid]].node, r);
+      }
+      __syncthreads();
+    }
+  }
 }
 
 // Bottom-up pass for one level: maximum h of the members (vh.w).
@@ -626,7 +748,7 @@ __global__ __launch_bounds__(kBlock) void k_split_count(const Node *__restrict__
 __global__ __launch_bounds__(kBlock) void k_split_write(const Node *__restrict__ nodes, int nn,
                                                         const int2 *__restrict__ bcount,
                                                         int32_t *__restrict__ subs,
-                                                        int2 *__restrict__ tops,
+                                                        TopNode *__restrict__ tops,
                                                         int32_t *__restrict__ counts) {
   __shared__ int lds[kBlock / kWave];
   __shared__ int na, nb;  // appended by this block
@@ -645,8 +767,18 @@ __global__ __launch_bounds__(kBlock) void k_split_write(const Node *__restrict__
     if (k >= nn) continue;
     const int4 meta = nodes[k].meta;
     if (is_terminal(meta, kSubtree)) subs[a + atomicAdd(&na, 1)] = k;
-    if (!(meta.w & kLeafBit) && meta.z > kSubtree)
-      tops[b + atomicAdd(&nb, 1)] = make_int2(k, meta.w & 255);
+    if (!(meta.w & kLeafBit) && meta.z > kSubtree) {
+      TopNode t;
+      t.node = k;
+      t.level = meta.w & 255;
+      int c = k + 1;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        t.child[j] = c < meta.x ? c : -1;
+        if (c < meta.x) c = nodes[c].meta.x;
+      }
+      tops[b + atomicAdd(&nb, 1)] = t;
+    }
   }
   __syncthreads();
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
@@ -897,7 +1029,7 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
     // (the lists of the moments in one buffer)
     if (dev_malloc(c, (void **)&o.nodes, cap * sizeof(Node)) != hipSuccess ||
         dev_malloc(c, (void **)&o.mom, cap * sizeof(double4)) != hipSuccess ||
-        dev_malloc(c, (void **)&o.tops, max_tops(o.cap_n) * sizeof(int2) +
+        dev_malloc(c, (void **)&o.tops, max_tops(o.cap_n) * sizeof(TopNode) +
                                             (cap + 2) * sizeof(int32_t)) != hipSuccess) {
       c->err = "device allocation of the octree nodes failed";
       return G3_ENOMEM;

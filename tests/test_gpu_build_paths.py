@@ -105,3 +105,43 @@ def test_forest_edges(ctx, sizes):
             np.testing.assert_allclose(got["com"][n0:n0 + nn], ref["com"], rtol=1e-12, atol=1e-12)
             m0, n0 = m0 + m, n0 + nn
         assert m0 == len(got["order"]) and n0 == len(got["start"])
+
+
+@pytest.mark.parametrize("n", [1, 2047, 2048, 2049, 16383, 16384, 16385, 40960])
+def test_target_lists_at_the_edges_of_the_scans(n):
+    # one tile, one workgroup, two launches: the listed rows are computed (the
+    # same counts as in a call for every member), the others stay
+    from paper_2003_10850_amd import inputs, ops
+    c = ops.Context(torch.device("cuda", 0))
+    g = torch.Generator(device="cuda").manual_seed(n)
+    pos, mass = torch.rand(n, 3, generator=g, device="cuda"), torch.ones(n, device="cuda")
+    tree = ops.Tree(c, pos, mass, None, (0.0, 0.0, 0.0, 1.0), inputs.Params(n_ngb=16.0))
+    every = ops.gravity(tree)["nterms"]
+    h = torch.full((n,), 0.9 * n ** (-1.0 / 3.0), device="cuda")
+    nngb = ops.density(tree, h=h, solve_h=False)["nngb"]
+    for part in (0.0, 0.3, 1.0):
+        on = torch.rand(n, generator=g, device="cuda") < part
+        on[-1] = True
+        act = on.nonzero().flatten().int().flip(0).contiguous()
+        for a, b in ((ops.gravity(tree, active=act)["nterms"], every),
+                     (ops.density(tree, h=h, active=act, solve_h=False)["nngb"], nngb)):
+            assert torch.equal(a, torch.where(on, b, torch.zeros_like(b)))
+
+
+def test_scans_of_more_than_four_thousand_tiles():
+    # 8.4e6 members: the tiles' sums are scanned by themselves first
+    from paper_2003_10850_amd import inputs, ops
+    n = 4096 * 2048 + 4321
+    c = ops.Context(torch.device("cuda", 0))
+    g = torch.Generator(device="cuda").manual_seed(8)
+    pos, mass = torch.rand(n, 3, generator=g, device="cuda"), torch.ones(n, device="cuda")
+    typ = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    typ[: n // 100] = 1  # the gas octree keeps more than 4096 tiles less one
+    tree = ops.Tree(c, pos, mass, typ, (0.0, 0.0, 0.0, 1.0), inputs.Params(theta=1.0))
+    order = tree.export(1)["order"]
+    assert torch.equal(order.sort().values, torch.arange(n // 100, n, device="cuda").int())
+    act = torch.tensor([n - 1, 0, 4096 * 2048, 17], dtype=torch.int32, device="cuda")
+    r = ops.gravity(tree, active=act)
+    on = torch.zeros(n, dtype=torch.bool, device="cuda")
+    on[act.long()] = True
+    assert torch.equal(r["nterms"] > 0, on)
