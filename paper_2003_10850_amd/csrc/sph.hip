@@ -535,11 +535,14 @@ __device__ __forceinline__ float rho_u_difference(float ri, float ui, float rj, 
   return __builtin_fmaf(ri, ui, -pj) - ej;
 }
 
+// A tile's candidates: (x, y, z, fl(h^2)), which is all that the neighbour test
+// reads, (v, m), (A, c, rho, 1/h) and the kernel's factor -22 C h^-5.
 template <int kWpb>
 struct HydroTile {
   float4 xm[kWpb][kTile];
   float4 vh[kWpb][kTile];
   float4 aux[kWpb][kTile];
+  float g[kWpb][kTile];
 };
 
 // The extra tile of the switches' inputs (a one-entry stand-in without them).
@@ -553,10 +556,14 @@ struct ExtTile {
 // kT > 1: a team serves a group, as in the density; else a wave walks the
 // octree itself. 2^20 gas particles of the clustered 2^21 box: 3.8 ms with a
 // wave a group, 4.1 with teams of 4 (their LDS holds 4 waves a SIMD, not 6),
-// 5.1 and 7.7 with 8 and 16; 2^15 gas particles: 2.9, 0.92, 0.65 and 0.55 ms. Bound by vector
+// 5.1 and 7.7 with 8 and 16; 2^15 gas particles: 2.9, 0.92, 0.65 and 0.55 ms.
+// The test reads one float4 an entry, four entries a step, and what depends
+// on the entry alone comes with it: 3.6 ms of the 3.75 that two float4 an entry
+// and the entry's h^-5 in every pair took, 1.53 of 1.66 with the switches at
+// 2.5e5 targets. Bound by vector
 // issue on a full chip, by the slowest groups otherwise.
 template <bool kF64, bool kExt, int kT>
-__global__ __launch_bounds__(kBlockOf<kT>) void k_hydro(
+__global__ __launch_bounds__(kBlockOf<kT>, kT == 1 && !kF64 && !kExt ? 6 : 1) void k_hydro(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const double *__restrict__ h64,
     const float4 *__restrict__ vh, const float4 *__restrict__ aux,
@@ -615,8 +622,8 @@ __global__ __launch_bounds__(kBlockOf<kT>) void k_hydro(
   }
   const float hi = valid ? mv.w : -1.0f;  // invalid lanes never want anything
   const float hi2 = valid ? sq_exact(hi) : -1.0f;
-  const float Ai = ma.x, ci = ma.y, rhoi = ma.z, hinvi = ma.w;
-  const float ki = kWendlandF * (hinvi * hinvi) * (hinvi * hinvi) * hinvi;
+  const float ci = ma.y, rhoi = ma.z, hinvi = ma.w, half_alpha = 0.5f * alpha;
+  const float ki = kWendlandF * (hinvi * hinvi) * (hinvi * hinvi) * hinvi, Aki = ma.x * ki;
   // totals with Neumaier compensation terms; per-tile partials are plain
   float ax = 0.f, ay = 0.f, az = 0.f, du = 0.f, vs = 0.f;
   float cax = 0.f, cay = 0.f, caz = 0.f, cdu = 0.f;
@@ -682,11 +689,14 @@ __global__ __launch_bounds__(kBlockOf<kT>) void k_hydro(
       const uint64_t km = __ballot(keep);
       const int slot = (int)__builtin_amdgcn_mbcnt_hi(
           (uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
-      // kept candidates in their order at the front; the scan stops at nc
+      // kept candidates in their order at the front, infinity behind (the scan
+      // takes whole groups of kStep)
+      T.xm[w][lane] = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
       if (keep) {
-        T.xm[w][slot] = vo;
-        T.vh[w][slot] = vv;
+        T.xm[w][slot] = make_float4(vo.x, vo.y, vo.z, sq_exact(vv.w));
+        T.vh[w][slot] = make_float4(vv.x, vv.y, vv.z, vo.w);
         T.aux[w][slot] = va;
+        T.g[w][slot] = kWendlandF * (va.w * va.w) * (va.w * va.w) * va.w;
         if constexpr (kExt) E.e[w][slot] = ve;
         if constexpr (kF64) tlos[w][slot] = vl;
       }
@@ -697,67 +707,66 @@ __global__ __launch_bounds__(kBlockOf<kT>) void k_hydro(
     // one pair (i, entry k) that passed the symmetric neighbour test; the
     // self pair (r = 0) passes too: it is counted and subtracted at the end,
     // and any pair at r = 0 adds nothing to the sums
-    auto pair = [&](int k, const float4 &q, const float4 &qv, float dx, float dy, float dz,
-                    float r2) {
-      {
-        const float4 qa = T.aux[w][k];
-        if (r2 > 0.0f) {
-          const float rinv = __builtin_amdgcn_rsqf(r2);
-          const float r = r2 * rinv;
-          const float hj5 = (qa.w * qa.w) * (qa.w * qa.w) * qa.w;
-          const float gi = ki * wendland_f(r * hinvi);
-          const float gj = kWendlandF * hj5 * wendland_f(r * qa.w);
-          // x_ij = x_i - x_j = -(dx, dy, dz); v_ij = v_i - v_j
-          const float vdx = (mv.x - qv.x) * dx + (mv.y - qv.y) * dy + (mv.z - qv.z) * dz;
-          const float vx = -vdx;  // v_ij . x_ij
-          const float wv = vx * rinv;
-          const float wneg = fminf(wv, 0.0f);
-          const float vsig_ij = ci + qa.y - 3.0f * wneg;
-          vs = fmaxf(vs, vsig_ij);
-          // the hardware reciprocal (1 ulp) in place of an IEEE division
-          const float rsum_inv = __builtin_amdgcn_rcpf(rhoi + qa.z);
-          float a_ij = alpha;
-          if constexpr (kExt) {
-            // (alpha_i + alpha_j)/2 times the mean Balsara factor
-            const float4 qe = E.e[w][k];
-            a_ij = 0.25f * (mx.x + qe.x) * (mx.y + qe.y);
-          }
-          const float Pi = a_ij * vsig_ij * (-wneg) * rsum_inv;
-          const float gbar = 0.5f * (gi + gj);
-          const float mj = q.w;
-          const float coef = mj * (Ai * gi + qa.x * gj + Pi * gbar);  // a_i -= coef x_ij
-          px += coef * dx;
-          py += coef * dy;
-          pz += coef * dz;
-          pu += mj * (Ai * gi + 0.5f * Pi * gbar) * vx;
-          if constexpr (kExt) {
-            // artificial conduction: m_j alpha_u v_u (u_i - u_j) gbar r / rhobar,
-            // v_u = sqrt(|P_i - P_j| / rhobar), rhobar = (rho_i + rho_j)/2
-            const float4 qe = E.e[w][k];
-            const float two_inv = 2.0f * rsum_inv;  // 1 / rhobar
-            const float dP = gm1 * rho_u_difference(mx.w, mx.z, qe.w, qe.z);
-            const float vu = __builtin_amdgcn_sqrtf(fabsf(dP) * two_inv);
-            pu += mj * alpha_u * vu * (mx.z - qe.z) * gbar * r * two_inv;
-          }
+    auto pair = [&](int k, float dx, float dy, float dz, float r2) {
+      if (r2 > 0.0f) {
+        const float4 qv = T.vh[w][k], qa = T.aux[w][k];
+        const float rinv = __builtin_amdgcn_rsqf(r2);
+        const float r = r2 * rinv;
+        const float wi = wendland_f(r * hinvi);
+        const float gj = T.g[w][k] * wendland_f(r * qa.w);
+        // x_ij = x_i - x_j = -(dx, dy, dz); v_ij = v_i - v_j
+        const float vdx = (mv.x - qv.x) * dx + (mv.y - qv.y) * dy + (mv.z - qv.z) * dz;
+        const float vx = -vdx;  // v_ij . x_ij
+        const float wv = vx * rinv;
+        const float wneg = fminf(wv, 0.0f);
+        const float vsig_ij = ci + qa.y - 3.0f * wneg;
+        vs = max_num(vs, vsig_ij);
+        // the hardware reciprocal (1 ulp) in place of an IEEE division
+        const float rsum_inv = __builtin_amdgcn_rcpf(rhoi + qa.z);
+        float ha_ij = half_alpha;
+        if constexpr (kExt) {
+          // (alpha_i + alpha_j)/2 times the mean Balsara factor
+          const float4 qe = E.e[w][k];
+          ha_ij = 0.125f * (mx.x + qe.x) * (mx.y + qe.y);
+        }
+        // Pi gbar = V with Pi = a_ij v_sig (-w) / (rho_i + rho_j), gbar = (g_i + g_j) / 2
+        const float gsum = ki * wi + gj;
+        const float V = ha_ij * vsig_ij * (-wneg) * rsum_inv * gsum;
+        const float mj = qv.w, Ag = Aki * wi;  // A_i g_i
+        const float coef = mj * (Ag + qa.x * gj + V);  // a_i -= coef x_ij
+        px += coef * dx;
+        py += coef * dy;
+        pz += coef * dz;
+        pu += mj * (Ag + 0.5f * V) * vx;
+        if constexpr (kExt) {
+          // artificial conduction: m_j alpha_u v_u (u_i - u_j) gbar r / rhobar,
+          // v_u = sqrt(|P_i - P_j| / rhobar), rhobar = (rho_i + rho_j)/2
+          const float4 qe = E.e[w][k];
+          const float two_inv = 2.0f * rsum_inv;  // 1 / rhobar
+          const float dP = gm1 * rho_u_difference(mx.w, mx.z, qe.w, qe.z);
+          const float vu = __builtin_amdgcn_sqrtf(fabsf(dP) * two_inv);
+          pu += mj * alpha_u * vu * (mx.z - qe.z) * gsum * r * rsum_inv;
         }
       }
     };
     // every lane tests every entry (read by broadcast)
     auto scan = [&](auto refine_c) {
       constexpr bool kRefine = decltype(refine_c)::value;
-      for (int k = 0; k < nc; ++k) {
+      constexpr int kStep = 4;
+      for (int k0 = 0; k0 < nc; k0 += kStep) {
+#pragma unroll
+      for (int k = k0; k < k0 + kStep; ++k) {
         const float4 q = T.xm[w][k];
-        const float4 qv = T.vh[w][k];
         // plain: the FP32 positions; mixed: the FP32 difference of the two
         // offsets from the group centre
         float dx = sub_exact(q.x, kF64 ? xo.x : xi.x);
         float dy = sub_exact(q.y, kF64 ? xo.y : xi.y);
         float dz = sub_exact(q.z, kF64 ? xo.z : xi.z);
         float r2 = dist2_exact(dx, dy, dz);
-        // r2 < fl(max(h_i, h_j)^2) taken as r2 < fl(h_i^2) or r2 < fl(h_j^2)
-        // (the same decision: rounding is monotone), without a max
-        const float hj2 = sq_exact(qv.w);
-        bool in = r2 < hi2 || r2 < hj2;
+        // r2 < fl(max(h_i, h_j)^2) (rounding is monotone)
+        const float hj2 = q.w;
+        const float H2 = max_num(hi2, hj2);
+        bool in = r2 < H2;
         if constexpr (kF64) {
           // the density's bands with E bounded by gext + H near the
           // threshold, E H <= 3 H^2 + gext^2: a narrow group decides on the
@@ -765,7 +774,6 @@ __global__ __launch_bounds__(kBlockOf<kT>) void k_hydro(
           // adds the low parts to every entry and decides on them outside
           // 2^-19 (H^2 + 2^-20 (3 H^2 + gext^2)); inside the band the FP64
           // test decides (rare: a wave-uniform branch)
-          const float H2 = fmaxf(hi2, hj2);
           const float eb = 3.0f * H2 + ext2;
           float bd = kBandOff * eb;
           if constexpr (kRefine) {
@@ -785,8 +793,9 @@ __global__ __launch_bounds__(kBlockOf<kT>) void k_hydro(
         }
         if (in) {
           ++np;
-          pair(k, q, qv, dx, dy, dz, r2);
+          pair(k, dx, dy, dz, r2);
         }
+      }
       }
     };
     if (kF64 && !fine)
