@@ -419,22 +419,26 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
 }
 
 // Waves of a team from the host's bound on the targets. Measured (us, cold
-// density solve and hydro force of clustered sets; one column a team of
-// 4, 8 or 16 waves, for the hydro force first none):
-//   groups           512         1024        2048        4096        8192
-//   density      2474 1748 1659  2474 1829 1916  2958 2231 2746  3629 3393 5057
-//                4499 4848 8701 (8192)
-//   FP64         4110 2701 2089  4153 3225 2500  4716 4609 3555  6704 8037 6382
-//                8321 13116 10905 (8192)
-//   hydro        4203 921 654 553 (512)  1414 1078 1144 (1024)
-//                2675 1306 1222 1439 (2048)  2294 1619 1716 2288 (4096)
-//                2538 2452 2850 4125 (8192)  3883 4187 5118 7673 (16384)
-// With fewer groups than CUs the time is that of the slowest group, and the
-// widest team is up to 2 times faster than the next one.
+// density solve and hydro force of clustered sets):
+//   groups          256   512  1024  2048  3125  4096  8192  16384
+//   density    4   1568  2474  2474  2958  2950  3629  4499   6054
+//              8   1141  1646  1845  2352  2781  3331  4829   7097
+//             12    980  1392  1561  2113  2782  3412  5248   8075
+//             16    931  1644  1929  2744  4074  5107  8739  13926
+//   FP64       4   2876  4110  4153  4716  5727  6704  8321  11848
+//              8   1645  2701  3225  4609  6588  8037 13116  20989
+//             16   1220  2089  2500  3555  5230  6382 10905  17705
+//   hydro   none         4203        2675        2294  2538   3883
+//              4    642   921  1414  1306  1418  1619  2452   4187
+//              8    407   599  1023  1074  1333  1581  2665   4808
+//             16    336   515  1067  1352  1783  2184  3983   7377
+// With fewer groups than CUs the time is that of the slowest group, which the
+// widest team serves fastest; later the number of waves that a CU holds counts
+// (teams of 12 in 80 registers: 24, of 16 in 107: 16).
 int density_team(int64_t max_targets, int f64) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
   if (f64) return groups <= 4096 ? 16 : 4;
-  return groups <= 768 ? 16 : (groups <= 6144 ? 8 : 4);
+  return groups <= 320 ? 16 : (groups <= 3072 ? 12 : (groups <= 6144 ? 8 : 4));
 }
 int hydro_team(int64_t max_targets) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;

@@ -38,10 +38,11 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// A round holds 16 tiles: one or more of every wave of the team.
+// A round holds one or more tiles of every wave of the team, as many of each.
 template <int T>
 struct TeamLds {
-  static constexpr int kTiles = 16;
+  static constexpr int kTiles = T == 12 ? 24 : 16;
+  static_assert(kTiles % T == 0, "as many tiles for every wave");
   static constexpr int kRound = kTiles * kWave;
   int32_t cand[kRound];
   uint64_t wmask[kTermWindow];

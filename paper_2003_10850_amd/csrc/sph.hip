@@ -104,8 +104,8 @@ constexpr float kFineExt = 1.0f;
 // 2^20 gas particles of a clustered 2^21 box: 8.0 ms with a wave a group, 6.0
 // with teams of 4 (the solve's uneven passes and the uneven groups spread over
 // four waves; held to 6 waves a SIMD: 6.9 ms at the 4 that 120 registers
-// allow); 7.1 and 14 with teams of 8 and 16. 2^17: 2.9, 2.2 and 2.7 ms with
-// teams; 2^15 gas particles: 7.0, 2.5, 1.7 and 1.7 ms.
+// allow); 7.1, 8.1 and 14 with teams of 8, 12 and 16. 2^17: 2.9, 2.2, 2.1 and
+// 2.7 ms with teams; 2^15 gas particles: 7.0, 2.5, 1.7, 1.4 and 1.7 ms.
 template <bool kF64, int kT>
 __global__ __launch_bounds__(kBlockOf<kT>, kT < 16 && !kF64 ? 6 : 1) void k_density(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
@@ -910,9 +910,10 @@ hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_group
                           unsigned long long *counters, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
   auto kern = sp.f64 ? (sp.team == 16 ? k_density<true, 16> : k_density<true, 4>)
-                     : (sp.team == 16  ? k_density<false, 16>
-                        : sp.team == 8 ? k_density<false, 8>
-                                       : k_density<false, 4>);
+                     : (sp.team == 16   ? k_density<false, 16>
+                        : sp.team == 12 ? k_density<false, 12>
+                        : sp.team == 8  ? k_density<false, 8>
+                                        : k_density<false, 4>);
   const int block = sp.team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(
       gas.nodes, gas.xm, gas.x64, gas.perm, gs, tm, sp.n_ngb, sp.h_tol, solve_h, sp.max_iter,
