@@ -140,14 +140,14 @@ __global__ void k_hsolve_bwd_prep(const int32_t *__restrict__ active, int64_t n_
 // turn and the waves' totals are added in their order, so the gradients are
 // the same on every run. 1.25e5 members of ~295 neighbours: 2886 us with one
 // wave a group, 1179 with teams of 4, 1108 at 80 registers (6 waves a SIMD),
-// 930 with the coefficients formed once a particle.
+// 930 with the coefficients formed once a particle, 828 with teams of 8.
 struct DTile {
   float4 x[kTile];  // position, mass
   float4 b[kTile];  // fl(h^2) or -1, 1/h, f1, f2
   float2 w[kTile];  // w1, w2
 };
 template <int kT>
-__global__ __launch_bounds__(kT * kWave, kT == 4 ? 6 : 1) void k_density_bwd(
+__global__ __launch_bounds__(kT * kWave, kT < 16 ? 6 : 1) void k_density_bwd(
     const float4 *__restrict__ xm, const float4 *__restrict__ bw,
     const int32_t *__restrict__ perm, const Groups gs, const Terms tm,
     float *__restrict__ g_pos, float *__restrict__ g_mass, float *__restrict__ g_h) {
@@ -849,9 +849,9 @@ __global__ void k_hydro_bwd_up(const int32_t *__restrict__ active, int64_t n_act
 // Bound by VALU issue (a pair is ~150 operations); 125 registers, four waves
 // a SIMD. Teams and tiles as in the density's adjoint. 1.25e5 particles of
 // ~295 neighbours: 10671 us with one wave a group and the two terms of a pair
-// by themselves, 2210 so.
+// by themselves, 2210 with teams of 4, 2131 of 8.
 template <int kT>
-__global__ __launch_bounds__(kT * kWave, kT == 4 ? 4 : 1) void k_hydro_bwd(
+__global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
     const float4 *__restrict__ xm, const float4 *__restrict__ vh,
     const float4 *__restrict__ aux, const float4 *__restrict__ up,
     const int32_t *__restrict__ perm, const Groups gs, const Terms tm, float alpha, float gamma, const float *__restrict__ u, const float *__restrict__ omega,
@@ -1003,7 +1003,7 @@ hipError_t launch_hydro_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int team = adjoint_team(m);
-  auto kern = team == 16 ? k_hydro_bwd<16> : k_hydro_bwd<4>;
+  auto kern = team == 16 ? k_hydro_bwd<16> : (team == 8 ? k_hydro_bwd<8> : k_hydro_bwd<4>);
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
       gas.xm, gas.vh, gas.aux, up, gas.perm, all_gas, tm, alpha, gamma, u, omega, g_pos, g_vel,
@@ -1065,7 +1065,7 @@ static hipError_t density_bwd(const Octree &gas, const Groups &gs, int64_t max_g
                               const Terms &tm, const float4 *bw, float *g_pos, float *g_mass,
                               float *g_h, hipStream_t s) {
   const int team = adjoint_team(gas.n);
-  auto kern = team == 16 ? k_density_bwd<16> : k_density_bwd<4>;
+  auto kern = team == 16 ? k_density_bwd<16> : (team == 8 ? k_density_bwd<8> : k_density_bwd<4>);
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
       gas.xm, bw, gas.perm, gs, tm, g_pos, g_mass, g_h);

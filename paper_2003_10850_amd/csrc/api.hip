@@ -442,7 +442,7 @@ int density_team(int64_t max_targets, int f64) {
 }
 int hydro_team(int64_t max_targets) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
-  return groups <= 768 ? 16 : (groups <= 2560 ? 8 : (groups <= 12288 ? 4 : 1));
+  return groups <= 768 ? 16 : (groups <= 5120 ? 8 : (groups <= 12288 ? 4 : 1));
 }
 // Gravity (us, clustered sets of 2^11, 2^12 and 2^13 groups, teams of 4/16):
 // FP32 553/437, 817/902, 1321/1811; FP64 664/637, 1046/1315, 1843/2666.
@@ -454,20 +454,28 @@ int gravity_team(int64_t max_targets) {
 int gravity_bwd_team(int64_t max_targets) {
   return (max_targets + kWave - 1) / kWave <= 768 ? 16 : 4;
 }
-// The SPH adjoints, conduction and velocity gradients, as the density: us of
+// The SPH adjoints, conduction and velocity gradients, as the density (us of
 // one density solve and hydro force with their gradients, and of one pass of
-// the modules (viscosity, conduction, gradients), teams of 4/16:
-//   groups       256        512        1024       1536       2048       4096
-//   gradients    3032/2136  5011/3681  7902/6858  7408/7512  7555/8196
-//   modules                 1582/1001  3375/2960             3181/3553  3941/5200
+// the modules with the force: viscosity, conduction, gradients):
+//   groups          256   512  1024  1536  2048  3125  4096  8192
+//   adjoints   4   3286  4593  6618  6309  6688  7980  8855 13842
+//              8   2588  3863  5675  5615  6280  7854  9207 14956
+//             16   2338  3386  6040  6514  7523  9892 11837 20724
+//   modules    4   1607  2171  3180  2885  3076  3394  3746  5641
+//              8   1129  1568  2449  2440  2614  3103  3484  5546
+//             16    958  1412  2313  2358  2615  3254  3731  6279
 // Conduction's pair is so light that one wave a group wins again where
-// groups are plenty (us, 1/4: 3242/2748 of 8192 groups, 8181/9138 of 65536).
+// groups are plenty (us, 1/4: 3242/2748 of 8192 groups, 7779/9138 of 65536).
 int adjoint_team(int64_t members) {
-  return (members + kWave - 1) / kWave <= 1536 ? 16 : 4;
+  const int64_t groups = (members + kWave - 1) / kWave;
+  return groups <= 640 ? 16 : (groups <= 3072 ? 8 : 4);
 }
-int velgrad_team(int64_t max_targets) { return adjoint_team(max_targets); }
+int velgrad_team(int64_t max_targets) {
+  const int64_t groups = (max_targets + kWave - 1) / kWave;
+  return groups <= 1536 ? 16 : (groups <= 8192 ? 8 : 4);
+}
 int conduction_team(int64_t max_targets) {
-  return (max_targets + kWave - 1) / kWave <= 24576 ? adjoint_team(max_targets) : 1;
+  return (max_targets + kWave - 1) / kWave <= 24576 ? velgrad_team(max_targets) : 1;
 }
 
 unsigned persistent_grid(const void *kern, int block, int64_t max_groups, int team) {

@@ -45,14 +45,14 @@ struct CondTile {
 // tiles. kT = 1: a wave walks the octree (hmax refit from h) by itself, four
 // to a workgroup: the pair is light, so with groups to fill the chip the
 // team's search is what it gains back. What depends on j alone is formed once
-// a candidate. 2.5e5 targets: 1945 us with one wave a group, 1143 with teams;
+// a candidate. 2.5e5 targets: 1945 us with one wave a group, 985 with teams;
 // 4.2e6: 8181 before, 7779 with one wave now, 9138 with teams.
 template <int kT>
 constexpr int kWavesOf = kT > 1 ? kT : 4;
 struct NoLds {};
 
 template <int kT>
-__global__ __launch_bounds__(kWavesOf<kT> * kWave, kT < 16 ? 8 : 1) void k_conduction(
+__global__ __launch_bounds__(kWavesOf<kT> * kWave, 8) void k_conduction(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const float4 *__restrict__ ch, const int32_t *__restrict__ perm, const Groups gs,
     int walk_leaf, const Terms tm, float *__restrict__ dudt, int32_t *__restrict__ npairs) {
@@ -229,7 +229,10 @@ hipError_t launch_conduction(const Octree &gas, const Groups &gs, int64_t max_gr
                              int walk_leaf, const Terms &tm, int team, const float4 *ch,
                              float *dudt, int32_t *npairs, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = team == 16 ? k_conduction<16> : (team == 4 ? k_conduction<4> : k_conduction<1>);
+  auto kern = team == 16  ? k_conduction<16>
+              : team == 8 ? k_conduction<8>
+              : team == 4 ? k_conduction<4>
+                          : k_conduction<1>;
   const int block = (team > 1 ? team : 4) * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
       gas.nodes, gas.xm, ch, gas.perm, gs, walk_leaf, tm, dudt, npairs);

@@ -27,9 +27,9 @@ struct VelTile {
 // in LDS (after the group-box cull) are scanned by every lane with the exact
 // neighbour test; each wave keeps the totals of its own tiles. 64 registers
 // (8 waves a SIMD) are worth 5% where groups are plenty. 2.5e5 targets: 2024 us
-// with one wave a group, 837 so; 4.2e6: 8495 and 8133.
+// with one wave a group, 687 so; 4.2e6: 8495 and 8133.
 template <int kT>
-__global__ __launch_bounds__(kT * kWave, kT == 4 ? 8 : 1) void k_velgrad(
+__global__ __launch_bounds__(kT * kWave, 8) void k_velgrad(
     const float4 *__restrict__ xm, const float4 *__restrict__ vh,
     const int32_t *__restrict__ perm, const Groups gs, const Terms tm,
     const float *__restrict__ rho, const float *__restrict__ omega, float *__restrict__ div_v,
@@ -191,7 +191,7 @@ hipError_t launch_velgrad(const Octree &gas, const Groups &gs, int64_t max_group
                           const Terms &tm, int team, const float *rho, const float *omega,
                           float *div_v, float *curl_v, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = team == 16 ? k_velgrad<16> : k_velgrad<4>;
+  auto kern = team == 16 ? k_velgrad<16> : (team == 8 ? k_velgrad<8> : k_velgrad<4>);
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
       gas.xm, gas.vh, gas.perm, gs, tm, rho, omega, div_v, curl_v);

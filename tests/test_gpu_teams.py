@@ -161,12 +161,13 @@ def close(a, b, what):
     assert bool(((a - b).abs() <= lim).all()), what
 
 
-@pytest.mark.parametrize("m", [64, 641, 5000])
-def test_adjoints_of_a_forest_equal_the_single_trees(ctx, m):
-    # the forest's 10^5 members and more take teams of 4, the single snapshots
-    # (which other tests hold against the oracle) teams of 16
+@pytest.mark.parametrize("m,total", [(64, 125000), (641, 210000), (5000, 125000),
+                                     (5000, 210000)])
+def test_adjoints_of_a_forest_equal_the_single_trees(ctx, m, total):
+    # the forest's members take teams of 8 or 4, the single snapshots (which
+    # other tests hold against the oracle) teams of 16
     from paper_2003_10850_amd import ops
-    count = -(-125000 // m)
+    count = -(-total // m)
     some = 25
     print(f"teams adjoint forest {count} x {m}", flush=True)
     p = inputs.Params(n_ngb=48.0)
@@ -195,10 +196,10 @@ def test_adjoints_of_a_forest_equal_the_single_trees(ctx, m):
             close(a[r], b, (int(k), i))
 
 
-@pytest.mark.parametrize("log_few", [10, 15, 19])
+@pytest.mark.parametrize("log_few", [10, 15, 18, 20])
 def test_conduction_and_gradients_of_every_team_size(ctx, log_few):
     # 1.6e6 targets: conduction without teams, gradients in teams of 4; the
-    # first 2^19 in teams of 4, fewer in teams of 16
+    # first 2^20 in teams of 4, 2^18 of 8, fewer of 16
     from paper_2003_10850_amd import g3, ops
     n = 1600000
     w = inputs.uniform(n=n, seed=21)
