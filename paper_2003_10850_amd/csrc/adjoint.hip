@@ -466,9 +466,9 @@ __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
 // the matrix cores, one-hot rows times the values, came to 4.8 ms, the FP32
 // products do not overlap), 3 the fixed-point conversion of 16 entries at
 // once; the atomics cost 0.3 ms. 5e5 targets of a clustered box: 3.95 ms with
-// one wave a group, 3.6 with teams of 4; 2^14 targets: 1.5 and 0.25.
+// one wave a group, 3.6 with teams of 4; 2^14 targets: 1.5 and 0.25 of 16.
 template <bool kFixed, bool kInside, int kT>
-__global__ __launch_bounds__(kT * kWave, kT == 4 ? 6 : 1) void k_gravity_bwd(
+__global__ __launch_bounds__(kT * kWave, kT < 16 ? 6 : 1) void k_gravity_bwd(
     const CNode *__restrict__ cnodes, const uint64_t *__restrict__ ckeys,
     const float4 *__restrict__ xm, const uint64_t *__restrict__ keys, const int32_t *__restrict__ perm, const Groups gs,
     float theta2, float eps2, float G, const float *__restrict__ g_acc,
@@ -1024,6 +1024,7 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
   auto pick = [&](auto fixed_c) {
     constexpr bool f = decltype(fixed_c)::value;
     if (gp.team == 16) return gp.inside_test ? k_gravity_bwd<f, true, 16> : k_gravity_bwd<f, false, 16>;
+    if (gp.team == 8) return gp.inside_test ? k_gravity_bwd<f, true, 8> : k_gravity_bwd<f, false, 8>;
     return gp.inside_test ? k_gravity_bwd<f, true, 4> : k_gravity_bwd<f, false, 4>;
   };
   const int block = gp.team * kWave;

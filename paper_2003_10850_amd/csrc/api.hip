@@ -444,15 +444,24 @@ int hydro_team(int64_t max_targets) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
   return groups <= 768 ? 16 : (groups <= 5120 ? 8 : (groups <= 12288 ? 4 : 1));
 }
-// Gravity (us, clustered sets of 2^11, 2^12 and 2^13 groups, teams of 4/16):
-// FP32 553/437, 817/902, 1321/1811; FP64 664/637, 1046/1315, 1843/2666.
+// Gravity and its adjoint with it (us, clustered sets):
+//   groups           64   256   512  1024  2048  3125  4096  8192  16384  32768
+//   FP32        4   158   197   209   307   565   717   819  1329   2282   4320
+//               8    99   121   155   273   421   535   678  1201   2243   4353
+//              16    77    90   131   212   352   520   661  1280   2496   5000
+//   FP64        4   216   282   307   384   694   936  1067  1830   3335   6496
+//               8   129   166   203   324   531   748   910  1708   3294   6524
+//              16    94   117   171   275   479   733   925  1816   3583   7316
+//   adjoint     4   555   705   794  1026  1681  2311  2827  4989   9388  18506
+//               8   378   463   604   946  1509  2196  2799  5276  10461  20989
+//              16   300   362   575   966  1708  2587  3362  6696  13502  27879
 int gravity_team(int64_t max_targets) {
-  return (max_targets + kWave - 1) / kWave <= 2560 ? 16 : 4;
+  const int64_t groups = (max_targets + kWave - 1) / kWave;
+  return groups <= 3584 ? 16 : (groups <= 20480 ? 8 : 4);
 }
-// Its adjoint (us with the forward pass, teams of 4/16): 586/358 of 256 groups,
-// 942/983 of 1024, 1551/1774 of 2048, 4709/6357 of 7812.
 int gravity_bwd_team(int64_t max_targets) {
-  return (max_targets + kWave - 1) / kWave <= 768 ? 16 : 4;
+  const int64_t groups = (max_targets + kWave - 1) / kWave;
+  return groups <= 768 ? 16 : (groups <= 4096 ? 8 : 4);
 }
 // The SPH adjoints, conduction and velocity gradients, as the density (us of
 // one density solve and hydro force with their gradients, and of one pass of

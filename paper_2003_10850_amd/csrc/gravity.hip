@@ -43,12 +43,14 @@ __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
 // the FP32 test could disagree with the FP64 one, the FP64 test decides.
 // The waves of a workgroup share a group: they take its items in rounds, item
 // j of a round by wave j % kT, and the items that these open follow in the
-// order of their parents, so the sums do not depend on timing. All particles
-// of a clustered 2^21 box: 6.5 ms with the preorder walk of one wave a group,
-// 4.9 with the items of one wave, 4.3 with teams of 4, 7.5 with teams of 16;
-// of 2^12 particles: 0.50, 0.38, 0.15 and 0.07 ms.
+// order of their parents, so the sums do not depend on timing. Held to 64
+// registers, 8 waves a SIMD: two teams of 16 share a CU (352 us for 2^17
+// particles of a clustered box, 451 at 4 waves a SIMD). All particles of a
+// clustered 2^21 box: 6.5 ms with the preorder walk of one wave a group, 4.9
+// with the items of one wave, 4.3 with teams of 4 or 8, 5.0 with teams of 16;
+// of 2^12 particles: 0.50, 0.38, 0.16, 0.10 and 0.08 ms.
 template <bool kF64, bool kInside, int kT>
-__global__ __launch_bounds__(kT * kWave, kT > 4 ? 4 : 8) void k_gravity(
+__global__ __launch_bounds__(kT * kWave, 8) void k_gravity(
     const CNode *__restrict__ cnodes, const uint64_t *__restrict__ ckeys,
     const double4 *__restrict__ cc64, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const uint64_t *__restrict__ keys,
@@ -248,8 +250,9 @@ hipError_t launch_gravity(const Octree &all, const Groups &gs, int64_t max_group
     return gp.f64 ? k_gravity<true, false, kT>
                   : (gp.inside_test ? k_gravity<false, true, kT> : k_gravity<false, false, kT>);
   };
-  auto kern = gp.team == 16 ? pick(std::integral_constant<int, 16>{})
-                            : pick(std::integral_constant<int, 4>{});
+  auto kern = gp.team == 16  ? pick(std::integral_constant<int, 16>{})
+              : gp.team == 8 ? pick(std::integral_constant<int, 8>{})
+                             : pick(std::integral_constant<int, 4>{});
   const int block = gp.team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, gp.team), block, 0, s>>>(
       all.cnodes, all.ckeys, all.cc64, all.xm, all.x64, all.keys, all.perm, gs, gp.theta2,

@@ -82,14 +82,15 @@ def test_active_sets_on_both_sides_of_the_team_rule(ctx, n_act):
     check(tree, t, p, dev_t(act), rows)
 
 
-@pytest.mark.parametrize("theta,eps", [(0.5, 1e-2), (0.7, 1e-2), (0.5, 0.0)])
-def test_adjoint_of_all_is_the_sum_of_the_halves(theta, eps):
-    # linear in the upstream gradients; 6e4 targets take teams of 4, the halves
-    # (as the small sets that other tests hold against the oracle) teams of 16.
+@pytest.mark.parametrize("n,theta,eps", [(60000, 0.5, 1e-2), (60000, 0.7, 1e-2),
+                                         (60000, 0.5, 0.0), (300000, 0.7, 1e-2)])
+def test_adjoint_of_all_is_the_sum_of_the_halves(n, theta, eps):
+    # linear in the upstream gradients; 6e4 targets take teams of 8, their halves
+    # (as the small sets that other tests hold against the oracle) teams of 16;
+    # 3e5 targets teams of 4, their halves of 8.
     # Per source the FP32 sums over 64 targets are the same or regrouped: one
     # rounding of 64 terms' sum each, 6e-8 x 64 of the largest at the worst
     from paper_2003_10850_amd import ops
-    n = 60000
     w = inputs.uniform(n=n, seed=4)
     p = inputs.Params(theta=theta, eps=eps)
     c = ops.Context(torch.device("cuda", 0))
@@ -111,3 +112,26 @@ def test_adjoint_of_all_is_the_sum_of_the_halves(theta, eps):
     for a, b, d in zip(grads(None), grads(ids[: n // 2]), grads(ids[n // 2:])):
         b = b.double() + d.double()
         assert float((a.double() - b).abs().max()) <= 4e-6 * float(b.abs().max())
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("n,theta", [(300000, 0.5), (300000, 0.7), (1400000, 0.5)])
+def test_larger_sets_take_smaller_teams_with_the_same_terms(n, theta, fp64):
+    # 3e5 targets take teams of 8, 1.4e6 of 4; a few thousand of them (as the
+    # sets that other tests hold against the oracle) teams of 16. The same
+    # terms, in sums of 64 that are cut elsewhere: 64 roundings of a partial
+    # sum at the worst, of terms that mostly point one way
+    from paper_2003_10850_amd import ops
+    w = inputs.uniform(n=n, seed=6)
+    p = inputs.Params(theta=theta, eps=1e-3)
+    c = ops.Context(torch.device("cuda", 0))
+    pos = torch.from_numpy(w.pos if fp64 else w.pos.astype(np.float32)).to("cuda:0")
+    mass = torch.from_numpy(w.mass.astype(np.float32)).to("cuda:0")
+    tree = ops.Tree(c, pos, mass, None, tuple(w.box), p)
+    few = torch.arange(0, n, n // 5000, dtype=torch.int32, device="cuda")
+    a, b = ops.gravity(tree), ops.gravity(tree, active=few)
+    at = few.long()
+    assert torch.equal(a["nterms"][at], b["nterms"][at])
+    for k in ("acc", "pot"):
+        x, y = a[k][at].double(), b[k][at].double()
+        assert float((x - y).abs().max()) <= 4e-6 * float(y.abs().max()), k
