@@ -428,10 +428,13 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
 //   FP64       4   2876  4110  4153  4716  5727  6704  8321  11848
 //              8   1645  2701  3225  4609  6588  8037 13116  20989
 //             16   1220  2089  2500  3555  5230  6382 10905  17705
-//   hydro   none         4203        2675        2294  2538   3883
-//              4    642   921  1414  1306  1418  1619  2452   4187
-//              8    407   599  1023  1074  1333  1581  2665   4808
-//             16    336   515  1067  1352  1783  2184  3983   7377
+//   hydro   none         4203        2675        2294  2440   3610
+//              8    399   608   955   980  1182  1346  2133   3781
+//             12    337   501   815   930  1170  1380  2320   4182
+//             16    340   513  1071  1350  1790  2186  3978   7374
+//   FP64       4    776  1126  1642  1595  1711  1971  2844   4942
+//              8    472   703  1222  1327  1626  1933  3187   5741
+//             16    406   621  1305  1667  2177  2673  4843   8964
 // With fewer groups than CUs the time is that of the slowest group, which the
 // widest team serves fastest; later the number of waves that a CU holds counts
 // (teams of 12 in 80 registers: 24, of 16 in 107: 16).
@@ -440,9 +443,13 @@ int density_team(int64_t max_targets, int f64) {
   if (f64) return groups <= 4096 ? 16 : 4;
   return groups <= 320 ? 16 : (groups <= 3072 ? 12 : (groups <= 6144 ? 8 : 4));
 }
-int hydro_team(int64_t max_targets) {
+// (wide: FP64 positions or the switches' inputs, whose LDS and registers hold
+// fewer waves a CU)
+int hydro_team(int64_t max_targets, bool wide) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
-  return groups <= 768 ? 16 : (groups <= 5120 ? 8 : (groups <= 12288 ? 4 : 1));
+  if (groups > 12288) return 1;
+  if (wide) return groups <= 768 ? 16 : (groups <= 3072 ? 8 : 4);
+  return groups <= 320 ? 16 : (groups <= 3072 ? 12 : 8);
 }
 // Gravity and its adjoint with it (us, clustered sets):
 //   groups           64   256   512  1024  2048  3125  4096  8192  16384  32768
@@ -1075,7 +1082,7 @@ int g3_hydro_force(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active,
   Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneHydro, active ? std::min<int64_t>(n_act, o.n) : o.n);
   SphParams sp = sph_params(c, p, t, tu);
-  sp.team = hydro_team(active ? std::min<int64_t>(n_act, o.n) : o.n);
+  sp.team = hydro_team(active ? std::min<int64_t>(n_act, o.n) : o.n, t->f64);
   st = ensure_h64(c, t, o);
   if (st) return st;
   TermBufs tb;
@@ -1270,7 +1277,7 @@ int g3_hydro_force_switches(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t 
   Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneHydro, active ? std::min<int64_t>(n_act, o.n) : o.n);
   SphParams sp = sph_params(c, p, t, tu);
-  sp.team = hydro_team(active ? std::min<int64_t>(n_act, o.n) : o.n);
+  sp.team = hydro_team(active ? std::min<int64_t>(n_act, o.n) : o.n, true);
   st = ensure_h64(c, t, o);
   if (st) return st;
   TermBufs tb;
@@ -1386,7 +1393,7 @@ static int tick_forces(g3_ctx *c, g3_tree *t, int64_t n, const g3_state *st,
     }
     const Tuning th = tuning_for(c, kTuneHydro, gas.n);
     SphParams sp = sph_params(c, p, t, th);
-    sp.team = hydro_team(gas.n);
+    sp.team = hydro_team(gas.n, t->f64);
     e = launch_hydro_prep(gas, vh, uh, st->h, st->rho, st->omega, sp.gamma, t->f64, s);
     if (e == hipSuccess) e = sph_radii(t, gas, sp, tb, s);
     if (e != hipSuccess) return hip_fail(c, e, "hydro prep at a tick");
@@ -1653,7 +1660,7 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
   };
   Octree &gas = t->gas;
   const int64_t ng = active ? std::min<int64_t>(n_act, gas.n) : gas.n;
-  const int team = hydro_team(ng);
+  const int team = hydro_team(ng, t->f64);
   TermBufs tb;
   if (gas.n > 0 && !reserve_terms(c, gas, t->n_snap, &tb))
     return finish(fail(c, G3_ENOMEM, "g3_autotune: allocation failed"));

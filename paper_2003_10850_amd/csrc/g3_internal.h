@@ -295,10 +295,10 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
                        hipStream_t s);
 
 // Waves of the team that serves one group, from the (host-side bound on the)
-// number of targets: 4, 8 or 16, for the density also 12, for the hydro force
-// and conduction also 1 (no team).
+// number of targets: 4, 8, 12 or 16, for the hydro force and conduction also 1 (no
+// team).
 int density_team(int64_t max_targets, int f64);
-int hydro_team(int64_t max_targets);
+int hydro_team(int64_t max_targets, bool wide);
 int gravity_team(int64_t max_targets);
 int gravity_bwd_team(int64_t max_targets);
 int adjoint_team(int64_t members);  // SPH adjoints: every gas member is a target

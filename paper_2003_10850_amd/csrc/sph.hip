@@ -554,16 +554,17 @@ struct ExtTile {
 // kExt: the improved-SPH switches (per-particle viscosity strengths and
 // Balsara factors, artificial conduction of strength alpha_u) from ext.
 // kT > 1: a team serves a group, as in the density; else a wave walks the
-// octree itself. 2^20 gas particles of the clustered 2^21 box: 3.8 ms with a
-// wave a group, 4.1 with teams of 4 (their LDS holds 4 waves a SIMD, not 6),
-// 5.1 and 7.7 with 8 and 16; 2^15 gas particles: 2.9, 0.92, 0.65 and 0.55 ms.
+// octree itself. 2^20 gas particles of the clustered 2^21 box: 3.6 ms with a
+// wave a group, 3.8 with teams of 8 and 4.2 of 12 (both held to 80 registers: 24
+// waves a CU), 7.4 with 16 (93 registers, 16 waves a CU); 2^17: 0.98, 0.93 and
+// 1.35 ms with teams; 2^15: 2.9, 0.61, 0.50 and 0.51 ms.
 // The test reads one float4 an entry, four entries a step, and what depends
 // on the entry alone comes with it: 3.6 ms of the 3.75 that two float4 an entry
 // and the entry's h^-5 in every pair took, 1.53 of 1.66 with the switches at
 // 2.5e5 targets. Bound by vector
 // issue on a full chip, by the slowest groups otherwise.
 template <bool kF64, bool kExt, int kT>
-__global__ __launch_bounds__(kBlockOf<kT>, kT == 1 && !kF64 && !kExt ? 6 : 1) void k_hydro(
+__global__ __launch_bounds__(kBlockOf<kT>, !kF64 && !kExt && kT < 16 ? 6 : 1) void k_hydro(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const double *__restrict__ h64,
     const float4 *__restrict__ vh, const float4 *__restrict__ aux,
@@ -946,10 +947,16 @@ hipError_t launch_hydro(const Octree &gas, const Groups &gs, int64_t max_groups,
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
   auto pick = [&](auto f64_c, auto ext_c) {
     constexpr bool f = decltype(f64_c)::value, e = decltype(ext_c)::value;
-    return sp.team == 16  ? k_hydro<f, e, 16>
-           : sp.team == 8 ? k_hydro<f, e, 8>
-           : sp.team == 4 ? k_hydro<f, e, 4>
-                          : k_hydro<f, e, 1>;
+    if constexpr (!f && !e)
+      return sp.team == 16   ? k_hydro<f, e, 16>
+             : sp.team == 12 ? k_hydro<f, e, 12>
+             : sp.team == 8  ? k_hydro<f, e, 8>
+                             : k_hydro<f, e, 1>;
+    else
+      return sp.team == 16  ? k_hydro<f, e, 16>
+             : sp.team == 8 ? k_hydro<f, e, 8>
+             : sp.team == 4 ? k_hydro<f, e, 4>
+                            : k_hydro<f, e, 1>;
   };
   const std::true_type yes;
   const std::false_type no;

@@ -130,7 +130,7 @@ def test_every_team_size_gives_the_same_bits(ctx, fp64):
 @pytest.mark.parametrize("log_few", [14, 16, 17, 18])
 def test_middle_team_sizes_give_the_same_bits(ctx, log_few):
     # 2^20 targets: density in teams of 4, hydro force without; the first 2^18
-    # in tree order take teams of 8 and 4, 2^17 and 2^16 of 12 and 8, 2^14 of 16
+    # in tree order take teams of 8, 2^17 and 2^16 of 12, 2^14 of 16
     from paper_2003_10850_amd import g3, ops
     n = 1 << 20
     w = inputs.uniform(n=n, seed=22)
