@@ -425,9 +425,9 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
 //              8   1141  1646  1845  2352  2781  3331  4829   7097
 //             12    980  1392  1561  2113  2782  3412  5248   8075
 //             16    931  1644  1929  2744  4074  5107  8739  13926
-//   FP64       4   2876  4110  4153  4716  5727  6704  8321  11848
-//              8   1645  2701  3225  4609  6588  8037 13116  20989
-//             16   1220  2089  2500  3555  5230  6382 10905  17705
+//   FP64       4   2978  4268  4306  4402  4910  5835  6173   8006
+//              8   1702  2458  2684  3443  4458  5292  7784  11795
+//             16   1214  2064  2511  3567  5242  6375 10907  17699
 //   hydro   none         4203        2675        2294  2440   3610
 //              8    399   608   955   980  1182  1346  2133   3781
 //             12    337   501   815   930  1170  1380  2320   4182
@@ -440,7 +440,7 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
 // (teams of 12 in 80 registers: 24, of 16 in 107: 16).
 int density_team(int64_t max_targets, int f64) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
-  if (f64) return groups <= 4096 ? 16 : 4;
+  if (f64) return groups <= 1280 ? 16 : (groups <= 4608 ? 8 : 4);
   return groups <= 320 ? 16 : (groups <= 3072 ? 12 : (groups <= 6144 ? 8 : 4));
 }
 // (wide: FP64 positions or the switches' inputs, whose LDS and registers hold

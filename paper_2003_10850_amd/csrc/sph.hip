@@ -23,6 +23,14 @@ constexpr int kTile = kWave;
 template <int kT>
 constexpr int kBlockOf = (kT > 1 ? kT : 4) * kWave;
 struct NoLds {};
+// Waves a SIMD that the registers are held to (1: as the compiler likes). The
+// density with FP64 positions: 137 registers hold 3; 11.8 ms for the 2^20 gas
+// particles of a clustered 2^21 box, 9.7, 8.7 and 8.0 held to 4, 5 and 6, though
+// some are spilled around the passes.
+template <bool kF64, int kT>
+constexpr int kDensityWaves = kT == 16 ? 1 : (kF64 && kT == 8 ? 4 : 6);
+template <bool kF64, bool kExt, int kT>
+constexpr int kHydroWaves = kExt ? 1 : (!kF64 && kT < 16 ? 6 : (kF64 && kT == 1 ? 5 : 1));
 
 // Wendland C6 in 3D, support radius h: W = C/h^3 w(q),
 // w(q) = (1-q)^8 (1 + 8q + 25q^2 + 32q^3); h dW/dh = C/h^3 wh(q),
@@ -107,7 +115,7 @@ constexpr float kFineExt = 1.0f;
 // allow); 7.1, 8.1 and 14 with teams of 8, 12 and 16. 2^17: 2.9, 2.2, 2.1 and
 // 2.7 ms with teams; 2^15 gas particles: 7.0, 2.5, 1.7, 1.4 and 1.7 ms.
 template <bool kF64, int kT>
-__global__ __launch_bounds__(kBlockOf<kT>, kT < 16 && !kF64 ? 6 : 1) void k_density(
+__global__ __launch_bounds__(kBlockOf<kT>, (kDensityWaves<kF64, kT>)) void k_density(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const int32_t *__restrict__ perm, const Groups gs,
     const Terms tm, float n_ngb, float tol, int solve, int max_iter, int walk_leaf,
@@ -564,7 +572,7 @@ struct ExtTile {
 // 2.5e5 targets. Bound by vector
 // issue on a full chip, by the slowest groups otherwise.
 template <bool kF64, bool kExt, int kT>
-__global__ __launch_bounds__(kBlockOf<kT>, !kF64 && !kExt && kT < 16 ? 6 : 1) void k_hydro(
+__global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k_hydro(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const double *__restrict__ h64,
     const float4 *__restrict__ vh, const float4 *__restrict__ aux,
@@ -910,7 +918,9 @@ hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_group
                           float *drho_dh, float *omega, int32_t *nngb,
                           unsigned long long *counters, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = sp.f64 ? (sp.team == 16 ? k_density<true, 16> : k_density<true, 4>)
+  auto kern = sp.f64 ? (sp.team == 16  ? k_density<true, 16>
+                        : sp.team == 8 ? k_density<true, 8>
+                                       : k_density<true, 4>)
                      : (sp.team == 16   ? k_density<false, 16>
                         : sp.team == 12 ? k_density<false, 12>
                         : sp.team == 8  ? k_density<false, 8>

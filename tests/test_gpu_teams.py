@@ -127,10 +127,12 @@ def test_every_team_size_gives_the_same_bits(ctx, fp64):
 
 
 
-@pytest.mark.parametrize("log_few", [14, 16, 17, 18])
-def test_middle_team_sizes_give_the_same_bits(ctx, log_few):
+@pytest.mark.parametrize("log_few,fp64", [(14, False), (16, False), (17, False), (18, False),
+                                          (14, True), (17, True)])
+def test_middle_team_sizes_give_the_same_bits(ctx, log_few, fp64):
     # 2^20 targets: density in teams of 4, hydro force without; the first 2^18
-    # in tree order take teams of 8, 2^17 and 2^16 of 12, 2^14 of 16
+    # in tree order take teams of 8, 2^17 and 2^16 of 12, 2^14 of 16 (with FP64
+    # positions 2^17 take teams of 8)
     from paper_2003_10850_amd import g3, ops
     n = 1 << 20
     w = inputs.uniform(n=n, seed=22)
@@ -138,12 +140,12 @@ def test_middle_team_sizes_give_the_same_bits(ctx, log_few):
     c = ops.Context(torch.device("cuda", 0))
     for kind in (g3.G3_TUNE_DENSITY, g3.G3_TUNE_HYDRO):
         c.set_tuning(kind, 128, -1)
-    tree = ops.Tree(c, dev_t(w.pos.astype(np.float32)), dev_t(w.mass.astype(np.float32)), None,
+    tree = ops.Tree(c, dev_t(w.pos if fp64 else w.pos.astype(np.float32)), dev_t(w.mass.astype(np.float32)), None,
                     tuple(w.box), p)
     few = torch.sort(tree.export(1)["order"][: 1 << log_few]).values
     g = torch.Generator(device="cuda").manual_seed(2)
     R = lambda *s: torch.rand(*s, generator=g, device="cuda")
-    h = 2.25 * n ** (-1.0 / 3.0) * (0.8 + 0.4 * R(n))
+    h = (2.25 * n ** (-1.0 / 3.0) * (0.8 + 0.4 * R(n))).to(torch.float64 if fp64 else torch.float32)
     vel, u, rho, om = R(n, 3) - 0.5, 0.5 + R(n), 0.5 + R(n), 0.5 + R(n)
     at = few.long()
     for a, b in ((ops.density(tree, h=h), ops.density(tree, h=h, active=few)),
