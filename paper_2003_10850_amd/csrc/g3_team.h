@@ -23,6 +23,12 @@
 namespace g3 {
 
 constexpr int kTermWindow = 64;
+// Up to this many accepted terminals of a window are written one after another
+// by the whole wave (about 30 instructions each), more by a lane each (about 5
+// instructions a member of the largest). Only the first form: 2670 us for a
+// forest of 40 snapshots, 6000 for density and force with gradients at 1.25e5
+// particles; 2550 and 5740 with both (lines of 10 to 32 within 1 %).
+constexpr int kFewTerms = 16;
 
 // Squared distance of two boxes with the rounding steps of box_dist2: never
 // larger than box_dist2 of a point inside [a_lo, a_hi].
@@ -110,6 +116,10 @@ __device__ __forceinline__ void team_search(const Terms &tm, int snap, TeamLds<T
     const uint64_t M = __ballot(maybe);
     if (M == 0ull) continue;
     const int nw = __popcll(M);
+    // the wave's first window stays in registers: its accepted terminals, a
+    // lane's first member, count and the members up to and with it
+    uint64_t acc0 = 0ull;
+    int st0 = 0, cnt0 = 0, inc0 = 0;
     {
       uint64_t mm = M;
       for (int k = 0; k < w; ++k) mm &= mm - 1ull;  // (0 stays 0)
@@ -136,7 +146,14 @@ __device__ __forceinline__ void team_search(const Terms &tm, int snap, TeamLds<T
           if (__ballot(box_dist2(xi, bl, bh) < reach2(want2, bl.w)) != 0ull) acc |= 1ull << b;
         }
         const int mine = ((acc >> lane) & 1ull) ? cnt : 0;
-        const int tot = __shfl(wave_incl_sum(mine, lane), kWave - 1, kWave);
+        const int inc = wave_incl_sum(mine, lane);
+        const int tot = __builtin_amdgcn_readlane(inc, kWave - 1);
+        if (k == w) {
+          acc0 = acc;
+          st0 = __float_as_int(hi.w);
+          cnt0 = mine;
+          inc0 = inc;
+        }
         if (lane == 0) {
           S.wmask[k] = acc;
           S.wid[k] = win;
@@ -154,14 +171,26 @@ __device__ __forceinline__ void team_search(const Terms &tm, int snap, TeamLds<T
       for (int k = w; k < nw; k += T) {
         const int kc = __shfl(wc, k, kWave), p1 = tc + __shfl(winc, k, kWave), p0 = p1 - kc;
         if (kc == 0 || p0 >= r0 + kRound || p1 <= r0) continue;
-        const uint64_t acc = S.wmask[k];
-        const int t = S.wid[k] * kTermWindow + lane;
-        int st = 0, cnt = 0;
-        if ((acc >> lane) & 1ull) {
-          st = __float_as_int(tm.hi[t].w);
-          cnt = __float_as_int(tm.hi[t + 1].w) - st;
+        uint64_t acc = acc0;
+        int st = st0, cnt = cnt0, inc = inc0;
+        if (k != w) {
+          acc = S.wmask[k];
+          const int t = S.wid[k] * kTermWindow + lane;
+          st = cnt = 0;
+          if ((acc >> lane) & 1ull) {
+            st = __float_as_int(tm.hi[t].w);
+            cnt = __float_as_int(tm.hi[t + 1].w) - st;
+          }
+          inc = wave_incl_sum(cnt, lane);
         }
-        const int at = p0 + wave_incl_sum(cnt, lane) - cnt - r0;  // position in the round
+        const int at = p0 + inc - cnt - r0;  // position in the round
+        if (__popcll(acc) > kFewTerms) {
+          // a lane writes the members of its terminal
+          const int i0 = max(0, -at), i1 = min(cnt, kRound - at);
+          for (int i = i0; __ballot(i < i1) != 0ull; ++i)
+            if (i < i1) S.cand[at + i] = st + i;
+          continue;
+        }
         uint64_t left = acc;
         while (left) {
           const int b = (int)__builtin_ctzll(left);
