@@ -199,7 +199,8 @@ __global__ __launch_bounds__(kWavesOf<kT> * kWave, 8) void k_conduction(
       sum[0] = du;
       cmp[0] = cdu;
     }
-    const float total = (sum[0] + cmp[0]) * (0.5f * kWendlandF * rinvi);
+    // (a target without a pair at r > 0 has none also where its rho is 0)
+    const float v = sum[0] + cmp[0], total = v == 0.0f ? v : v * (0.5f * kWendlandF * rinvi);
     if (valid && (kT == 1 || w == 0)) {
       const int cid = perm[s];
       if (dudt) dudt[cid] = total;

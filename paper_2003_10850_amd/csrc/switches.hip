@@ -135,12 +135,18 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_velgrad(
     team_totals<kT, 4, sizeof(VelTile) / 4>((float *)tiles, w, lane, sum, cmp);
     if (valid && w == 0) {
       const int cid = perm[s];
-      const float norm = fi5 / (omega[cid] * rho[cid]);
-      if (div_v) div_v[cid] = (sum[0] + cmp[0]) * norm;
+      const float norm = 1.0f / (omega[cid] * rho[cid]);
+      // (a target without a neighbour has no gradient also where h^-5 overflows)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float v = sum[k] + cmp[k];
+        sum[k] = (v == 0.0f ? v : v * fi5) * norm;
+      }
+      if (div_v) div_v[cid] = sum[0];
       if (curl_v) {
-        curl_v[3 * cid] = (sum[1] + cmp[1]) * norm;
-        curl_v[3 * cid + 1] = (sum[2] + cmp[2]) * norm;
-        curl_v[3 * cid + 2] = (sum[3] + cmp[3]) * norm;
+        curl_v[3 * cid] = sum[1];
+        curl_v[3 * cid + 1] = sum[2];
+        curl_v[3 * cid + 2] = sum[3];
       }
     }
   }  // groups

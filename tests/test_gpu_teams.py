@@ -223,3 +223,19 @@ def test_conduction_and_gradients_of_every_team_size(ctx, log_few):
     a, b = [ops.velocity_gradients(tree, vel, h, rho, om, active=x) for x in (None, few)]
     for k in a:
         close(a[k][at], b[k][at], k)
+
+
+def test_targets_without_neighbours_have_no_rates(ctx):
+    # h = 0, h whose h^-5 overflows, and rho = 0 where no pair is at r > 0
+    from paper_2003_10850_amd import ops
+    n = 200
+    g = torch.Generator(device="cuda").manual_seed(5)
+    pos, one = torch.rand(n, 3, generator=g, device="cuda"), torch.ones(n, device="cuda")
+    tree = ops.Tree(ctx, pos, one, None, (0.0, 0.0, 0.0, 1.0), inputs.Params(n_ngb=16.0))
+    h = torch.full((n,), 1e-9, device="cuda")
+    h[::3] = 0.0
+    rho = one.clone()
+    c = ops.conduction(tree, one, h, torch.zeros(n, device="cuda"), 1.0, 0.0)
+    assert torch.equal(c["dudt"], torch.zeros(n, device="cuda"))
+    v = ops.velocity_gradients(tree, pos.clone(), h, rho, one)
+    assert not v["div"].any() and not v["curl"].any()
