@@ -781,8 +781,8 @@ struct HSide {
 // second term's position and velocity partials take the sign of its neighbour
 // side.
 __device__ __forceinline__ void hydro_pair_adjoint(const HSide &P, const HSide &Q, float alpha,
-                                                   bool q_on, float dx, float dy, float dz,
-                                                   float r2, float *d) {
+                                                   bool p_on, bool q_on, float dx, float dy,
+                                                   float dz, float r2, float *d) {
   const float rinv = __builtin_amdgcn_rsqf(r2), r = r2 * rinv;
   const float vxx = P.vh.x - Q.vh.x, vyy = P.vh.y - Q.vh.y, vzz = P.vh.z - Q.vh.z;
   const float vx = vxx * dx + vyy * dy + vzz * dz;
@@ -811,9 +811,12 @@ __device__ __forceinline__ void hydro_pair_adjoint(const HSide &P, const HSide &
   const float dgp = P.aux.x * (ep - mp * sq) + hb;
   const float dgq = Q.aux.x * (eq - mq * sp) + hb;
   const float dPw = dPi * Pw;
-  const float Lvx = mq * P.up.w * (Tp + 0.5f * V) + mp * Q.up.w * (Tq + 0.5f * V) + dPw * rinv;
+  // (a side without upstream gradients adds nothing, not 0 times its factors)
+  const float tp = p_on ? mq * P.up.w * (Tp + 0.5f * V) : 0.0f;
+  const float tq = q_on ? mp * Q.up.w * (Tq + 0.5f * V) : 0.0f;
+  const float Lvx = tp + tq + dPw * rinv;
   const float lr = (dgp * gpr + dgq * gqr - dPw * w * rinv) * rinv;
-  const float cp = -mq * K, cq = mp * K;
+  const float cp = p_on ? -mq * K : 0.0f, cq = q_on ? mp * K : 0.0f;
   d[0] += cp * P.up.x + cq * Q.up.x + Lvx * vxx + lr * dx;
   d[1] += cp * P.up.y + cq * Q.up.y + Lvx * vyy + lr * dy;
   d[2] += cp * P.up.z + cq * Q.up.z + Lvx * vzz + lr * dz;
@@ -823,8 +826,7 @@ __device__ __forceinline__ void hydro_pair_adjoint(const HSide &P, const HSide &
   d[6] += dgp * gph;
   d[7] += gp * (ep - mp * sq);
   d[8] += dPi * Pc;
-  d[9] -= dPi * Pi * rs;
-  // (only a target's neighbour is owed a mass partial: not 0 times its factors)
+  d[9] -= neg ? dPi * Pi * rs : 0.0f;
   if (q_on) d[10] += vq * (Tq + 0.5f * V) - K * sq;
 }
 
@@ -940,7 +942,7 @@ __global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
         const float r2 = dist2_exact(dx, dy, dz);
         const bool in = valid && r2 < sq_exact(fmaxf(hp, Q.vh.w)) && r2 > 0.0f;
         const bool q_on = Q.up.x != 0.f || Q.up.y != 0.f || Q.up.z != 0.f || Q.up.w != 0.f;
-        if (in && (p_on || q_on)) hydro_pair_adjoint(P, Q, alpha, q_on, -dx, -dy, -dz, r2, part);
+        if (in && (p_on || q_on)) hydro_pair_adjoint(P, Q, alpha, p_on, q_on, -dx, -dy, -dz, r2, part);
       }
 #pragma unroll
       for (int k = 0; k < kN; ++k) neumaier_add(acc[k], cmp[k], part[k]);

@@ -239,3 +239,25 @@ def test_targets_without_neighbours_have_no_rates(ctx):
     assert torch.equal(c["dudt"], torch.zeros(n, device="cuda"))
     v = ops.velocity_gradients(tree, pos.clone(), h, rho, one)
     assert not v["div"].any() and not v["curl"].any()
+
+
+@pytest.mark.parametrize("approach", [0.0, 1.0, -1.0])
+def test_an_infinite_factor_without_upstream_stays_out_of_the_adjoint(ctx, approach):
+    # rho = 0 makes the second particle's pressure factor infinite; only the
+    # first has an upstream gradient, of its acceleration alone, and no term of
+    # its velocity, u, h and rho gradients holds that factor
+    from paper_2003_10850_amd import ops
+    pos = dev_t(np.float32([[0.45, 0.5, 0.5], [0.55, 0.5, 0.5]]))
+    one = torch.ones(2, device="cuda")
+    tree = ops.Tree(ctx, pos, one, None, (0.0, 0.0, 0.0, 1.0), inputs.Params(n_ngb=16.0))
+    vel = torch.zeros_like(pos)
+    vel[0, 0] = approach
+    rho = dev_t(np.float32([1.0, 0.0]))
+    x = [t.clone().requires_grad_(True) for t in (pos, vel, one, one, 0.3 * one, rho, one)]
+    acc = ops.hydro_force_ad(tree, *x)[0]
+    up = torch.zeros_like(acc)
+    up[0] = torch.tensor([1.0, 0.5, -0.25])
+    _, gv, _, gu, gh, gr, go = torch.autograd.grad(acc, x, up)
+    assert torch.isfinite(gv).all()
+    for g in (gu, gh, gr, go):
+        assert torch.isfinite(g[0])
