@@ -764,6 +764,11 @@ __device__ __forceinline__ void wc6_f_derivs(float r, float hinv, float &F, floa
 struct HSide {
   float4 xm, vh, aux, up;
 };
+// A tile of them, array by array: (x, y, z, fl(h^2)), which is all that the
+// neighbour test reads, (v, m), aux and up.
+struct HSides {
+  float4 xh[kTile], vm[kTile], aux[kTile], up[kTile];
+};
 
 // What one particle p of a pair is owed: by the pair term whose target is p,
 // and by the one whose target is its neighbour q. A term with target i and
@@ -848,10 +853,19 @@ __global__ void k_hydro_bwd_up(const int32_t *__restrict__ active, int64_t n_act
 // the pair (target p, neighbour q) if p is active, and (target q,
 // neighbour p) if q is active. Then A and c are mapped back to u, rho and
 // Omega: A = (gamma-1) u / (Omega rho), c = sqrt(gamma (gamma-1) u).
-// Bound by VALU issue (a pair is ~150 operations); 125 registers, four waves
-// a SIMD. Teams and tiles as in the density's adjoint. 1.25e5 particles of
+// Bound by VALU issue (a pair is ~150 operations); 128 registers, four waves
+// a SIMD. Teams as in the density's adjoint. 1.25e5 particles of
 // ~295 neighbours: 10671 us with one wave a group and the two terms of a pair
 // by themselves, 2210 with teams of 4, 2131 of 8.
+// A lane is a neighbour of a quarter of the entries that any lane neighbours, so
+// the pairs are not taken entry by entry: the tests give each lane a bit mask of
+// the tile, and the lanes take their own entries side by side, as many steps as
+// the busiest lane has. Neighbours in tree order come in runs that one lane takes
+// whole; a tile therefore holds every ntiles-th candidate of a round, which needs
+// 0.5 to 0.66 of the steps, against 0.9 with consecutive ones. Density and force
+// with gradients, entry by entry and so: 710 and 696 us at 3000 particles, 3390 and
+// 3240 at 6e4, 5790 and 5180 at 2.5e5, 8160 and 7365 at 5e5 (5400 and 7360 with
+// three waves a SIMD and 146 registers, nothing spilled).
 template <int kT>
 __global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
     const float4 *__restrict__ xm, const float4 *__restrict__ vh,
@@ -861,7 +875,7 @@ __global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
     float *__restrict__ g_h, float *__restrict__ g_u, float *__restrict__ g_rho,
     float *__restrict__ g_omega) {
   __shared__ TeamLds<kT> search;
-  __shared__ HSide T[kT][kTile];
+  __shared__ HSides T[kT];
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
   int range = 0;
   for (int g; (g = team_next_group(gs, range, search)) >= 0;) {
@@ -873,7 +887,7 @@ __global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
     P.vh = vh[s];
     P.aux = aux[s];
     P.up = up[s];
-    const float hp = valid ? P.vh.w : -1.0f;
+    const float hp = valid ? P.vh.w : -1.0f, hp2 = sq_exact(fmaxf(hp, 0.0f));
     const bool p_on = valid && (P.up.x != 0.f || P.up.y != 0.f || P.up.z != 0.f || P.up.w != 0.f);
     constexpr int kN = 11;
     float acc[kN], cmp[kN];
@@ -927,22 +941,68 @@ __global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
         const uint64_t km = __ballot(keep);
         const int slot = (int)__builtin_amdgcn_mbcnt_hi(
             (uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
-        // kept candidates in their order at the front; the scan stops at nc
-        if (keep) T[w][slot] = Q;
+        // kept candidates in their order at the front, infinity behind (the
+        // tests take whole groups of kStep)
+        T[w].xh[lane] = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+        if (keep) {
+          T[w].xh[slot] = make_float4(Q.xm.x, Q.xm.y, Q.xm.z, sq_exact(fmaxf(Q.vh.w, 0.0f)));
+          T[w].vm[slot] = make_float4(Q.vh.x, Q.vh.y, Q.vh.z, Q.xm.w);
+          T[w].aux[slot] = Q.aux;
+          T[w].up[slot] = Q.up;
+        }
         nc = __popcll(km);
       }
       wave_sync();
+      // the entries with upstream gradients; a lane without takes only these
+      uint64_t qm;
+      {
+        const float4 qu = T[w].up[lane];
+        qm = __ballot(lane < nc && (qu.x != 0.f || qu.y != 0.f || qu.z != 0.f || qu.w != 0.f));
+      }
+      const uint32_t on[2] = {__brev((uint32_t)qm), __brev((uint32_t)(qm >> 32))};
       float part[kN];
 #pragma unroll
       for (int k = 0; k < kN; ++k) part[k] = 0.0f;
-      for (int k = 0; k < nc; ++k) {
-        const HSide Q = T[w][k];
+      // entries [32 half, 32 half + 32) that the lane takes, the first in the
+      // highest bit
+      auto tests = [&](int half) {
+        constexpr int kStep = 4;
+        uint32_t hits = 0;
+        int k = 32 * half;
+        for (; k < min(nc, 32 * half + 32); k += kStep) {
+#pragma unroll
+          for (int i = 0; i < kStep; ++i) {
+            const float4 q = T[w].xh[k + i];
+            const float r2 = dist2_exact(sub_exact(q.x, P.xm.x), sub_exact(q.y, P.xm.y),
+                                         sub_exact(q.z, P.xm.z));
+            hits = 2u * hits + (r2 < max_num(hp2, q.w) && r2 > 0.0f ? 1u : 0u);
+          }
+        }
+        const int free = 32 * half + 32 - k;  // untested entries of a short tile
+        hits = valid && free < 32 ? hits << free : 0u;
+        return p_on ? hits : hits & on[half];
+      };
+      uint32_t now = tests(0), next = tests(1), q_now = on[0];
+      for (int base = 0; (now | next) != 0u;) {
+        if (now == 0u) {
+          now = next;
+          next = 0u;
+          base = 32;
+          q_now = on[1];
+        }
+        const int z = __builtin_clz(now), k = base + z;
+        const uint32_t bit = 0x80000000u >> z;
+        now &= ~bit;
+        HSide Q;
+        Q.xm = T[w].xh[k];
+        Q.vh = T[w].vm[k];
+        Q.aux = T[w].aux[k];
+        Q.up = T[w].up[k];
+        Q.xm.w = Q.vh.w;  // the mass
         const float dx = sub_exact(Q.xm.x, P.xm.x), dy = sub_exact(Q.xm.y, P.xm.y),
                     dz = sub_exact(Q.xm.z, P.xm.z);  // x_q - x_p
-        const float r2 = dist2_exact(dx, dy, dz);
-        const bool in = valid && r2 < sq_exact(fmaxf(hp, Q.vh.w)) && r2 > 0.0f;
-        const bool q_on = Q.up.x != 0.f || Q.up.y != 0.f || Q.up.z != 0.f || Q.up.w != 0.f;
-        if (in && (p_on || q_on)) hydro_pair_adjoint(P, Q, alpha, p_on, q_on, -dx, -dy, -dz, r2, part);
+        hydro_pair_adjoint(P, Q, alpha, p_on, (q_now & bit) != 0u, -dx, -dy, -dz,
+                           dist2_exact(dx, dy, dz), part);
       }
 #pragma unroll
       for (int k = 0; k < kN; ++k) neumaier_add(acc[k], cmp[k], part[k]);
@@ -953,12 +1013,13 @@ __global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
         [](float h, float hmax) { return h < 0.0f ? -1.0f : sq_exact(fmaxf(h, hmax)); },
         [&](int ntiles, int count) {
           for (int j = w; j < ntiles; j += kT) {
-            const int nc = min(kTile, count - j * kTile);
-            cand = lane < nc ? search.cand[j * kTile + lane] : 0;
+            // (every ntiles-th candidate of the round)
+            const int nc = (count - j + ntiles - 1) / ntiles;
+            cand = lane < nc ? search.cand[j + lane * ntiles] : 0;
             flush(nc);
           }
         });
-    team_totals<kT, kN, sizeof(HSide) * kTile / 4>((float *)T, w, lane, acc, cmp);
+    team_totals<kT, kN, sizeof(HSides) / 4>((float *)T, w, lane, acc, cmp);
     if (valid && w == 0) {
       float tot[kN];
 #pragma unroll

@@ -261,3 +261,27 @@ def test_an_infinite_factor_without_upstream_stays_out_of_the_adjoint(ctx, appro
     assert torch.isfinite(gv).all()
     for g in (gu, gh, gr, go):
         assert torch.isfinite(g[0])
+
+
+@pytest.mark.parametrize("n", [2, 65, 1000, 30000])
+def test_hydro_adjoint_of_parts_of_the_upstream_adds_up(ctx, n):
+    # the gradients are linear in the upstream ones, whichever side of a pair
+    # holds them: sums of a few hundred FP32 terms that cancel in part, 1e-5 of
+    # the largest
+    from paper_2003_10850_amd import ops
+    g = torch.Generator(device="cuda").manual_seed(n)
+    R = lambda *s: torch.rand(*s, generator=g, device="cuda")
+    pos, mass = R(n, 3), (0.5 + R(n)) / n
+    tree = ops.Tree(ctx, pos, mass, None, (0.0, 0.0, 0.0, 1.0), inputs.Params(n_ngb=16.0))
+    x = [t.requires_grad_(True) for t in (pos.clone(), R(n, 3) - 0.5, mass.clone(), 0.5 + R(n),
+                                          1.2 * n ** (-1.0 / 3.0) * (0.8 + 0.4 * R(n)),
+                                          0.5 + R(n), 0.5 + R(n))]
+    ups = (R(n, 3) - 0.5, R(n) - 0.5)
+
+    def grads(on):
+        f = ops.hydro_force_ad(tree, *x)
+        return torch.autograd.grad(f[:2], x, [u * (on if u.dim() == 1 else on[:, None]) for u in ups])
+
+    few = (torch.arange(n, device="cuda") % 7 == 1).float()
+    for a, b, c in zip(grads(few), grads(1.0 - few), grads(torch.ones_like(few))):
+        assert (a + b - c).abs().max() <= 1e-5 * c.abs().max()
