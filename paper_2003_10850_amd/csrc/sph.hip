@@ -794,7 +794,8 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k
             bd = kBandOff * (H2 + ldexpf(eb, -20));
           }
           in = r2 < H2;
-          const bool near = valid && fabsf(r2 - H2) <= bd;
+          // (the entries behind nc have no index, and lie in a band that overflows)
+          const bool near = valid && k < nc && fabsf(r2 - H2) <= bd;
           if (__ballot(near) != 0ull && near) {
             const int j = __float_as_int(tlos[w][k].w);
             in = within64(x64[s], x64[j], fmax(hi64, h64[j]));
