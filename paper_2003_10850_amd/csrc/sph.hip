@@ -698,9 +698,12 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k
       const uint64_t km = __ballot(keep);
       const int slot = (int)__builtin_amdgcn_mbcnt_hi(
           (uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
-      // kept candidates in their order at the front, infinity behind (the scan
-      // takes whole groups of kStep)
-      T.xm[w][lane] = make_float4(INFINITY, INFINITY, INFINITY, 0.f);
+      // kept candidates in their order at the front, behind them (the scan takes
+      // whole groups of kStep) no number: it fails the test, and is also not near
+      // the threshold where the mixed test's band overflows (such an entry has no
+      // index that the FP64 test could read)
+      const float none = __builtin_nanf("");
+      T.xm[w][lane] = make_float4(none, none, none, 0.f);
       if (keep) {
         T.xm[w][slot] = make_float4(vo.x, vo.y, vo.z, sq_exact(vv.w));
         T.vh[w][slot] = make_float4(vv.x, vv.y, vv.z, vo.w);
@@ -794,8 +797,7 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k
             bd = kBandOff * (H2 + ldexpf(eb, -20));
           }
           in = r2 < H2;
-          // (the entries behind nc have no index, and lie in a band that overflows)
-          const bool near = valid && k < nc && fabsf(r2 - H2) <= bd;
+          const bool near = valid && fabsf(r2 - H2) <= bd;
           if (__ballot(near) != 0ull && near) {
             const int j = __float_as_int(tlos[w][k].w);
             in = within64(x64[s], x64[j], fmax(hi64, h64[j]));
