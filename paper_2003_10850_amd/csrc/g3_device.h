@@ -63,9 +63,6 @@ __device__ __forceinline__ float sq_exact(float a) {
   return a * a;
 }
 
-// Wendland C6 in 3D with support radius h (Dehnen & Aly 2012): the
-// normalisation C = 1365 / (64 pi), and the radial factor of
-// F = (1/r) dW/dr = -22 C/h^5 (1-q)^7 (1 + 7q + 16q^2) as a function of
 // fmaxf in one instruction (the compiler first turns signalling NaNs of
 // either side into quiet ones, two more); the other one when one is a NaN.
 __device__ __forceinline__ float max_num(float a, float b) {
@@ -74,6 +71,9 @@ __device__ __forceinline__ float max_num(float a, float b) {
   return r;
 }
 
+// Wendland C6 in 3D with support radius h (Dehnen & Aly 2012): the
+// normalisation C = 1365 / (64 pi), and the radial factor of
+// F = (1/r) dW/dr = -22 C/h^5 (1-q)^7 (1 + 7q + 16q^2) as a function of
 // q = r/h: wendland_f(q) = (1-q)^7 (1 + 7q + 16q^2), zero at and beyond the
 // support.
 constexpr float kWendlandC = 6.7889530412636603f;

@@ -93,11 +93,8 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_gravity(
     px = py = pz = pp = 0.f;
     since = 0;
   };
-  // one source at offset (dx, dy, dz), squared softened distance r2s, for the
-  // lanes that use it: masked here (not the mass), so that an unused source
-  // adds exact zeros also at r2s = 0 (the own particle with zero softening)
-  auto term = [&](bool use, float dx, float dy, float dz, float r2s, float m) {
-    const float rinv = use ? __builtin_amdgcn_rsqf(r2s) : 0.0f;
+  // one source at offset (dx, dy, dz), inverse softened distance rinv
+  auto add = [&](bool use, float dx, float dy, float dz, float rinv, float m) {
     const float mr = m * rinv;
     const float mr3 = mr * rinv * rinv;
     px += mr3 * dx;
@@ -106,11 +103,31 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_gravity(
     pp -= mr;
     pn += use ? 1 : 0;
   };
+  // a member, for the lanes that use it: the inverse distance is masked, so that
+  // an unused one adds exact zeros also at r2s = 0 (the own particle with zero
+  // softening)
+  auto term = [&](bool use, float dx, float dy, float dz, float r2s, float m) {
+    add(use, dx, dy, dz, use ? __builtin_amdgcn_rsqf(r2s) : 0.0f, m);
+  };
+  // A node, for the lanes that accept it. Its mass may be above FP32's largest
+  // number near the root, where every lane opens it, and infinity times a masked
+  // distance of zero is no zero: the lanes branch (all of a clustered 2^21 box:
+  // 4143 us with the distance masked, 3995 so). Teams of 16 have few waves, where
+  // the branch costs 3 %; they mask, and branch only below a root that heavy.
+  constexpr bool kMayMask = !kF64 && kT == 16;
+  auto node_term = [&](auto mask_c, bool use, float dx, float dy, float dz, float r2s, float m) {
+    if constexpr (decltype(mask_c)::value) {
+      term(use, dx, dy, dz, r2s, m);
+    } else if (use) {
+      add(true, dx, dy, dz, __builtin_amdgcn_rsqf(r2s), m);
+    }
+  };
 
   // One item: `count` children at cnodes[first], or -count members from
   // `first`, for the lanes of `mask` (all wave-uniform); open(first, count,
   // mask) receives the items that it opens.
-  auto item = [&](int first, int count, uint64_t mask, const auto &opened) {
+  auto items = [&](auto mask_c) {
+  return [&](int first, int count, uint64_t mask, const auto &opened) {
     const bool act = __builtin_amdgcn_inverse_ballot_w64(mask);
     if (count > 0) {
       auto visit = [&](const CNode &nd, const double4 &cn, uint64_t nk) {
@@ -155,7 +172,7 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_gravity(
           }
           open = act && !accept;
         }
-        term(accept, dx, dy, dz, r2 + eps2, nd.com_m.w);
+        node_term(mask_c, accept, dx, dy, dz, r2 + eps2, nd.com_m.w);
         const uint64_t om = __ballot(open);
         if (om) opened(nd.meta.x, nd.meta.y, om);
       };
@@ -201,10 +218,18 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_gravity(
     }
     if (since >= kFlush) flush();
   };
+  };
 
   const int root = __builtin_amdgcn_readfirstlane(grp.snap);
   const uint64_t all = grp.count < kWave ? (1ull << grp.count) - 1ull : ~0ull;
-  team_items(S, root, all, w, lane, item);
+  if constexpr (kMayMask) {
+    if (cnodes[root].com_m.w < INFINITY)
+      team_items(S, root, all, w, lane, items(std::true_type{}));
+    else
+      team_items(S, root, all, w, lane, items(std::false_type{}));
+  } else {
+    team_items(S, root, all, w, lane, items(std::false_type{}));
+  }
   flush();
   float4 tt = tot[lane], tc4 = comp[lane];
   nts[w][lane] = pn;

@@ -50,3 +50,25 @@ def test_fp64_pair_counts_where_the_decision_band_overflows(ctx, n):
     H = np.maximum(h[:, None], h[None])
     want = ((d[..., 0] ** 2 + d[..., 1] ** 2) + d[..., 2] ** 2 < H * H).sum(1) - 1
     np.testing.assert_array_equal(f["npairs"].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("theta", [0.5, 0.7])
+def test_gravity_below_nodes_heavier_than_fp32_holds(ctx, theta, fp64):
+    # the root's mass overflows FP32; no particle accepts it
+    from paper_2003_10850_amd import ops
+    n, side = 4096, 1e6
+    rng = np.random.default_rng(3)
+    pos = rng.random((n, 3)) * side
+    if not fp64:
+        pos = pos.astype(np.float32)
+    mass = (1.5e35 * rng.uniform(0.7, 1.3, n)).astype(np.float32)
+    p = inputs.Params(n_ngb=32.0, theta=theta, eps=1e4, G=1e-30)
+    box = (0.0, 0.0, 0.0, side)
+    tree = ops.Tree(ctx, dev_t(pos), dev_t(mass), None, box, p)
+    g = host(ops.gravity(tree))
+    pr = dataclasses.replace(p, flags=oracle.FLAG_FP64_DECISIONS if fp64 else 0)
+    ref = oracle.gravity(oracle.Tree(pos.astype(np.float64), mass.astype(np.float64), box), pr)
+    np.testing.assert_array_equal(g["nterms"], ref["nterms"])
+    assert (np.linalg.norm(g["acc"] - ref["acc"], axis=1) / ref["S"]).max() < 1e-5
+    assert (np.abs(g["pot"] - ref["pot"]) / np.abs(ref["pot"])).max() < 2e-6
