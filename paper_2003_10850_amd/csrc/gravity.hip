@@ -26,7 +26,7 @@ namespace g3 {
 
 namespace {
 
-// Terms of plain FP32 partial sums between two compensated additions.
+// Terms of plain FP32 partial sums between two compensated additions, at most.
 constexpr int kFlush = 64;
 
 // The opening test, exact in FP32: fl(l * l) < fl(theta2 * r2).
@@ -212,11 +212,11 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_gravity(
 #pragma unroll
         for (int q = 0; q < 4; ++q) member(m + q);
         since += 4;
-        if (since >= kFlush) flush();
+        if (since > kFlush - 4) flush();
       }
       for (; m < end; ++m, ++since) member(m);
     }
-    if (since >= kFlush) flush();
+    if (since > kFlush - 8) flush();  // (the next item may be 8 children)
   };
   };
 
