@@ -105,14 +105,16 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_velgrad(
         if (r2 < hi2 && r2 > 0.0f) {
           const float4 qv = T.vh[k];
           const float r = r2 * __builtin_amdgcn_rsqf(r2);
-          // m_j F(r, h_i) without the constant and h_i^-5, applied at the
-          // end: grad_i W = F (x_i - x_j) = -F (dx, dy, dz)
-          const float mf = q.w * wendland_f(r * hinv);
+          // m_j F(r, h_i): grad_i W = F (x_i - x_j) = -F (dx, dy, dz). The factor
+          // of h goes with the mass: sums of m v x alone leave FP32's range in
+          // large or small units
+          const float mf = q.w * fi5 * wendland_f(r * hinv);
+          const float gx = -mf * dx, gy = -mf * dy, gz = -mf * dz;
           const float ux = qv.x - mv.x, uy = qv.y - mv.y, uz = qv.z - mv.z;
-          pd -= mf * (ux * dx + uy * dy + uz * dz);
-          px += mf * (uy * dz - uz * dy);
-          py += mf * (uz * dx - ux * dz);
-          pz += mf * (ux * dy - uy * dx);
+          pd += ux * gx + uy * gy + uz * gz;
+          px -= uy * gz - uz * gy;
+          py -= uz * gx - ux * gz;
+          pz -= ux * gy - uy * gx;
         }
       }
       neumaier_add(sum[0], cmp[0], pd);
@@ -136,12 +138,8 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_velgrad(
     if (valid && w == 0) {
       const int cid = perm[s];
       const float norm = 1.0f / (omega[cid] * rho[cid]);
-      // (a target without a neighbour has no gradient also where h^-5 overflows)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float v = sum[k] + cmp[k];
-        sum[k] = (v == 0.0f ? v : v * fi5) * norm;
-      }
+      for (int k = 0; k < 4; ++k) sum[k] = (sum[k] + cmp[k]) * norm;
       if (div_v) div_v[cid] = sum[0];
       if (curl_v) {
         curl_v[3 * cid] = sum[1];

@@ -72,3 +72,25 @@ def test_gravity_below_nodes_heavier_than_fp32_holds(ctx, theta, fp64):
     np.testing.assert_array_equal(g["nterms"], ref["nterms"])
     assert (np.linalg.norm(g["acc"] - ref["acc"], axis=1) / ref["S"]).max() < 1e-5
     assert (np.abs(g["pot"] - ref["pot"]) / np.abs(ref["pot"])).max() < 2e-6
+
+
+@pytest.mark.parametrize("mass,speed,side", [(2e33, 1e7, 3e3), (1e-36, 1e-3, 0.1), (1e-3, 1.0, 1.0)])
+def test_velocity_gradients_in_large_and_small_units(ctx, mass, speed, side):
+    from paper_2003_10850_amd import ops
+    n = 3000
+    rng = np.random.default_rng(8)
+    pos = (rng.random((n, 3)) * side).astype(np.float32)
+    vel = (speed * rng.normal(0, 1, (n, 3))).astype(np.float32)
+    m = (mass * rng.uniform(0.7, 1.3, n)).astype(np.float32)
+    h = (2.3 * side * n ** (-1.0 / 3.0) * rng.uniform(0.8, 1.2, n)).astype(np.float32)
+    rho = (n * mass / side ** 3 * rng.uniform(0.7, 1.3, n)).astype(np.float32)
+    om = rng.uniform(0.8, 1.2, n).astype(np.float32)
+    box = (0.0, 0.0, 0.0, side)
+    p = inputs.Params(n_ngb=48.0)
+    tree = ops.Tree(ctx, dev_t(pos), dev_t(m), None, box, p)
+    v = host(ops.velocity_gradients(tree, dev_t(vel), dev_t(h), dev_t(rho), dev_t(om)))
+    t = oracle.Tree(pos.astype(np.float64), m.astype(np.float64), box, gas_only=True,
+                    type=np.zeros(n, np.uint8))
+    ref = oracle.velgrad(t, p, vel, h, rho, om)
+    assert (np.abs(v["div"] - ref["div"]) / ref["S_div"]).max() < 1e-5
+    assert (np.linalg.norm(v["curl"] - ref["curl"], axis=1) / ref["S_curl"]).max() < 1e-5
