@@ -632,7 +632,7 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k
   const float hi = valid ? mv.w : -1.0f;  // invalid lanes never want anything
   const float hi2 = valid ? sq_exact(hi) : -1.0f;
   const float ci = ma.y, rhoi = ma.z, hinvi = ma.w, half_alpha = 0.5f * alpha;
-  const float ki = kWendlandF * (hinvi * hinvi) * (hinvi * hinvi) * hinvi, Aki = ma.x * ki;
+  const float Ai = ma.x, ki = kWendlandF * (hinvi * hinvi) * (hinvi * hinvi) * hinvi;
   // totals with Neumaier compensation terms; per-tile partials are plain
   float ax = 0.f, ay = 0.f, az = 0.f, du = 0.f, vs = 0.f;
   float cax = 0.f, cay = 0.f, caz = 0.f, cdu = 0.f;
@@ -724,7 +724,9 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k
         const float4 qv = T.vh[w][k], qa = T.aux[w][k];
         const float rinv = __builtin_amdgcn_rsqf(r2);
         const float r = r2 * rinv;
-        const float wi = wendland_f(r * hinvi);
+        // (A_i and h_i^-5 only with the kernel between them: alone their product
+        // may overflow, also for a pair beyond h_i, where g_i is zero)
+        const float gi = ki * wendland_f(r * hinvi);
         const float gj = T.g[w][k] * wendland_f(r * qa.w);
         // x_ij = x_i - x_j = -(dx, dy, dz); v_ij = v_i - v_j
         const float vdx = (mv.x - qv.x) * dx + (mv.y - qv.y) * dy + (mv.z - qv.z) * dz;
@@ -742,9 +744,9 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k
           ha_ij = 0.125f * (mx.x + qe.x) * (mx.y + qe.y);
         }
         // Pi gbar = V with Pi = a_ij v_sig (-w) / (rho_i + rho_j), gbar = (g_i + g_j) / 2
-        const float gsum = ki * wi + gj;
+        const float gsum = gi + gj;
         const float V = ha_ij * vsig_ij * (-wneg) * rsum_inv * gsum;
-        const float mj = qv.w, Ag = Aki * wi;  // A_i g_i
+        const float mj = qv.w, Ag = Ai * gi;
         const float coef = mj * (Ag + qa.x * gj + V);  // a_i -= coef x_ij
         px += coef * dx;
         py += coef * dy;

@@ -94,3 +94,33 @@ def test_velocity_gradients_in_large_and_small_units(ctx, mass, speed, side):
     ref = oracle.velgrad(t, p, vel, h, rho, om)
     assert (np.abs(v["div"] - ref["div"]) / ref["S_div"]).max() < 1e-5
     assert (np.linalg.norm(v["curl"] - ref["curl"], axis=1) / ref["S_curl"]).max() < 1e-5
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+def test_hydro_force_on_a_particle_with_a_tiny_h_and_a_large_pressure(ctx, fp64):
+    # A h^-5 of the first particle overflows; its pairs lie beyond its own h,
+    # where its kernel is zero
+    from paper_2003_10850_amd import ops
+    n = 130
+    rng = np.random.default_rng(4)
+    pos = 0.3 + 0.4 * rng.random((n, 3))
+    if not fp64:
+        pos = pos.astype(np.float32)
+    mass = np.full(n, 1.0 / n, np.float32)
+    vel = rng.normal(0, 0.1, (n, 3)).astype(np.float32)
+    h = rng.uniform(0.15, 0.2, n).astype(pos.dtype)
+    u, rho = [rng.uniform(0.5, 1.5, n).astype(np.float32) for _ in range(2)]
+    h[0], u[0], rho[0] = 1e-6, 1e6, 1e-3
+    one = np.ones(n, np.float32)
+    p = inputs.Params(n_ngb=32.0)
+    box = (0.0, 0.0, 0.0, 1.0)
+    tree = ops.Tree(ctx, dev_t(pos), dev_t(mass), None, box, p)
+    f = host(ops.hydro_force(tree, dev_t(vel), dev_t(u), dev_t(h), dev_t(rho), dev_t(one)))
+    t = oracle.Tree(pos.astype(np.float64), mass.astype(np.float64), box, gas_only=True,
+                    type=np.zeros(n, np.uint8))
+    pr = dataclasses.replace(p, flags=oracle.FLAG_FP64_DECISIONS if fp64 else 0)
+    ref = oracle.hydro(t, pr, vel, u, h, rho, one)
+    assert ref["npairs"][0] > 0
+    np.testing.assert_array_equal(f["npairs"], ref["npairs"])
+    assert (np.linalg.norm(f["acc"] - ref["acc"], axis=1) / ref["S"]).max() < 1e-5
+    assert np.isfinite(f["dudt"]).all()
