@@ -1066,7 +1066,11 @@ hipError_t launch_hydro_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int team = adjoint_team(m);
-  auto kern = team == 16 ? k_hydro_bwd<16> : (team == 8 ? k_hydro_bwd<8> : k_hydro_bwd<4>);
+  auto kern = team == 16  ? k_hydro_bwd<16>
+              : team == 8 ? k_hydro_bwd<8>
+              : team == 4 ? k_hydro_bwd<4>
+                          : nullptr;
+  if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
       gas.xm, gas.vh, gas.aux, up, gas.perm, all_gas, tm, alpha, gamma, u, omega, g_pos, g_vel,
@@ -1082,7 +1086,7 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
                               double *rr, float *g_pos, float *g_mass, hipStream_t s) {
   const int64_t m = all.n, nn = all.nnodes;
   if (m == 0 || nn == 0) return hipSuccess;
-  if (!all.cnodes) return hipErrorInvalidValue;
+  if (!all.cnodes || (gp.team != 16 && gp.team != 8 && gp.team != 4)) return hipErrorInvalidValue;
   const int64_t na = active ? n_act : m;
   auto pick = [&](auto fixed_c) {
     constexpr bool f = decltype(fixed_c)::value;
@@ -1129,7 +1133,11 @@ static hipError_t density_bwd(const Octree &gas, const Groups &gs, int64_t max_g
                               const Terms &tm, const float4 *bw, float *g_pos, float *g_mass,
                               float *g_h, hipStream_t s) {
   const int team = adjoint_team(gas.n);
-  auto kern = team == 16 ? k_density_bwd<16> : (team == 8 ? k_density_bwd<8> : k_density_bwd<4>);
+  auto kern = team == 16  ? k_density_bwd<16>
+              : team == 8 ? k_density_bwd<8>
+              : team == 4 ? k_density_bwd<4>
+                          : nullptr;
+  if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
       gas.xm, bw, gas.perm, gs, tm, g_pos, g_mass, g_h);

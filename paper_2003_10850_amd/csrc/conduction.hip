@@ -233,7 +233,9 @@ hipError_t launch_conduction(const Octree &gas, const Groups &gs, int64_t max_gr
   auto kern = team == 16  ? k_conduction<16>
               : team == 8 ? k_conduction<8>
               : team == 4 ? k_conduction<4>
-                          : k_conduction<1>;
+              : team == 1 ? k_conduction<1>
+                          : nullptr;
+  if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = (team > 1 ? team : 4) * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
       gas.nodes, gas.xm, ch, gas.perm, gs, walk_leaf, tm, dudt, npairs);

@@ -277,7 +277,9 @@ hipError_t launch_gravity(const Octree &all, const Groups &gs, int64_t max_group
   };
   auto kern = gp.team == 16  ? pick(std::integral_constant<int, 16>{})
               : gp.team == 8 ? pick(std::integral_constant<int, 8>{})
-                             : pick(std::integral_constant<int, 4>{});
+              : gp.team == 4 ? pick(std::integral_constant<int, 4>{})
+                             : nullptr;
+  if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = gp.team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, gp.team), block, 0, s>>>(
       all.cnodes, all.ckeys, all.cc64, all.xm, all.x64, all.keys, all.perm, gs, gp.theta2,

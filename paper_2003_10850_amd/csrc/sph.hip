@@ -925,11 +925,14 @@ hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_group
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
   auto kern = sp.f64 ? (sp.team == 16  ? k_density<true, 16>
                         : sp.team == 8 ? k_density<true, 8>
-                                       : k_density<true, 4>)
+                        : sp.team == 4 ? k_density<true, 4>
+                                       : nullptr)
                      : (sp.team == 16   ? k_density<false, 16>
                         : sp.team == 12 ? k_density<false, 12>
                         : sp.team == 8  ? k_density<false, 8>
-                                        : k_density<false, 4>);
+                        : sp.team == 4  ? k_density<false, 4>
+                                        : nullptr);
+  if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = sp.team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(
       gas.nodes, gas.xm, gas.x64, gas.perm, gs, tm, sp.n_ngb, sp.h_tol, solve_h, sp.max_iter,
@@ -966,17 +969,20 @@ hipError_t launch_hydro(const Octree &gas, const Groups &gs, int64_t max_groups,
       return sp.team == 16   ? k_hydro<f, e, 16>
              : sp.team == 12 ? k_hydro<f, e, 12>
              : sp.team == 8  ? k_hydro<f, e, 8>
-                             : k_hydro<f, e, 1>;
+             : sp.team == 1  ? k_hydro<f, e, 1>
+                             : nullptr;
     else
       return sp.team == 16  ? k_hydro<f, e, 16>
              : sp.team == 8 ? k_hydro<f, e, 8>
              : sp.team == 4 ? k_hydro<f, e, 4>
-                            : k_hydro<f, e, 1>;
+             : sp.team == 1 ? k_hydro<f, e, 1>
+                            : nullptr;
   };
   const std::true_type yes;
   const std::false_type no;
   auto kern = sp.f64 ? (ext ? pick(yes, yes) : pick(yes, no))
                      : (ext ? pick(no, yes) : pick(no, no));
+  if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = (sp.team > 1 ? sp.team : 4) * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(
       gas.nodes, gas.xm, gas.x64, gas.h64, gas.vh, gas.aux, ext, gas.perm, gs, tm, sp.alpha,

@@ -195,7 +195,11 @@ hipError_t launch_velgrad(const Octree &gas, const Groups &gs, int64_t max_group
                           const Terms &tm, int team, const float *rho, const float *omega,
                           float *div_v, float *curl_v, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = team == 16 ? k_velgrad<16> : (team == 8 ? k_velgrad<8> : k_velgrad<4>);
+  auto kern = team == 16  ? k_velgrad<16>
+              : team == 8 ? k_velgrad<8>
+              : team == 4 ? k_velgrad<4>
+                          : nullptr;
+  if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
       gas.xm, gas.vh, gas.perm, gs, tm, rho, omega, div_v, curl_v);
