@@ -437,9 +437,26 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
 //             16    406   621  1305  1667  2177  2673  4843   8964
 // With fewer groups than CUs the time is that of the slowest group, which the
 // widest team serves fastest; later the number of waves that a CU holds counts
-// (teams of 12 in 80 registers: 24, of 16 in 107: 16).
-int density_team(int64_t max_targets, int f64) {
+// (teams of 12 in 80 registers: 24, of 16 in 107: 16). Where every CU has a
+// hundred groups, a team's barriers and its search, which every wave of it takes,
+// cost more than the uneven groups and passes that it levels out (us, cold solve
+// of uniform sets at 48 and 295 neighbours, of clustered ones at 64 and 295):
+//   groups                16384  20100  24800  32768  65536 131072
+//   48 uniform      4      2533   3106   3739   4789  10679  18186
+//                none      2787   3204   3661   4370   8697  16004
+//   295 uniform     4      3942   4974   6086   7593  15955
+//                none      4162   5036   5931   7138  13166
+//   64 clustered    4      3330   4031   4873   5937  11992
+//                none      4070   4730   5228   5565   9921
+//   295 clustered   4      6210   7198   8882  10798  20243  36670
+//                none      7614   8004   9315  10768  17460  29975
+//   FP64, 295 cl.   4      8358   9647  11911  14402  26209
+//                none     10806  11777  14131  15500  21783
+//   FP64, 48 unif.  4      3351                       14753
+//                none      3204                        9803
+int density_team(int64_t max_targets, int f64, bool solve) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
+  if (groups > (solve ? 28672 : 49152)) return 1;
   if (f64) return groups <= 1280 ? 16 : (groups <= 4608 ? 8 : 4);
   return groups <= 320 ? 16 : (groups <= 3072 ? 12 : (groups <= 6144 ? 8 : 4));
 }
@@ -1045,14 +1062,15 @@ int g3_density(g3_ctx *c, const g3_tree *t, int64_t n_act, const int32_t *active
   const Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneDensity, active ? std::min<int64_t>(n_act, o.n) : o.n);
   SphParams sp = sph_params(c, p, t, tu);
-  sp.team = density_team(active ? std::min<int64_t>(n_act, o.n) : o.n, t->f64);
+  sp.team = density_team(active ? std::min<int64_t>(n_act, o.n) : o.n, t->f64, solve_h != 0);
   TermBufs tb;
-  if (o.n > 0 && !reserve_terms(c, o, t->n_snap, &tb))
+  if (sp.team > 1 && o.n > 0 && !reserve_terms(c, o, t->n_snap, &tb))
     return fail(c, G3_ENOMEM, "g3_density: allocation of the terminal list failed");
   Work wk;
   st = prepare_work(c, t, o, t->iperm_gas, n_act, active, &wk, s, tu.split);
   if (st) return st;
-  hipError_t e = build_terms(o, t->n_snap, sp.walk_leaf, false, tb, s);
+  hipError_t e =
+      sp.team > 1 ? build_terms(o, t->n_snap, sp.walk_leaf, false, tb, s) : hipSuccess;
   if (e != hipSuccess) return hip_fail(c, e, "g3_density");
   KernelTimer timer(c, kTuneDensity, s);
   e = launch_density(o, wk.gs, wk.max_groups, sp, tb.terms(), solve_h ? 1 : 0, h, rho, drho_dh,
@@ -1372,13 +1390,14 @@ static int tick_forces(g3_ctx *c, g3_tree *t, int64_t n, const g3_state *st,
     SphParams spd = sph_params(c, p, t, td);
     spd.team = density_team(gas.n, t->f64);
     TermBufs tb;
-    if (!reserve_terms(c, gas, t->n_snap, &tb))
+    const int hteam = hydro_team(gas.n, t->f64);
+    if ((spd.team > 1 || hteam > 1) && !reserve_terms(c, gas, t->n_snap, &tb))
       return fail(c, G3_ENOMEM, "tick: allocation of the terminal list failed");
     Work wd;
     rc = prepare_work(c, t, gas, t->iperm_gas, gas.n, nullptr, &wd, s, td.split, nullptr, bins,
                       kmin);
     if (rc) return rc;
-    e = build_terms(gas, t->n_snap, spd.walk_leaf, false, tb, s);
+    if (spd.team > 1) e = build_terms(gas, t->n_snap, spd.walk_leaf, false, tb, s);
     if (e == hipSuccess)
       e = launch_density(gas, wd.gs, wd.max_groups, spd, tb.terms(), 1, st->h, st->rho, nullptr,
                          st->omega, nullptr, c->counters, s);
@@ -1393,7 +1412,7 @@ static int tick_forces(g3_ctx *c, g3_tree *t, int64_t n, const g3_state *st,
     }
     const Tuning th = tuning_for(c, kTuneHydro, gas.n);
     SphParams sp = sph_params(c, p, t, th);
-    sp.team = hydro_team(gas.n, t->f64);
+    sp.team = hteam;
     e = launch_hydro_prep(gas, vh, uh, st->h, st->rho, st->omega, sp.gamma, t->f64, s);
     if (e == hipSuccess) e = sph_radii(t, gas, sp, tb, s);
     if (e != hipSuccess) return hip_fail(c, e, "hydro prep at a tick");
@@ -1684,7 +1703,7 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
             return hipErrorUnknown;
           SphParams sp = sph_params(c, p, t, tu);
           sp.team = density_team(ng, t->f64);
-          r = build_terms(gas, t->n_snap, sp.walk_leaf, false, tb, s);
+          if (sp.team > 1) r = build_terms(gas, t->n_snap, sp.walk_leaf, false, tb, s);
           if (r != hipSuccess) return r;
           return launch_density(gas, wk.gs, wk.max_groups, sp, tb.terms(), 1, hs, nullptr,
                                 nullptr, nullptr, nullptr, c->counters, s);

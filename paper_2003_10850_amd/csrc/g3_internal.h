@@ -295,9 +295,9 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
                        hipStream_t s);
 
 // Waves of the team that serves one group, from the (host-side bound on the)
-// number of targets: 4, 8, 12 or 16, for the hydro force and conduction also 1 (no
-// team).
-int density_team(int64_t max_targets, int f64);
+// number of targets: 4, 8, 12 or 16, for the density, the hydro force and
+// conduction also 1 (no team).
+int density_team(int64_t max_targets, int f64, bool solve = true);
 int hydro_team(int64_t max_targets, bool wide);
 int gravity_team(int64_t max_targets);
 int gravity_bwd_team(int64_t max_targets);
@@ -358,7 +358,7 @@ struct SphParams {
   const unsigned *absmax;  // FP64 trees: device bits of max |x| (walk pad 2^-20 of it)
 };
 
-// tm: the terminals of sp.walk_leaf (the hydro force: when sp.team > 1).
+// tm: the terminals of sp.walk_leaf (when sp.team > 1).
 hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_groups,
                           const SphParams &sp, const Terms &tm, int solve_h, void *h, float *rho,
                           float *drho_dh, float *omega, int32_t *nngb,

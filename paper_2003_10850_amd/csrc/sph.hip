@@ -107,6 +107,8 @@ constexpr float kFineExt = 1.0f;
 
 // A team of kT waves (g3_team.h) serves a group: every wave holds the group's
 // targets and takes the same solve steps, the search and the tiles are shared.
+// kT = 1: a wave walks the octree by itself, where groups are plenty (2^22 uniform
+// gas at 48 neighbours: 10.7 ms with teams of 4, 8.7 so); the same sums, bit for bit.
 // Bound by vector issue on a full chip (a neighbour pass of one wave is about
 // 5e4 instructions) and by the slowest groups otherwise. Cold solve of the
 // 2^20 gas particles of a clustered 2^21 box: 8.0 ms with a wave a group, 6.0
@@ -125,17 +127,25 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kDensityWaves<kF64, kT>)) void k_den
     unsigned long long *__restrict__ counters) {
   using HT = typename std::conditional<kF64, double, float>::type;
   HT *h = (HT *)hptr;
-  __shared__ TeamLds<kT> search;
-  __shared__ TeamSums<kT, 3> sums;
+  constexpr int kWpb = kBlockOf<kT> / kWave;
+  constexpr int kTeam = kT > 1 ? kT : 4;
+  using SearchLds = typename std::conditional<(kT > 1), TeamLds<kTeam>, NoLds>::type;
+  using SumLds = typename std::conditional<(kT > 1), TeamSums<kTeam, 3>, NoLds>::type;
+  __shared__ SearchLds search;
+  __shared__ SumLds sums;
   // FP64 positions: the walk's pad for the rounding of the FP32 copies
   const float slack = kF64 ? ldexpf(__uint_as_float(*absmax), -20) : 0.0f;
-  __shared__ float4 tiles[kT][kTile];
+  __shared__ float4 tiles[kWpb][kTile];
   // mixed precision: the low parts of the offsets, and the sorted index of
   // each entry as the fourth component
-  __shared__ float4 tlos[kT][kF64 ? kTile : 1];
+  __shared__ float4 tlos[kWpb][kF64 ? kTile : 1];
   const int w = (int)(threadIdx.x >> 6), lane = lane_id();
   int range = 0;
-  for (int g; (g = team_next_group(gs, range, search)) >= 0;) {
+  auto take_group = [&]() {
+    if constexpr (kT > 1) return team_next_group<kTeam>(gs, range, search);
+    else return next_group(gs, range);
+  };
+  for (int g; (g = take_group()) >= 0;) {
   const Group grp = group_at(gs, g);
   const int64_t t = grp.t0 + lane;
   const bool valid = lane < grp.count;
@@ -350,9 +360,9 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kDensityWaves<kF64, kT>)) void k_den
       }
       wave_sync();
     };
-    {
+    if constexpr (kT > 1) {
       float ts = 0.0f, tcmp = 0.0f;  // this wave's component of the totals
-      team_search(
+      team_search<kTeam>(
           tm, grp.snap, search, xi, hw2, tlo, thi, hmax2,
           [](float want2, float) { return want2; },
           [&](int ntiles, int count) {
@@ -376,6 +386,48 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kDensityWaves<kF64, kT>)) void k_den
 #pragma unroll
       for (int v = 0; v < kT; ++v) cnt += sums.count[v][lane];
       __syncthreads();
+    } else {
+      float csw = 0.0f, cswh = 0.0f, csss = 0.0f;
+      sw = swh = sss = 0.0f;
+      auto flush = [&](int nc) {
+        float pw, pwh, pss;
+        tile_sums(nc, pw, pwh, pss);
+        neumaier_add(sw, csw, pw);
+        neumaier_add(swh, cswh, pwh);
+        neumaier_add(sss, csss, pss);
+      };
+      // The next node is cur + 1 (descend) or the skip target: both are loaded
+      // while the current one is tested, so a step waits for one load.
+      int tc = 0, cur = grp.root;
+      const int last = grp.end - 1;
+      Node nd = nodes[cur];
+      while (cur < grp.end) {
+        const int next_a = cur + 1, next_b = nd.meta.x;
+        const Node nda = nodes[min(next_a, last)], ndb = nodes[min(next_b, last)];
+        bool descend = false;
+        if (__ballot(box_dist2(xi, nd.lo_h, nd.hi_l) < hw2) != 0ull) {
+          // a small subtree is taken whole: its members are one contiguous run
+          descend = !(nd.meta.w & kLeafBit) && nd.meta.z > walk_leaf;
+          int st = nd.meta.y, c = descend ? 0 : nd.meta.z;
+          while (c > 0) {
+            const int take = min(c, kTile - tc);
+            if (lane >= tc && lane < tc + take) cand = st + lane - tc;
+            tc += take;
+            st += take;
+            c -= take;
+            if (tc == kTile) {
+              flush(kTile);
+              tc = 0;
+            }
+          }
+        }
+        cur = descend ? next_a : next_b;
+        nd = descend ? nda : ndb;
+      }
+      if (tc > 0) flush(tc);
+      sw += csw;
+      swh += cswh;
+      sss += csss;
     }
 
     if (live) {
@@ -481,12 +533,12 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kDensityWaves<kF64, kT>)) void k_den
     }
   }
   // counters: [0] non-converged particles, [1] walk passes, [2] waves
-  if (threadIdx.x == 0) {
+  if (kT > 1 ? threadIdx.x == 0 : lane == 0) {
     atomicAdd(&counters[1], (unsigned long long)passes);
     atomicAdd(&counters[2], 1ull);
   }
 
-  if (valid && w == 0) {
+  if (valid && (kT == 1 || w == 0)) {
     const float hinv = 1.0f / (float)res_h;
     const float r = kC * res_sw * hinv * hinv * hinv;
     if (solve) h[cid] = res_h;
@@ -926,14 +978,16 @@ hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_group
   auto kern = sp.f64 ? (sp.team == 16  ? k_density<true, 16>
                         : sp.team == 8 ? k_density<true, 8>
                         : sp.team == 4 ? k_density<true, 4>
+                        : sp.team == 1 ? k_density<true, 1>
                                        : nullptr)
                      : (sp.team == 16   ? k_density<false, 16>
                         : sp.team == 12 ? k_density<false, 12>
                         : sp.team == 8  ? k_density<false, 8>
                         : sp.team == 4  ? k_density<false, 4>
+                        : sp.team == 1  ? k_density<false, 1>
                                         : nullptr);
   if (!kern) return hipErrorInvalidValue;  // (no such team)
-  const int block = sp.team * kWave;
+  const int block = (sp.team > 1 ? sp.team : 4) * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(
       gas.nodes, gas.xm, gas.x64, gas.perm, gs, tm, sp.n_ngb, sp.h_tol, solve_h, sp.max_iter,
       sp.walk_leaf, sp.absmax, h, rho, drho_dh, omega, nngb, counters);

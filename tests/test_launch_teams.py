@@ -74,8 +74,8 @@ def velgrad(lib, team):
 
 
 @pytest.mark.parametrize("call,teams", [
-    (lambda l, t: density(l, 0, t), {4, 8, 12, 16}),
-    (lambda l, t: density(l, 1, t), {4, 8, 16}),
+    (lambda l, t: density(l, 0, t), {1, 4, 8, 12, 16}),
+    (lambda l, t: density(l, 1, t), {1, 4, 8, 16}),
     (lambda l, t: hydro(l, 0, t), {1, 8, 12, 16}),
     (lambda l, t: hydro(l, 0, t, True), {1, 4, 8, 16}),
     (lambda l, t: hydro(l, 1, t), {1, 4, 8, 16}),
@@ -91,7 +91,7 @@ def test_teams_without_a_kernel_are_refused(lib, call, teams):
 
 
 @pytest.mark.parametrize("rule,args,teams", [
-    ("density_team", (0,), {4, 8, 12, 16}), ("density_team", (1,), {4, 8, 16}),
+    ("density_team", (0, 1), {1, 4, 8, 12, 16}), ("density_team", (1, 0), {1, 4, 8, 16}),
     ("hydro_team", (0,), {1, 8, 12, 16}), ("hydro_team", (1,), {1, 4, 8, 16}),
     ("gravity_team", (), {4, 8, 16}), ("gravity_bwd_team", (), {4, 8, 16}),
     ("adjoint_team", (), {4, 8, 16}), ("velgrad_team", (), {4, 8, 16}),
