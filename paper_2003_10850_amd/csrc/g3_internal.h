@@ -21,8 +21,7 @@ struct __align__(16) Node {
   float4 com_m;  // centre of mass (FP32 copy of the FP64 moment), mass
   float4 lo_h;   // tight bounding box lower corner, max h of gas members
   float4 hi_l;   // tight bounding box upper corner, cube side l
-  int4 meta;     // skip, first member, member count,
-                 // level | leaf << 8 | min(parent's member count, 65535) << 16
+  int4 meta;     // skip, first member, member count, level | leaf << 8
 };
 static_assert(sizeof(Node) == 64, "node must be 64 bytes");
 
@@ -74,6 +73,7 @@ struct Octree {
   uint32_t *cbase = nullptr; // [nnodes + 1]
   int64_t cap_cnodes = 0, cap_cc64 = 0;
   double4 *mom = nullptr;    // [nnodes] FP64 (M, M x, M y, M z)
+  uint32_t *tcode = nullptr; // [nnodes] what a terminal list asks (see term_code)
   // the moments' order: roots of small subtrees, and the nodes above them
   int32_t *subs = nullptr;    // [nnodes]
   TopNode *tops = nullptr;    // [cap_tops]

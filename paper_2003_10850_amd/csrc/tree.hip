@@ -318,10 +318,9 @@ __global__ __launch_bounds__(kBlock) void k_nodes(
       Node nd;
       nd.lo_h = make_float4(0.f, 0.f, 0.f, 0.f);
       nd.hi_l = make_float4(0.f, 0.f, 0.f, ldexpf(side, -l));
-      // the parent's member count follows (k_parents); a root has none and
-      // counts as inside an unbounded node; the moments fill com_m and the boxes
+      // (the moments fill com_m and the boxes)
       nd.meta = make_int4(end >= m ? (int)nnodes : (int)off[end], (int)p, end - (int)p,
-                          l | (l == d ? kLeafBit : 0) | (l == 0 ? (int)0xffff0000u : 0));
+                          l | (l == d ? kLeafBit : 0));
       Node &to = nodes[(int64_t)at + (l - delta)];
       to.lo_h = nd.lo_h;
       to.hi_l = nd.hi_l;
@@ -330,24 +329,33 @@ __global__ __launch_bounds__(kBlock) void k_nodes(
   }
 }
 
-// The parent's member count into every node that has one; nch (nullable): the
-// number of children of every node.
-__global__ void k_parents(Node *__restrict__ nodes, int64_t nnodes, uint32_t *__restrict__ nch) {
+// A node in four bytes for the terminal lists: its own member count (a leaf: 0)
+// in the low half, its parent's in the high half, both cut off above what a
+// walk_leaf can be. A root counts as inside an unbounded node.
+constexpr uint32_t kRootCode = 0xffff0000u;
+__device__ __forceinline__ uint32_t term_code(int4 meta, uint32_t parent) {
+  return ((meta.w & kLeafBit) ? 0u : (uint32_t)min(meta.z, 65535)) | parent;
+}
+__device__ __forceinline__ bool is_terminal(uint32_t code, int walk_leaf) {
+  return (int)(code & 0xffffu) <= walk_leaf && (int)(code >> 16) > walk_leaf;
+}
+__device__ __forceinline__ bool is_root(uint32_t code) { return code >= kRootCode; }
+
+// The codes of all nodes; nch (nullable): the number of children of every node.
+__global__ void k_parents(const Node *__restrict__ nodes, int64_t nnodes,
+                          uint32_t *__restrict__ tcode, uint32_t *__restrict__ nch) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= nnodes) return;
   const int4 meta = nodes[k].meta;
-  if (meta.w & kLeafBit) {
-    if (nch) nch[k] = 0;
-    return;
-  }
-  const int pc = (int)((unsigned)min(meta.z, 65535) << 16);
+  if ((meta.w & 255) == 0) tcode[k] = term_code(meta, kRootCode);
   uint32_t nc = 0;
-  int64_t c = k + 1;
-  for (; c < meta.x; ++nc) {
-    const int4 cm = nodes[c].meta;
-    // (the low half as k_nodes wrote it; children are no roots)
-    nodes[c].meta.w = (cm.w & 0xffff) | pc;
-    c = cm.x;
+  if (!(meta.w & kLeafBit)) {
+    const uint32_t pc = (uint32_t)min(meta.z, 65534) << 16;
+    for (int64_t c = k + 1; c < meta.x; ++nc) {
+      const int4 cm = nodes[c].meta;
+      tcode[c] = term_code(cm, pc);
+      c = cm.x;
+    }
   }
   if (nch) nch[k] = nc;
 }
@@ -651,10 +659,6 @@ __global__ void k_zero_one(unsigned *p) {
 constexpr int kTermPer = 8;  // nodes per thread
 constexpr int kTermTile = kBlock * kTermPer;
 
-__device__ __forceinline__ bool is_terminal(int4 meta, int walk_leaf) {
-  return ((meta.w & kLeafBit) || meta.z <= walk_leaf) && (int)((unsigned)meta.w >> 16) > walk_leaf;
-}
-
 __device__ __forceinline__ int block_sum(int v, int *lds /* [kBlock / kWave] */) {
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) v += __shfl_xor(v, d);
@@ -667,14 +671,14 @@ __device__ __forceinline__ int block_sum(int v, int *lds /* [kBlock / kWave] */)
   return t;
 }
 
-__global__ __launch_bounds__(kBlock) void k_term_count(const Node *__restrict__ nodes, int nn,
-                                                       int walk_leaf,
+__global__ __launch_bounds__(kBlock) void k_term_count(const uint32_t *__restrict__ tcode,
+                                                       int nn, int walk_leaf,
                                                        int32_t *__restrict__ bcount) {
   __shared__ int lds[kBlock / kWave];
   int c = 0;
   for (int q = 0; q < kTermPer; ++q) {
     const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
-    if (k < nn && is_terminal(nodes[k].meta, walk_leaf)) ++c;
+    if (k < nn && is_terminal(tcode[k], walk_leaf)) ++c;
   }
   c = block_sum(c, lds);
   if (threadIdx.x == 0) bcount[blockIdx.x] = c;
@@ -684,7 +688,7 @@ __global__ __launch_bounds__(kBlock) void k_term_count(const Node *__restrict__ 
 // them: a snapshot's root sets its first one and the end of the snapshot
 // before it.
 __global__ __launch_bounds__(kBlock) void k_term_write(
-    const Node *__restrict__ nodes, int nn, int walk_leaf, const int32_t *__restrict__ bcount,
+    const uint32_t *__restrict__ tcode, int nn, int walk_leaf, const int32_t *__restrict__ bcount,
     const int32_t *__restrict__ nroot, int n_snap, int32_t *__restrict__ tnode,
     int32_t *__restrict__ tcount, int2 *__restrict__ range) {
   __shared__ int lds[kBlock / kWave];
@@ -694,9 +698,8 @@ __global__ __launch_bounds__(kBlock) void k_term_write(
   const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
   for (int q = 0; q < kTermPer; ++q) {
     const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
-    int4 meta = make_int4(0, 0, 0, 0);
-    if (k < nn) meta = nodes[k].meta;
-    const bool f = k < nn && is_terminal(meta, walk_leaf);
+    const uint32_t code = k < nn ? tcode[k] : 0u;
+    const bool f = k < nn && is_terminal(code, walk_leaf);
     const uint64_t m = __ballot(f);
     if (lane == 0) lds[w] = __popcll(m);
     __syncthreads();
@@ -709,7 +712,7 @@ __global__ __launch_bounds__(kBlock) void k_term_write(
     at += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
     if (f) tnode[at] = k;
-    if (k < nn && (meta.w & 255) == 0) {  // a root
+    if (is_root(code)) {
       if (n_snap == 1) {
         range[0].x = at;
       } else {
@@ -729,23 +732,24 @@ __global__ __launch_bounds__(kBlock) void k_term_write(
 
 // The subtree roots and the (node, level) above them, in tree order; counts
 // [0] and [1]. The same two passes as the terminals.
-__global__ __launch_bounds__(kBlock) void k_split_count(const Node *__restrict__ nodes, int nn,
-                                                        int2 *__restrict__ bcount) {
+__global__ __launch_bounds__(kBlock) void k_split_count(const uint32_t *__restrict__ tcode,
+                                                        int nn, int2 *__restrict__ bcount) {
   __shared__ int lds[kBlock / kWave];
   int a = 0, b = 0;
   for (int q = 0; q < kTermPer; ++q) {
     const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
     if (k >= nn) continue;
-    const int4 meta = nodes[k].meta;
-    a += is_terminal(meta, kSubtree);
-    b += !(meta.w & kLeafBit) && meta.z > kSubtree;
+    const uint32_t code = tcode[k];
+    a += is_terminal(code, kSubtree);
+    b += (int)(code & 0xffffu) > kSubtree;
   }
   a = block_sum(a, lds);
   b = block_sum(b, lds);
   if (threadIdx.x == 0) bcount[blockIdx.x] = make_int2(a, b);
 }
 
-__global__ __launch_bounds__(kBlock) void k_split_write(const Node *__restrict__ nodes, int nn,
+__global__ __launch_bounds__(kBlock) void k_split_write(const Node *__restrict__ nodes,
+                                                        const uint32_t *__restrict__ tcode, int nn,
                                                         const int2 *__restrict__ bcount,
                                                         int32_t *__restrict__ subs,
                                                         TopNode *__restrict__ tops,
@@ -765,9 +769,10 @@ __global__ __launch_bounds__(kBlock) void k_split_write(const Node *__restrict__
   for (int q = 0; q < kTermPer; ++q) {
     const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
     if (k >= nn) continue;
-    const int4 meta = nodes[k].meta;
-    if (is_terminal(meta, kSubtree)) subs[a + atomicAdd(&na, 1)] = k;
-    if (!(meta.w & kLeafBit) && meta.z > kSubtree) {
+    const uint32_t code = tcode[k];
+    if (is_terminal(code, kSubtree)) subs[a + atomicAdd(&na, 1)] = k;
+    if ((int)(code & 0xffffu) > kSubtree) {
+      const int4 meta = nodes[k].meta;
       TopNode t;
       t.node = k;
       t.level = meta.w & 255;
@@ -1026,11 +1031,11 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
       if (p) (void)hipFree(p);
     o.nodes = nullptr; o.mom = nullptr; o.tops = nullptr; o.cap_nodes = 0;
     const int64_t cap = nnodes + nnodes / 8 + 64;
-    // (the lists of the moments in one buffer)
+    // (the lists of the moments and the terminal codes in one buffer)
     if (dev_malloc(c, (void **)&o.nodes, cap * sizeof(Node)) != hipSuccess ||
         dev_malloc(c, (void **)&o.mom, cap * sizeof(double4)) != hipSuccess ||
         dev_malloc(c, (void **)&o.tops, max_tops(o.cap_n) * sizeof(TopNode) +
-                                            (cap + 2) * sizeof(int32_t)) != hipSuccess) {
+                                            (2 * cap + 2) * sizeof(int32_t)) != hipSuccess) {
       c->err = "device allocation of the octree nodes failed";
       return G3_ENOMEM;
     }
@@ -1082,6 +1087,7 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
   }
   o.subs = (int32_t *)(o.tops + o.cap_tops);
   o.nsplit = o.subs + o.cap_nodes;
+  o.tcode = (uint32_t *)(o.nsplit + 2);
   // per-block counts of the list pass
   int2 *bcount = (int2 *)scratch(c, kMisc, 64 + (nnodes / kTermTile + 2) * sizeof(int2));
   if (!bcount) { c->err = "device allocation of build scratch failed"; return G3_ENOMEM; }
@@ -1091,11 +1097,12 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
   k_nodes<<<nblk(m), kBlock, 0, s>>>(o.keys, m, o.soff, t->n_snap, t->sbox, off, lev, nnodes,
                                      o.nodes);
   k_nroot<<<nblk(t->n_snap + 1), kBlock, 0, s>>>(off, o.soff, t->n_snap, o.nroot);
-  k_parents<<<nblk(nnodes), kBlock, 0, s>>>(o.nodes, nnodes, nch);
+  k_parents<<<nblk(nnodes), kBlock, 0, s>>>(o.nodes, nnodes, o.tcode, nch);
   if (nnodes > kSmallNodes) {
     const unsigned nb = (unsigned)((nnodes + kTermTile - 1) / kTermTile);
-    k_split_count<<<nb, kBlock, 0, s>>>(o.nodes, (int)nnodes, bcount);
-    k_split_write<<<nb, kBlock, 0, s>>>(o.nodes, (int)nnodes, bcount, o.subs, o.tops, o.nsplit);
+    k_split_count<<<nb, kBlock, 0, s>>>(o.tcode, (int)nnodes, bcount);
+    k_split_write<<<nb, kBlock, 0, s>>>(o.nodes, o.tcode, (int)nnodes, bcount, o.subs, o.tops,
+                                        o.nsplit);
   }
   launch_moments(t, o, s);
   if (grav) {
@@ -1167,8 +1174,8 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
   if (o.nnodes == 0) return hipSuccess;
   const int nn = (int)o.nnodes;
   const unsigned nb = (unsigned)((nn + kTermTile - 1) / kTermTile);
-  k_term_count<<<nb, kBlock, 0, s>>>(o.nodes, nn, walk_leaf, b.bcount);
-  k_term_write<<<nb, kBlock, 0, s>>>(o.nodes, nn, walk_leaf, b.bcount, o.nroot, n_snap, b.node,
+  k_term_count<<<nb, kBlock, 0, s>>>(o.tcode, nn, walk_leaf, b.bcount);
+  k_term_write<<<nb, kBlock, 0, s>>>(o.tcode, nn, walk_leaf, b.bcount, o.nroot, n_snap, b.node,
                                      b.count, b.range);
   const unsigned nf = (unsigned)std::min<int64_t>((nn + kWave - 1) / kWave, 512);
   k_term_fill<<<nf, kFillBlock, 0, s>>>(o.nodes, b.node, b.count, with_h ? o.vh : nullptr,
