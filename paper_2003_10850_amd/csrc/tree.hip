@@ -684,20 +684,19 @@ __global__ __launch_bounds__(kBlock) void k_term_count(const uint32_t *__restric
   if (threadIdx.x == 0) bcount[blockIdx.x] = c;
 }
 
-// The terminals' node indices in tree order, and each snapshot's range of
-// them: a snapshot's root sets its first one and the end of the snapshot
-// before it.
-__global__ __launch_bounds__(kBlock) void k_term_write(
-    const uint32_t *__restrict__ tcode, int nn, int walk_leaf, const int32_t *__restrict__ bcount,
-    const int32_t *__restrict__ nroot, int n_snap, int32_t *__restrict__ tnode,
-    int32_t *__restrict__ tcount, int2 *__restrict__ range) {
-  __shared__ int lds[kBlock / kWave];
-  int pre = 0;
-  for (int b = (int)threadIdx.x; b < (int)blockIdx.x; b += kBlock) pre += bcount[b];
-  int base = block_sum(pre, lds);
+// The indices of the terminals among the nodes [k0, k0 + kThreads kTermPer), in
+// tree order from `base` on, and each snapshot's range of them: a snapshot's root
+// sets its first one and the end of the snapshot before it. Returns the end.
+template <int kThreads>
+__device__ __forceinline__ int write_terms(const uint32_t *__restrict__ tcode, int nn,
+                                           int walk_leaf, int k0, int base,
+                                           const int32_t *__restrict__ nroot, int n_snap,
+                                           int32_t *tnode, int32_t *__restrict__ tcount,
+                                           int2 *__restrict__ range,
+                                           int *lds /* [kThreads / kWave] */) {
   const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
-  for (int q = 0; q < kTermPer; ++q) {
-    const int k = (int)blockIdx.x * kTermTile + q * kBlock + (int)threadIdx.x;
+  for (int q = 0; q < kTermPer && k0 + q * kThreads < nn; ++q) {
+    const int k = k0 + q * kThreads + (int)threadIdx.x;
     const uint32_t code = k < nn ? tcode[k] : 0u;
     const bool f = k < nn && is_terminal(code, walk_leaf);
     const uint64_t m = __ballot(f);
@@ -705,7 +704,7 @@ __global__ __launch_bounds__(kBlock) void k_term_write(
     __syncthreads();
     int at = base, tot = 0;
 #pragma unroll
-    for (int v = 0; v < kBlock / kWave; ++v) {
+    for (int v = 0; v < kThreads / kWave; ++v) {
       if (v < w) at += lds[v];
       tot += lds[v];
     }
@@ -728,6 +727,19 @@ __global__ __launch_bounds__(kBlock) void k_term_write(
     base += tot;
     __syncthreads();
   }
+  return base;
+}
+
+__global__ __launch_bounds__(kBlock) void k_term_write(
+    const uint32_t *__restrict__ tcode, int nn, int walk_leaf, const int32_t *__restrict__ bcount,
+    const int32_t *__restrict__ nroot, int n_snap, int32_t *__restrict__ tnode,
+    int32_t *__restrict__ tcount, int2 *__restrict__ range) {
+  __shared__ int lds[kBlock / kWave];
+  int pre = 0;
+  for (int b = (int)threadIdx.x; b < (int)blockIdx.x; b += kBlock) pre += bcount[b];
+  const int base = block_sum(pre, lds);
+  (void)write_terms<kBlock>(tcode, nn, walk_leaf, (int)blockIdx.x * kTermTile, base, nroot, n_snap,
+                            tnode, tcount, range, lds);
 }
 
 // The subtree roots and the (node, level) above them, in tree order; counts
@@ -797,13 +809,14 @@ __global__ __launch_bounds__(kBlock) void k_split_write(const Node *__restrict__
 // the members' loads; one launch, where a refit of every node's largest h
 // takes one launch a level (11 of them, 5-6 us each, on 10^6 gas particles).
 constexpr int kFillBlock = 1024;
-__global__ __launch_bounds__(kFillBlock) void k_term_fill(
-    const Node *__restrict__ nodes, const int32_t *__restrict__ tnode,
-    const int32_t *__restrict__ tcount, const float4 *__restrict__ vh, int m,
-    float4 *__restrict__ lo, float4 *__restrict__ hi, float4 *__restrict__ wlo,
-    float4 *__restrict__ whi) {
-  __shared__ float4 sl[kWave], sh[kWave];
-  const int n = *tcount;
+struct WindowLds {
+  float4 lo[kWave], hi[kWave];
+};
+__device__ __forceinline__ void fill_windows(const Node *__restrict__ nodes, const int32_t *tnode,
+                                             int n, const float4 *__restrict__ vh, int m,
+                                             float4 *__restrict__ lo, float4 *__restrict__ hi,
+                                             float4 *__restrict__ wlo, float4 *__restrict__ whi,
+                                             WindowLds &S) {
   const int sub = (int)(threadIdx.x & 15u), q = (int)(threadIdx.x >> 4);
   for (int b = (int)blockIdx.x; b * kWave < n; b += (int)gridDim.x) {
     const int t = b * kWave + q;
@@ -828,12 +841,12 @@ __global__ __launch_bounds__(kFillBlock) void k_term_fill(
       }
     }
     if (sub == 0) {
-      sl[q] = l;
-      sh[q] = h;
+      S.lo[q] = l;
+      S.hi[q] = h;
     }
     __syncthreads();
     if (threadIdx.x < (unsigned)kWave) {
-      float4 a = sl[threadIdx.x], c = sh[threadIdx.x];
+      float4 a = S.lo[threadIdx.x], c = S.hi[threadIdx.x];
 #pragma unroll
       for (int d = 1; d < kWave; d <<= 1) {
         a.x = fminf(a.x, __shfl_xor(a.x, d));
@@ -851,6 +864,34 @@ __global__ __launch_bounds__(kFillBlock) void k_term_fill(
     }
     __syncthreads();
   }
+}
+
+__global__ __launch_bounds__(kFillBlock) void k_term_fill(
+    const Node *__restrict__ nodes, const int32_t *__restrict__ tnode,
+    const int32_t *__restrict__ tcount, const float4 *__restrict__ vh, int m,
+    float4 *__restrict__ lo, float4 *__restrict__ hi, float4 *__restrict__ wlo,
+    float4 *__restrict__ whi) {
+  __shared__ WindowLds S;
+  fill_windows(nodes, tnode, *tcount, vh, m, lo, hi, wlo, whi, S);
+}
+
+// The whole list of a small tree by one workgroup, one launch for three (us, with
+// the tree walk that the lists replaced, with three launches, with one: velocity
+// gradients of one particle 60, 75, 67, of 100 68, 77, 73; density of one particle
+// 79, 88, 80).
+constexpr int kSmallTerms = kSmallNodes;
+__global__ __launch_bounds__(kFillBlock) void k_term_small(
+    const Node *__restrict__ nodes, const uint32_t *__restrict__ tcode, int nn, int walk_leaf,
+    const int32_t *__restrict__ nroot, int n_snap, const float4 *__restrict__ vh, int m,
+    int32_t *__restrict__ tcount, int2 *__restrict__ range, float4 *__restrict__ lo,
+    float4 *__restrict__ hi, float4 *__restrict__ wlo, float4 *__restrict__ whi) {
+  static_assert(kSmallTerms <= kFillBlock * kTermPer, "one pass over the nodes");
+  __shared__ int32_t tnode[kSmallTerms];
+  __shared__ int lds[kFillBlock / kWave];
+  __shared__ WindowLds S;
+  const int n = write_terms<kFillBlock>(tcode, nn, walk_leaf, 0, 0, nroot, n_snap, tnode, tcount,
+                                        range, lds);
+  fill_windows(nodes, tnode, n, vh, m, lo, hi, wlo, whi, S);
 }
 
 // The gravity walk's node copies (after the moments): every internal node
@@ -1173,6 +1214,12 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
                        hipStream_t s) {
   if (o.nnodes == 0) return hipSuccess;
   const int nn = (int)o.nnodes;
+  if (nn <= kSmallTerms) {
+    k_term_small<<<1, kFillBlock, 0, s>>>(o.nodes, o.tcode, nn, walk_leaf, o.nroot, n_snap,
+                                          with_h ? o.vh : nullptr, (int)o.n, b.count, b.range,
+                                          b.lo, b.hi, b.wlo, b.whi);
+    return hipGetLastError();
+  }
   const unsigned nb = (unsigned)((nn + kTermTile - 1) / kTermTile);
   k_term_count<<<nb, kBlock, 0, s>>>(o.tcode, nn, walk_leaf, b.bcount);
   k_term_write<<<nb, kBlock, 0, s>>>(o.tcode, nn, walk_leaf, b.bcount, o.nroot, n_snap, b.node,
