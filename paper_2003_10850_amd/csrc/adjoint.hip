@@ -146,7 +146,7 @@ struct DTile {
   float4 b[kTile];  // fl(h^2) or -1, 1/h, f1, f2
   float2 w[kTile];  // w1, w2
 };
-template <int kT>
+template <int kT, bool kDeep = false>
 __global__ __launch_bounds__(kT * kWave, kT < 16 ? 6 : 1) void k_density_bwd(
     const float4 *__restrict__ xm, const float4 *__restrict__ bw,
     const int32_t *__restrict__ perm, const Groups gs, const Terms tm,
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kT * kWave, kT < 16 ? 6 : 1) void k_density_bwd(
       neumaier_add(sum[4], cmp[4], ph);
       wave_sync();
     };
-    team_search(
+    team_search<kT, kDeep>(
         tm, grp.snap, search, make_float3(me.x, me.y, me.z), want, tlo, thi, hg,
         [](float h, float hmax) { return h < 0.0f ? -1.0f : sq_exact(fmaxf(h, hmax)); },
         [&](int ntiles, int count) {
@@ -866,7 +866,7 @@ __global__ void k_hydro_bwd_up(const int32_t *__restrict__ active, int64_t n_act
 // with gradients, entry by entry and so: 710 and 696 us at 3000 particles, 3390 and
 // 3240 at 6e4, 5790 and 5180 at 2.5e5, 8160 and 7365 at 5e5 (5400 and 7360 with
 // three waves a SIMD and 146 registers, nothing spilled).
-template <int kT>
+template <int kT, bool kDeep = false>
 __global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
     const float4 *__restrict__ xm, const float4 *__restrict__ vh,
     const float4 *__restrict__ aux, const float4 *__restrict__ up,
@@ -1008,7 +1008,7 @@ __global__ __launch_bounds__(kT * kWave, kT < 16 ? 4 : 1) void k_hydro_bwd(
       for (int k = 0; k < kN; ++k) neumaier_add(acc[k], cmp[k], part[k]);
       wave_sync();
     };
-    team_search(
+    team_search<kT, kDeep>(
         tm, grp.snap, search, make_float3(P.xm.x, P.xm.y, P.xm.z), want, tlo, thi, hg,
         [](float h, float hmax) { return h < 0.0f ? -1.0f : sq_exact(fmaxf(h, hmax)); },
         [&](int ntiles, int count) {
@@ -1070,6 +1070,7 @@ hipError_t launch_hydro_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
               : team == 8 ? k_hydro_bwd<8>
               : team == 4 ? k_hydro_bwd<4>
                           : nullptr;
+  if (tm.deep) kern = team == 4 ? k_hydro_bwd<4, true> : nullptr;
   if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(
@@ -1137,6 +1138,7 @@ static hipError_t density_bwd(const Octree &gas, const Groups &gs, int64_t max_g
               : team == 8 ? k_density_bwd<8>
               : team == 4 ? k_density_bwd<4>
                           : nullptr;
+  if (tm.deep) kern = team == 4 ? k_density_bwd<4, true> : nullptr;
   if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(

@@ -782,6 +782,9 @@ static int build_forest_body(g3_ctx *c, g3_tree *t, int32_t n_snap, const int64_
   double smax = 0.0;
   for (int32_t k = 0; k < n_snap; ++k) smax = std::max(smax, box[4 * k + 3]);
   t->max_side = smax;
+  t->max_members = 0;
+  for (int32_t k = 0; k < n_snap; ++k)
+    t->max_members = std::max(t->max_members, snap_off[k + 1] - snap_off[k]);
   if (t->f64 && !t->absmax &&
       dev_malloc(c, (void **)&t->absmax, sizeof(unsigned)) != hipSuccess)
     return fail(c, G3_ENOMEM, "g3_build_forest: allocation failed");
@@ -965,6 +968,20 @@ static SphParams sph_params(const g3_ctx *c, const g3_params *p, const g3_tree *
   return sp;
 }
 
+// The deep search, where a snapshot's list has twenty rows of 64 windows or more
+// (a terminal holds about half of walk_leaf members), or where unsplit groups of
+// so few targets may hold far more terminals in their box than they reach (in a
+// list of one row there is little to leave out). us, every row and deep: velocity
+// gradients of 3e6 members (11 rows) 4750 and 5110, of 8e6 (30 rows) 14500 and
+// 14180, of 1.6e7 23560 and 21620; the density's adjoint of 8e6 (61 rows) 37400 and
+// 33900; the force of 64 random targets of 4e6 4580 and 1610.
+static bool deep_search(const g3_tree *t, const Octree &o, int64_t max_targets, int walk_leaf,
+                        int split) {
+  const int64_t members = std::min(o.n, t->max_members);
+  const int64_t row = (int64_t)walk_leaf * (kWave * kWave / 2);
+  return members / 20 >= row || (split == -1 && max_targets <= o.n / 64 && members >= row);
+}
+
 // The largest h of the nodes that a symmetric search reads: the terminals'
 // for a team, every node's for a walk (from o.vh, filled just before).
 static hipError_t sph_radii(const g3_tree *t, Octree &o, const SphParams &sp, const TermBufs &tb,
@@ -1062,8 +1079,10 @@ int g3_density(g3_ctx *c, const g3_tree *t, int64_t n_act, const int32_t *active
   const Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneDensity, active ? std::min<int64_t>(n_act, o.n) : o.n);
   SphParams sp = sph_params(c, p, t, tu);
-  sp.team = density_team(active ? std::min<int64_t>(n_act, o.n) : o.n, t->f64, solve_h != 0);
+  const int64_t max_t = active ? std::min<int64_t>(n_act, o.n) : o.n;
+  sp.team = density_team(max_t, t->f64, solve_h != 0);
   TermBufs tb;
+  tb.deep = deep_search(t, o, max_t, tu.walk_leaf, tu.split);
   if (sp.team > 1 && o.n > 0 && !reserve_terms(c, o, t->n_snap, &tb))
     return fail(c, G3_ENOMEM, "g3_density: allocation of the terminal list failed");
   Work wk;
@@ -1100,10 +1119,12 @@ int g3_hydro_force(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active,
   Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneHydro, active ? std::min<int64_t>(n_act, o.n) : o.n);
   SphParams sp = sph_params(c, p, t, tu);
-  sp.team = hydro_team(active ? std::min<int64_t>(n_act, o.n) : o.n, t->f64);
+  const int64_t max_t = active ? std::min<int64_t>(n_act, o.n) : o.n;
+  sp.team = hydro_team(max_t, t->f64);
   st = ensure_h64(c, t, o);
   if (st) return st;
   TermBufs tb;
+  tb.deep = deep_search(t, o, max_t, tu.walk_leaf, tu.split);
   if (sp.team > 1 && o.n > 0 && !reserve_terms(c, o, t->n_snap, &tb))
     return fail(c, G3_ENOMEM, "g3_hydro_force: allocation of the terminal list failed");
   Work wk;
@@ -1173,7 +1194,9 @@ int g3_conduction(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active,
   const Tuning tu = tuning_for(c, kTuneHydro, active ? std::min<int64_t>(n_act, o.n) : o.n);
   float4 *ch = (float4 *)scratch(c, kCondCh, (size_t)o.n * sizeof(float4));
   TermBufs tb;
-  const int team = conduction_team(active ? std::min<int64_t>(n_act, o.n) : o.n);
+  const int64_t max_t = active ? std::min<int64_t>(n_act, o.n) : o.n;
+  const int team = conduction_team(max_t);
+  tb.deep = deep_search(t, o, max_t, tu.walk_leaf, tu.split);
   if (!ch || (team > 1 && !reserve_terms(c, o, t->n_snap, &tb)))
     return fail(c, G3_ENOMEM, "g3_conduction: allocation failed");
   Work wk;
@@ -1233,6 +1256,7 @@ int g3_velocity_gradients(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *a
   if (st) return st;
   // (v, h) in sorted order, then the gather search
   hipError_t e = launch_hydro_prep(o, vel, nullptr, h, nullptr, nullptr, 1.0f, 0, s);
+  tb.deep = deep_search(t, o, wk.max_targets, tu.walk_leaf, tu.split);
   if (e == hipSuccess) e = build_terms(o, t->n_snap, tu.walk_leaf, false, tb, s);
   if (e == hipSuccess)
     e = launch_velgrad(o, wk.gs, wk.max_groups, tb.terms(), velgrad_team(wk.max_targets), rho,
@@ -1295,10 +1319,12 @@ int g3_hydro_force_switches(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t 
   Octree &o = t->gas;
   const Tuning tu = tuning_for(c, kTuneHydro, active ? std::min<int64_t>(n_act, o.n) : o.n);
   SphParams sp = sph_params(c, p, t, tu);
-  sp.team = hydro_team(active ? std::min<int64_t>(n_act, o.n) : o.n, true);
+  const int64_t max_t = active ? std::min<int64_t>(n_act, o.n) : o.n;
+  sp.team = hydro_team(max_t, true);
   st = ensure_h64(c, t, o);
   if (st) return st;
   TermBufs tb;
+  tb.deep = deep_search(t, o, max_t, tu.walk_leaf, tu.split);
   if (sp.team > 1 && o.n > 0 && !reserve_terms(c, o, t->n_snap, &tb))
     return fail(c, G3_ENOMEM, "g3_hydro_force_switches: allocation of the terminal list failed");
   float4 *ext = (float4 *)scratch(c, kHydroExt, (size_t)std::max<int64_t>(o.n, 1) * sizeof(float4));
@@ -1397,6 +1423,7 @@ static int tick_forces(g3_ctx *c, g3_tree *t, int64_t n, const g3_state *st,
     rc = prepare_work(c, t, gas, t->iperm_gas, gas.n, nullptr, &wd, s, td.split, nullptr, bins,
                       kmin);
     if (rc) return rc;
+    tb.deep = deep_search(t, gas, gas.n, td.walk_leaf, td.split);
     if (spd.team > 1) e = build_terms(gas, t->n_snap, spd.walk_leaf, false, tb, s);
     if (e == hipSuccess)
       e = launch_density(gas, wd.gs, wd.max_groups, spd, tb.terms(), 1, st->h, st->rho, nullptr,
@@ -1413,6 +1440,7 @@ static int tick_forces(g3_ctx *c, g3_tree *t, int64_t n, const g3_state *st,
     const Tuning th = tuning_for(c, kTuneHydro, gas.n);
     SphParams sp = sph_params(c, p, t, th);
     sp.team = hteam;
+    tb.deep = deep_search(t, gas, gas.n, th.walk_leaf, th.split);
     e = launch_hydro_prep(gas, vh, uh, st->h, st->rho, st->omega, sp.gamma, t->f64, s);
     if (e == hipSuccess) e = sph_radii(t, gas, sp, tb, s);
     if (e != hipSuccess) return hip_fail(c, e, "hydro prep at a tick");
@@ -1703,6 +1731,7 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
             return hipErrorUnknown;
           SphParams sp = sph_params(c, p, t, tu);
           sp.team = density_team(ng, t->f64);
+          tb.deep = deep_search(t, gas, ng, leaf, split);
           if (sp.team > 1) r = build_terms(gas, t->n_snap, sp.walk_leaf, false, tb, s);
           if (r != hipSuccess) return r;
           return launch_density(gas, wk.gs, wk.max_groups, sp, tb.terms(), 1, hs, nullptr,
@@ -1738,6 +1767,7 @@ int g3_autotune(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *active, con
             return hipErrorUnknown;
           SphParams sp = sph_params(c, p, t, tu);
           sp.team = team;
+          tb.deep = deep_search(t, gas, ng, leaf, split);
           const hipError_t r =
               team > 1 ? build_terms(gas, t->n_snap, sp.walk_leaf, true, tb, s) : hipSuccess;
           if (r != hipSuccess) return r;
@@ -1802,6 +1832,7 @@ int g3_density_backward(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t *act
   Octree &o = t->gas;
   if (o.n == 0) return G3_OK;
   TermBufs tb;
+  tb.deep = deep_search(t, o, o.n, kAdjointLeaf, -1);
   if (!reserve_terms(c, o, t->n_snap, &tb))
     return fail(c, G3_ENOMEM, "g3_density_backward: scratch allocation failed");
   Work wk;
@@ -1837,6 +1868,7 @@ int g3_density_solve_backward(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_
   Octree &o = t->gas;
   if (o.n == 0) return G3_OK;
   TermBufs tb;
+  tb.deep = deep_search(t, o, o.n, kAdjointLeaf, -1);
   if (!reserve_terms(c, o, t->n_snap, &tb))
     return fail(c, G3_ENOMEM, "g3_density_solve_backward: scratch allocation failed");
   Work wk;
@@ -1876,6 +1908,7 @@ int g3_hydro_force_backward(g3_ctx *c, g3_tree *t, int64_t n_act, const int32_t 
   const SphParams sp = sph_params(c, p, t, Tuning());
   float4 *up = (float4 *)scratch(c, kAdjSrc, o.n * sizeof(float4));
   TermBufs tb;
+  tb.deep = deep_search(t, o, o.n, kAdjointLeaf, -1);
   if (!up || !reserve_terms(c, o, t->n_snap, &tb))
     return fail(c, G3_ENOMEM, "g3_hydro_force_backward: scratch allocation failed");
   Work wk;

@@ -51,7 +51,7 @@ template <int kT>
 constexpr int kWavesOf = kT > 1 ? kT : 4;
 struct NoLds {};
 
-template <int kT>
+template <int kT, bool kDeep = false>
 __global__ __launch_bounds__(kWavesOf<kT> * kWave, 8) void k_conduction(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const float4 *__restrict__ ch, const int32_t *__restrict__ perm, const Groups gs,
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kWavesOf<kT> * kWave, 8) void k_conduction(
     };
     float sum[1] = {}, cmp[1] = {};
     if constexpr (kT > 1) {
-      team_search(
+      team_search<kT, kDeep>(
           tm, grp.snap, search, xi, hi, tlo, thi, gh,
           [](float h, float hmax) { return h > 0.0f ? sq_exact(fmaxf(h, hmax)) : -1.0f; },
           [&](int ntiles, int count) {
@@ -230,11 +230,15 @@ hipError_t launch_conduction(const Octree &gas, const Groups &gs, int64_t max_gr
                              int walk_leaf, const Terms &tm, int team, const float4 *ch,
                              float *dudt, int32_t *npairs, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = team == 16  ? k_conduction<16>
-              : team == 8 ? k_conduction<8>
-              : team == 4 ? k_conduction<4>
-              : team == 1 ? k_conduction<1>
-                          : nullptr;
+  auto pick = [&](auto deep_c) {
+    constexpr bool d = decltype(deep_c)::value;
+    return team == 16  ? k_conduction<16, d>
+           : team == 8 ? k_conduction<8, d>
+           : team == 4 ? k_conduction<4, d>
+           : team == 1 ? k_conduction<1>
+                       : nullptr;
+  };
+  auto kern = tm.deep ? pick(std::true_type{}) : pick(std::false_type{});
   if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = (team > 1 ? team : 4) * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(

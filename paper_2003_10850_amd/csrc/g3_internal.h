@@ -126,6 +126,7 @@ struct g3_tree {
   double4 *sbox = nullptr;        // device copy of the boxes
   int64_t cap_snap = 0;
   double max_side = 0;            // largest snapshot side
+  int64_t max_members = 0;        // members of the largest snapshot
   int32_t leaf = 8;
   bool built = false;  // false until a build has completed (a failed build leaves it false)
   int32_t f64 = 0;   // positions (and h) are FP64: the mixed-precision path
@@ -273,20 +274,25 @@ inline int64_t max_groups_of(int64_t max_targets, int64_t n_snap) {
 // The terminal nodes of one octree for a walk_leaf: the nodes of at most
 // walk_leaf members (and larger leaves) whose parent holds more, in tree
 // order. They partition the sorted members, so a terminal's member count is
-// the difference of two starts. 64 consecutive terminals form a window.
+// the difference of two starts. 64 consecutive terminals form a window, 64
+// consecutive windows a block (deep lists only).
 struct Terms {
   const float4 *lo, *hi;    // [count + 1] box, lo.w = largest h, hi.w = first
                             // member as bits (entry `count`: the member count)
   const float4 *wlo, *whi;  // windows: box, wlo.w = largest h
   const int2 *range;        // [n_snap] terminals of each snapshot
+  const float4 *blo, *bhi;  // blocks: as the windows (deep lists)
+  bool deep;                // the launch takes the deep search (see team_search)
 };
 
 // Buffers of a terminal list (ctx scratch), taken before a call's launches.
 struct TermBufs {
   int32_t *node = nullptr, *bcount = nullptr, *count = nullptr;
   float4 *lo = nullptr, *hi = nullptr, *wlo = nullptr, *whi = nullptr;
+  float4 *blo = nullptr, *bhi = nullptr;
   int2 *range = nullptr;
-  Terms terms() const { return Terms{lo, hi, wlo, whi, range}; }
+  bool deep = false;
+  Terms terms() const { return Terms{lo, hi, wlo, whi, range, blo, bhi, deep}; }
 };
 // False when the scratch cannot be had.
 bool reserve_terms(g3_ctx *c, const Octree &o, int n_snap, TermBufs *b);

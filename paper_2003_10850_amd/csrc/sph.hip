@@ -27,8 +27,10 @@ struct NoLds {};
 // density with FP64 positions: 137 registers hold 3; 11.8 ms for the 2^20 gas
 // particles of a clustered 2^21 box, 9.7, 8.7 and 8.0 held to 4, 5 and 6, though
 // some are spilled around the passes.
-template <bool kF64, int kT>
-constexpr int kDensityWaves = kT == 16 ? 1 : (kF64 && kT == 8 ? 4 : 6);
+// The deep search needs the registers of 4 waves: held to 6, the compiler spills the
+// targets' ids for the lanes without a guess alone (tests/test_spills.py).
+template <bool kF64, int kT, bool kDeep>
+constexpr int kDensityWaves = kT == 16 ? 1 : (kDeep || (kF64 && kT == 8) ? 4 : 6);
 template <bool kF64, bool kExt, int kT>
 constexpr int kHydroWaves = kExt ? 1 : (!kF64 && kT < 16 ? 6 : (kF64 && kT == 1 ? 5 : 1));
 
@@ -116,8 +118,8 @@ constexpr float kFineExt = 1.0f;
 // four waves; held to 6 waves a SIMD: 6.9 ms at the 4 that 120 registers
 // allow); 7.1, 8.1 and 14 with teams of 8, 12 and 16. 2^17: 2.9, 2.2, 2.1 and
 // 2.7 ms with teams; 2^15 gas particles: 7.0, 2.5, 1.7, 1.4 and 1.7 ms.
-template <bool kF64, int kT>
-__global__ __launch_bounds__(kBlockOf<kT>, (kDensityWaves<kF64, kT>)) void k_density(
+template <bool kF64, int kT, bool kDeep = false>
+__global__ __launch_bounds__(kBlockOf<kT>, (kDensityWaves<kF64, kT, kDeep>)) void k_density(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const int32_t *__restrict__ perm, const Groups gs,
     const Terms tm, float n_ngb, float tol, int solve, int max_iter, int walk_leaf,
@@ -362,7 +364,7 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kDensityWaves<kF64, kT>)) void k_den
     };
     if constexpr (kT > 1) {
       float ts = 0.0f, tcmp = 0.0f;  // this wave's component of the totals
-      team_search<kTeam>(
+      team_search<kTeam, kDeep>(
           tm, grp.snap, search, xi, hw2, tlo, thi, hmax2,
           [](float want2, float) { return want2; },
           [&](int ntiles, int count) {
@@ -623,7 +625,7 @@ struct ExtTile {
 // and the entry's h^-5 in every pair took, 1.53 of 1.66 with the switches at
 // 2.5e5 targets. Bound by vector
 // issue on a full chip, by the slowest groups otherwise.
-template <bool kF64, bool kExt, int kT>
+template <bool kF64, bool kExt, int kT, bool kDeep = false>
 __global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k_hydro(
     const Node *__restrict__ nodes, const float4 *__restrict__ xm,
     const double4 *__restrict__ x64, const double *__restrict__ h64,
@@ -881,7 +883,7 @@ __global__ __launch_bounds__(kBlockOf<kT>, (kHydroWaves<kF64, kExt, kT>)) void k
 
   if constexpr (kT > 1) {
     float ts = 0.f, tcmp = 0.f;  // this wave's component of the totals
-    team_search<kTeam>(
+    team_search<kTeam, kDeep>(
         tm, grp.snap, search, xi, hi, tlo, thi, gh,
         [&](float h, float hmax) {
           // a lane without a target (-1) reaches nothing
@@ -975,17 +977,22 @@ hipError_t launch_density(const Octree &gas, const Groups &gs, int64_t max_group
                           float *drho_dh, float *omega, int32_t *nngb,
                           unsigned long long *counters, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = sp.f64 ? (sp.team == 16  ? k_density<true, 16>
-                        : sp.team == 8 ? k_density<true, 8>
-                        : sp.team == 4 ? k_density<true, 4>
-                        : sp.team == 1 ? k_density<true, 1>
-                                       : nullptr)
-                     : (sp.team == 16   ? k_density<false, 16>
-                        : sp.team == 12 ? k_density<false, 12>
-                        : sp.team == 8  ? k_density<false, 8>
-                        : sp.team == 4  ? k_density<false, 4>
-                        : sp.team == 1  ? k_density<false, 1>
-                                        : nullptr);
+  auto pick = [&](auto deep_c) {
+    constexpr bool d = decltype(deep_c)::value;
+    if (sp.f64)
+      return sp.team == 16  ? k_density<true, 16, d>
+             : sp.team == 8 ? k_density<true, 8, d>
+             : sp.team == 4 ? k_density<true, 4, d>
+             : sp.team == 1 ? k_density<true, 1>
+                            : nullptr;
+    return sp.team == 16   ? k_density<false, 16, d>
+           : sp.team == 12 ? k_density<false, 12, d>
+           : sp.team == 8  ? k_density<false, 8, d>
+           : sp.team == 4  ? k_density<false, 4, d>
+           : sp.team == 1  ? k_density<false, 1>
+                           : nullptr;
+  };
+  auto kern = tm.deep ? pick(std::true_type{}) : pick(std::false_type{});
   if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = (sp.team > 1 ? sp.team : 4) * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(
@@ -1017,25 +1024,29 @@ hipError_t launch_hydro(const Octree &gas, const Groups &gs, int64_t max_groups,
                         float *vsig, int32_t *npairs, hipStream_t s, const float4 *ext,
                         float alpha_u) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto pick = [&](auto f64_c, auto ext_c) {
+  auto pick = [&](auto f64_c, auto ext_c, auto deep_c) {
     constexpr bool f = decltype(f64_c)::value, e = decltype(ext_c)::value;
+    constexpr bool d = decltype(deep_c)::value;
     if constexpr (!f && !e)
-      return sp.team == 16   ? k_hydro<f, e, 16>
-             : sp.team == 12 ? k_hydro<f, e, 12>
-             : sp.team == 8  ? k_hydro<f, e, 8>
+      return sp.team == 16   ? k_hydro<f, e, 16, d>
+             : sp.team == 12 ? k_hydro<f, e, 12, d>
+             : sp.team == 8  ? k_hydro<f, e, 8, d>
              : sp.team == 1  ? k_hydro<f, e, 1>
                              : nullptr;
     else
-      return sp.team == 16  ? k_hydro<f, e, 16>
-             : sp.team == 8 ? k_hydro<f, e, 8>
-             : sp.team == 4 ? k_hydro<f, e, 4>
+      return sp.team == 16  ? k_hydro<f, e, 16, d>
+             : sp.team == 8 ? k_hydro<f, e, 8, d>
+             : sp.team == 4 ? k_hydro<f, e, 4, d>
              : sp.team == 1 ? k_hydro<f, e, 1>
                             : nullptr;
   };
+  auto pick_deep = [&](auto f64_c, auto ext_c) {
+    return tm.deep ? pick(f64_c, ext_c, std::true_type{}) : pick(f64_c, ext_c, std::false_type{});
+  };
   const std::true_type yes;
   const std::false_type no;
-  auto kern = sp.f64 ? (ext ? pick(yes, yes) : pick(yes, no))
-                     : (ext ? pick(no, yes) : pick(no, no));
+  auto kern = sp.f64 ? (ext ? pick_deep(yes, yes) : pick_deep(yes, no))
+                     : (ext ? pick_deep(no, yes) : pick_deep(no, no));
   if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = (sp.team > 1 ? sp.team : 4) * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, sp.team), block, 0, s>>>(

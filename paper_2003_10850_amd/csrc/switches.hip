@@ -28,7 +28,7 @@ struct VelTile {
 // neighbour test; each wave keeps the totals of its own tiles. 64 registers
 // (8 waves a SIMD) are worth 5% where groups are plenty. 2.5e5 targets: 2024 us
 // with one wave a group, 687 so; 4.2e6: 8495 and 8133.
-template <int kT>
+template <int kT, bool kDeep = false>
 __global__ __launch_bounds__(kT * kWave, 8) void k_velgrad(
     const float4 *__restrict__ xm, const float4 *__restrict__ vh,
     const int32_t *__restrict__ perm, const Groups gs, const Terms tm,
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_velgrad(
       wave_sync();
     };
 
-    team_search(
+    team_search<kT, kDeep>(
         tm, grp.snap, search, xi, hi > 0.0f ? hi2 : -1.0f, tlo, thi, hmax2,
         [](float want2, float) { return want2; },
         [&](int ntiles, int count) {
@@ -195,10 +195,14 @@ hipError_t launch_velgrad(const Octree &gas, const Groups &gs, int64_t max_group
                           const Terms &tm, int team, const float *rho, const float *omega,
                           float *div_v, float *curl_v, hipStream_t s) {
   if (max_groups <= 0 || gas.nnodes == 0) return hipSuccess;
-  auto kern = team == 16  ? k_velgrad<16>
-              : team == 8 ? k_velgrad<8>
-              : team == 4 ? k_velgrad<4>
-                          : nullptr;
+  auto pick = [&](auto deep_c) {
+    constexpr bool d = decltype(deep_c)::value;
+    return team == 16  ? k_velgrad<16, d>
+           : team == 8 ? k_velgrad<8, d>
+           : team == 4 ? k_velgrad<4, d>
+                       : nullptr;
+  };
+  auto kern = tm.deep ? pick(std::true_type{}) : pick(std::false_type{});
   if (!kern) return hipErrorInvalidValue;  // (no such team)
   const int block = team * kWave;
   kern<<<persistent_grid((const void *)kern, block, max_groups, team), block, 0, s>>>(

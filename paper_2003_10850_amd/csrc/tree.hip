@@ -894,6 +894,33 @@ __global__ __launch_bounds__(kFillBlock) void k_term_small(
   fill_windows(nodes, tnode, n, vh, m, lo, hi, wlo, whi, S);
 }
 
+// Boxes and largest h of the blocks, a wave each.
+__global__ __launch_bounds__(kWave) void k_term_blocks(const int32_t *__restrict__ tcount,
+                                                       const float4 *__restrict__ wlo,
+                                                       const float4 *__restrict__ whi,
+                                                       float4 *__restrict__ blo,
+                                                       float4 *__restrict__ bhi) {
+  const int nw = (*tcount + kWave - 1) / kWave, lane = (int)threadIdx.x;
+  for (int b = (int)blockIdx.x; b * kWave < nw; b += (int)gridDim.x) {
+    const int k = min(b * kWave + lane, nw - 1);
+    float4 a = wlo[k], c = whi[k];
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      a.x = fminf(a.x, __shfl_xor(a.x, d));
+      a.y = fminf(a.y, __shfl_xor(a.y, d));
+      a.z = fminf(a.z, __shfl_xor(a.z, d));
+      a.w = fmaxf(a.w, __shfl_xor(a.w, d));
+      c.x = fmaxf(c.x, __shfl_xor(c.x, d));
+      c.y = fmaxf(c.y, __shfl_xor(c.y, d));
+      c.z = fmaxf(c.z, __shfl_xor(c.z, d));
+    }
+    if (lane == 0) {
+      blo[b] = a;
+      bhi[b] = c;
+    }
+  }
+}
+
 // The gravity walk's node copies (after the moments): every internal node
 // writes its children's, a root also its own.
 __global__ void k_cnodes(const Node *__restrict__ nodes, const double4 *__restrict__ c64,
@@ -1195,7 +1222,7 @@ hipError_t refit_hmax(Octree &o, hipStream_t s) {
 
 bool reserve_terms(g3_ctx *c, const Octree &o, int n_snap, TermBufs *b) {
   const size_t nn = (size_t)o.nnodes, nw = nn / kWave + 2, nb = nn / kTermTile + 2;
-  const size_t f4 = 2 * (nn + 1) + 2 * nw;
+  const size_t nblocks = nw / kWave + 1, f4 = 2 * (nn + 1) + 2 * nw + 2 * nblocks;
   char *p = (char *)scratch(c, kTermBuf, f4 * sizeof(float4) + (size_t)n_snap * sizeof(int2) +
                                              (nn + nb + 4) * sizeof(int32_t));
   if (!p) return false;
@@ -1203,7 +1230,9 @@ bool reserve_terms(g3_ctx *c, const Octree &o, int n_snap, TermBufs *b) {
   b->hi = b->lo + nn + 1;
   b->wlo = b->hi + nn + 1;
   b->whi = b->wlo + nw;
-  b->range = (int2 *)(b->whi + nw);
+  b->blo = b->whi + nw;
+  b->bhi = b->blo + nblocks;
+  b->range = (int2 *)(b->bhi + nblocks);
   b->node = (int32_t *)(b->range + n_snap);
   b->bcount = b->node + nn;
   b->count = b->bcount + nb;
@@ -1218,15 +1247,18 @@ hipError_t build_terms(const Octree &o, int n_snap, int walk_leaf, bool with_h, 
     k_term_small<<<1, kFillBlock, 0, s>>>(o.nodes, o.tcode, nn, walk_leaf, o.nroot, n_snap,
                                           with_h ? o.vh : nullptr, (int)o.n, b.count, b.range,
                                           b.lo, b.hi, b.wlo, b.whi);
-    return hipGetLastError();
+  } else {
+    const unsigned nb = (unsigned)((nn + kTermTile - 1) / kTermTile);
+    k_term_count<<<nb, kBlock, 0, s>>>(o.tcode, nn, walk_leaf, b.bcount);
+    k_term_write<<<nb, kBlock, 0, s>>>(o.tcode, nn, walk_leaf, b.bcount, o.nroot, n_snap, b.node,
+                                       b.count, b.range);
+    const unsigned nf = (unsigned)std::min<int64_t>((nn + kWave - 1) / kWave, 512);
+    k_term_fill<<<nf, kFillBlock, 0, s>>>(o.nodes, b.node, b.count, with_h ? o.vh : nullptr,
+                                          (int)o.n, b.lo, b.hi, b.wlo, b.whi);
   }
-  const unsigned nb = (unsigned)((nn + kTermTile - 1) / kTermTile);
-  k_term_count<<<nb, kBlock, 0, s>>>(o.tcode, nn, walk_leaf, b.bcount);
-  k_term_write<<<nb, kBlock, 0, s>>>(o.tcode, nn, walk_leaf, b.bcount, o.nroot, n_snap, b.node,
-                                     b.count, b.range);
-  const unsigned nf = (unsigned)std::min<int64_t>((nn + kWave - 1) / kWave, 512);
-  k_term_fill<<<nf, kFillBlock, 0, s>>>(o.nodes, b.node, b.count, with_h ? o.vh : nullptr,
-                                        (int)o.n, b.lo, b.hi, b.wlo, b.whi);
+  if (b.deep)
+    k_term_blocks<<<(unsigned)(nn / (kWave * kWave) + 1), kWave, 0, s>>>(b.count, b.wlo, b.whi,
+                                                                         b.blo, b.bhi);
   return hipGetLastError();
 }
 

@@ -1,5 +1,12 @@
-"""The density by single waves that walk the octree, where groups are plenty, and
-the lists of small trees.
+"""The ways a group's neighbours are found beside the plain team search (a wave
+that walks the octree by itself, the deep search of long lists and of few targets
+among many members, lists at the ends of walk_leaf, lists of small trees), at the
+sizes where they can go wrong, against the oracle.
+
+Tolerances: counts exact; the density within 2e-6 of the FP64 sums (FP32 terms
+of one sign, each good to a few 1e-7, added with compensation), accelerations,
+rates and gradients within 1e-5 of the L1 sum of their terms, as the parity tests
+have.
 """
 import dataclasses
 
@@ -17,6 +24,124 @@ BOX = (0.0, 0.0, 0.0, 1.0)
 
 def dev_t(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def gas_set(kind, n, rng):
+    pos = rng.random((n, 3))
+    if kind == "halo":
+        pos = np.clip(0.5 + 0.05 * rng.normal(0, 1, (n, 3)), 0.0, 1.0 - 1e-6)
+    elif kind == "line":
+        pos[:, 1:] = 0.5 + 1e-2 * (pos[:, 1:] - 0.5)
+    return pos
+
+
+# deep by the targets: 64 or a few thousand of 2e5 (terminals of 16 and 64
+# members: 2 to 7 blocks); deep by the list: all of them with terminals of 4; not
+# deep: terminals of up to 4096 members, nodes of more than 65535; deep in a tree
+# of fewer than 2048 nodes
+@pytest.mark.parametrize("kind,n,sizes,leaf,few,fp64", [
+    ("uniform", 200000, None, 16, 1, False), ("uniform", 200000, None, 16, 64, False),
+    ("uniform", 200000, None, 64, 3001, False), ("line", 200000, None, 16, 200, False),
+    ("uniform", 200000, None, 16, 130, True), ("uniform", 200000, None, 4, None, False),
+    ("uniform", 200000, None, 4, None, True), ("uniform", 190011, [10, 100000, 1, 90000], 2, 900, False),
+    ("uniform", 190011, [10, 100000, 1, 90000], 2, None, False),
+    ("uniform", 140000, None, 4096, None, False), ("uniform", 3000, None, 1, 40, False)])
+def test_searches_against_oracle(kind, n, sizes, leaf, few, fp64):
+    from paper_2003_10850_amd import g3, ops
+    print(f"search {kind} n={n} leaf={leaf} few={few} fp64={fp64}", flush=True)
+    rng = np.random.default_rng(n + leaf)
+    ft = np.float64 if fp64 else np.float32
+    pos = gas_set(kind, n, rng).astype(ft)
+    mass = np.full(n, 1.0 / n, np.float32)
+    vel = rng.normal(0, 0.1, (n, 3)).astype(np.float32)
+    u, rho, om = [rng.uniform(0.5, 1.5, n).astype(np.float32) for _ in range(3)]
+    h = (2.2 * n ** (-1.0 / 3.0) * rng.uniform(0.7, 1.3, n)).astype(ft)
+    if kind == "line":
+        h *= 0.1
+    off = [0, n] if sizes is None else list(np.concatenate([[0], np.cumsum(sizes)]))
+    p = inputs.Params(n_ngb=48.0)
+    c = ops.Context(torch.device("cuda", 0))
+    for k in (g3.G3_TUNE_DENSITY, g3.G3_TUNE_HYDRO):
+        c.set_tuning(k, leaf, -1)
+    tree = ops.Tree(c, dev_t(pos), dev_t(mass), None, BOX if sizes is None else [BOX] * len(sizes),
+                    p, snap_off=None if sizes is None else off)
+    act = np.arange(n) if few is None else np.sort(rng.choice(n, few, replace=False))
+    a = None if few is None else dev_t(act.astype(np.int32))
+    got = dict(ops.density(tree, h=dev_t(h), active=a, solve_h=False))
+    got |= {"f_" + k: v for k, v in ops.hydro_force(
+        tree, dev_t(vel), dev_t(u), dev_t(h), dev_t(rho), dev_t(om), active=a).items()}
+    if not fp64:
+        got |= {"c_" + k: v for k, v in ops.conduction(
+            tree, dev_t(u), dev_t(h), dev_t(rho), 1.0, 0.0, active=a).items()}
+        got |= {"v_" + k: v for k, v in ops.velocity_gradients(
+            tree, dev_t(vel), dev_t(h), dev_t(rho), dev_t(om), active=a).items()}
+    got = {k: v.cpu().numpy() for k, v in got.items()}
+    pr = dataclasses.replace(p, flags=oracle.FLAG_FP64_DECISIONS if fp64 else 0)
+    for lo, hi in zip(off[:-1], off[1:]):
+        r = slice(lo, hi)
+        ids = act[(act >= lo) & (act < hi)] - lo
+        if ids.size == 0:
+            continue
+        ids = ids if ids.size < 20000 else np.sort(rng.choice(ids, 20000, replace=False))
+        t = oracle.Tree(pos[r].astype(np.float64), mass[r].astype(np.float64), BOX, gas_only=True,
+                        type=np.zeros(hi - lo, np.uint8))
+        H = h[r].astype(np.float64)
+
+        def rel(key, ref, val, S):
+            d = got[key][r][ids] - ref[val][ids]
+            e = np.linalg.norm(d.reshape(len(ids), -1), axis=1)
+            s = ref[S][ids]
+            assert (e[s > 0] / s[s > 0]).max(initial=0) < 1e-5, key
+
+        ref = oracle.density(t, pr, active=ids, h=H, solve_h=False)
+        np.testing.assert_array_equal(got["nngb"][r][ids], ref["nngb"][ids])
+        assert (np.abs(got["rho"][r][ids] / ref["rho"][ids] - 1.0)).max() < 2e-6
+        ref = oracle.hydro(t, pr, vel[r], u[r], H, rho[r], om[r], active=ids)
+        np.testing.assert_array_equal(got["f_npairs"][r][ids], ref["npairs"][ids])
+        rel("f_acc", ref, "acc", "S")
+        if not fp64:
+            ref = oracle.conduction(t, pr, u[r], H, rho[r], 1.0, 0.0, active=ids)
+            np.testing.assert_array_equal(got["c_npairs"][r][ids], ref["npairs"][ids])
+            rel("c_dudt", ref, "dudt", "S")
+
+
+@pytest.mark.parametrize("kind,leaf,few,fp64", [
+    ("uniform", 16, 1, False), ("uniform", 64, 3000, False), ("halo", 16, 2500, False),
+    ("halo", 64, 65, False), ("line", 16, 700, False), ("halo", 16, 1500, True),
+    ("line", 64, 130, True)])
+def test_the_deep_search_has_the_bits_of_the_plain_one(kind, leaf, few, fp64):
+    # few targets of the first snapshot take the deep search, with the members of
+    # the second one (whose groups are others) beside them the plain one
+    from paper_2003_10850_amd import g3, ops
+    print(f"deep {kind} leaf={leaf} few={few} fp64={fp64}", flush=True)
+    m, pad = 200000, 20000
+    n = m + pad
+    rng = np.random.default_rng(leaf + few)
+    ft = np.float64 if fp64 else np.float32
+    pos = np.concatenate([gas_set(kind, m, rng), rng.random((pad, 3))]).astype(ft)
+    h = (2.2 * m ** (-1.0 / 3.0) * rng.uniform(0.7, 1.3, n)).astype(ft)
+    h *= dict(uniform=1.0, halo=0.4, line=0.1)[kind]
+    c = ops.Context(torch.device("cuda", 0))
+    for k in (g3.G3_TUNE_DENSITY, g3.G3_TUNE_HYDRO):
+        c.set_tuning(k, leaf, -1)
+    tree = ops.Tree(c, dev_t(pos), dev_t(np.full(n, 1.0 / m, np.float32)), None, [BOX] * 2,
+                    inputs.Params(n_ngb=48.0), snap_off=[0, m, n])
+    g = torch.Generator(device="cuda").manual_seed(2)
+    R = lambda *s: torch.rand(*s, generator=g, device="cuda")
+    vel, u, rho, om, hh = R(n, 3) - 0.5, 0.5 + R(n), 0.5 + R(n), 0.5 + R(n), dev_t(h)
+    ids = np.sort(rng.choice(m, few, replace=False)).astype(np.int32)
+    sets = [dev_t(ids), dev_t(np.concatenate([ids, np.arange(m, n, dtype=np.int32)]))]
+    at = sets[0].long()
+    calls = [lambda a: ops.density(tree, h=hh, active=a, solve_h=False),
+             lambda a: ops.density(tree, h=hh, active=a),
+             lambda a: ops.hydro_force(tree, vel, u, hh, rho, om, active=a)]
+    for call in calls:
+        x, y = [call(a) for a in sets]
+        for k in x:
+            assert torch.equal(x[k][at], y[k][at]), k
+    if not fp64:
+        x, y = [ops.conduction(tree, u, hh, rho, 1.0, 0.0, active=a) for a in sets]
+        assert torch.equal(x["npairs"][at], y["npairs"][at])
 
 
 @pytest.mark.parametrize("pad", [(), (0, 9, 1)])
