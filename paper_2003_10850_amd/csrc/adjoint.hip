@@ -465,8 +465,9 @@ __device__ __forceinline__ bool open_accept(float l, float theta2, float r2) {
 // reduction (16 and three LDS permutes before the half-wave swaps; sums by
 // the matrix cores, one-hot rows times the values, came to 4.8 ms, the FP32
 // products do not overlap), 3 the fixed-point conversion of 16 entries at
-// once; the atomics cost 0.3 ms. 5e5 targets of a clustered box: 3.95 ms with
-// one wave a group, 3.6 with teams of 4; 2^14 targets: 1.5 and 0.25 of 16.
+// once; the atomics cost 0.3 ms. 5e5 targets of a clustered box: 3.6 ms with one
+// wave a group, 3.4 with teams of 4; 2^22: 24.5 and 27.6 (24.6 with the preorder
+// walk before the items); 2^14 targets: 1.5 and 0.23 with teams of 16.
 template <bool kFixed, bool kInside, int kT>
 __global__ __launch_bounds__(kT * kWave, kT < 16 ? 6 : 1) void k_gravity_bwd(
     const CNode *__restrict__ cnodes, const uint64_t *__restrict__ ckeys,
@@ -1087,13 +1088,15 @@ hipError_t launch_gravity_bwd(const Octree &all, const Groups &gs, int64_t max_g
                               double *rr, float *g_pos, float *g_mass, hipStream_t s) {
   const int64_t m = all.n, nn = all.nnodes;
   if (m == 0 || nn == 0) return hipSuccess;
-  if (!all.cnodes || (gp.team != 16 && gp.team != 8 && gp.team != 4)) return hipErrorInvalidValue;
+  if (!all.cnodes || (gp.team != 16 && gp.team != 8 && gp.team != 4 && gp.team != 1))
+    return hipErrorInvalidValue;
   const int64_t na = active ? n_act : m;
   auto pick = [&](auto fixed_c) {
     constexpr bool f = decltype(fixed_c)::value;
     if (gp.team == 16) return gp.inside_test ? k_gravity_bwd<f, true, 16> : k_gravity_bwd<f, false, 16>;
     if (gp.team == 8) return gp.inside_test ? k_gravity_bwd<f, true, 8> : k_gravity_bwd<f, false, 8>;
-    return gp.inside_test ? k_gravity_bwd<f, true, 4> : k_gravity_bwd<f, false, 4>;
+    if (gp.team == 4) return gp.inside_test ? k_gravity_bwd<f, true, 4> : k_gravity_bwd<f, false, 4>;
+    return gp.inside_test ? k_gravity_bwd<f, true, 1> : k_gravity_bwd<f, false, 1>;
   };
   const int block = gp.team * kWave;
   if (gp.eps2 > 0.0f) {

@@ -468,24 +468,34 @@ int hydro_team(int64_t max_targets, bool wide) {
   if (wide) return groups <= 768 ? 16 : (groups <= 3072 ? 8 : 4);
   return groups <= 320 ? 16 : (groups <= 3072 ? 12 : 8);
 }
-// Gravity and its adjoint with it (us, clustered sets):
-//   groups           64   256   512  1024  2048  3125  4096  8192  16384  32768
-//   FP32        4   158   197   209   307   565   717   819  1329   2282   4320
-//               8    99   121   155   273   421   535   678  1201   2243   4353
-//              16    77    90   131   212   352   520   661  1280   2496   5000
+// Gravity (us, clustered sets):
+//   groups           64   256   512  1024  2048  3072  4096  8192  16384  24576
+//   FP32        4   118   158   210   312   556   654   793  1230   2121   3076
+//               8    79   100   159   267   379   487   601  1098   2044   3056
+//              16    64    78   131   197   322   460   600  1190   2379   3621
+//   (last column: 32768 groups)
 //   FP64        4   216   282   307   384   694   936  1067  1830   3335   6496
 //               8   129   166   203   324   531   748   910  1708   3294   6524
 //              16    94   117   171   275   479   733   925  1816   3583   7316
-//   adjoint     4   555   705   794  1026  1681  2311  2827  4989   9388  18506
-//               8   378   463   604   946  1509  2196  2799  5276  10461  20989
-//              16   300   362   575   966  1708  2587  3362  6696  13502  27879
 int gravity_team(int64_t max_targets) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
   return groups <= 3584 ? 16 : (groups <= 20480 ? 8 : 4);
 }
+// Its adjoint (us; clustered sets, then uniform ones):
+//   groups         64  256  320  512  768 1024 1536 2048 3072 4096 8192 12288 16384 65536
+//   none                                         1500 1932 2359 3808  5398  6791 24470
+//            4    271  393  421  483  529  643  864 1082 1490 1873 3559  5246  6914 27620
+//            8    198  271  325  383  471  624  848 1073 1530 2057 4010  5982  7992 32580
+//           16    151  231  328  398  547  695 1008 1311 1971 2628 5293  7998 10740
+//   uniform none                                 1272 1612 1982 3336  4487  5533 20540
+//            4    259  340  351  423  505  612  760  899 1239 1583 3015  4345  5741 24090
+//            8    181  239  263  339  450  552  731  937 1330 1757 3472  5114  6823 28840
+//           16    152  220  281  368  484  637  890 1155 1690 2290 4594  6777  9075
+// A wave's own list of items needs no barriers: with a full chip it is the best.
 int gravity_bwd_team(int64_t max_targets) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
-  return groups <= 768 ? 16 : (groups <= 4096 ? 8 : 4);
+  if (groups > 14336) return 1;
+  return groups <= 320 ? 16 : (groups <= 1920 ? 8 : 4);
 }
 // The SPH adjoints, conduction and velocity gradients, as the density (us of
 // one density solve and hydro force with their gradients, and of one pass of

@@ -401,7 +401,7 @@ struct GravParams {
   int inside_test;  // evaluate the cube-containment test (theta^2 >= 1/3)
   int f64;          // FP64 positions: mixed-precision kernels, FP64 decisions
   double theta;     // opening angle (FP64 decisions)
-  int team = 4;     // forward: waves that serve one group together (4 or 16)
+  int team = 4;     // waves that serve one group together: 4, 8 or 16, the adjoint also 1
 };
 hipError_t launch_gravity(const Octree &all, const Groups &gs, int64_t max_groups,
                           const GravParams &gp, float *acc, float *pot, int32_t *nterms,

@@ -1,7 +1,7 @@
 """The ways a group's neighbours are found beside the plain team search (a wave
 that walks the octree by itself, the deep search of long lists and of few targets
-among many members, lists at the ends of walk_leaf, lists of small trees), at the
-sizes where they can go wrong, against the oracle.
+among many members, lists at the ends of walk_leaf), at the sizes where they can
+go wrong, against the oracle; and the gravity adjoint without teams.
 
 Tolerances: counts exact; the density within 2e-6 of the FP64 sums (FP32 terms
 of one sign, each good to a few 1e-7, added with compensation), accelerations,
@@ -209,3 +209,29 @@ def test_density_without_a_team_has_the_same_bits(fp64):
     for k in a:
         assert torch.equal(a[k][at], b[k][at]), k
     assert c.nonconverged() == 0
+
+
+@pytest.mark.parametrize("theta,eps", [(0.5, 1e-3), (0.8, 1e-3), (0.6, 0.0)])
+def test_gravity_adjoint_without_a_team_adds_up(theta, eps):
+    # the gradients are linear in the upstream ones: all of 10^6 targets (no team)
+    # against two halves in tree order (teams of 4, the same groups), 1e-5 of the
+    # largest (sums of a few hundred FP32 terms that cancel in part)
+    from paper_2003_10850_amd import ops
+    n = 1000000
+    g = torch.Generator(device="cuda").manual_seed(9)
+    R = lambda *s: torch.rand(*s, generator=g, device="cuda")
+    pos, mass = R(n, 3), (0.5 + R(n)) / n
+    c = ops.Context(torch.device("cuda", 0))
+    tree = ops.Tree(c, pos, mass, None, BOX, inputs.Params(n_ngb=16.0, theta=theta, eps=eps))
+    x = [pos.clone().requires_grad_(True), mass.clone().requires_grad_(True)]
+    ups = (R(n, 3) - 0.5, R(n) - 0.5)
+    order = tree.export(0)["order"]
+
+    def grads(active):
+        f = ops.gravity_ad(tree, x[0], x[1], active=active)
+        return torch.autograd.grad(f, x, ups)
+
+    cut = 64 * (n // 128)
+    halves = [grads(torch.sort(q).values) for q in (order[:cut], order[cut:])]
+    for a, b, s in zip(*halves, grads(None)):
+        assert (a + b - s).abs().max() <= 1e-5 * s.abs().max()

@@ -82,7 +82,7 @@ def velgrad(lib, team):
     (lambda l, t: hydro(l, 1, t, True), {1, 4, 8, 16}),
     (lambda l, t: gravity(l, 0, t), {4, 8, 16}),
     (lambda l, t: gravity(l, 1, t), {4, 8, 16}),
-    (lambda l, t: gravity_bwd(l, 0, t), {4, 8, 16}),
+    (lambda l, t: gravity_bwd(l, 0, t), {1, 4, 8, 16}),
     (lambda l, t: conduction(l, t), {1, 4, 8, 16}),
     (lambda l, t: velgrad(l, t), {4, 8, 16})])
 def test_teams_without_a_kernel_are_refused(lib, call, teams):
@@ -93,7 +93,7 @@ def test_teams_without_a_kernel_are_refused(lib, call, teams):
 @pytest.mark.parametrize("rule,args,teams", [
     ("density_team", (0, 1), {1, 4, 8, 12, 16}), ("density_team", (1, 0), {1, 4, 8, 16}),
     ("hydro_team", (0,), {1, 8, 12, 16}), ("hydro_team", (1,), {1, 4, 8, 16}),
-    ("gravity_team", (), {4, 8, 16}), ("gravity_bwd_team", (), {4, 8, 16}),
+    ("gravity_team", (), {4, 8, 16}), ("gravity_bwd_team", (), {1, 4, 8, 16}),
     ("adjoint_team", (), {4, 8, 16}), ("velgrad_team", (), {4, 8, 16}),
     ("conduction_team", (), {1, 4, 8, 16})])
 def test_the_rules_name_teams_that_have_a_kernel(lib, rule, args, teams):
