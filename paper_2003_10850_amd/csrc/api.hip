@@ -419,7 +419,7 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
 }
 
 // Waves of a team from the host's bound on the targets. Measured (us, cold
-// density solve and hydro force of clustered sets):
+// density solve of clustered sets):
 //   groups          256   512  1024  2048  3125  4096  8192  16384
 //   density    4   1568  2474  2474  2958  2950  3629  4499   6054
 //              8   1141  1646  1845  2352  2781  3331  4829   7097
@@ -428,13 +428,6 @@ int prepare_work(g3_ctx *c, const g3_tree *t, const Octree &o, const int32_t *ip
 //   FP64       4   2978  4268  4306  4402  4910  5835  6173   8006
 //              8   1702  2458  2684  3443  4458  5292  7784  11795
 //             16   1214  2064  2511  3567  5242  6375 10907  17699
-//   hydro   none         4203        2675        2294  2440   3610
-//              8    399   608   955   980  1182  1346  2133   3781
-//             12    337   501   815   930  1170  1380  2320   4182
-//             16    340   513  1071  1350  1790  2186  3978   7374
-//   FP64       4    776  1126  1642  1595  1711  1971  2844   4942
-//              8    472   703  1222  1327  1626  1933  3187   5741
-//             16    406   621  1305  1667  2177  2673  4843   8964
 // With fewer groups than CUs the time is that of the slowest group, which the
 // widest team serves fastest; later the number of waves that a CU holds counts
 // (teams of 12 in 80 registers: 24, of 16 in 107: 16). Where every CU has a
@@ -460,13 +453,34 @@ int density_team(int64_t max_targets, int f64, bool solve) {
   if (f64) return groups <= 1280 ? 16 : (groups <= 4608 ? 8 : 4);
   return groups <= 320 ? 16 : (groups <= 3072 ? 12 : (groups <= 6144 ? 8 : 4));
 }
+// Hydro force (us; clustered sets at 295 neighbours, then uniform ones at 64):
+//   groups           64   128   256   320   512   768  1024  2048  3072  4096  8192 12288 16384
+//   FP32   none                                             3209  2093  2003  2427  3006  3589
+//              8    176   246   334   391   415   533   630   982   990  1171  2048  2895  3704
+//             12    159   209   276   324   367   454   582   855   953  1194  2181  3118  4080
+//             16    156   205   275   338   390   547   685  1142  1437  1877  3651  5308  6963
+//   switches none                                           3755  2520  2266  2796  3424  4044
+//              4    301   454   606   688   702   881  1054  1472  1342  1524  2511  3406  4380
+//              8    213   300   409   482   498   665   807  1251  1326  1625  2961  4177  5419
+//             16    200   259   350   427   496   687   867  1421  1770  2279  4386  6345  8315
+//   FP64       4                776        1126        1642  1711        1971  2844        4942
+//              8                472         703        1222  1626        1933  3187        5741
+//             16                406         621        1305  2177        2673  4843        8964
+//   FP32,  none                                              602   851  1068  1681  2100  2379
+//   uniform    8    111   107   119   129   181   242   269   361   466   579   932  1353  1655
+//             12     92    98   117   130   179   195   224   317   423   539   934  1377  1684
+//             16    105   101   114   128   158   190   212   358   533   769  1302  1912  2586
+//   switches,  none                                          640   859  1086  1661  2013  2379
+//   uniform    4    137   141   151   156   194   258   316   391   517   651  1047  1378  1756
+//              8    120   121   126   141   188   222   233   344   463   622  1039  1480  1960
+//             16    116   117   127   148   178   218   245   415   621   887  1493  2218  3034
 // (wide: FP64 positions or the switches' inputs, whose LDS and registers hold
 // fewer waves a CU)
 int hydro_team(int64_t max_targets, bool wide) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
   if (groups > 12288) return 1;
   if (wide) return groups <= 768 ? 16 : (groups <= 3072 ? 8 : 4);
-  return groups <= 320 ? 16 : (groups <= 3072 ? 12 : 8);
+  return groups <= 256 ? 16 : (groups <= 3072 ? 12 : 8);
 }
 // Gravity (us, clustered sets):
 //   groups           64   256   512  1024  2048  3072  4096  8192  16384  24576
@@ -497,22 +511,44 @@ int gravity_bwd_team(int64_t max_targets) {
   if (groups > 14336) return 1;
   return groups <= 320 ? 16 : (groups <= 1920 ? 8 : 4);
 }
-// The SPH adjoints, conduction and velocity gradients, as the density (us of
-// one density solve and hydro force with their gradients, and of one pass of
-// the modules with the force: viscosity, conduction, gradients):
-//   groups          256   512  1024  1536  2048  3125  4096  8192
-//   adjoints   4   3286  4593  6618  6309  6688  7980  8855 13842
-//              8   2588  3863  5675  5615  6280  7854  9207 14956
-//             16   2338  3386  6040  6514  7523  9892 11837 20724
-//   modules    4   1607  2171  3180  2885  3076  3394  3746  5641
-//              8   1129  1568  2449  2440  2614  3103  3484  5546
-//             16    958  1412  2313  2358  2615  3254  3731  6279
-// Conduction's pair is so light that one wave a group wins again where
-// groups are plenty (us, 1/4: 3242/2748 of 8192 groups, 7779/9138 of 65536).
+// The SPH adjoints (us, of the density's and of the force's; clustered sets at 295
+// neighbours, then uniform ones at 64):
+//   groups           256   512   768  1024  1536  2048  3072  4096  6144  8192 16384
+//   density    4     455   532   661   811   979  1081   999  1188  1509  1905  3256
+//              8     278   348   457   553   704   853   909  1120  1569  2048  3740
+//             16     219   341   487   621   867  1070  1426  1883  2817  3739  7212
+//   force      4     838  1018  1360  1634  1678  1721  1636  1780  2241  2797  4865
+//              8     469   717   861  1082  1263  1441  1499  1768  2403  3069  5620
+//             16     398   643   896  1051  1348  1570  1830  2257  3170  4137  7785
+//   density,   4     120   163   209   276   377   424   515   630   793   958  1590
+//   uniform    8     103   154   204   233   263   312   409   515   692   850  1494
+//             16      95   144   183   202   283   369   566   818  1097  1389  2796
+//   force,     4     104   164   218   293   357   406   560   672   882  1084  2004
+//   uniform    8     100   160   185   210   259   312   450   574   778   983  1834
+//             16     101   149   188   217   291   363   550   792  1152  1451  2771
 int adjoint_team(int64_t members) {
   const int64_t groups = (members + kWave - 1) / kWave;
-  return groups <= 640 ? 16 : (groups <= 3072 ? 8 : 4);
+  return groups <= 640 ? 16 : (groups <= 4608 ? 8 : 4);
 }
+// Velocity gradients and conduction (us, clustered sets at 295 neighbours, then
+// uniform ones at 64):
+//   groups             256   512  1024  1536  2048  3072  4096  6144  8192 16384 24576
+//   gradients    4     595   695   707   728   833   824   868  1054  1375  2166  2999
+//                8     358   422   474   503   582   638   740   968  1324  2200  3157
+//               16     261   321   415   490   590   713   873  1195  1632  2912  4350
+//   conduction none                     2497  2652  1867  1814  2109  2388  3315  4218
+//                4     442   514   717   942  1106  1087  1145  1366  1666  2743  3723
+//                8     280   346   562   652   791   796   958  1263  1603  2852  3981
+//               16     230   309   478   604   731   841  1058  1518  1979  3757  5260
+//   gradients,   4     317   346   400   430   501   549   642   824  1143  1761  2460
+//   uniform      8     202   227   296   317   371   443   526   724  1053  1699  2438
+//               16     143   184   250   287   339   443   533   747  1102  1826  2730
+//   conduction, none                     484   579   796  1021  1483  1932  2597  3630
+//   uniform      4     125   177   291   407   519   645   758   922  1108  1685  2628
+//                8     109   172   286   330   351   466   562   740   909  1519  2440
+//               16     103   168   216   257   302   406   539   714   918  1615  2571
+// Conduction's pair is so light that one wave a group wins again where groups are
+// plenty (us, 1/4: 7779/9138 of 65536 clustered groups).
 int velgrad_team(int64_t max_targets) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
   return groups <= 1536 ? 16 : (groups <= 8192 ? 8 : 4);
