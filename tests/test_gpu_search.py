@@ -1,7 +1,8 @@
 """The ways a group's neighbours are found beside the plain team search (a wave
 that walks the octree by itself, the deep search of long lists and of few targets
 among many members, lists at the ends of walk_leaf), at the sizes where they can
-go wrong, against the oracle; and the gravity adjoint without teams.
+go wrong, against the oracle or the other way; and team sizes that no other test
+takes.
 
 Tolerances: counts exact; the density within 2e-6 of the FP64 sums (FP32 terms
 of one sign, each good to a few 1e-7, added with compensation), accelerations,
@@ -235,3 +236,49 @@ def test_gravity_adjoint_without_a_team_adds_up(theta, eps):
     halves = [grads(torch.sort(q).values) for q in (order[:cut], order[cut:])]
     for a, b, s in zip(*halves, grads(None)):
         assert (a + b - s).abs().max() <= 1e-5 * s.abs().max()
+
+
+@pytest.mark.parametrize("log_few,fp64", [(14, False), (17, False), (19, False), (14, True),
+                                          (17, True), (19, True)])
+def test_switches_in_teams_have_the_bits_of_single_waves(log_few, fp64):
+    # 2^20 targets take no team; the first 2^14, 2^17 and 2^19 in tree order, the
+    # same groups, take teams of 16 (and the deep search), 8 and 4
+    from paper_2003_10850_amd import g3, ops
+    n = 1 << 20
+    g = torch.Generator(device="cuda").manual_seed(8)
+    R = lambda *s: torch.rand(*s, generator=g, device="cuda")
+    ft = torch.float64 if fp64 else torch.float32
+    c = ops.Context(torch.device("cuda", 0))
+    c.set_tuning(g3.G3_TUNE_HYDRO, 128, -1)
+    tree = ops.Tree(c, R(n, 3).to(ft), torch.full((n,), 1.0 / n, device="cuda"), None, BOX,
+                    inputs.Params(n_ngb=48.0))
+    few = torch.sort(tree.export(1)["order"][: 1 << log_few]).values
+    h = (2.25 * n ** (-1.0 / 3.0) * (0.8 + 0.4 * R(n))).to(ft)
+    x = [R(n, 3) - 0.5, 0.5 + R(n), h, 0.5 + R(n), 0.5 + R(n), inputs.SwitchParams(alpha_u=0.7)]
+    kw = dict(alpha=0.05 + R(n), balsara=R(n))
+    a = ops.hydro_force_switches(tree, *x, **kw)
+    b = ops.hydro_force_switches(tree, *x, **kw, active=few)
+    at = few.long()
+    for k in a:
+        assert torch.equal(a[k][at], b[k][at]), k
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+def test_gravity_with_the_inside_test_in_teams_of_4(fp64):
+    # 1.4e6 targets in teams of 4 and 5600 of them in teams of 16: the same terms,
+    # in sums of 64 that are cut elsewhere (64 roundings of 6e-8 at the worst, of
+    # terms that mostly point one way)
+    from paper_2003_10850_amd import ops
+    n = 1400000
+    g = torch.Generator(device="cuda").manual_seed(10)
+    pos = torch.rand(n, 3, generator=g, device="cuda").to(torch.float64 if fp64 else torch.float32)
+    tree = ops.Tree(ops.Context(torch.device("cuda", 0)), pos,
+                    torch.full((n,), 1.0 / n, device="cuda"), None, BOX,
+                    inputs.Params(theta=0.7, eps=1e-3))
+    few = torch.arange(0, n, 250, dtype=torch.int32, device="cuda")
+    a, b = ops.gravity(tree), ops.gravity(tree, active=few)
+    at = few.long()
+    assert torch.equal(a["nterms"][at], b["nterms"][at])
+    for k in ("acc", "pot"):
+        x, y = a[k][at].double(), b[k][at].double()
+        assert float((x - y).abs().max()) <= 4e-6 * float(y.abs().max()), k
