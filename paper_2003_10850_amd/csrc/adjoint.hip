@@ -857,7 +857,7 @@ __global__ void k_hydro_bwd_up(const int32_t *__restrict__ active, int64_t n_act
 // Bound by VALU issue (a pair is ~150 operations); 128 registers, four waves
 // a SIMD. Teams as in the density's adjoint. 1.25e5 particles of
 // ~295 neighbours: 10671 us with one wave a group and the two terms of a pair
-// by themselves, 2210 with teams of 4, 2131 of 8.
+// by themselves; 1678 with teams of 4, 1430 of 8.
 // A lane is a neighbour of a quarter of the entries that any lane neighbours, so
 // the pairs are not taken entry by entry: the tests give each lane a bit mask of
 // the tile, and the lanes take their own entries side by side, as many steps as

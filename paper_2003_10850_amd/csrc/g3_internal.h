@@ -227,7 +227,7 @@ size_t radix_tmp_bytes(int64_t n);
 hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, uint64_t *keys_alt,
                             uint32_t *vals_alt, int64_t n, int bits, void *tmp, hipStream_t s);
 
-// Tree build of one octree (members already selected in `ids`/`keys`).
+// Tree build of one octree of m members.
 // The gas octree (o == t->gas) takes its members from the all-particle
 // octree built before it, which finds them by `type` (nullptr: all gas) and
 // returns their number in *m_gas.
@@ -408,8 +408,8 @@ hipError_t launch_gravity(const Octree &all, const Groups &gs, int64_t max_group
                           hipStream_t s);
 
 // Adjoints. Gradients are ADDED to the caller-order arrays (nullable).
-// Density: every gas member walks its symmetric neighbourhood (all_gas:
-// the groups of every gas member); tm: the terminals of kAdjointLeaf, with h.
+// Density: teams search the symmetric neighbourhoods of every gas member
+// (all_gas: their groups); tm: the terminals of kAdjointLeaf, with h.
 hipError_t launch_density_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
                               const Groups &all_gas, int64_t max_groups, const Terms &tm,
                               int64_t n_act, const int32_t *active, const float *h,
@@ -426,7 +426,7 @@ hipError_t launch_density_solve_bwd(Octree &gas, const int32_t *iperm, int64_t n
                                     const float *h,
                                     const float *rho, const float *drho, const float *g_h,
                                     float *g_pos, float *g_mass, hipStream_t s);
-// Hydro: like the density (every gas member, symmetric walk) after the
+// Hydro: like the density (every gas member, symmetric search) after the
 // hydro prep of vh and aux; scratch up [n_gas].
 hipError_t launch_hydro_bwd(Octree &gas, const int32_t *iperm, int64_t n_caller,
                             const Groups &all_gas, int64_t max_groups, const Terms &tm,

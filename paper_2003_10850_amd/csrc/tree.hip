@@ -971,8 +971,9 @@ static void fill_cnodes(const g3_tree *t, const Octree &o, hipStream_t s) {
                                              t->f64 ? o.cc64 : nullptr);
 }
 
-// Selects the members (gas only for the gas octree), sorts them and builds
-// the topology and moments. SYNCS once to read the node count.
+// The all-particle octree: keys, sort, topology, moments and gravity's node copies,
+// and which members are gas. The gas octree, built next: those members in the same
+// order, topology and moments. SYNCS once to read the node count.
 int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
                  const float *mass, int64_t m, hipStream_t s, const uint8_t *type,
                  int64_t *m_gas) {
@@ -1011,16 +1012,12 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
     }
     o.cap_n = m;
   }
-  uint64_t *kalt = (uint64_t *)scratch(c, kSortKeys, m * sizeof(uint64_t));
-  uint32_t *valt = (uint32_t *)scratch(c, kSortVals, m * sizeof(uint32_t));
-  void *rtmp = scratch(c, kSortTmp, radix_tmp_bytes(m));
-  uint32_t *vals = (uint32_t *)scratch(c, kIds, m * sizeof(uint32_t));
   uint32_t *cnt = (uint32_t *)scratch(c, kCounts, (m + 1) * sizeof(uint32_t));
   uint32_t *off = (uint32_t *)scratch(c, kOffsets, (m + 1) * sizeof(uint32_t));
   uint8_t *lev = (uint8_t *)scratch(c, kLevel, 2 * m);
   uint32_t *stmp = (uint32_t *)scratch(c, kScanTmp, scan_tmp_elems(m) * sizeof(uint32_t));
   int32_t *maxlev = (int32_t *)scratch(c, kMisc, 64);
-  if (!kalt || !valt || !rtmp || !vals || !cnt || !off || !lev || !stmp || !maxlev) {
+  if (!cnt || !off || !lev || !stmp || !maxlev) {
     c->err = "device allocation of build scratch failed";
     return G3_ENOMEM;
   }
@@ -1037,6 +1034,14 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
     k_compact_sorted<<<nblk(n), kBlock, 0, s>>>(flags, slot, n, t->all, o.keys, o.perm, o.xm, x64,
                                                  t->iperm_gas);
   } else {
+    uint64_t *kalt = (uint64_t *)scratch(c, kSortKeys, m * sizeof(uint64_t));
+    uint32_t *valt = (uint32_t *)scratch(c, kSortVals, m * sizeof(uint32_t));
+    void *rtmp = scratch(c, kSortTmp, radix_tmp_bytes(m));
+    uint32_t *vals = (uint32_t *)scratch(c, kIds, m * sizeof(uint32_t));
+    if (!kalt || !valt || !rtmp || !vals) {
+      c->err = "device allocation of build scratch failed";
+      return G3_ENOMEM;
+    }
     if (f64)
       k_keys<double><<<nblk(m), kBlock, 0, s>>>((const double *)pos, m, t->coff, t->sbox,
                                                 t->n_snap, mass, o.keys, vals, nullptr);
@@ -1062,8 +1067,6 @@ int build_octree(g3_ctx *c, g3_tree *t, Octree &o, const void *pos, int f64,
         e = hipMemcpyAsync(vals, valt, m * sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
       if (e != hipSuccess) { c->err = "snapshot sort copy failed"; return G3_EHIP; }
     }
-  }
-  if (!gas) {
     if (f64)
       k_permute<double><<<nblk(m), kBlock, 0, s>>>(vals, m, (const double *)pos, mass, o.xm, x64,
                                                    t->iperm_all, o.perm);
