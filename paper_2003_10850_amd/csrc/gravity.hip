@@ -112,9 +112,11 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_gravity(
   // A node, for the lanes that accept it. Its mass may be above FP32's largest
   // number near the root, where every lane opens it, and infinity times a masked
   // distance of zero is no zero: the lanes branch (all of a clustered 2^21 box:
-  // 4143 us with the distance masked, 3995 so). Teams of 16 have few waves, where
-  // the branch costs 3 %; they mask, and branch only below a root that heavy.
-  constexpr bool kMayMask = !kF64 && kT == 16;
+  // 4143 us with the distance masked, 4030 so). Below a lighter root, teams of 16
+  // and launches with a workgroup for every group mask: few waves hide the branch
+  // there (3 % of teams of 16; 2 to 4e4 targets of such a box in teams of 4:
+  // 1.16 ms masked, 1.26 with the branch).
+  constexpr bool kMayMask = !kF64;
   auto node_term = [&](auto mask_c, bool use, float dx, float dy, float dz, float r2s, float m) {
     if constexpr (decltype(mask_c)::value) {
       term(use, dx, dy, dz, r2s, m);
@@ -223,7 +225,8 @@ __global__ __launch_bounds__(kT * kWave, 8) void k_gravity(
   const int root = __builtin_amdgcn_readfirstlane(grp.snap);
   const uint64_t all = grp.count < kWave ? (1ull << grp.count) - 1ull : ~0ull;
   if constexpr (kMayMask) {
-    if (cnodes[root].com_m.w < INFINITY)
+    if (cnodes[root].com_m.w < INFINITY &&
+        (kT == 16 || gs.gstart[*gs.nseg] <= (int)gridDim.x))
       team_items(S, root, all, w, lane, items(std::true_type{}));
     else
       team_items(S, root, all, w, lane, items(std::false_type{}));
