@@ -74,6 +74,26 @@ def test_gravity_below_nodes_heavier_than_fp32_holds(ctx, theta, fp64):
     assert (np.abs(g["pot"] - ref["pot"]) / np.abs(ref["pot"])).max() < 2e-6
 
 
+@pytest.mark.parametrize("fp64", [False, True])
+@pytest.mark.parametrize("n,theta", [(1 << 18, 0.7), (1400000, 0.5)])
+def test_gravity_below_a_heavy_root_in_teams_of_8_and_4(ctx, n, theta, fp64):
+    # masses, lengths and G scaled by powers of two (an even one for the lengths,
+    # whose square root is taken of r^2): every product and sum has the same digits,
+    # but the root's mass is above FP32's largest number
+    from paper_2003_10850_amd import ops
+    g = torch.Generator(device="cuda").manual_seed(12)
+    pos = torch.rand(n, 3, generator=g, device="cuda").to(torch.float64 if fp64 else torch.float32)
+    mass = (0.5 + torch.rand(n, generator=g, device="cuda")) / n
+    out = []
+    for m, x in ((1.0, 1.0), (2.0 ** 130, 2.0 ** 20)):
+        tree = ops.Tree(ctx, pos * x, (mass.double() * m).float(), None, (0.0, 0.0, 0.0, x),
+                        inputs.Params(theta=theta, eps=2.0 ** -9 * x, G=1.0 / m))
+        f = ops.gravity(tree)
+        out.append((f["acc"] * x * x, f["pot"] * x, f["nterms"]))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("mass,speed,side", [(2e33, 1e7, 3e3), (1e-36, 1e-3, 0.1), (1e-3, 1.0, 1.0)])
 def test_velocity_gradients_in_large_and_small_units(ctx, mass, speed, side):
     from paper_2003_10850_amd import ops
