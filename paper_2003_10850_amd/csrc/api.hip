@@ -475,12 +475,14 @@ int density_team(int64_t max_targets, int f64, bool solve) {
 //              8    120   121   126   141   188   222   233   344   463   622  1039  1480  1960
 //             16    116   117   127   148   178   218   245   415   621   887  1493  2218  3034
 // (wide: FP64 positions or the switches' inputs, whose LDS and registers hold
-// fewer waves a CU)
+// fewer waves a CU; a few hundred groups are mostly those of a small part of many
+// particles, wider than these: 2e4 of 10^6, 313 groups, 775 us with teams of 16, 825
+// with teams of 12, the densest of them 565 and 589)
 int hydro_team(int64_t max_targets, bool wide) {
   const int64_t groups = (max_targets + kWave - 1) / kWave;
   if (groups > 12288) return 1;
   if (wide) return groups <= 768 ? 16 : (groups <= 3072 ? 8 : 4);
-  return groups <= 256 ? 16 : (groups <= 3072 ? 12 : 8);
+  return groups <= 320 ? 16 : (groups <= 3072 ? 12 : 8);
 }
 // Gravity (us, clustered sets):
 //   groups           64   256   512  1024  2048  3072  4096  8192  16384  24576
@@ -1014,18 +1016,24 @@ static SphParams sph_params(const g3_ctx *c, const g3_params *p, const g3_tree *
   return sp;
 }
 
-// The deep search, where a snapshot's list has twenty rows of 64 windows or more
-// (a terminal holds about half of walk_leaf members), or where unsplit groups of
-// so few targets may hold far more terminals in their box than they reach (in a
-// list of one row there is little to leave out). us, every row and deep: velocity
-// gradients of 3e6 members (11 rows) 4750 and 5110, of 8e6 (30 rows) 14500 and
-// 14180, of 1.6e7 23560 and 21620; the density's adjoint of 8e6 (61 rows) 37400 and
-// 33900; the force of 64 random targets of 4e6 4580 and 1610.
+// The deep search, where a snapshot's list has fifteen rows of 64 windows or more
+// (a terminal holds about half of walk_leaf members), or where unsplit groups of a
+// part of the members hold far more terminals in their box than they reach: a
+// quarter in ten rows, a 64th in one. us, every row and deep, of clustered sets and
+// uniform ones: velocity gradients of 1.5e6 members (11 rows) 2572 and 2535, 2337
+// and 2206, of 4e6 (31) 6573 and 5990, 5897 and 5583, of 8e6 (61) 12969 and 12318,
+// 12963 and 10795; the adjoints of 1.5e6 5977 and 5768, 5076 and 5343, of 2e6 (15)
+// 7727 and 7577, 6926 and 6650, of 8e6 33323 and 27925, 26318 and 24556; the
+// conduction of a quarter of 1.5e6 1273 and 1147, 876 and 874, of 4e6 2874 and 2534,
+// 2486 and 2012; the force of a 16th of 2e6 1318 and 1091, 1050 and 851, of 64 of
+// 4e6 uniform ones 4580 and 1610.
 static bool deep_search(const g3_tree *t, const Octree &o, int64_t max_targets, int walk_leaf,
                         int split) {
   const int64_t members = std::min(o.n, t->max_members);
   const int64_t row = (int64_t)walk_leaf * (kWave * kWave / 2);
-  return members / 20 >= row || (split == -1 && max_targets <= o.n / 64 && members >= row);
+  if (members / 15 >= row) return true;
+  return split == -1 && ((max_targets <= o.n / 4 && members / 10 >= row) ||
+                         (max_targets <= o.n / 64 && members >= row));
 }
 
 // The largest h of the nodes that a symmetric search reads: the terminals'

@@ -86,37 +86,6 @@ __device__ __forceinline__ int wave_incl_sum(int v, int lane) {
   return v;
 }
 
-// The rows of 64 windows that a search looks into, in order: every one of
-// [w0, w1], from w0 on; deep: those of the aligned blocks whose box passes.
-template <bool kDeep>
-struct Rows {
-  int c0, w1;
-  __device__ __forceinline__ Rows(int w0, int w1) : c0(w0 - kWave), w1(w1) {}
-  template <typename Pass>
-  __device__ __forceinline__ int next(const Pass &) {
-    c0 += kWave;
-    return c0 <= w1 ? c0 : -1;
-  }
-};
-template <>
-struct Rows<true> {
-  uint64_t left = 0ull;
-  int at, last;  // blocks
-  __device__ __forceinline__ Rows(int w0, int w1) : at(w0 / kWave - kWave), last(w1 / kWave) {}
-  template <typename Pass>
-  __device__ __forceinline__ int next(const Pass &pass) {
-    while (left == 0ull) {
-      at += kWave;
-      if (at > last) return -1;
-      const int b = at + lane_id();
-      left = __ballot(b <= last && pass(b));
-    }
-    const int b = (int)__builtin_ctzll(left);
-    left &= left - 1ull;
-    return (at + b) * kWave;
-  }
-};
-
 // Finds the candidates of the group in tree order and hands them to
 // `round(ntiles, count)`: S.cand[0..count) are candidates (sorted indices)
 // that make up ntiles tiles of 64 (the last one of a group may be short).
@@ -145,42 +114,9 @@ __device__ __forceinline__ void team_search(const Terms &tm, int snap, TeamLds<T
   const int tb = __builtin_amdgcn_readfirstlane(tr.x), te = __builtin_amdgcn_readfirstlane(tr.y);
   if (tb >= te) return;
   const int w0 = tb / kTermWindow, w1 = (te - 1) / kTermWindow;
-  const float ex = fmaxf(thi.x - tlo.x, fmaxf(thi.y - tlo.y, thi.z - tlo.z));
-  const bool wide = kDeep && ex * ex > 16.0f * reach2(gmax2, 0.0f);
   int tc = 0;  // candidates waiting in S.cand
-  Rows<kDeep> rows(w0, w1);
-  for (int c0; (c0 = rows.next([&](int b) {
-         const float4 lo = tm.blo[b], hi = tm.bhi[b];
-         return box_box_dist2(tlo, thi, lo, hi) < reach2(gmax2, lo.w);
-       })) >= 0;) {
-    bool maybe = false;
-    float4 wl = make_float4(0.f, 0.f, 0.f, 0.f), wh = wl;
-    if ((!kDeep || c0 + lane >= w0) && c0 + lane <= w1) {
-      wl = tm.wlo[c0 + lane];
-      wh = tm.whi[c0 + lane];
-      maybe = box_box_dist2(tlo, thi, wl, wh) < reach2(gmax2, wl.w);
-    }
-    uint64_t M = __ballot(maybe);
-    if (kDeep && wide && M != 0ull) {
-      uint64_t mine = 0ull, mm = M;
-      for (int k = 0; mm; ++k, mm &= mm - 1ull) {
-        if (k % T != w) continue;
-        const int b = (int)__builtin_ctzll(mm);
-        const float4 bl = make_float4(lane_value(wl.x, b), lane_value(wl.y, b),
-                                      lane_value(wl.z, b), lane_value(wl.w, b));
-        const float4 bh = make_float4(lane_value(wh.x, b), lane_value(wh.y, b),
-                                      lane_value(wh.z, b), 0.0f);
-        if (__ballot(box_dist2(xi, bl, bh) < reach2(want2, bl.w)) != 0ull) mine |= 1ull << b;
-      }
-      if (lane == 0) S.wmask[w] = mine;
-      __syncthreads();
-      M = 0ull;
-      for (int v = 0; v < T; ++v) M |= S.wmask[v];
-      M = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(M >> 32)) << 32) |
-          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)M);
-      __syncthreads();  // wmask is free again
-    }
-    if (M == 0ull) continue;
+  // the windows c0 + b for the bits b of M (at least one), by every wave
+  auto windows = [&](int c0, uint64_t M) {
     const int nw = __popcll(M);
     // the wave's first window stays in registers: its accepted terminals, a
     // lane's first member, count and the members up to and with it
@@ -275,6 +211,60 @@ __device__ __forceinline__ void team_search(const Terms &tm, int snap, TeamLds<T
     }
     tc = total % kRound;
     __syncthreads();  // wmask, wid and wcnt are free again
+  };
+  if constexpr (!kDeep) {
+    for (int c0 = w0; c0 <= w1; c0 += kWave) {
+      bool maybe = false;
+      if (c0 + lane <= w1) {
+        const float4 lo = tm.wlo[c0 + lane], hi = tm.whi[c0 + lane];
+        maybe = box_box_dist2(tlo, thi, lo, hi) < reach2(gmax2, lo.w);
+      }
+      const uint64_t M = __ballot(maybe);
+      if (M != 0ull) windows(c0, M);
+    }
+  } else {
+    const float ex = fmaxf(thi.x - tlo.x, fmaxf(thi.y - tlo.y, thi.z - tlo.z));
+    const bool wide = ex * ex > 16.0f * reach2(gmax2, 0.0f);
+    for (int b0 = w0 / kWave; b0 <= w1 / kWave; b0 += kWave) {
+      bool look = false;
+      if (b0 + lane <= w1 / kWave) {
+        const float4 lo = tm.blo[b0 + lane], hi = tm.bhi[b0 + lane];
+        look = box_box_dist2(tlo, thi, lo, hi) < reach2(gmax2, lo.w);
+      }
+      for (uint64_t blocks = __ballot(look); blocks; blocks &= blocks - 1ull) {
+        const int c0 = (b0 + (int)__builtin_ctzll(blocks)) * kWave;
+        bool maybe = false;
+        float4 wl = make_float4(0.f, 0.f, 0.f, 0.f), wh = wl;
+        if (c0 + lane >= w0 && c0 + lane <= w1) {
+          wl = tm.wlo[c0 + lane];
+          wh = tm.whi[c0 + lane];
+          maybe = box_box_dist2(tlo, thi, wl, wh) < reach2(gmax2, wl.w);
+        }
+        uint64_t M = __ballot(maybe);
+        if (M == 0ull) continue;
+        if (wide) {
+          uint64_t mine = 0ull, mm = M;
+          for (int k = 0; mm; ++k, mm &= mm - 1ull) {
+            if (k % T != w) continue;
+            const int b = (int)__builtin_ctzll(mm);
+            const float4 bl = make_float4(lane_value(wl.x, b), lane_value(wl.y, b),
+                                          lane_value(wl.z, b), lane_value(wl.w, b));
+            const float4 bh = make_float4(lane_value(wh.x, b), lane_value(wh.y, b),
+                                          lane_value(wh.z, b), 0.0f);
+            if (__ballot(box_dist2(xi, bl, bh) < reach2(want2, bl.w)) != 0ull) mine |= 1ull << b;
+          }
+          if (lane == 0) S.wmask[w] = mine;
+          __syncthreads();
+          M = 0ull;
+          for (int v = 0; v < T; ++v) M |= S.wmask[v];
+          M = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(M >> 32)) << 32) |
+              (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)M);
+          __syncthreads();  // wmask is free again
+          if (M == 0ull) continue;
+        }
+        windows(c0, M);
+      }
+    }
   }
   if (tc > 0) {
     if (threadIdx.x == 0) S.next = 0;
