@@ -46,8 +46,18 @@
  *    allocate ctx scratch only when a call needs more than an earlier one.
  *    Run each call once outside capture with the same sizes, then capture
  *    it (hipStreamBeginCapture or torch.cuda.graph); replays reproduce the
- *    eager results. Builds, g3_walk, g3_autotune and g3_ctx_stats SYNC and
- *    cannot be captured.
+ *    eager results. A captured call holds the tree's node counts and buffers:
+ *    replays follow a refit, a rebuild needs a new capture. Builds, g3_walk,
+ *    g3_autotune and g3_ctx_stats SYNC and cannot be captured.
+ *  - Same bits: a target's density and hydro force depend on its group (64
+ *    consecutive targets of a snapshot, or fewer where the tuned split cuts),
+ *    not on the other targets of the call. Gravity, conduction, the velocity
+ *    gradients and the _backward calls serve a group by as many wavefronts as
+ *    suit the number of targets, and add up their totals in a fixed order:
+ *    the same call gives the same bits (but for g3_gravity_backward with
+ *    eps = 0), while calls of very different numbers
+ *    of targets (a snapshot in a forest and on its own tree, too) agree to
+ *    FP32 rounding. Counts are exact in every call.
  *
  * Physics (the paper prints no formula; these are the published methods
  * Gadget builds on): Wendland C6 kernel with support radius h (Dehnen & Aly

@@ -36,6 +36,13 @@ def gas_set(kind, n, rng):
     return pos
 
 
+def within(what, got, ref, S):
+    # 1e-5 of the L1 sum, and 1e-7 of its median for what only the edge of the
+    # support feeds (the adjoint tests' bar)
+    err, floor = np.abs(got - ref), 1e-7 * np.median(S[S > 0]) if np.any(S > 0) else 0.0
+    assert (err <= 1e-5 * S + floor).all(), (what, (err / (1e-5 * S + floor + 1e-300)).max())
+
+
 # deep by the targets: 64 or a few thousand of 2e5 (terminals of 16 and 64
 # members: 2 to 7 blocks); deep by the list: all of them with terminals of 4; not
 # deep: terminals of up to 4096 members, nodes of more than 65535; deep in a tree
@@ -104,6 +111,52 @@ def test_searches_against_oracle(kind, n, sizes, leaf, few, fp64):
             ref = oracle.conduction(t, pr, u[r], H, rho[r], 1.0, 0.0, active=ids)
             np.testing.assert_array_equal(got["c_npairs"][r][ids], ref["npairs"][ids])
             rel("c_dudt", ref, "dudt", "S")
+            ref = oracle.velgrad(t, pr, vel[r], H, rho[r], om[r], active=ids)
+            within("v_div", got["v_div"][r][ids], ref["div"][ids], ref["S_div"][ids])
+            within("v_curl", np.abs(got["v_curl"][r] - ref["curl"])[ids].max(1), 0.0,
+                   ref["S_curl"][ids])
+
+
+def test_adjoints_of_long_lists_against_oracle():
+    # lists of 16 rows of windows: the deep adjoints, upstream gradients at every
+    # particle (at few, the edge of the support alone would feed many entries)
+    from paper_2003_10850_amd import g3, ops
+    n = 2000000
+    print(f"deep adjoints n={n}", flush=True)
+    rng = np.random.default_rng(14)
+    pos = rng.random((n, 3)).astype(np.float32)
+    mass = ((0.5 + rng.random(n)) / n).astype(np.float32)
+    h = (2.2 * n ** (-1.0 / 3.0) * rng.uniform(0.7, 1.3, n)).astype(np.float32)
+    vel, ga = rng.normal(0, 0.1, (2, n, 3)).astype(np.float32)
+    u, rho, om, gr, gd, go = rng.uniform(0.5, 1.5, (6, n)).astype(np.float32)
+    p = inputs.Params(n_ngb=48.0)
+    c = ops.Context(torch.device("cuda", 0))
+    tree = ops.Tree(c, dev_t(pos), dev_t(mass), None, BOX, p)
+    t = oracle.Tree(pos.astype(np.float64), mass.astype(np.float64), BOX, gas_only=True,
+                    type=np.zeros(n, np.uint8))
+    H = h.astype(np.float64)
+    f = oracle.density(t, p, h=H, solve_h=False)
+    new = lambda *k: torch.zeros(*k, device="cuda")
+    D = {k: dev_t(v) for k, v in dict(
+        h=h, u=u, rho=rho, om=om, vel=vel, ga=ga, gr=gr, gd=gd, go=go,
+        fr=f["rho"].astype(np.float32), fd=f["drho_dh"].astype(np.float32)).items()}
+    P = lambda *k: [D[x].data_ptr() for x in k]
+    prm, st = g3.g3_params.of(p), torch.cuda.current_stream().cuda_stream
+    o = dict(pos=new(n, 3), mass=new(n), h=new(n))
+    g3.g3_density_backward(c.handle, tree.handle, n, 0, prm,
+                           *P("h", "fr", "fd", "gr", "gd", "go"),
+                           *[o[k].data_ptr() for k in ("pos", "mass", "h")], st)
+    ref = oracle.density_backward(t, p, H, gr, gd, go)
+    for k in o:
+        within("density " + k, o[k].cpu().numpy(), ref[k], ref["S"][k])
+    names = ("pos", "vel", "mass", "h", "u", "rho", "omega")
+    o = {k: new(n, 3) if k in ("pos", "vel") else new(n) for k in names}
+    g3.g3_hydro_force_backward(c.handle, tree.handle, n, 0, prm,
+                               *P("vel", "u", "h", "rho", "om", "ga", "gd"),
+                               *[o[k].data_ptr() for k in names], st)
+    ref = oracle.hydro_backward(t, p, vel, u, H, rho, om, ga, gd)
+    for k in names:
+        within("hydro " + k, o[k].cpu().numpy(), ref[k], ref["S"][k])
 
 
 @pytest.mark.parametrize("kind,leaf,few,fp64", [
