@@ -55,9 +55,9 @@
  *    gradients and the _backward calls serve a group by as many wavefronts as
  *    suit the number of targets, and add up their totals in a fixed order:
  *    the same call gives the same bits (but for g3_gravity_backward with
- *    eps = 0), while calls of very different numbers
- *    of targets (a snapshot in a forest and on its own tree, too) agree to
- *    FP32 rounding. Counts are exact in every call.
+ *    eps = 0), while calls of very different numbers of targets (a snapshot
+ *    in a forest and on its own tree, too) agree to FP32 rounding. Counts are
+ *    exact in every call.
  *
  * Physics (the paper prints no formula; these are the published methods
  * Gadget builds on): Wendland C6 kernel with support radius h (Dehnen & Aly
